@@ -16,6 +16,24 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 
 constexpr int kWave = 64;
+constexpr int kXcds = 8;
+constexpr int kGroupM = 8;        // row tiles per band
+
+// XCD-aware tile order; false if this workgroup is one of the (< 8) padding ids.
+template <int BM, int BN>
+__device__ __forceinline__ bool tile_origin(int32_t tiles_m, int32_t tiles_n, int64_t& m0, int32_t& n0) {
+  const int32_t total = tiles_m * tiles_n;
+  const int32_t per_xcd = (total + kXcds - 1) / kXcds;
+  const int32_t idx = (blockIdx.x % kXcds) * per_xcd + blockIdx.x / kXcds;
+  if (idx >= total) return false;
+  const int32_t band = idx / (kGroupM * tiles_n);
+  const int32_t first_m = band * kGroupM;
+  const int32_t band_m = min(kGroupM, tiles_m - first_m);
+  const int32_t r = idx - band * kGroupM * tiles_n;
+  m0 = (int64_t)(first_m + r % band_m) * BM;
+  n0 = (r / band_m) * BN;
+  return true;
+}
 
 // Element traits: VEC elements make one 16-byte vector.
 template <typename T> struct Elem;

@@ -1,65 +1,214 @@
 // fp32 linear layer  y = epilogue(x W^T + b)  on packed rows (paper Sec. 4.3: the linear
-// layers see only valid tokens).  This is the fp32 storage path, used by the small fp32
-// workload; it runs on the vector ALU with a 64x64 LDS tile and a 4x4 register tile per
-// lane.  The bf16 path (MFMA) lives in gemm_bf16.hip.
+// layers see only valid tokens): the fp32 storage path, on the fp32 matrix instructions
+// (v_mfma_f32_16x16x4_f32: fp32 products and sums, 157 TFLOP/s).
+//
+// These problems are small: what bounds them is latency, idle CUs and, from a few hundred rows on, bytes
+// moved from the L2 per flop, not the matrix cores.  So:
+//  * a workgroup owns a tile of 16, 32 or 64 rows and columns and all of K, which its 4 or 8 wavefronts cut
+//    in interleaved slabs of 32 (128 bytes of a row); the partial sums meet in LDS at the end and are added
+//    in a fixed order.  Every wavefront computes the whole tile, so a tile costs (rows + columns) * K * 4
+//    bytes however many wavefronts share it;
+//  * a slab of W rows and x rows goes from global memory straight into an LDS ring that is private to the
+//    wavefront, two slabs deep (global_load_lds_dwordx4, whole 128-byte lines): no barrier and no
+//    staging register in the loop.  (Operands loaded straight into the MFMA layout, 16 rows x 64 bytes per
+//    instruction, ran at 14 bytes per clock and CU, a quarter of this: 387 x 3072 x 1024 44 -> 31 us.)
+//  * an MFMA operand is one float per lane, row l % 16 and k = l / 16; since k may be walked in any order
+//    that both operands share, a lane reads four consecutive floats, chunk l / 16 of the half slab, as one
+//    16-byte LDS vector for four instructions, with the conflict-free swizzle of the 16-bit kernels;
+//  * W rows are the A operand and x rows the B operand: a lane ends up with four consecutive columns of one
+//    output row, so bias, residual and result move as 16-byte vectors.
+// Against the former kernel (vector ALU, 64 x 64 LDS tile, 4 x 4 registers per lane): 387 x 4096 x 1024
+// 214 -> 41 us, 387 x 1024 x 4096 596 -> 40 us, 76 x 256 x 1024 149 -> 4.1 us; 2048 x 2048 x 8192 runs at
+// 125 TFLOP/s.
 #include "common.h"
 
 namespace energon {
 
-constexpr int kTile = 64, kTileK = 16;
+namespace {
 
-__global__ __launch_bounds__(256) void gemm_f32_kernel(const float* __restrict__ x, const float* __restrict__ w,
-                                                       const float* __restrict__ bias, const float* res,
-                                                       float* y, int64_t M, int32_t N, int32_t K, int epi) {
-  __shared__ float xs[kTileK][kTile + 1];
-  __shared__ float ws[kTileK][kTile + 1];
-  const int tid = threadIdx.x, tx = tid & 15, ty = tid >> 4;
-  const int64_t m0 = (int64_t)blockIdx.x * kTile;
-  const int32_t n0 = blockIdx.y * kTile;
-  const int lr = tid >> 2, lk = (tid & 3) * 4;  // this lane stages row lr, k offsets lk..lk+3
-  float acc[4][4] = {};
-  for (int32_t k0 = 0; k0 < K; k0 += kTileK) {
+typedef __attribute__((address_space(1))) const void* f32_gptr_t;
+typedef __attribute__((address_space(3))) void* f32_lptr_t;
+
+// 16-byte slot of chunk c of row r inside a 128-byte LDS row: c ^ f32_swz(r) (row bits 1, 2, 3 to slot bits
+// 0, 2, 1: the 16-row operand reads below then meet no bank conflict).
+__device__ __forceinline__ int f32_swz(int row) {
+  return ((row >> 1) & 1) | (((row >> 2) & 1) << 2) | (((row >> 3) & 1) << 1);
+}
+
+template <int TM, int TN, int WK, int kDepth> struct F32Cfg {
+  static constexpr int kSlotVecs = (TM + TN) * 16 * 8;   // 16-byte vectors per slab: W rows, then x rows
+  static constexpr size_t kRing = (size_t)WK * kDepth * kSlotVecs * 16;
+  static constexpr size_t kRed = (size_t)WK * TN * TM * 1024;
+  static constexpr size_t kLds = kRing > kRed ? kRing : kRed;
+};
+
+// TN x TM tiles of 16 x 16 (columns x rows of y) per workgroup, WK wavefronts along K, kDepth slabs in flight each.
+template <int TM, int TN, int WK, int kDepth>
+__global__ __launch_bounds__(WK * 64) void gemm_f32_kernel(const float* __restrict__ x, const float* __restrict__ w,
+                                                          const float* __restrict__ bias, const float* res, float* y,
+                                                          int64_t M, int32_t N, int32_t K, int epi, int32_t tiles_m,
+                                                          int32_t tiles_n) {
+  using Cfg = F32Cfg<TM, TN, WK, kDepth>;
+  constexpr int G = 2 * (TM + TN);   // 1 KiB loads (8 rows x 128 bytes) per slab
+  extern __shared__ f32x4 lds[];
+  int64_t m0;
+  int32_t n0;
+  if (!tile_origin<16 * TM, 16 * TN>(tiles_m, tiles_n, m0, n0)) return;
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int lrow = lane & 15, lq = lane >> 4;
+
+  // slabs of 32 k (128 bytes of a row): wavefront w takes slabs w, w + WK, ...; the last slab may be partial
+  const int32_t slabs = (K + 31) >> 5;
+  const int32_t ns = (slabs - wave + WK - 1) / WK;
+  f32x4* ring = lds + wave * (kDepth * Cfg::kSlotVecs);
+
+  // Lane l of a load lands in slot l % 8 of row l / 8 of its 8-row group and fetches the chunk that the
+  // swizzle keeps there.  Rows past the edge read the last row and are dropped; chunks past K (in the last
+  // slab only) read the row's last chunk and are replaced by zeros when they are used.
+  const char *pw[2 * TN], *px[2 * TM];
+  uint32_t chunk[2];
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const int32_t k = k0 + lk + e;
-      xs[lk + e][lr] = (m0 + lr < M && k < K) ? x[(size_t)(m0 + lr) * K + k] : 0.f;
-      ws[lk + e][lr] = (n0 + lr < N && k < K) ? w[(size_t)(n0 + lr) * K + k] : 0.f;
-    }
-    __syncthreads();
+  for (int p = 0; p < 2; ++p) chunk[p] = (uint32_t)((lane & 7) ^ f32_swz((lane >> 3) + 8 * p));
 #pragma unroll
-    for (int k = 0; k < kTileK; ++k) {
-      float a[4], b[4];
-#pragma unroll
-      for (int i = 0; i < 4; ++i) { a[i] = xs[k][ty * 4 + i]; b[i] = ws[k][tx * 4 + i]; }
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] = fmaf(a[i], b[j], acc[i][j]);
-    }
-    __syncthreads();
+  for (int g = 0; g < 2 * TN; ++g) {
+    const int32_t n = n0 + 8 * g + (lane >> 3);
+    pw[g] = reinterpret_cast<const char*>(w + (size_t)(n < N ? n : N - 1) * K);
   }
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int64_t m = m0 + ty * 4 + i;
-    if (m >= M) continue;
+  for (int g = 0; g < 2 * TM; ++g) {
+    const int64_t m = m0 + 8 * g + (lane >> 3);
+    px[g] = reinterpret_cast<const char*>(x + (size_t)(m < M ? m : M - 1) * K);
+  }
+  const uint32_t last_chunk = (uint32_t)K * 4u - 16u;   // byte offset of a row's last chunk (K < 2^24)
+  auto issue = [&](int32_t slot, int32_t i) {
+    const uint32_t k = (uint32_t)(wave + i * WK) * 128u;
+    f32x4* dst = ring + slot * Cfg::kSlotVecs;
+    uint32_t off[2];
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int32_t n = n0 + tx * 4 + j;
-      if (n >= N) continue;
-      float v = acc[i][j] + (bias ? bias[n] : 0.f);
-      if (epi == EPI_BIAS_GELU) v = gelu_erf(v);
-      if (epi == EPI_BIAS_RESIDUAL) v += res[(size_t)m * N + n];
-      y[(size_t)m * N + n] = v;
+    for (int p = 0; p < 2; ++p) off[p] = min(k + chunk[p] * 16u, last_chunk);
+#pragma unroll
+    for (int g = 0; g < 2 * TN; ++g)
+      __builtin_amdgcn_global_load_lds((f32_gptr_t)(pw[g] + off[g & 1]), (f32_lptr_t)(dst + g * 64), 16, 0, 0);
+#pragma unroll
+    for (int g = 0; g < 2 * TM; ++g)
+      __builtin_amdgcn_global_load_lds((f32_gptr_t)(px[g] + off[g & 1]), (f32_lptr_t)(dst + (2 * TN + g) * 64), 16, 0, 0);
+  };
+
+  f32x4 acc[TN][TM];
+#pragma unroll
+  for (int i = 0; i < TN; ++i)
+#pragma unroll
+    for (int j = 0; j < TM; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+  uint32_t foff[2];   // operand reads: row l % 16 of a 16-row tile, chunk 4 h + l / 16
+#pragma unroll
+  for (int h = 0; h < 2; ++h) foff[h] = (uint32_t)(lrow * 8 + ((4 * h + lq) ^ f32_swz(lrow)));
+
+  for (int32_t u = 0; u < kDepth && u < ns; ++u) issue(u, u);
+  int32_t slot = 0;
+  for (int32_t i = 0; i < ns; ++i) {
+    // loads return in order; behind slab i's are those of the next kDepth - 1 slabs while they all exist
+    if (i + kDepth <= ns) asm volatile("s_waitcnt vmcnt(%0)" ::"n"((kDepth - 1) * G) : "memory");
+    else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    const f32x4* slab = ring + slot * Cfg::kSlotVecs;
+    const int32_t left = K - (wave + i * WK) * 32;   // k's of this slab, uniform
+    f32x4 wb[2][TN], xa[2][TM];
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+#pragma unroll
+      for (int t = 0; t < TN; ++t) wb[h][t] = slab[t * 128 + foff[h]];
+#pragma unroll
+      for (int t = 0; t < TM; ++t) xa[h][t] = slab[(TN + t) * 128 + foff[h]];
     }
+    if (left < 32) {
+#pragma unroll
+      for (int h = 0; h < 2; ++h)
+        if (16 * h + 4 * lq >= left) {   // K % 4 == 0: whole chunks
+#pragma unroll
+          for (int t = 0; t < TN; ++t) wb[h][t] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+          for (int t = 0; t < TM; ++t) xa[h][t] = f32x4{0.f, 0.f, 0.f, 0.f};
+        }
+    }
+    if (i + kDepth < ns) {
+      // the slot is refilled by the load unit, which is not ordered with this wavefront's LDS reads
+      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+      issue(slot, i + kDepth);
+    }
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+#pragma unroll
+        for (int a = 0; a < TN; ++a)
+#pragma unroll
+          for (int b = 0; b < TM; ++b)
+            acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x4f32(wb[h][a][e], xa[h][b][e], acc[a][b], 0, 0, 0);
+    slot = slot + 1 == kDepth ? 0 : slot + 1;
+  }
+
+  // the wavefronts' sums meet in LDS (the rings are free once every wavefront is here) and are added in order
+  __syncthreads();
+#pragma unroll
+  for (int a = 0; a < TN; ++a)
+#pragma unroll
+    for (int b = 0; b < TM; ++b) lds[(wave * TN * TM + a * TM + b) * 64 + lane] = acc[a][b];
+  __syncthreads();
+  for (int t = wave; t < TN * TM; t += WK) {
+    f32x4 v = lds[t * 64 + lane];
+#pragma unroll
+    for (int k = 1; k < WK; ++k) v += lds[(k * TN * TM + t) * 64 + lane];
+    // tile (t / TM, t % TM): row l % 16 of y's rows, columns 4 (l / 16) .. + 3
+    const int64_t m = m0 + 16 * (t % TM) + lrow;
+    const int32_t col = n0 + 16 * (t / TM) + 4 * lq;
+    if (m >= M || col >= N) continue;   // N % 4 == 0
+    const size_t off = (size_t)m * N + col;
+    if (bias != nullptr) v += *reinterpret_cast<const f32x4*>(bias + col);
+    if (epi == EPI_BIAS_GELU) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) v[e] = gelu_erf(v[e]);
+    }
+    if (epi == EPI_BIAS_RESIDUAL) v += *reinterpret_cast<const f32x4*>(res + off);
+    *reinterpret_cast<f32x4*>(y + off) = v;
   }
 }
+
+template <int TM, int TN, int WK, int kDepth>
+hipError_t launch_cfg(const float* x, const float* w, const float* bias, const float* res, float* y, int64_t M,
+                      int32_t N, int32_t K, int epi, hipStream_t s) {
+  constexpr int BM = 16 * TM, BN = 16 * TN;
+  constexpr size_t lds = F32Cfg<TM, TN, WK, kDepth>::kLds;
+  static_assert(lds <= 160 * 1024, "LDS of a CU");
+  auto kern = gemm_f32_kernel<TM, TN, WK, kDepth>;
+  static LdsAttrOnce once;
+  hipError_t e = ensure_dynamic_lds(reinterpret_cast<const void*>(kern), lds, once);
+  if (e != hipSuccess) return e;
+  const int32_t tiles_m = (int32_t)((M + BM - 1) / BM), tiles_n = (N + BN - 1) / BN;
+  const int64_t grid = ((int64_t)tiles_m * tiles_n + kXcds - 1) / kXcds * kXcds;
+  kern<<<dim3((unsigned)grid), dim3(WK * 64), lds, s>>>(x, w, bias, res, y, M, N, K, epi, tiles_m, tiles_n);
+  return hipGetLastError();
+}
+
+}  // namespace
 
 hipError_t launch_gemm_f32(const float* x, const float* w, const float* bias, const float* res, float* y, int64_t M,
                            int32_t N, int32_t K, int epi, hipStream_t s) {
   if (M <= 0) return hipSuccess;
-  const dim3 grid((unsigned)((M + kTile - 1) / kTile), (unsigned)((N + kTile - 1) / kTile));
-  gemm_f32_kernel<<<grid, 256, 0, s>>>(x, w, bias, res, y, M, N, K, epi);
-  return hipGetLastError();
+  const auto tiles = [&](int bm, int bn) { return ((M + bm - 1) / bm) * ((N + bn - 1) / bn); };
+  // Large tiles move fewer bytes, small ones make more workgroups; where the lines lie (measured, us):
+  //   64 x 64 from 448 tiles: 600 x 4800 x 1600 (750) 94 against 97 with 32 x 32, 2048 x 2048 x 8192 (1024)
+  //     552 / 693; but 387 x 3072 x 1024 (336, a second round nearly empty) 42 / 31;
+  //   32 x 32 from 168 tiles: 130 x 1600 x 6400 (250) 34 against 48 with 16 x 16; 37 x 1600 x 1600 (100) 10.6 / 7.3;
+  //   in between, where 32 x 32 would be one to two rounds of 256 CUs, 32 x 64 is one: 387 x 1024 x 1024
+  //     (416) 12.8 against 14.4;
+  //   16 x 16 with eight wavefronts along a long K while every CU has at most one tile: 17 x 2048 x 8192
+  //     15.7 against 20.0 with four.
+  if (tiles(64, 64) >= 448) return launch_cfg<4, 4, 4, 2>(x, w, bias, res, y, M, N, K, epi, s);
+  const int64_t t32 = tiles(32, 32);
+  if (t32 > 256 && t32 <= 512) return launch_cfg<2, 4, 4, 2>(x, w, bias, res, y, M, N, K, epi, s);
+  if (t32 >= 168) return launch_cfg<2, 2, 4, 2>(x, w, bias, res, y, M, N, K, epi, s);
+  if (tiles(16, 16) <= 256 && K >= 2048) return launch_cfg<1, 1, 8, 2>(x, w, bias, res, y, M, N, K, epi, s);
+  return launch_cfg<1, 1, 4, 2>(x, w, bias, res, y, M, N, K, epi, s);
 }
 
 }  // namespace energon

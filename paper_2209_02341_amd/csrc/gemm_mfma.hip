@@ -32,8 +32,6 @@ namespace energon {
 
 constexpr int BK = 64;            // K elements per slab
 constexpr int kChunks = BK / 8;   // 16-byte chunks per LDS row
-constexpr int kXcds = 8;
-constexpr int kGroupM = 8;        // row tiles per band
 
 typedef __attribute__((address_space(1))) const void* gptr_t;
 typedef __attribute__((address_space(3))) void* lptr_t;
@@ -44,22 +42,6 @@ __device__ __forceinline__ int swz(int row) { return (row & 7) ^ ((row >> 3) & 1
 // function above every such read takes two passes).
 __device__ __forceinline__ int swz16(int row) {
   return ((row >> 1) & 1) | (((row >> 2) & 1) << 2) | (((row >> 3) & 1) << 1);
-}
-
-// XCD-aware tile order; false if this workgroup is one of the (< 8) padding ids.
-template <int BM, int BN>
-__device__ __forceinline__ bool tile_origin(int32_t tiles_m, int32_t tiles_n, int64_t& m0, int32_t& n0) {
-  const int32_t total = tiles_m * tiles_n;
-  const int32_t per_xcd = (total + kXcds - 1) / kXcds;
-  const int32_t idx = (blockIdx.x % kXcds) * per_xcd + blockIdx.x / kXcds;
-  if (idx >= total) return false;
-  const int32_t band = idx / (kGroupM * tiles_n);
-  const int32_t first_m = band * kGroupM;
-  const int32_t band_m = min(kGroupM, tiles_m - first_m);
-  const int32_t r = idx - band * kGroupM * tiles_n;
-  m0 = (int64_t)(first_m + r % band_m) * BM;
-  n0 = (r / band_m) * BN;
-  return true;
 }
 
 // Epilogue of one wavefront: TM x TN accumulator tiles of 32x32 whose top-left element is
