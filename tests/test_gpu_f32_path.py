@@ -1,9 +1,11 @@
-"""fp32 storage: the linear kernel on the fp32 matrix instructions, at the edges of its tiles
-and of the dispatch between tile sizes, against the oracle.
+"""fp32 storage: the linear and the attention kernels on the fp32 matrix instructions, at the edges of their
+tiles and of the dispatch between tile sizes, against the oracle.
 
 Bound of the linear: any order of summing K products in fp32 is off by at most (K + 2) u sum |x w| with
 u = 2^-24 (K - 1 additions, a rounding per product, the bias); the epilogue's few roundings are relative to
 the result and its terms (8 u covers them) and GeLU (slope <= 1.13) adds its fit, 1.3e-7 absolute.
+Bound of the attention: the logits are off by d u sum |q k| <= eps, which moves every softmax weight by a
+factor within exp(+-2 eps) of itself, and the weighted sum of len values adds (len + 8) u of its terms.
 """
 import numpy as np
 import pytest
@@ -45,3 +47,41 @@ def test_linear_f32(M, N, K, epi):
     out = hz.to_host(yd)
     assert np.all(np.abs(out[:M] - ref) <= bound)
     assert np.all(out[M] == 3.0), "row past M was written"
+
+
+def _attention(qkv, lens, nh, d):
+    lens = np.asarray(lens, np.int32)
+    cu = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    T = int(cu[-1])
+    od = torch.full((T + 1, nh * d), 3.0, device="cuda")
+    E.energon_attention(hz.to_device(qkv, wl.F32), od[:T], torch.from_numpy(cu).cuda(), len(lens), int(lens.max()), nh, d)
+    out = hz.to_host(od)
+    assert np.all(out[T] == 3.0), "row past T was written"
+    return out[:T], cu
+
+
+@pytest.mark.parametrize("lens,nh,d", [([1, 15, 16, 17, 0, 64, 65], 3, 64), ([129, 2, 80], 2, 128)])
+def test_attention_f32(lens, nh, d):
+    A = nh * d
+    qkv = np.random.default_rng(d).standard_normal((sum(lens), 3 * A)).astype(np.float32)
+    out, cu = _attention(qkv, lens, nh, d)
+    for b, n in enumerate(lens):
+        if n == 0:
+            continue
+        blk = qkv[cu[b]:cu[b + 1]].astype(np.float64)
+        ref = orc.masked_causal_attention(blk[:, :A], blk[:, A:2 * A], blk[:, 2 * A:], n, nh, d)
+        qa, ka = (np.abs(blk[:, j * A:(j + 1) * A]).reshape(n, nh, d) for j in (0, 1))
+        eps = (d + 4) * U * np.einsum("ihc,jhc->hij", qa, ka).max() / np.sqrt(d)
+        bound = (2 * eps + (n + 16) * U) * np.abs(blk[:, 2 * A:]).max(axis=0)
+        assert np.all(np.abs(out[cu[b]:cu[b + 1]] - ref) <= bound)
+
+
+def test_attention_f32_bad_token_reaches_later_tokens_only():
+    n, nh, d, bad = 40, 2, 64, 37
+    A = nh * d
+    qkv = np.random.default_rng(0).standard_normal((n, 3 * A)).astype(np.float32)
+    clean, _ = _attention(qkv, [n], nh, d)
+    qkv[bad, 2 * A:] = np.inf
+    out, _ = _attention(qkv, [n], nh, d)
+    assert np.allclose(out[:bad], clean[:bad], rtol=0, atol=1e-6)   # same weights, another order of the sums
+    assert not np.isfinite(out[bad:]).any()
