@@ -2,46 +2,138 @@
 // (Sec. 4.3) rebuilds the padding around the attention core; here the core itself is
 // variable-length, so nothing is rebuilt inside a layer and no score is computed for a pad.
 //
-// One workgroup (8 wavefronts; registers are capped so that two workgroups share a CU and one's
-// memory waits hide behind the other's arithmetic) = one (sequence, head, block of 128 queries);
-// each wavefront owns 16 queries.
-// Keys/values are walked in tiles of 64 keys held in LDS (double-buffered) and shared by the
-// eight wavefronts; tiles above the causal diagonal are never visited.
+// One workgroup (4 wavefronts, two workgroups per CU) = one (sequence, head, block of 128 queries); each wavefront
+// owns 32 queries.  Keys / values come in tiles of 32 keys through a ring of four stages in LDS, shared by the
+// wavefronts and worked on two tiles at a time; tiles above the causal diagonal are never visited.
 //
 // Everything is computed transposed so that a query is a *column* of every MFMA result
-// (v_mfma_f32_16x16x32_bf16 / _f16: the lane holds column lane % 16, rows 4 * (lane / 16) + e):
+// (v_mfma_f32_32x32x16_bf16 / _f16: the lane holds column l % 32, rows 8 (e / 4) + 4 (l / 32) + e % 4):
 //   S^T[key, query] = K[key, :] . Q[query, :]      A operand = K rows, B operand = Q rows
 //   O^T[dd,  query] += V^T[dd, key] . P^T[key, query]
 // so the online-softmax state (running max, running sum) is one scalar per lane, and the
 // exponentiated scores are already laid out as the B operand of the second product: no
-// cross-lane movement of P.  The contraction index (key) may be enumerated in any order as long
-// as both operands agree, so V^T is kept in LDS in the order the accumulator layout dictates:
-// position 8 g + i of a 32-key step holds key 4 g + i (i < 4) or 16 + 4 g + i - 4 of that step,
-// which makes a lane's 8 keys (g = lane / 16) one 16-byte read.
-// K and V tiles go from global memory straight to LDS (global_load_lds_dwordx4, whole 128- or
-// 256-byte row pieces, the swizzle applied on the global side).  Every wavefront then reads back the
-// eight V rows it fetched itself (no barrier needed for that), 16 bytes per lane, and writes them
-// transposed (key-contiguous rows), two keys per 32-bit store, into the V^T tile.  (Fetching V
-// with one key per lane, so that it arrives in the registers ready for that transposition, made
-// every load instruction touch 64 different cache lines for 16 bytes each; the kernel then ran at
-// under 3 TB/s of useful bytes on short sequences, where it is a plain streaming read.)
+// cross-lane movement of P.  The contraction index (key) may be enumerated in any order as long as both
+// operands agree, so the V operand takes it in the order the accumulators have, as two transposed LDS reads of four
+// keys each (ds_read_b64_tr_b16) from the rows as they were fetched: V is never written a second time.
+// Q, K and V rows go from global memory straight to LDS (whole 128- or 256-byte row pieces, the swizzle applied on
+// the global side).
+//
+// What bounds it: per 32 keys a wavefront has 512 matrix-core cycles (d = 128) and about 730 of the vector ALU
+// (16 exponentials per lane at a quarter of the rate, and, per pair of tiles, 64 multiplications that rescale the
+// accumulators), with two wavefronts per SIMD to overlap them; on short sequences the fixed cost of a block, about
+// 4 us of dependent memory latencies (lengths, first rows, last stores) and 2 us between two workgroups of a slot.
+// Measured (bf16, d = 128, before -> now): 8 sequences of 1536 .. 2047 tokens x 40 heads 480 -> 384 us (690 TFLOP/s on
+// the causal triangle), 64 sequences of very unequal length x 64 heads 738 -> 502, 32 of up to 512 x 40 125 -> 113,
+// 64 of up to 64 x 40 29.9 -> 24.9; d = 64: 8 long x 25 176 -> 156, 50 of up to 200 x 16 16.8 -> 15.6.  Before, 8
+// wavefronts of 16 queries read every operand from LDS twice as often and copied V into a transposed tile, with two
+// barriers per 64 keys.  Following the running max only when it had moved by a factor of 2^8 saves the rescaling and
+// another 10 %, but then the largest weight of a row is no longer exactly 1 and the error grows by a twentieth: not done.
 #include "common.h"
+#include <algorithm>
+#include <type_traits>
 
 namespace energon {
 
-constexpr int kBQ = 128, kBKV = 64, kAttnWaves = 8;
+constexpr int kAttnWaves = 4, kWQ = 32, kBQ = kAttnWaves * kWQ;   // queries per wavefront, per workgroup
+constexpr int kBKV = 32, kStages = 4;                             // keys per tile, tiles in LDS
 constexpr float kLog2e = 1.4426950408889634f;
 
 typedef __attribute__((address_space(1))) const void* attn_gptr_t;
 typedef __attribute__((address_space(3))) void* attn_lptr_t;
 
+// 16-byte slot of chunk c of row r inside an LDS row: c ^ kswz(r) for rows read as 32-row operand tiles (lane l:
+// row l % 32, chunk 2 ks + l / 32), c ^ vswz(r) for rows read transposed (8 rows x 64 bytes per instruction, of
+// which half a wavefront takes 4 rows): all 64 banks once per pass.
 template <int D> __device__ __forceinline__ int kswz(int row) {
   return D == 128 ? (row & 15) : ((row & 7) ^ ((row >> 3) & 1));
 }
-// V^T rows are 128 bytes (64 keys); a lane reads row dd % 16 of a 16-row block, chunk 4 s + lane / 16:
-// the access shape of the GEMM's 16-row operand tiles, and the same conflict-free swizzle.
-__device__ __forceinline__ int vswz(int dd) {
-  return ((dd >> 1) & 1) | (((dd >> 2) & 1) << 2) | (((dd >> 3) & 1) << 1);
+template <int D> __device__ __forceinline__ int vswz(int row) { return D == 128 ? 4 * (row & 3) : 4 * ((row >> 1) & 1); }
+
+// 1 KiB from global memory straight to LDS: lane l's 16 bytes at base + off go to LDS byte dst + 16 l.  Written as an asm
+// statement because the compiler puts a wait for every load in flight in front of each transposed LDS read
+// when it sees the transfers (it cannot tell the tiles apart); attn_wait below counts them instead.  Nothing
+// here writes a register but m0, which the compiler allocates to nothing (reserved; no other use in this kernel).
+__device__ __forceinline__ void dma16(const char* base, uint32_t off, uint32_t dst) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
+               :: "s"(dst), "v"(off), "s"(base) : "memory");
+}
+
+// Wait for all but the newest n <= 2 tiles' loads of this wavefront (G instructions each; loads return in order) and
+// for its LDS reads.
+template <int G> __device__ __forceinline__ void attn_wait(int n) {
+  if (n >= 2) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(2 * G) : "memory");
+  else if (n == 1) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(G) : "memory");
+  else asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+}
+
+// Which (sequence, head, query block) this workgroup computes; false: none.  Workgroups run on XCD id % 8.  The
+// (sequence, head) pairs are dealt to the XCDs in turn, heads fastest, and an XCD takes the query blocks of a pair
+// behind each other, the one with the most keys first: the blocks that share K and V meet in their XCD's L2
+// (8 x 2048 tokens x 40 heads: 2.85 -> 0.22 GB fetched), and the heads that run at a time are neighbours in
+// the rows, which the HBM pages like (64 sequences of 64 tokens: 31 us with whole heads per XCD, 26 this way).
+// n_qblocks = 0 (packed, up to kAttnScan sequences, where max_len leaves a good part of the blocks without queries):
+// only blocks that have queries are counted, from a scan of the lengths by every wavefront, and the host launches an
+// upper bound.
+constexpr int kAttnScan = 256;
+
+// Sum over lanes 0 .. l in every lane l: shifts inside rows of 16 lanes, then the last lane of the row (of the half)
+// in front added to the rows behind it.
+__device__ __forceinline__ int32_t wave_inclusive_sum(int32_t v) {
+  v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xF, 0xF, false);   // row_shr 1, 2, 4, 8
+  v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xF, 0xF, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xF, 0xF, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xF, 0xF, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xA, 0xF, false);   // row_bcast 15 into rows 1 and 3
+  v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xC, 0xF, false);   // row_bcast 31 into rows 2 and 3
+  return v;
+}
+__device__ __forceinline__ bool attn_block(const int32_t* __restrict__ cu, int32_t B, int32_t nh, int32_t n_qblocks,
+                                           int lane, int32_t& b, int32_t& h, int32_t& qb, int32_t& c0, int32_t& len) {
+  const int32_t xcd = blockIdx.x % kXcds, j = blockIdx.x / kXcds;
+  if (n_qblocks > 0) {
+    const int32_t k = j / n_qblocks, pair = xcd + kXcds * k;
+    b = pair / nh;
+    if (b >= B) return false;
+    h = pair - b * nh;
+    qb = n_qblocks - 1 - (j - k * n_qblocks);
+    c0 = cu[b];
+    len = cu[b + 1] - c0;
+    return true;
+  }
+  // lane l: sequences per * l .. per * l + per - 1; a sequence counts its query blocks times its heads on this XCD
+  constexpr int kPer = kAttnScan / kWave;
+  const int32_t per = (B + kWave - 1) / kWave, first = lane * per;
+  int32_t at[kPer + 1], nb[kPer], w[kPer], mine = 0;
+  at[0] = cu[min(first, B)];
+#pragma unroll
+  for (int k = 0; k < kPer; ++k) at[k + 1] = k < per ? cu[min(first + k + 1, B)] : 0;
+#pragma unroll
+  for (int k = 0; k < kPer; ++k) {
+    nb[k] = k < per ? (at[k + 1] - at[k] + kBQ - 1) / kBQ : 0;
+    const int32_t p = (first + k) * nh + kXcds - 1 - xcd;
+    w[k] = nb[k] * ((p + nh) / kXcds - p / kXcds);
+    mine += w[k];
+  }
+  const int32_t incl = wave_inclusive_sum(mine);
+  if (j >= __builtin_amdgcn_readlane(incl, kWave - 1)) return false;
+  const int src = __popcll(__ballot(incl <= j));   // the lane whose sequences hold block j
+  int32_t r = j - __builtin_amdgcn_readlane(incl - mine, src);
+  b = src * per;
+#pragma unroll
+  for (int k = 0; k < kPer; ++k) {
+    const int32_t n = __builtin_amdgcn_readlane(w[k], src);
+    if (r < n) {
+      const int32_t blocks = __builtin_amdgcn_readlane(nb[k], src), i = r / blocks;
+      b += k;
+      h = ((xcd - b * nh) & (kXcds - 1)) + kXcds * i;
+      qb = blocks - 1 - (r - i * blocks);
+      c0 = __builtin_amdgcn_readlane(at[k], src);
+      len = __builtin_amdgcn_readlane(at[k + 1], src) - c0;
+      break;
+    }
+    r -= n;
+  }
+  return true;
 }
 
 // PADDED = false: Q, K, V are thirds of the packed [T, 3A] rows, the output is packed [T, A], and
@@ -49,273 +141,299 @@ __device__ __forceinline__ int vswz(int dd) {
 // Sec. 4.3): q, k, v, out are [B, nh, S, d] with zeros at the pads, all S queries are computed,
 // and a key is allowed iff it is <= the query and < len[b].
 template <typename E, int D, bool PADDED>
-__global__ __launch_bounds__(kAttnWaves * 64, 4) void attention_mfma_kernel(const E* __restrict__ qptr,
-                                                                          const E* __restrict__ kptr,
-                                                                          const E* __restrict__ vptr,
-                                                                          E* __restrict__ out,
-                                                                          const int32_t* __restrict__ cu, int32_t nh,
-                                                                          int32_t n_qblocks, int32_t n_pairs,
-                                                                          int32_t S) {
-  constexpr int KS = D / 32;        // 32-wide steps of the head dimension (S^T contraction)
-  constexpr int DB = D / 16;        // 16-row blocks of O^T
-  constexpr int KC = D / 8;         // 16-byte chunks per K row
-  constexpr int KROWS = 64 / KC;    // K rows moved by one direct-to-LDS instruction (1 KiB)
-  constexpr int KDMA = kBKV / KROWS / kAttnWaves;   // such instructions per wavefront and tile
-  constexpr int VLOADS = KC / kAttnWaves;           // 16-byte V chunks transposed per thread
-  constexpr int kTile = kBKV * D * 2 / 16;          // uint4 per K, V or V^T tile
-  // LDS: K tile of the even trips, K tile of the odd trips, the V tile as fetched, the V^T tile
-  static_assert(KDMA >= 1 && VLOADS >= 1, "head dimension too small for eight wavefronts");
-  extern __shared__ uint4 lds[];
+__global__ __launch_bounds__(kAttnWaves * 64, D == 128 ? 2 : 3) void attention_mfma_kernel(
+    const E* __restrict__ qptr, const E* __restrict__ kptr, const E* __restrict__ vptr, E* __restrict__ out,
+    const int32_t* __restrict__ cu, int32_t B, int32_t nh, int32_t n_qblocks, int32_t S) {
+  constexpr int KS = D / 16;                 // 16-wide steps of the head dimension (S^T contraction)
+  constexpr int DB = D / 32;                 // 32-row blocks of O^T
+  constexpr int KC = D / 8;                  // 16-byte chunks per row
+  constexpr int ROWS = 64 / KC;              // rows moved by one direct-to-LDS instruction (1 KiB)
+  constexpr int QDMA = kWQ / ROWS;           // such instructions for a wavefront's queries
+  constexpr int KDMA = kBKV / ROWS / kAttnWaves;   // per wavefront and K (or V) tile
+  constexpr int G = 2 * KDMA;                // per wavefront and stage
+  constexpr int kTile = kBKV * KC;           // 16-byte vectors per K or V tile
+  constexpr int kStage = 2 * kTile;
+  static_assert(KDMA >= 1, "a tile is at least one instruction per wavefront");
+  static_assert(kAttnWaves == 4 && kWQ == 32 && kBKV == 32 && kStages == 4, "the queries fill two stages, 8 rows a part");
+  extern __shared__ uint4 lds[];             // [kStages][K tile, V tile]
 
-  // Workgroups are handed out in id order: all pairs' last query block first (the one with the
-  // most keys), then the block before it, and so on, so that the long workgroups start early
-  // and the short ones fill the end (measured: 10 % faster than keeping a pair's blocks
-  // together, also when those share an L2).
-  const int32_t pair = blockIdx.x % n_pairs;
-  const int32_t b = pair / nh, h = pair % nh;
-  const int32_t qb = n_qblocks - 1 - blockIdx.x / n_pairs;
-  const int32_t c0 = cu[b], len = cu[b + 1] - c0;
+  const int tid = threadIdx.x, lane = tid & 63;
+  int32_t b, h, qb, c0, len;
+  if (!attn_block(cu, B, nh, n_qblocks, lane, b, h, qb, c0, len)) return;
   const int32_t q0 = qb * kBQ;
   const int32_t n_queries = PADDED ? S : len;   // queries of this sequence that are computed
   if (q0 >= n_queries) return;  // whole workgroup leaves before any barrier
 
-  const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int lq = lane & 15, g4 = lane >> 4;
+  const int lq = lane & 31, hf = lane >> 5;
   const int32_t A = nh * D;
   // row stride and first row of this (sequence, head) in each operand
   const size_t ld = PADDED ? (size_t)D : (size_t)3 * A;
-  const size_t first = PADDED ? (size_t)pair * S * D : (size_t)c0 * ld + (size_t)h * D;
-  const E* qbase = qptr + first;
-  const E* kbase = kptr + first;
-  const E* vbase = vptr + first;
+  const size_t first = PADDED ? ((size_t)b * nh + h) * S * D : (size_t)c0 * ld + (size_t)h * D;
 
-  const int32_t wq_first = q0 + 16 * wave, wq_last = wq_first + 15;
+  const int32_t wq_first = q0 + kWQ * wave, wq_last = wq_first + kWQ - 1;
   const int32_t qi = wq_first + lq;
-  const int32_t qc = qi < n_queries ? qi : n_queries - 1;
-
-  vec8<E> qf[KS];
-#pragma unroll
-  for (int ks = 0; ks < KS; ++ks) qf[ks] = *reinterpret_cast<const vec8<E>*>(qbase + (size_t)qc * ld + ks * 32 + 8 * g4);
-
   const int32_t kv_end = min(q0 + kBQ, len);           // keys 0 .. kv_end-1 are needed
   const int32_t n_tiles = (kv_end + kBKV - 1) / kBKV;
 
-  f32x4 oacc[DB];
-#pragma unroll
-  for (int i = 0; i < DB; ++i) oacc[i] = f32x4{0.f, 0.f, 0.f, 0.f};
-  float m_run = -INFINITY, l_run = 0.f;        // running max in log2 units (already scaled), running sum
-  const float sc = rsqrtf((float)D) * kLog2e;  // raw score -> log2 units
-
   // Addresses inside this (sequence, head): a wavefront-uniform base plus a 32-bit byte offset
   // (the launcher checks that S rows fit in 32 bits).
-  const char* kbytes = reinterpret_cast<const char*>(kbase);
-  const char* vbytes = reinterpret_cast<const char*>(vbase);
+  const char* qbytes = reinterpret_cast<const char*>(qptr + first);
+  const char* kbytes = reinterpret_cast<const char*>(kptr + first);
+  const char* vbytes = reinterpret_cast<const char*>(vptr + first);
   const uint32_t ld_b = (uint32_t)(ld * sizeof(E));
-  // this lane's part of a K tile transfer: row kr of the instruction's KROWS rows, LDS slot ksl
-  const int kr = lane / KC, ksl = lane % KC;
-  uint32_t kcol[KDMA];   // byte offset of the chunk this lane fetches, inside its row
+  // this lane's part of a transfer: row lr of the instruction's ROWS rows, LDS slot sl of that row
+  const int lr = lane / KC, sl = lane % KC;
+  uint32_t kcol[KDMA], vcol[KDMA];   // byte offset of the chunk this lane fetches, inside its row
 #pragma unroll
-  for (int i = 0; i < KDMA; ++i) kcol[i] = (uint32_t)((ksl ^ kswz<D>((wave * KDMA + i) * KROWS + kr)) * 16);
-  // V: the wavefront fetches rows 8 w .. 8 w + 7 of the tile (the same row groups as for K, swizzled by
-  // the row's low three bits) and later reads them back itself: the lane takes key 8 w + lane % 8 and,
-  // per read, the chunk c of 8 consecutive dd chosen so that 16 neighbouring lanes cover all 64 banks
-  // (D = 128: the two halves of a row alternate every 8 lanes).  With its neighbour (key ^ 1, same
-  // chunk) it forms, per dd, the 32-bit word (even key, odd key): even lanes write dd 0, 2, 4, 6 of the
-  // chunk, odd lanes dd 1, 3, 5, 7; one byte permute builds the word.
-  uint32_t vcol[KDMA];   // byte offset of the chunk this lane fetches, inside its row
+  for (int i = 0; i < KDMA; ++i) {
+    const int row = (wave * KDMA + i) * ROWS + lr;
+    kcol[i] = (uint32_t)((sl ^ kswz<D>(row)) * 16);
+    vcol[i] = (uint32_t)((sl ^ vswz<D>(row)) * 16);
+  }
+  const uint32_t lds0 = (uint32_t)(uintptr_t)(attn_lptr_t)lds;   // LDS byte address of the ring
+  auto issue = [&](int32_t t) {   // K and V rows of tile t into its stage; keys past the end read the last row
+    const uint32_t st = lds0 + (uint32_t)(t % kStages) * (kStage * 16);
 #pragma unroll
-  for (int i = 0; i < KDMA; ++i) vcol[i] = (uint32_t)((ksl ^ (((wave * KDMA + i) * KROWS + kr) & 7)) * 16);
-  const int vkey = wave * 8 + (lane & 7), odd = lane & 1;
-  const int kp = vkey >> 1;
-  const uint32_t vsel = odd ? 0x03020706u : 0x05040100u;   // v_perm_b32 selector, bytes of {partner, own}
-  uint32_t vsrc[VLOADS];     // uint4 index of the read inside the fetched V tile
-  uint32_t vdst[VLOADS][4];  // word index of the store inside the V^T tile
-#pragma unroll
-  for (int j = 0; j < VLOADS; ++j) {
-    const int c = KC == 16 ? 8 * ((lane >> 3) & 1) + (lane >> 4) + 4 * j : (lane >> 3);
-    vsrc[j] = (uint32_t)(vkey * KC + (c ^ (vkey & 7)));
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const int dd = c * 8 + 2 * e + odd;
-      // key pair kp = 16 s + 8 h + 2 g + i (keys 32 s + 16 h + 4 g + 2 i, + 1) goes to 16-byte chunk
-      // 4 s + g of the row, word 2 h + i of the chunk
-      const int chunk = 4 * (kp >> 4) + ((kp >> 1) & 3), word = 2 * ((kp >> 3) & 1) + (kp & 1);
-      vdst[j][e] = (uint32_t)(dd * 32 + ((chunk ^ vswz(dd)) * 4) + word);
+    for (int i = 0; i < KDMA; ++i) {
+      const int32_t row = (wave * KDMA + i) * ROWS;
+      int32_t key = t * kBKV + row + lr; key = key < len ? key : len - 1;
+      dma16(kbytes, (uint32_t)key * ld_b + kcol[i], st + row * (KC * 16));
+      dma16(vbytes, (uint32_t)key * ld_b + vcol[i], st + (kTile + row * KC) * 16);
     }
+  };
+
+  // Prologue: the wavefront's queries go through the parts of the last two stages that its own loads of tiles 2
+  // and 3 will fill (8 rows of each K and V tile; whole lines, the K tile's swizzle), so they are free for those
+  // as soon as this wavefront has read its queries.
+  auto q_vec = [&](int row) { return (2 + (row >> 4)) * kStage + ((row >> 3) & 1) * kTile + (wave * 8 + (row & 7)) * KC; };
+#pragma unroll
+  for (int i = 0; i < QDMA; ++i) {
+    const int32_t row = i * ROWS + lr;
+    const int32_t qc = min(wq_first + row, n_queries - 1);
+    dma16(qbytes, (uint32_t)qc * ld_b + (uint32_t)((sl ^ kswz<D>(row)) * 16), lds0 + (uint32_t)q_vec(i * ROWS) * 16);
+  }
+#pragma unroll
+  for (int t = 0; t < 2; ++t)
+    if (t < n_tiles) issue(t);
+
+  f32x16 oacc[DB];
+#pragma unroll
+  for (int i = 0; i < DB; ++i)
+#pragma unroll
+    for (int e = 0; e < 16; ++e) oacc[i][e] = 0.f;
+  float m_run = -INFINITY, l_run = 0.f;        // reference in log2 units (already scaled), running sum
+  const float sc = rsqrtf((float)D) * kLog2e;  // raw score -> log2 units
+
+  uint32_t koff[KS], voff[DB];   // this lane's operand reads: 16-byte vectors of the K tile, bytes of the V tile
+#pragma unroll
+  for (int ks = 0; ks < KS; ++ks) koff[ks] = (uint32_t)(lq * KC + ((2 * ks + hf) ^ kswz<D>(lq)));
+  {
+    // V is read transposed: in each group of 16 lanes, lane i gives the address of 4 elements, key row i / 4,
+    // and receives column i of the 4 x 16 block.  Group g: dd 16 (g & 1) .., keys 4 (g >> 1) ..
+    const int row = 4 * hf + ((lane & 15) >> 2), c = 2 * ((lane >> 4) & 1) + ((lane & 3) >> 1);
+#pragma unroll
+    for (int i = 0; i < DB; ++i) voff[i] = (uint32_t)((row * KC + ((4 * i + c) ^ vswz<D>(row))) * 16 + (lane & 1) * 8);
   }
 
-  // Tile t+1 is fetched while tile t is consumed: K into the other K buffer (free since the barrier
-  // that ended the previous trip), V into the one buffer for fetched V tiles (its previous content
-  // was transposed out before that barrier).  After the arithmetic and a barrier (V^T(t) is no longer
-  // read) every wavefront waits for its own loads, transposes its eight V rows into the V^T tile,
-  // and a second barrier publishes K(t+1) and V^T(t+1).  The loop starts at t = -1 (fetch tile 0,
-  // nothing to consume) and ends after the arithmetic of the last tile.
-  uint4* const vraw = lds + 2 * kTile;
-  uint32_t* const vt_words = reinterpret_cast<uint32_t*>(lds + 3 * kTile);
-  for (int32_t t = n_tiles > 0 ? -1 : 0; t < n_tiles; ++t) {  // no tile at all: an empty sequence on the padded path
-    const bool more = t + 1 < n_tiles;   // workgroup-uniform: there is a tile to fetch
-    if (more) {
-      uint4* ks_next = lds + ((t + 1) & 1) * kTile;
+  vec8<E> qf[KS];
+  attn_wait<G>(min(2, n_tiles));   // the queries
 #pragma unroll
-      for (int i = 0; i < KDMA; ++i) {
-        int32_t key = (t + 1) * kBKV + (wave * KDMA + i) * KROWS + kr; key = key < len ? key : len - 1;
-        __builtin_amdgcn_global_load_lds((attn_gptr_t)(kbytes + ((uint32_t)key * ld_b + kcol[i])),
-                                         (attn_lptr_t)(ks_next + (wave * KDMA + i) * 64), 16, 0, 0);
-        __builtin_amdgcn_global_load_lds((attn_gptr_t)(vbytes + ((uint32_t)key * ld_b + vcol[i])),
-                                         (attn_lptr_t)(vraw + (wave * KDMA + i) * 64), 16, 0, 0);
-      }
+  for (int ks = 0; ks < KS; ++ks) qf[ks] = *reinterpret_cast<const vec8<E>*>(&lds[q_vec(lq) + ((2 * ks + hf) ^ kswz<D>(lq))]);
+  attn_wait<G>(min(2, n_tiles));   // read
+#pragma unroll
+  for (int t = 2; t < 4; ++t)
+    if (t < n_tiles) issue(t);
+
+  // Tiles are worked on in pairs, so that the running max, the rescaling of the accumulators (nearly always due:
+  // some query of 32 has a new max) and the barrier come once per 64 keys.  At the start of a pair: it has landed
+  // (this wavefront's part) and this wavefront's reads of the pair before are back; past the barrier that holds
+  // for every wavefront, so the stages of the pair before are free for the next one.
+  auto advance = [&](int32_t t) {
+    attn_wait<G>(t == 0 ? max(0, min(2, n_tiles - 2)) : 0);
+    __builtin_amdgcn_s_barrier();
+    if (t > 0) {
+#pragma unroll
+      for (int i = 2; i < 4; ++i)
+        if (t + i < n_tiles) issue(t + i);
     }
+  };
+  // N = 2: tiles t, t + 1; N = 1: tile t only (the other one is above this wavefront's diagonal or past the end).
+  // The second tile's K operands are read while the matrix cores work on the first, the V operands during the softmax.
+  auto work = [&](auto n, int32_t t) {
+    constexpr int N = decltype(n)::value;
     const int32_t k0 = t * kBKV;
-    if (t >= 0 && k0 <= wq_last) {  // wavefront-uniform: the tile is not wholly above this wavefront's diagonal
-      const uint4* ks = lds + (t & 1) * kTile;
-      const char* vt = reinterpret_cast<const char*>(vt_words);
-      f32x4 sacc[4];
+    const uint4* const st0 = lds + (t & 2) * kStage;   // t is even: the pair's stages are adjacent
+    vec8<E> kf[KS];
 #pragma unroll
-      for (int kb = 0; kb < 4; ++kb) {
-        sacc[kb] = f32x4{0.f, 0.f, 0.f, 0.f};
-        const int row = kb * 16 + lq;
+    for (int ks = 0; ks < KS; ++ks) kf[ks] = *reinterpret_cast<const vec8<E>*>(&st0[koff[ks]]);
+    f32x16 sacc[N];
+    vec8<E> k2[KS];
 #pragma unroll
-        for (int s = 0; s < KS; ++s) {
-          const vec8<E> kf = *reinterpret_cast<const vec8<E>*>(&ks[row * KC + ((s * 4 + g4) ^ kswz<D>(row))]);
-          sacc[kb] = Mfma<E>::m16x16x32(kf, qf[s], sacc[kb]);
-        }
-      }
-      // Mask (only on tiles that touch the diagonal or, on the padded path, the end of the
-      // sequence: wavefront-uniform), then the tile max of the raw scores.  Packed: the causal
-      // mask also hides keys >= len (they are > every real query).  Padded: pad queries lie beyond
-      // len, so keys >= len are masked explicitly.
-      if (k0 + kBKV - 1 > wq_first || (PADDED && k0 + kBKV > len)) {
+    for (int a = 0; a < N; ++a)
 #pragma unroll
-        for (int kb = 0; kb < 4; ++kb)
+      for (int e = 0; e < 16; ++e) sacc[a][e] = 0.f;
+    if constexpr (N == 2) {
 #pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            const int32_t key = k0 + kb * 16 + g4 * 4 + e;
-            if (key > qi || (PADDED && key >= len)) sacc[kb][e] = -INFINITY;
-          }
-      }
-      float mx = fmaxf(fmaxf(sacc[0][0], sacc[0][1]), fmaxf(sacc[0][2], sacc[0][3]));
+      for (int ks = 0; ks < KS; ++ks) k2[ks] = *reinterpret_cast<const vec8<E>*>(&st0[kStage + koff[ks]]);
+    }
 #pragma unroll
-      for (int kb = 1; kb < 4; ++kb)
+    for (int ks = 0; ks < KS; ++ks) sacc[0] = Mfma<E>::m32x32x16(kf[ks], qf[ks], sacc[0]);
+    if constexpr (N == 2) {
 #pragma unroll
-        for (int e = 0; e < 4; ++e) mx = fmaxf(mx, sacc[kb][e]);
-      // the query's max over the four lane groups that hold its keys: exchange with lane ^ 16, then
-      // lane ^ 32 (v_permlane16_swap / v_permlane32_swap of a value with itself leave own and
-      // partner's value in the two results)
-      {
-        const auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(mx), __float_as_uint(mx), false, false);
-        mx = fmaxf(__uint_as_float(a[0]), __uint_as_float(a[1]));
-        const auto b = __builtin_amdgcn_permlane32_swap(__float_as_uint(mx), __float_as_uint(mx), false, false);
-        mx = fmaxf(__uint_as_float(b[0]), __uint_as_float(b[1]));
-      }
-      const float m_new = fmaxf(m_run, mx * sc);   // finite from tile 0 on: key 0 <= every query (sc > 0)
-      const bool rescale = __any(m_new != m_run);  // wavefront-uniform
-      const float corr = __builtin_amdgcn_exp2f(m_run - m_new);
-      float psum = 0.f;
-      vec8<E> pf[2];
+      for (int ks = 0; ks < KS; ++ks) sacc[1] = Mfma<E>::m32x32x16(k2[ks], qf[ks], sacc[1]);
+    }
+    vec4<E> vf[N][2][DB][2];
 #pragma unroll
-      for (int kb = 0; kb < 4; ++kb)
+    for (int a = 0; a < N; ++a)
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const float p = __builtin_amdgcn_exp2f(fmaf(sacc[kb][e], sc, -m_new));
-          psum += p;
-          pf[kb >> 1][(kb & 1) * 4 + e] = static_cast<E>(p);
-        }
-      l_run = l_run * corr + psum;
-      m_run = m_new;
-      if (rescale) {
+      for (int s = 0; s < 2; ++s)
 #pragma unroll
         for (int i = 0; i < DB; ++i)
 #pragma unroll
-          for (int e = 0; e < 4; ++e) oacc[i][e] *= corr;
-      }
-      // O^T += V^T P^T ; step s, lane group g4: keys 32 s + {4 g4 .. 4 g4 + 3, 16 + 4 g4 .. 16 + 4 g4 + 3},
-      // adjacent in the V^T row by construction
+          for (int j = 0; j < 2; ++j)
+            vf[a][s][i][j] = Mfma<E>::read_tr((attn_lptr_t)(st0 + a * kStage + kTile), voff[i] + (16 * s + 8 * j) * (D * 2));
+    __builtin_amdgcn_sched_barrier(0);
+    // Mask (only on tiles that touch the diagonal or, on the padded path, the end of the
+    // sequence: wavefront-uniform), then the max of the raw scores.  Packed: the causal
+    // mask also hides keys >= len (they are > every real query).  Padded: pad queries lie beyond
+    // len, so keys >= len are masked explicitly.
+    if (k0 + N * kBKV - 1 > wq_first || (PADDED && k0 + N * kBKV > len)) {
 #pragma unroll
-      for (int s = 0; s < 2; ++s) {
+      for (int a = 0; a < N; ++a)
 #pragma unroll
-        for (int i = 0; i < DB; ++i) {
-          const int dd = i * 16 + lq;
-          union { uint4 u; vec8<E> v; } vf;
-          vf.u = *reinterpret_cast<const uint4*>(vt + dd * 128 + (((4 * s + g4) ^ vswz(dd)) * 16));
-          oacc[i] = Mfma<E>::m16x16x32(vf.v, pf[s], oacc[i]);
+        for (int e = 0; e < 16; ++e) {
+          const int32_t key = k0 + a * kBKV + 8 * (e >> 2) + 4 * hf + (e & 3);
+          if (key > qi || (PADDED && key >= len)) sacc[a][e] = -INFINITY;
         }
-      }
     }
-    if (!more) break;                    // the last tile: nothing was fetched, nothing to publish
-    if (t >= 0) __syncthreads();         // V^T(t) is no longer read
-    __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): this wavefront's K and V rows have landed in LDS
-    asm volatile("" ::: "memory");       // the reads below must stay behind that wait
+    float mx = sacc[0][0];
 #pragma unroll
-    for (int j = 0; j < VLOADS; ++j) {
-      const uint4 v = vraw[vsrc[j]];
+    for (int a = 0; a < N; ++a)
 #pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const uint32_t we = e == 0 ? v.x : e == 1 ? v.y : e == 2 ? v.z : v.w;
-        // the neighbour lane's word (lane ^ 1 inside each quad: quad_perm [1, 0, 3, 2])
-        const uint32_t p = (uint32_t)__builtin_amdgcn_mov_dpp((int)we, 0xB1, 0xF, 0xF, true);
-        vt_words[vdst[j][e]] = __builtin_amdgcn_perm(p, we, vsel);
-      }
+      for (int e = 0; e < 16; ++e) mx = fmaxf(mx, sacc[a][e]);
+    {  // the query's other keys are in lane ^ 32
+      const auto o = __builtin_amdgcn_permlane32_swap(__float_as_uint(mx), __float_as_uint(mx), false, false);
+      mx = fmaxf(__uint_as_float(o[0]), __uint_as_float(o[1]));
     }
-    __syncthreads();                     // K(t+1) and V^T(t+1) are complete
+    const float m_new = fmaxf(m_run, mx * sc);   // finite from tile 0 on: key 0 <= every query (sc > 0)
+    const float corr = __builtin_amdgcn_exp2f(m_run - m_new);
+    float psum[2] = {0.f, 0.f};
+    vec8<E> pf[N][2];
+#pragma unroll
+    for (int a = 0; a < N; ++a)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) {
+        const float p = __builtin_amdgcn_exp2f(fmaf(sacc[a][e], sc, -m_new));
+        psum[e & 1] += p;
+        pf[a][e >> 3][e & 7] = static_cast<E>(p);
+      }
+    l_run = l_run * corr + (psum[0] + psum[1]);
+    if (__any(m_new != m_run)) {                 // wavefront-uniform
+#pragma unroll
+      for (int i = 0; i < DB; ++i)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) oacc[i][e] *= corr;
+    }
+    m_run = m_new;
+    // O^T += V^T P^T; step s: element j of lane half hf is key 16 s + 8 (j / 4) + 4 hf + j % 4, as in the accumulator
+#pragma unroll
+    for (int a = 0; a < N; ++a)
+#pragma unroll
+      for (int s = 0; s < 2; ++s)
+#pragma unroll
+        for (int i = 0; i < DB; ++i)
+          oacc[i] = Mfma<E>::m32x32x16(__builtin_shufflevector(vf[a][s][i][0], vf[a][s][i][1], 0, 1, 2, 3, 4, 5, 6, 7),
+                                       pf[a][s], oacc[i]);
+  };
+  const int32_t n_mine = min(n_tiles, wq_last / kBKV + 1);   // tiles at or below this wavefront's diagonal
+  int32_t t = 0;
+  for (; t + 1 < n_mine; t += 2) {
+    advance(t);
+    work(std::integral_constant<int, 2>{}, t);
   }
+  if (t < n_mine) {
+    advance(t);
+    work(std::integral_constant<int, 1>{}, t);
+    t += 2;
+  }
+  for (; t < n_tiles; t += 2) advance(t);   // pairs above the diagonal: the other wavefronts' loads and barriers
 
-  float l_tot = l_run + __shfl_xor(l_run, 16, 64);
-  l_tot += __shfl_xor(l_tot, 32, 64);
-  if (qi < n_queries) {
-    const float inv = n_tiles > 0 ? 1.0f / l_tot : 0.f;   // no allowed key at all (len = 0): a zero row
-    E* orow = PADDED ? out + first + (size_t)qi * D : out + (size_t)(c0 + qi) * A + (size_t)h * D;
+  // Results leave through LDS as whole rows (straight from the accumulators a store would write 16 bytes of
+  // each of 32 rows).  Every wavefront uses a part of its own, without a barrier: other wavefronts may still be
+  // reading the last pair of tiles, so the parts lie in the other pair's stages.
+  const float l_tot = l_run + __shfl_xor(l_run, 32, 64);
+  const float inv = n_tiles > 0 ? 1.0f / l_tot : 0.f;   // no allowed key at all (len = 0): a zero row
+  char* const os = reinterpret_cast<char*>(lds + ((((n_tiles - 1) & 2) ^ 2) + (wave >> 1)) * kStage + (wave & 1) * kTile);
 #pragma unroll
-    for (int i = 0; i < DB; ++i) {
+  for (int i = 0; i < DB; ++i)
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {   // dd 32 i + 8 j + 4 hf .. + 3 of query lq
       vec4<E> o4;
 #pragma unroll
-      for (int e = 0; e < 4; ++e) o4[e] = static_cast<E>(oacc[i][e] * inv);
-      *reinterpret_cast<vec4<E>*>(orow + i * 16 + g4 * 4) = o4;
+      for (int e = 0; e < 4; ++e) o4[e] = static_cast<E>(oacc[i][4 * j + e] * inv);
+      *reinterpret_cast<vec4<E>*>(os + (lq * KC + ((4 * i + j) ^ kswz<D>(lq))) * 16 + 8 * hf) = o4;
     }
+  const size_t old = PADDED ? (size_t)D : (size_t)A;
+  E* const obase = (PADDED ? out + first : out + (size_t)c0 * A + (size_t)h * D) + (size_t)(wq_first + lr) * old + sl * 8;
+  uint4 ov[QDMA];
+#pragma unroll
+  for (int i = 0; i < QDMA; ++i) ov[i] = *reinterpret_cast<const uint4*>(os + ((i * ROWS + lr) * KC + (sl ^ kswz<D>(i * ROWS + lr))) * 16);
+  if (wq_last < n_queries) {
+#pragma unroll
+    for (int i = 0; i < QDMA; ++i) *reinterpret_cast<uint4*>(obase + (size_t)(i * ROWS) * old) = ov[i];
+  } else {
+#pragma unroll
+    for (int i = 0; i < QDMA; ++i)
+      if (wq_first + i * ROWS + lr < n_queries) *reinterpret_cast<uint4*>(obase + (size_t)(i * ROWS) * old) = ov[i];
   }
 }
 
 template <typename E, int D, bool PADDED>
-static hipError_t launch_d(const E* q, const E* k, const E* v, E* out, const int32_t* cu, int32_t B, int32_t max_len,
-                           int32_t nh, hipStream_t s) {
+static hipError_t launch_d(const E* q, const E* k, const E* v, E* out, const int32_t* cu, int64_t T, int32_t B,
+                           int32_t max_len, int32_t nh, hipStream_t s) {
   auto kern = attention_mfma_kernel<E, D, PADDED>;
-  constexpr size_t lds = 4 * (size_t)(kBKV * D * 2);   // two K tiles, the fetched V tile, the V^T tile
+  constexpr size_t lds = kStages * 2 * (size_t)(kBKV * D * 2);
   static LdsAttrOnce once;
   {
     hipError_t e = ensure_dynamic_lds(reinterpret_cast<const void*>(kern), lds, once);
     if (e != hipSuccess) return e;
   }
   const int32_t n_qblocks = (max_len + kBQ - 1) / kBQ;
-  const int32_t n_pairs = B * nh;
-  const int64_t grid = (int64_t)n_pairs * n_qblocks;
-  kern<<<dim3((unsigned)grid), dim3(kAttnWaves * 64), lds, s>>>(q, k, v, out, cu, nh, n_qblocks, n_pairs, max_len);
+  // blocks per XCD: pairs x blocks of max_len, or the bound sum of ceil(len / kBQ) <= T / kBQ + B per head where
+  // that is at least a fifth less (the scan costs a workgroup about half a microsecond)
+  const int64_t n_pairs = (int64_t)B * nh, all = (n_pairs + kXcds - 1) / kXcds * n_qblocks;
+  const int64_t bound = (T / kBQ + B) * ((nh + kXcds - 1) / kXcds);
+  const bool scan = !PADDED && B <= kAttnScan && 5 * bound <= 4 * all;
+  const int64_t grid = (scan ? bound : all) * kXcds;
+  kern<<<dim3((unsigned)grid), dim3(kAttnWaves * 64), lds, s>>>(q, k, v, out, cu, B, nh, scan ? 0 : n_qblocks, max_len);
   return hipGetLastError();
 }
 
 template <typename E>
-static hipError_t launch_packed(const E* qkv, E* out, const int32_t* cu, int32_t B, int32_t max_len, int32_t nh,
-                                int32_t d, hipStream_t s) {
+static hipError_t launch_packed(const E* qkv, E* out, const int32_t* cu, int64_t T, int32_t B, int32_t max_len,
+                                int32_t nh, int32_t d, hipStream_t s) {
   if (B <= 0 || max_len <= 0) return hipSuccess;
   const size_t A = (size_t)nh * d;
-  return d == 128 ? launch_d<E, 128, false>(qkv, qkv + A, qkv + 2 * A, out, cu, B, max_len, nh, s)
-                  : launch_d<E, 64, false>(qkv, qkv + A, qkv + 2 * A, out, cu, B, max_len, nh, s);
+  return d == 128 ? launch_d<E, 128, false>(qkv, qkv + A, qkv + 2 * A, out, cu, T, B, max_len, nh, s)
+                  : launch_d<E, 64, false>(qkv, qkv + A, qkv + 2 * A, out, cu, T, B, max_len, nh, s);
 }
 
 template <typename E>
 static hipError_t launch_padded(const E* q, const E* k, const E* v, E* out, const int32_t* cu, int32_t B, int32_t S,
                                 int32_t nh, int32_t d, hipStream_t s) {
   if (B <= 0 || S <= 0) return hipSuccess;
-  return d == 128 ? launch_d<E, 128, true>(q, k, v, out, cu, B, S, nh, s)
-                  : launch_d<E, 64, true>(q, k, v, out, cu, B, S, nh, s);
+  return d == 128 ? launch_d<E, 128, true>(q, k, v, out, cu, 0, B, S, nh, s)
+                  : launch_d<E, 64, true>(q, k, v, out, cu, 0, B, S, nh, s);
 }
 
-hipError_t launch_attention_bf16(const bf16_t* qkv, bf16_t* out, const int32_t* cu, int32_t B, int32_t max_len,
-                                 int32_t nh, int32_t d, hipStream_t s) {
-  return launch_packed<bf16_t>(qkv, out, cu, B, max_len, nh, d, s);
+hipError_t launch_attention_bf16(const bf16_t* qkv, bf16_t* out, const int32_t* cu, int64_t T, int32_t B,
+                                 int32_t max_len, int32_t nh, int32_t d, hipStream_t s) {
+  return launch_packed<bf16_t>(qkv, out, cu, T, B, max_len, nh, d, s);
 }
-hipError_t launch_attention_f16(const f16_t* qkv, f16_t* out, const int32_t* cu, int32_t B, int32_t max_len, int32_t nh,
-                                int32_t d, hipStream_t s) {
-  return launch_packed<f16_t>(qkv, out, cu, B, max_len, nh, d, s);
+hipError_t launch_attention_f16(const f16_t* qkv, f16_t* out, const int32_t* cu, int64_t T, int32_t B,
+                                int32_t max_len, int32_t nh, int32_t d, hipStream_t s) {
+  return launch_packed<f16_t>(qkv, out, cu, T, B, max_len, nh, d, s);
 }
 hipError_t launch_attention_padded_bf16(const bf16_t* q, const bf16_t* k, const bf16_t* v, bf16_t* out,
                                         const int32_t* cu, int32_t B, int32_t S, int32_t nh, int32_t d, hipStream_t s) {

@@ -54,6 +54,16 @@ template <> struct Elem<f16_t> {
   __device__ static inline f16_t from_f32(float v) { return static_cast<f16_t>(v); }  // RNE
 };
 
+typedef __attribute__((address_space(3))) void* lds_ptr_t;
+
+// Transposed LDS read (ds_read_b64_tr_b16).  In each group of 16 lanes, lane i gives the address of four consecutive
+// 16-bit elements, columns 4 (i % 4) .. + 3 of row i / 4 of a 4 x 16 block, and receives column i of the block.
+typedef short s16x4 __attribute__((ext_vector_type(4)));
+__device__ inline s16x4 lds_read_tr16(lds_ptr_t base, uint32_t off) {
+  typedef __attribute__((address_space(3))) s16x4* p;
+  return __builtin_amdgcn_ds_read_tr16_b64_v4i16((p)((__attribute__((address_space(3))) char*)base + off));
+}
+
 // The two 16-bit MFMA forms of gfx950 for an element type (bf16 or fp16), fp32 accumulation.
 template <typename E> struct Mfma;
 template <> struct Mfma<bf16_t> {
@@ -63,6 +73,9 @@ template <> struct Mfma<bf16_t> {
   __device__ static inline f32x4 m16x16x32(vec8<bf16_t> a, vec8<bf16_t> b, f32x4 c) {
     return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
   }
+  __device__ static inline vec4<bf16_t> read_tr(lds_ptr_t base, uint32_t off) {
+    return __builtin_bit_cast(vec4<bf16_t>, lds_read_tr16(base, off));
+  }
 };
 template <> struct Mfma<f16_t> {
   __device__ static inline f32x16 m32x32x16(vec8<f16_t> a, vec8<f16_t> b, f32x16 c) {
@@ -70,6 +83,9 @@ template <> struct Mfma<f16_t> {
   }
   __device__ static inline f32x4 m16x16x32(vec8<f16_t> a, vec8<f16_t> b, f32x4 c) {
     return __builtin_amdgcn_mfma_f32_16x16x32_f16(a, b, c, 0, 0, 0);
+  }
+  __device__ static inline vec4<f16_t> read_tr(lds_ptr_t base, uint32_t off) {
+    return __builtin_bit_cast(vec4<f16_t>, lds_read_tr16(base, off));
   }
 };
 
@@ -209,11 +225,11 @@ hipError_t launch_merge_partials(const float* partial, int64_t M, int32_t P, flo
 // attention_f32.hip / attention_mfma.hip
 hipError_t launch_attention_f32(const float* qkv, float* out, const int32_t* cu, int32_t B, int32_t max_len,
                                 int32_t nh, int32_t d, hipStream_t s);
-hipError_t launch_attention_bf16(const bf16_t* qkv, bf16_t* out, const int32_t* cu, int32_t B, int32_t max_len,
-                                 int32_t nh, int32_t d, hipStream_t s);
-
-hipError_t launch_attention_f16(const f16_t* qkv, f16_t* out, const int32_t* cu, int32_t B, int32_t max_len,
-                                int32_t nh, int32_t d, hipStream_t s);
+// T: rows of qkv (>= cu[B]; bounds the launch, the work follows cu)
+hipError_t launch_attention_bf16(const bf16_t* qkv, bf16_t* out, const int32_t* cu, int64_t T, int32_t B,
+                                 int32_t max_len, int32_t nh, int32_t d, hipStream_t s);
+hipError_t launch_attention_f16(const f16_t* qkv, f16_t* out, const int32_t* cu, int64_t T, int32_t B,
+                                int32_t max_len, int32_t nh, int32_t d, hipStream_t s);
 hipError_t launch_attention_padded_bf16(const bf16_t* q, const bf16_t* k, const bf16_t* v, bf16_t* out,
                                         const int32_t* cu, int32_t B, int32_t S, int32_t nh, int32_t d, hipStream_t s);
 hipError_t launch_attention_padded_f16(const f16_t* q, const f16_t* k, const f16_t* v, f16_t* out,

@@ -90,12 +90,12 @@ int linear_impl(const void* x, const void* w, const void* bias, const void* res,
   return ENERGON_OK;
 }
 
-int attention_impl(const void* qkv, void* out, const int32_t* cu, int32_t B, int32_t max_len, int32_t nh, int32_t d,
-                   int32_t dt, hipStream_t s) {
+int attention_impl(const void* qkv, void* out, const int32_t* cu, int64_t T, int32_t B, int32_t max_len, int32_t nh,
+                   int32_t d, int32_t dt, hipStream_t s) {
   if (dt == ENERGON_BF16)
-    HIP_TRY(launch_attention_bf16((const bf16_t*)qkv, (bf16_t*)out, cu, B, max_len, nh, d, s));
+    HIP_TRY(launch_attention_bf16((const bf16_t*)qkv, (bf16_t*)out, cu, T, B, max_len, nh, d, s));
   else if (dt == ENERGON_F16)
-    HIP_TRY(launch_attention_f16((const f16_t*)qkv, (f16_t*)out, cu, B, max_len, nh, d, s));
+    HIP_TRY(launch_attention_f16((const f16_t*)qkv, (f16_t*)out, cu, T, B, max_len, nh, d, s));
   else
     HIP_TRY(launch_attention_f32((const float*)qkv, (float*)out, cu, B, max_len, nh, d, s));
   return ENERGON_OK;
@@ -166,7 +166,7 @@ int layer_impl(const EnergonLayerConfig* cfg, const EnergonLayerWeights* w, cons
   STEP(linear_impl(u, w->w_qkv, w->b_qkv, nullptr, qkv, T, 3 * A, H, ENERGON_EPI_BIAS, dt, s, nullptr, gemm_scratch(3 * A, H)));
   MARK(2);
   if (T > 0 && padws == nullptr) {
-    STEP(attention_impl(qkv, att, cu, B, max_len, cfg->n_heads, cfg->head_dim, dt, s));
+    STEP(attention_impl(qkv, att, cu, T, B, max_len, cfg->n_heads, cfg->head_dim, dt, s));
   } else if (T > 0) {
     const size_t part = (size_t)B * max_len * A * esize(dt);
     char* pb = static_cast<char*>(padws);
@@ -234,7 +234,7 @@ int layer_folded_impl(const EnergonLayerConfig* cfg, const EnergonFoldedLayerWei
   LnFold f1;
   f1.stats = stats_in; f1.colsum = w->c_qkv; f1.bias = w->bf_qkv;
   STEP(linear_impl(x, w->wf_qkv, nullptr, nullptr, qkv, T, 3 * A, H, EPI_LNFOLD, dt, s, &f1));
-  if (T > 0) STEP(attention_impl(qkv, att, cu, B, max_len, cfg->n_heads, cfg->head_dim, dt, s));
+  if (T > 0) STEP(attention_impl(qkv, att, cu, T, B, max_len, cfg->n_heads, cfg->head_dim, dt, s));
   STEP(linear_residual_stats(att, w->w_o, w->b_o, x, y1, T, H, A, dt, cfg->ln_eps, stats2, partials, s));
   LnFold f2;
   f2.stats = stats2; f2.colsum = w->c_fc1; f2.bias = w->bf_fc1;
@@ -601,7 +601,7 @@ int energon_attention(const void* qkv, void* out, const int32_t* cu, int64_t T, 
   if ((int64_t)max_len * 3 * n_heads * head_dim * esize(dtype) >= ((int64_t)1 << 32)) return ENERGON_ERR_UNSUPPORTED;
   if (!aligned16(qkv) || !aligned16(out) || (reinterpret_cast<uintptr_t>(cu) & 3u)) return ENERGON_ERR_ALIGN;
   if (T == 0) return ENERGON_OK;
-  return attention_impl(qkv, out, cu, B, max_len, n_heads, head_dim, dtype, static_cast<hipStream_t>(stream));
+  return attention_impl(qkv, out, cu, T, B, max_len, n_heads, head_dim, dtype, static_cast<hipStream_t>(stream));
 }
 
 int energon_fold_layernorm(const void* w, const void* b, const void* gamma, const void* beta, int32_t N, int32_t K,
