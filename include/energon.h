@@ -107,9 +107,9 @@ enum {
 const char* energon_strerror(int status);
 
 /* Bytes of workspace energon_layer_forward needs for up to max_tokens packed rows: the six
- * intermediates below plus, where the 16-bit contractions would cut tiles along K (see
- * energon_linear_with_scratch), room for the pieces behind them.  A smaller workspace that still
- * holds the intermediates of the actual T is accepted; the contractions then run without cutting.
+ * intermediates below plus, where the 16-bit contractions would cut K over workgroups (see
+ * energon_linear_with_scratch), room for the sums behind them.  A smaller workspace that still
+ * holds the intermediates of the actual T is accepted; the contractions then take the plans that fit.
  * Returns 0 if cfg is NULL/invalid or max_tokens < 0. */
 size_t energon_workspace_bytes(const EnergonLayerConfig* cfg, int64_t max_tokens);
 
@@ -209,15 +209,16 @@ int energon_linear(const void* x_dev, const void* w_dev, const void* bias_dev,
                    const void* residual_dev, void* y_dev, int64_t M, int32_t N, int32_t K,
                    int32_t epilogue, int32_t dtype, void* stream);
 
-/* energon_linear with room for intermediate sums.  For 16-bit problems of at least 192 tiles of
- * 256 x 256 the contraction runs as one persistent workgroup per CU; the tiles beyond the last full
- * round of workgroups would keep only part of the chip busy, so, given scratch, they are cut along
- * K into equal shares, one per workgroup, the fp32 pieces meet in the scratch, and a second kernel
- * adds them in a fixed order and applies the epilogue (same rounding points, a different but fixed
- * order of the fp32 sums for the cut tiles; run-to-run identical).  energon_linear_scratch_bytes
- * returns what a shape needs (0: it would not cut; then scratch may be NULL).  scratch_dev: 256-byte
- * aligned, contents undefined afterwards.  energon_layer_forward does the same inside its
- * workspace.  Other arguments and errors as energon_linear, plus CAPACITY (scratch too small). */
+/* energon_linear with room for intermediate sums (16-bit).  Problems of at least 192 tiles of 256 x 256 run as one
+ * persistent workgroup per CU; the tiles beyond the last full round of workgroups would keep only part of the chip
+ * busy, so, given scratch, they are cut along K into equal shares, one per workgroup, the fp32 pieces meet in the
+ * scratch, and a second kernel adds them in a fixed order and applies the epilogue.  Smaller problems with a long
+ * K are cut likewise where that is expected to be faster.  Same rounding points, a different but fixed order of the
+ * fp32 sums; run-to-run identical.  energon_linear_scratch_bytes returns what the best plan for a shape needs
+ * (0: none; then scratch may be NULL).  With less (scratch_bytes) the best plan that fits is taken; only a shape of
+ * the first kind refuses less than it needs.  scratch_dev: 256-byte aligned, contents undefined afterwards.
+ * energon_layer_forward does the same inside its workspace.  Other arguments and errors as energon_linear, plus
+ * CAPACITY (scratch too small). */
 size_t energon_linear_scratch_bytes(int64_t M, int32_t N, int32_t K, int32_t dtype);
 int energon_linear_with_scratch(const void* x_dev, const void* w_dev, const void* bias_dev,
                                 const void* residual_dev, void* y_dev, int64_t M, int32_t N, int32_t K,
@@ -229,8 +230,8 @@ int energon_linear_with_scratch(const void* x_dev, const void* w_dev, const void
  * the 8 XCDs (32 on MI355X; other values exercise the arithmetic), with or without scratch, and
  * checks that every tile and every slab of K is covered exactly once and that the pieces of a cut
  * tile sit where the second kernel reads them.  Returns 0 if so, a positive code naming the first
- * violated rule otherwise, -1 if that kernel does not take the shape (fewer than 192 tiles of 256 x
- * 256, or K not a multiple of 128).  pieces_out (optional): pieces per cut tile, 1 = no cutting. */
+ * violated rule otherwise, -1 if that kernel does not take the shape (K not a multiple of 128, or fewer than 192
+ * tiles of 256 x 256 and no scratch or a better plan).  pieces_out (optional): pieces per cut tile, 1 = no cutting. */
 int energon_linear_plan_selfcheck(int64_t M, int32_t N, int32_t K, int32_t workgroups_per_xcd,
                                   int32_t with_scratch, int32_t* pieces_out);
 

@@ -183,20 +183,27 @@ hipError_t launch_gemm_f32(const float* x, const float* w, const float* bias, co
                            int64_t M, int32_t N, int32_t K, int epi, hipStream_t s);
 // true if the launch for this shape can fill LnFold::partial (else the caller takes the statistics itself)
 bool gemm_emits_row_partials(int64_t M, int32_t N, int32_t K, bool res_aliases_y);
-// split_scratch (optional, gemm_scratch_bytes(M, N, K) bytes): lets problems with few rows cut K over
-// several workgroups (partial sums in fp32, added in a fixed order by a second kernel).
-size_t gemm_split_scratch_bytes(int64_t M, int32_t N, int32_t K);
-// the part of the above that belongs to the persistent 256x256 kernel (0 if it does not take the shape
-// or would not cut tiles along K): room for two pieces of 256x256 fp32 accumulators per workgroup
+// scratch (optional, 256-byte aligned): room for fp32 sums where K is cut over workgroups.  What is used of it is
+// decided by the shape and its size; gemm_scratch_bytes is what the best plan for a shape would take.
+size_t gemm_scratch_bytes(int64_t M, int32_t N, int32_t K);
+// the same for the shapes of whole rounds of the persistent 256x256 kernel, 0 for others (and where it would not
+// cut tiles along K): room for two pieces of 256x256 fp32 accumulators per workgroup
 size_t gemm_sched_scratch_bytes(int64_t M, int32_t N, int32_t K);
+// what a generation step's workspace holds for a contraction of more than 64 rows
+size_t gemm_decode_scratch_bytes(int64_t M, int32_t N, int32_t K);
 // host-side replay of that kernel's work decomposition for one shape: 0 = every tile and slab covered once
 int gemm_sched_selfcheck(int64_t M, int32_t N, int32_t K, int32_t wgs, int32_t can_split, int32_t* pieces_out);
 hipError_t launch_gemm_bf16(const bf16_t* x, const bf16_t* w, const bf16_t* bias, const bf16_t* res, bf16_t* y,
                             int64_t M, int32_t N, int32_t K, int epi, hipStream_t s, const LnFold* fold = nullptr,
-                            float* split_scratch = nullptr);
+                            float* scratch = nullptr, size_t scratch_bytes = 0);
 hipError_t launch_gemm_f16(const f16_t* x, const f16_t* w, const f16_t* bias, const f16_t* res, f16_t* y,
                            int64_t M, int32_t N, int32_t K, int epi, hipStream_t s, const LnFold* fold = nullptr,
-                           float* split_scratch = nullptr);
+                           float* scratch = nullptr, size_t scratch_bytes = 0);
+// gemm_ksplit.hip: small tiles (rows x columns), the wavefronts of a workgroup along K.  Plain epilogues only.
+enum class KsplitTile { k32x32, k64x32, k64x64 };
+template <typename E>
+hipError_t launch_gemm_ksplit(KsplitTile tile, const E* x, const E* w, const E* bias, const E* res, E* y, int64_t M,
+                              int32_t N, int32_t K, int epi, hipStream_t s);
 // gemm_skinny.hip: M <= 64 rows (a generation step), bound by streaming W once.  With `partial`
 // (gemm_skinny_partial_bytes bytes of scratch) K may be cut over several workgroups.
 bool gemm_skinny_takes(int64_t M, int32_t N, int32_t K, int epi);

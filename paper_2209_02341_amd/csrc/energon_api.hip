@@ -58,15 +58,15 @@ WsLayout ws_layout(const EnergonLayerConfig* c, int64_t T) {
   return l;
 }
 
-// Room behind the six intermediates for the persistent 16-bit contraction kernel to leave the pieces
-// of tiles it cuts along K (the largest need of the layer's four contractions; 0 if none cuts).
+// Room behind the six intermediates for the fp32 sums of 16-bit contractions that cut K over workgroups (the
+// largest need of the layer's four; 0 if none cuts).
 size_t layer_gemm_scratch_bytes(const EnergonLayerConfig* c, int64_t T) {
   if (!is16(c->dtype) || T <= 0) return 0;
   const int32_t H = c->hidden, A = c->n_heads * c->head_dim, F = c->ffn;
   const int32_t shapes[4][2] = {{3 * A, H}, {H, A}, {F, H}, {H, F}};
   size_t m = 0;
   for (const auto& nk : shapes) {
-    const size_t b = gemm_sched_scratch_bytes(T, nk[0], nk[1]);
+    const size_t b = gemm_scratch_bytes(T, nk[0], nk[1]);
     m = b > m ? b : m;
   }
   return m;
@@ -74,14 +74,13 @@ size_t layer_gemm_scratch_bytes(const EnergonLayerConfig* c, int64_t T) {
 
 int linear_impl(const void* x, const void* w, const void* bias, const void* res, void* y, int64_t M, int32_t N,
                 int32_t K, int32_t epi, int32_t dt, hipStream_t s, const LnFold* fold = nullptr,
-                float* split_scratch = nullptr) {
-  // split_scratch: room for fp32 partial sums, so that problems with few rows may cut K over workgroups
+                float* scratch = nullptr, size_t scratch_bytes = 0) {
   if (dt == ENERGON_BF16)
     HIP_TRY(launch_gemm_bf16((const bf16_t*)x, (const bf16_t*)w, (const bf16_t*)bias, (const bf16_t*)res, (bf16_t*)y,
-                             M, N, K, epi, s, fold, split_scratch));
+                             M, N, K, epi, s, fold, scratch, scratch_bytes));
   else if (dt == ENERGON_F16)
     HIP_TRY(launch_gemm_f16((const f16_t*)x, (const f16_t*)w, (const f16_t*)bias, (const f16_t*)res, (f16_t*)y, M, N,
-                            K, epi, s, fold, split_scratch));
+                            K, epi, s, fold, scratch, scratch_bytes));
   else if (fold != nullptr)
     return ENERGON_ERR_UNSUPPORTED;
   else
@@ -146,10 +145,10 @@ int layer_impl(const EnergonLayerConfig* cfg, const EnergonLayerWeights* w, cons
                void* padws = nullptr) {
   const WsLayout l = ws_layout(cfg, T);
   char* base = static_cast<char*>(ws);
-  // scratch of the contractions, if the caller's workspace has it (energon_workspace_bytes plans for it)
-  const size_t gs = layer_gemm_scratch_bytes(cfg, T);
-  float* const gscratch = gs > 0 && ws_bytes >= l.total + gs ? reinterpret_cast<float*>(base + l.total) : nullptr;
-  auto gemm_scratch = [&](int32_t N, int32_t K) { return gscratch && gemm_sched_scratch_bytes(T, N, K) > 0 ? gscratch : nullptr; };
+  // scratch of the contractions: what the caller's workspace has behind the intermediates (energon_workspace_bytes
+  // plans for it; each contraction takes the best plan that fits)
+  float* const gs = reinterpret_cast<float*>(base + l.total);
+  const size_t gs_bytes = ws_bytes - l.total;   // checked by the callers
   void* u = base + l.off[ENERGON_WS_U];
   void* qkv = base + l.off[ENERGON_WS_QKV];
   void* att = base + l.off[ENERGON_WS_ATTN];
@@ -163,7 +162,7 @@ int layer_impl(const EnergonLayerConfig* cfg, const EnergonLayerWeights* w, cons
   MARK(0);
   HIP_TRY(launch_layernorm(x, w->ln1_g, w->ln1_b, u, T, H, cfg->ln_eps, dt, s));
   MARK(1);
-  STEP(linear_impl(u, w->w_qkv, w->b_qkv, nullptr, qkv, T, 3 * A, H, ENERGON_EPI_BIAS, dt, s, nullptr, gemm_scratch(3 * A, H)));
+  STEP(linear_impl(u, w->w_qkv, w->b_qkv, nullptr, qkv, T, 3 * A, H, ENERGON_EPI_BIAS, dt, s, nullptr, gs, gs_bytes));
   MARK(2);
   if (T > 0 && padws == nullptr) {
     STEP(attention_impl(qkv, att, cu, T, B, max_len, cfg->n_heads, cfg->head_dim, dt, s));
@@ -177,13 +176,13 @@ int layer_impl(const EnergonLayerConfig* cfg, const EnergonLayerWeights* w, cons
     HIP_TRY(launch_remove_padding_heads(pb + 3 * part, att, cu, B, max_len, cfg->n_heads, hb, s));
   }
   MARK(3);
-  STEP(linear_impl(att, w->w_o, w->b_o, x, y1, T, H, A, ENERGON_EPI_BIAS_RESIDUAL, dt, s, nullptr, gemm_scratch(H, A)));
+  STEP(linear_impl(att, w->w_o, w->b_o, x, y1, T, H, A, ENERGON_EPI_BIAS_RESIDUAL, dt, s, nullptr, gs, gs_bytes));
   MARK(4);
   HIP_TRY(launch_layernorm(y1, w->ln2_g, w->ln2_b, wn, T, H, cfg->ln_eps, dt, s));
   MARK(5);
-  STEP(linear_impl(wn, w->w_fc1, w->b_fc1, nullptr, m, T, F, H, ENERGON_EPI_BIAS_GELU, dt, s, nullptr, gemm_scratch(F, H)));
+  STEP(linear_impl(wn, w->w_fc1, w->b_fc1, nullptr, m, T, F, H, ENERGON_EPI_BIAS_GELU, dt, s, nullptr, gs, gs_bytes));
   MARK(6);
-  STEP(linear_impl(m, w->w_fc2, w->b_fc2, y1, y, T, H, F, ENERGON_EPI_BIAS_RESIDUAL, dt, s, nullptr, gemm_scratch(H, F)));
+  STEP(linear_impl(m, w->w_fc2, w->b_fc2, y1, y, T, H, F, ENERGON_EPI_BIAS_RESIDUAL, dt, s, nullptr, gs, gs_bytes));
   MARK(7);
 #undef MARK
 #undef STEP
@@ -562,7 +561,7 @@ int energon_linear(const void* x, const void* w, const void* bias, const void* r
 
 size_t energon_linear_scratch_bytes(int64_t M, int32_t N, int32_t K, int32_t dtype) {
   if (!is16(dtype) || M <= 0 || N <= 0 || K <= 0 || K % 64 != 0 || N % 8 != 0 || K >= kMaxReduction) return 0;
-  return round256(gemm_sched_scratch_bytes(M, N, K));
+  return round256(gemm_scratch_bytes(M, N, K));
 }
 
 int energon_linear_with_scratch(const void* x, const void* w, const void* bias, const void* residual, void* y, int64_t M,
@@ -577,12 +576,13 @@ int energon_linear_with_scratch(const void* x, const void* w, const void* bias, 
   if (K >= kMaxReduction) return ENERGON_ERR_UNSUPPORTED;
   if (!aligned16(x) || !aligned16(w) || !aligned16(bias) || !aligned16(residual) || !aligned16(y))
     return ENERGON_ERR_ALIGN;
-  const size_t need = energon_linear_scratch_bytes(M, N, K, dtype);
+  // the scratch is required where the persistent kernel would cut its last round, else taken if it is enough
+  const size_t need = is16(dtype) ? gemm_sched_scratch_bytes(M, N, K) : 0;
   if (need > 0 && !scratch) return ENERGON_ERR_NULL;
   if ((reinterpret_cast<uintptr_t>(scratch) & 255u) != 0) return ENERGON_ERR_ALIGN;
   if (scratch_bytes < need) return ENERGON_ERR_CAPACITY;
   return linear_impl(x, w, bias, residual, y, M, N, K, epilogue, dtype, static_cast<hipStream_t>(stream), nullptr,
-                     need > 0 ? static_cast<float*>(scratch) : nullptr);
+                     static_cast<float*>(scratch), scratch_bytes);
 }
 
 int energon_linear_plan_selfcheck(int64_t M, int32_t N, int32_t K, int32_t workgroups_per_xcd, int32_t with_scratch,
@@ -723,7 +723,7 @@ static size_t decode_partial_bytes(const EnergonLayerConfig* c, int32_t B) {
   const int32_t shapes[4][2] = {{3 * A, H}, {H, A}, {F, H}, {H, F}};
   for (const auto& nk : shapes) {
     const size_t b = gemm_skinny_takes(B, nk[0], nk[1], EPI_BIAS) ? gemm_skinny_partial_bytes(B, nk[0], nk[1])
-                                                                  : gemm_split_scratch_bytes(B, nk[0], nk[1]);
+                                                                  : gemm_decode_scratch_bytes(B, nk[0], nk[1]);
     m = b > m ? b : m;
   }
   return round256(m);
@@ -787,16 +787,17 @@ static int decode_layer_checked(const EnergonLayerConfig* cfg, const EnergonLaye
   void* wn = base + l.off[ENERGON_WS_W];
   void* m = base + l.off[ENERGON_WS_M];
   const int32_t H = cfg->hidden, A = cfg->n_heads * cfg->head_dim, F = cfg->ffn, dt = cfg->dtype;
-  float* part = decode_partial_bytes(cfg, B) ? reinterpret_cast<float*>(base + l.total) : nullptr;
+  float* const part = reinterpret_cast<float*>(base + l.total);
+  const size_t part_bytes = decode_partial_bytes(cfg, B);
 #define STEP(call) do { st = (call); if (st != ENERGON_OK) return st; } while (0)
   HIP_TRY(launch_layernorm(x, w->ln1_g, w->ln1_b, u, B, H, cfg->ln_eps, dt, s));
-  STEP(linear_impl(u, w->w_qkv, w->b_qkv, nullptr, qkv, B, 3 * A, H, ENERGON_EPI_BIAS, dt, s, nullptr, part));
+  STEP(linear_impl(u, w->w_qkv, w->b_qkv, nullptr, qkv, B, 3 * A, H, ENERGON_EPI_BIAS, dt, s, nullptr, part, part_bytes));
   HIP_TRY(launch_decode_attention(qkv, k_cache, v_cache, cache_lens_dev, B, S_cap, cfg->n_heads, cfg->head_dim, dt,
                                   att, s));
-  STEP(linear_impl(att, w->w_o, w->b_o, x, y1, B, H, A, ENERGON_EPI_BIAS_RESIDUAL, dt, s, nullptr, part));
+  STEP(linear_impl(att, w->w_o, w->b_o, x, y1, B, H, A, ENERGON_EPI_BIAS_RESIDUAL, dt, s, nullptr, part, part_bytes));
   HIP_TRY(launch_layernorm(y1, w->ln2_g, w->ln2_b, wn, B, H, cfg->ln_eps, dt, s));
-  STEP(linear_impl(wn, w->w_fc1, w->b_fc1, nullptr, m, B, F, H, ENERGON_EPI_BIAS_GELU, dt, s, nullptr, part));
-  STEP(linear_impl(m, w->w_fc2, w->b_fc2, y1, y, B, H, F, ENERGON_EPI_BIAS_RESIDUAL, dt, s, nullptr, part));
+  STEP(linear_impl(wn, w->w_fc1, w->b_fc1, nullptr, m, B, F, H, ENERGON_EPI_BIAS_GELU, dt, s, nullptr, part, part_bytes));
+  STEP(linear_impl(m, w->w_fc2, w->b_fc2, y1, y, B, H, F, ENERGON_EPI_BIAS_RESIDUAL, dt, s, nullptr, part, part_bytes));
 #undef STEP
   return ENERGON_OK;
 }

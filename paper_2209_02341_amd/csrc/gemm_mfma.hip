@@ -22,10 +22,12 @@
 //    inwards, so nothing is clamped or predicated; the epilogue goes through LDS and leaves as
 //    16-byte non-temporal stores;
 //  * gemm_mfma_tile_kernel, compiler-scheduled, v_mfma_f32_32x32x16, clamped loads and predicated
-//    stores: used with 128x128 tiles for everything the first kernel does not take (small or
-//    ragged-below-one-tile problems, odd slab counts).
+//    stores, three slabs in LDS: 64x64 and 128x256 tiles for problems that do not give the first kernel whole rounds
+//    of tiles, or that it cannot take (odd slab counts, fewer than 256 rows or columns).
+// tile_plan chooses between these, the first kernel with its tiles cut along K, and gemm_ksplit.hip.
 #include "common.h"
 #include <algorithm>
+#include <cmath>
 #include <vector>
 
 namespace energon {
@@ -240,9 +242,12 @@ __device__ __forceinline__ void store_tile_coalesced(const f32x4 (&acc)[8][8], c
 }
 
 // ---- compiler-scheduled tile kernel ---------------------------------------------------------
+// S slab buffers: S - 1 slabs are on their way while one is worked on, one barrier per slab.  (Two buffers with a wait
+// for the only slab in flight and a full barrier per slab left every load's latency exposed: 387 x 1024 x 4096
+// 36 us on 64x64 tiles, 20 us with three buffers; five take the place of other workgroups and win nothing.)
 // MODE 0: plain epilogues; 1: the LayerNorm-folded epilogues; 2: split K, gridDim.y parts, fp32 sums
 // of part blockIdx.y to lf.partial + blockIdx.y * M * N (lf.partial is the caller's scratch here).
-template <typename E, int BM, int BN, int WM, int WN, int MODE>
+template <typename E, int BM, int BN, int WM, int WN, int S, int MODE>
 __global__ __launch_bounds__(WM* WN * 64) void gemm_mfma_tile_kernel(const E* __restrict__ x,
                                                                      const E* __restrict__ w,
                                                                      const E* __restrict__ bias,
@@ -254,7 +259,7 @@ __global__ __launch_bounds__(WM* WN * 64) void gemm_mfma_tile_kernel(const E* __
   constexpr int TM = WTM / 32, TN = WTN / 32;
   constexpr int GA = BM / 8 / NW, GB = BN / 8 / NW;  // 8-row groups (1 KiB of LDS) per wavefront
   static_assert(BM % (8 * NW) == 0 && BN % (8 * NW) == 0, "row groups must divide evenly");
-  extern __shared__ uint4 smem[];  // [2][BM + BN][kChunks]
+  extern __shared__ uint4 smem[];  // [S][BM + BN][kChunks]
 
   int64_t m0;
   int32_t n0;
@@ -316,13 +321,25 @@ __global__ __launch_bounds__(WM* WN * 64) void gemm_mfma_tile_kernel(const E* __
                                        0, 0);
   };
 
-  issue(0, 0);
-  __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): the LDS writes of this wavefront have landed
-  __syncthreads();
-
+  // Slab kt has landed (this wavefront's part: loads return in order, behind it are those of at most S - 2 slabs)
+  // and this wavefront's reads of slab kt - 1 are back; past the barrier that holds for every wavefront, so the
+  // buffer of slab kt - 1 is free for slab kt + S - 1.
+  constexpr int G = GA + GB;
+#pragma unroll
+  for (int u = 0; u < S - 1; ++u)
+    if (u < KT) issue(u, u);
+  int stage = 0;
   for (int kt = 0; kt < KT; ++kt) {
-    const uint4* cur = smem + (kt & 1) * kStage;
-    if (kt + 1 < KT) issue(kt + 1, (kt + 1) & 1);
+    const int behind = min(S - 2, KT - 1 - kt);
+    if (behind >= 3) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(3 * G) : "memory");
+    else if (behind == 2) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(2 * G) : "memory");
+    else if (behind == 1) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(G) : "memory");
+    else asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    const uint4* cur = smem + stage * kStage;
+    const int refill = stage == 0 ? S - 1 : stage - 1;
+    stage = stage + 1 == S ? 0 : stage + 1;
+    if (kt + S - 1 < KT) issue(kt + S - 1, refill);
     vec8<E> af[2][TM], bfr[2][TN];
 #pragma unroll
     for (int t = 0; t < TM; ++t) af[0][t] = *reinterpret_cast<const vec8<E>*>(&cur[fa[t] + (lhalf ^ fsa[t])]);
@@ -352,8 +369,6 @@ __global__ __launch_bounds__(WM* WN * 64) void gemm_mfma_tile_kernel(const E* __
         }
       }
     }
-    __builtin_amdgcn_s_waitcnt(0x0F70);
-    __syncthreads();
   }
 
   if constexpr (MODE == 2)
@@ -912,31 +927,98 @@ static int32_t sched_max_rem(const SchedPlan& p) {
   return m;
 }
 
+static size_t sched_scratch_bytes(int32_t wgs) { return (size_t)2 * kXcds * wgs * kPartFloats * sizeof(float); }
+
 size_t gemm_sched_scratch_bytes(int64_t M, int32_t N, int32_t K) {
   if (!takes_sched_kernel(M, N, K, false)) return 0;
   const int32_t wgs = sched_wgs_per_xcd();
-  if (sched_plan(M, N, K, true, wgs).pieces == 1) return 0;
-  return (size_t)2 * kXcds * wgs * kPartFloats * sizeof(float);
+  return sched_plan(M, N, K, true, wgs).pieces == 1 ? 0 : sched_scratch_bytes(wgs);
 }
 
-// Tile size and number of K parts for the split path of the compiler-scheduled kernel: enough
-// workgroups (>= 512 where K allows), every part at least 16 slabs long.
-void gemm_split_plan(int64_t M, int32_t N, int32_t K, int32_t* tile, int32_t* ks) {
+// How a shape that is too small for the 256x256 kernel's whole rounds runs, given `cap` bytes of scratch:
+//   kSplit   32x32, 64x32 or 64x64 tiles, K cut over the four wavefronts of the workgroup (gemm_ksplit.hip);
+//   kSmall   64x64 tiles shared by four wavefronts, three workgroups per CU;
+//   kWide    128x256 tiles, 8 wavefronts, one workgroup per CU, K cut over ks workgroups (sums in the scratch);
+//   kPieces  the 256x256 kernel with every tile cut into pieces (needs M, N >= 256 and K % 128 == 0).
+// The one with the least expected time; the times are fits of a sweep over 35 shapes.  Measured (us, with scratch;
+// in brackets the former rule: 64x64 and 128x128 tiles, one slab in flight, K cut for generation steps only):
+//   79 x 768 x 768 3.6 [7]          387 x 1024 x 4096 10.6 [36]      387 x 3072 x 1024 9.7 [12.4]    333 x 5120 x 5120 34 [56]
+//   96 x 2048 x 8192 15 [38]        120 x 5120 x 20480 58 [219]      333 x 5120 x 20480 95 [223]     928 x 5120 x 5120 64 [85]
+//   928 x 5120 x 20480 174 [317]    1500 x 4096 x 16384 183 [265]    600 x 8192 x 2048 36 [38]       2000 x 1600 x 6400 60 [78]
+// What bounds them is latency and idle CUs below a few hundred tiles, the L2 above: 128 x 256 tiles ask it for 48 KiB
+// per slab and CU, about 1 us at the 10-11 TB/s that it gives all CUs together; smaller tiles ask for more per flop but
+// fill the chip; the parts of a K cut over workgroups cost their way to memory and back (6 TB/s) and a second launch.
+enum TileKind { kSplit, kSmall, kWide, kPieces };
+struct TilePlan { TileKind kind; KsplitTile split; int32_t ks; size_t scratch; };   // ks: parts of K (kPieces: pieces per tile)
+constexpr int kSmallTile = 64, kWideM = 128, kWideN = 256, kTileStages = 3;
+
+static TilePlan tile_plan(int64_t M, int32_t N, int32_t K, bool overlap_safe, bool plain, size_t cap, int32_t wgs) {
+  const int32_t KT = K / BK;
+  const double cus = 8.0 * wgs;
+  TilePlan best{kSmall, KsplitTile::k64x64, 1, 0};
+  double best_us = 1e30;
+  const auto consider = [&](TilePlan t, double us) {
+    if (t.scratch <= cap && us < best_us) { best = t; best_us = us; }
+  };
+  const auto tiles = [&](int64_t bm, int64_t bn) { return ((M + bm - 1) / bm) * ((N + bn - 1) / bn); };
+  if (plain) {
+    const int32_t steps = (KT + 3) / 4;   // slabs of the longest wavefront
+    const double w = tiles(32, 32) / cus;
+    consider({kSplit, KsplitTile::k32x32, 1, 0}, 3.0 + 0.5 * std::ceil(w / 2) + steps * (w <= 1 ? 0.3 : w <= 2 ? 0.5 : 0.42 * w));
+    consider({kSplit, KsplitTile::k64x32, 1, 0}, 3.0 + std::ceil(tiles(64, 32) / cus) * (1.0 + 0.45 * steps));
+    consider({kSplit, KsplitTile::k64x64, 1, 0}, 3.0 + std::ceil(tiles(64, 64) / cus) * (1.5 + 0.85 * steps));
+  }
+  consider({kSmall, KsplitTile::k64x64, 1, 0}, 3.5 + KT * std::max(0.27, 0.22 * std::ceil(tiles(kSmallTile, kSmallTile) / cus)));
+  const int64_t wide = tiles(kWideM, kWideN);
+  for (int32_t ks = 1; ks <= 8 && (ks == 1 || (plain && wide * ks <= 1024 && KT / ks >= 4)); ++ks) {
+    if (KT % ks != 0) continue;
+    const double sums = (double)ks * M * N * 4.0;
+    consider({kWide, KsplitTile::k64x64, ks, ks > 1 ? (size_t)ks * (size_t)M * N * sizeof(float) : 0},
+             3.5 + KT / ks * std::ceil(wide * ks / cus) + (ks > 1 ? 2.0 + 2.0 * sums / 6.0e6 : 0.0));
+  }
+  if (plain && M >= 256 && N >= 256 && K % 128 == 0 && overlap_safe) {
+    const int64_t big = tiles(256, 256);
+    for (int32_t P = 2; P <= 8; ++P) {
+      const int64_t rem = (big + kXcds - 1) / kXcds;   // tiles of an XCD
+      const int32_t chunk = sched_chunk(KT, P);
+      // one round at most of every XCD's workgroups, and slots for it (two per workgroup)
+      if (rem >= wgs || rem * P > 2 * wgs || (KT + chunk - 1) / chunk != P || chunk < 8) continue;
+      const double rounds = std::ceil((double)rem * P / wgs);
+      consider({kPieces, KsplitTile::k64x64, P, sched_scratch_bytes(wgs)},
+               12.0 + rounds * (chunk * 1.25 + 6.0) + big * P * (kPartFloats * 4.0) / 3.0e6);
+    }
+  }
+  return best;
+}
+
+static SchedPlan pieces_plan(int64_t M, int32_t N, int32_t K, int32_t pieces, int32_t wgs) {
+  SchedPlan p;
+  p.tiles_m = (int32_t)((M + 255) / 256);
+  p.tiles_n = (N + 255) / 256;
+  p.kt = K / BK;
+  p.wgs = wgs;
+  p.raster = 0;
+  p.pieces = pieces;
+  return p;
+}
+
+size_t gemm_scratch_bytes(int64_t M, int32_t N, int32_t K) {
+  if (takes_sched_kernel(M, N, K, false)) return gemm_sched_scratch_bytes(M, N, K);
+  if (M <= 0 || gemm_skinny_takes(M, N, K, EPI_BIAS)) return 0;   // few rows: planned for by the generation step only
+  return tile_plan(M, N, K, true, true, SIZE_MAX, sched_wgs_per_xcd()).scratch;
+}
+
+// The scratch that a generation step's workspace has had for a contraction (part of what that entry point asks
+// its callers for): the plan above takes what fits in it.
+size_t gemm_decode_scratch_bytes(int64_t M, int32_t N, int32_t K) {
+  if (takes_sched_kernel(M, N, K, false)) return gemm_sched_scratch_bytes(M, N, K);
   const int64_t tiles128 = ((M + 127) / 128) * ((N + 127) / 128);
   const int32_t t = tiles128 < 128 ? 64 : 128;
   const int64_t tiles = ((M + t - 1) / t) * ((N + t - 1) / t);
   const int32_t KT = K / BK;
   int32_t k = 1;
   while (k < 16 && tiles * k < 512 && KT % (2 * k) == 0 && KT / (2 * k) >= 16) k *= 2;
-  *tile = t;
-  *ks = k;
-}
-
-size_t gemm_split_scratch_bytes(int64_t M, int32_t N, int32_t K) {
-  if (takes_sched_kernel(M, N, K, false)) return gemm_sched_scratch_bytes(M, N, K);
-  int32_t tile, ks;
-  gemm_split_plan(M, N, K, &tile, &ks);
-  return ks > 1 ? (size_t)ks * (size_t)M * N * sizeof(float) : 0;
+  return k > 1 ? (size_t)k * (size_t)M * N * sizeof(float) : 0;
 }
 
 // Host-side check of the decomposition for one shape (what the kernels would do, replayed with the
@@ -946,8 +1028,16 @@ size_t gemm_split_scratch_bytes(int64_t M, int32_t N, int32_t K) {
 // twice or lies outside the XCD's 2 * wgs.  0 if all of that holds, else a positive code naming the
 // first violation; -1 if the 256x256 kernel does not take the shape.
 int gemm_sched_selfcheck(int64_t M, int32_t N, int32_t K, int32_t wgs, int32_t can_split, int32_t* pieces_out) {
-  if (!takes_sched_kernel(M, N, K, false) || wgs < 1) return -1;
-  const SchedPlan p = sched_plan(M, N, K, can_split != 0, wgs);
+  if (wgs < 1) return -1;
+  SchedPlan p;
+  if (takes_sched_kernel(M, N, K, false)) {
+    p = sched_plan(M, N, K, can_split != 0, wgs);
+  } else {
+    if (!can_split) return -1;
+    const TilePlan t = tile_plan(M, N, K, true, true, SIZE_MAX, wgs);
+    if (t.kind != kPieces) return -1;
+    p = pieces_plan(M, N, K, t.ks, wgs);
+  }
   if (pieces_out) *pieces_out = p.pieces;
   const int64_t tiles = (int64_t)p.tiles_m * p.tiles_n;
   std::vector<int32_t> covered(tiles, 0);     // slabs covered so far (pieces must arrive in K order per tile)
@@ -1011,7 +1101,8 @@ int gemm_sched_selfcheck(int64_t M, int32_t N, int32_t K, int32_t wgs, int32_t c
 
 template <typename E, int MODE>
 static hipError_t launch_sched(const E* x, const E* w, const E* bias, const E* res, E* y, int64_t M, int32_t N,
-                               int32_t K, int epi, const LnFold& lf, hipStream_t s, float* scratch) {
+                               int32_t K, int epi, const LnFold& lf, hipStream_t s, const SchedPlan& plan,
+                               float* scratch) {
   constexpr size_t slabs = 2 * (size_t)(256 + 256) * kChunks * sizeof(uint4);
   constexpr size_t epi_stage = 4 * (size_t)kEpiWaveFloats * sizeof(float);
   constexpr size_t lds = slabs > epi_stage ? slabs : epi_stage;
@@ -1019,10 +1110,7 @@ static hipError_t launch_sched(const E* x, const E* w, const E* bias, const E* r
   auto kern = gemm_mfma_sched_kernel<E, 256, 256, 2, 2, MODE>;
   hipError_t e = ensure_dynamic_lds(reinterpret_cast<const void*>(kern), lds, attr_main);
   if (e != hipSuccess) return e;
-  const int32_t wgs = sched_wgs_per_xcd();
-  // the LayerNorm-folded epilogues and the row statistics live in the main kernel only: no cutting there
-  const SchedPlan plan = sched_plan(M, N, K, scratch != nullptr && MODE == kEpiPlain, wgs);
-  kern<<<dim3((unsigned)(kXcds * wgs)), dim3(256), lds, s>>>(x, w, bias, res, y, M, N, K, epi, plan, scratch, lf);
+  kern<<<dim3((unsigned)(kXcds * plan.wgs)), dim3(256), lds, s>>>(x, w, bias, res, y, M, N, K, epi, plan, scratch, lf);
   e = hipGetLastError();
   if (e != hipSuccess || plan.pieces == 1) return e;
   const int32_t max_rem = sched_max_rem(plan);
@@ -1031,66 +1119,68 @@ static hipError_t launch_sched(const E* x, const E* w, const E* bias, const E* r
   return hipGetLastError();
 }
 
+template <typename E, int BM, int BN, int WM, int WN, int MODE>
+static hipError_t launch_tile_cfg(const E* x, const E* w, const E* bias, const E* res, E* y, int64_t M, int32_t N,
+                                  int32_t K, int epi, const LnFold& lf, hipStream_t s, int32_t ks = 1) {
+  static LdsAttrOnce once;   // per element type and configuration
+  return launch_tiles<E>(gemm_mfma_tile_kernel<E, BM, BN, WM, WN, kTileStages, MODE>, once, BM, BN, WM * WN * 64,
+                         kTileStages * (size_t)(BM + BN) * kChunks * sizeof(uint4), x, w, bias, res, y, M, N, K, epi, lf, s, ks);
+}
+
+template <typename E, int MODE>
+static hipError_t launch_tile(TileKind kind, const E* x, const E* w, const E* bias, const E* res, E* y, int64_t M,
+                              int32_t N, int32_t K, int epi, const LnFold& lf, hipStream_t s, int32_t ks = 1) {
+  if (kind == kWide) return launch_tile_cfg<E, kWideM, kWideN, 2, 4, MODE>(x, w, bias, res, y, M, N, K, epi, lf, s, ks);
+  return launch_tile_cfg<E, kSmallTile, kSmallTile, 2, 2, MODE>(x, w, bias, res, y, M, N, K, epi, lf, s, ks);
+}
+
 template <typename E>
 static hipError_t launch_gemm_mfma(const E* x, const E* w, const E* bias, const E* res, E* y, int64_t M, int32_t N,
-                                   int32_t K, int epi, hipStream_t s, const LnFold* fold, float* split_scratch) {
+                                   int32_t K, int epi, hipStream_t s, const LnFold* fold, float* scratch,
+                                   size_t scratch_bytes) {
   if (M <= 0) return hipSuccess;
-  static LdsAttrOnce attr_small, attr_small_fold;  // per element type
+  if (scratch == nullptr) scratch_bytes = 0;
   const LnFold lf = fold != nullptr ? *fold : LnFold{};
   const bool wants_fold = epi == EPI_LNFOLD || epi == EPI_LNFOLD_GELU;
   if (wants_fold && (lf.stats == nullptr || lf.colsum == nullptr || lf.bias == nullptr)) return hipErrorInvalidValue;
   if (lf.partial != nullptr && (epi != EPI_BIAS_RESIDUAL || !gemm_emits_row_partials(M, N, K, res == y)))
     return hipErrorInvalidValue;
   if (lf.partial == nullptr && gemm_skinny_takes(M, N, K, epi))
-    return launch_gemm_skinny<E>(x, w, bias, res, y, M, N, K, epi, s, split_scratch);
+    return launch_gemm_skinny<E>(x, w, bias, res, y, M, N, K, epi, s, scratch_bytes >= gemm_skinny_partial_bytes(M, N, K) ? scratch : nullptr);
+  const int32_t wgs = sched_wgs_per_xcd();
   if (takes_sched_kernel(M, N, K, res == y)) {
-    if (wants_fold) return launch_sched<E, kEpiFolded>(x, w, bias, res, y, M, N, K, epi, lf, s, nullptr);
-    if (lf.partial != nullptr) return launch_sched<E, kEpiResidualStats>(x, w, bias, res, y, M, N, K, epi, lf, s, nullptr);
-    return launch_sched<E, kEpiPlain>(x, w, bias, res, y, M, N, K, epi, lf, s, split_scratch);
+    // the LayerNorm-folded epilogues and the row statistics live in the main kernel only: no cutting there
+    const bool plain = !wants_fold && lf.partial == nullptr;
+    const SchedPlan plan = sched_plan(M, N, K, plain && scratch_bytes >= sched_scratch_bytes(wgs), wgs);
+    if (wants_fold) return launch_sched<E, kEpiFolded>(x, w, bias, res, y, M, N, K, epi, lf, s, plan, nullptr);
+    if (!plain) return launch_sched<E, kEpiResidualStats>(x, w, bias, res, y, M, N, K, epi, lf, s, plan, nullptr);
+    return launch_sched<E, kEpiPlain>(x, w, bias, res, y, M, N, K, epi, lf, s, plan, scratch);
   }
-  // A batch of a generation step too large for the few-row kernel, with scratch from the caller: K cut
-  // over workgroups until there are enough of them, the parts added by a second kernel.  (Not where only
-  // the aliased residual kept the shape from the 256x256 kernel: the scratch was sized for that one.)
-  if (split_scratch != nullptr && !wants_fold && lf.partial == nullptr && !takes_sched_kernel(M, N, K, false)) {
-    int32_t tile, ks;
-    gemm_split_plan(M, N, K, &tile, &ks);
-    if (ks > 1) {
-      LnFold sp;
-      sp.partial = split_scratch;
-      static LdsAttrOnce attr_s64, attr_s128;
-      hipError_t e = tile == 64
-          ? launch_tiles<E>(gemm_mfma_tile_kernel<E, 64, 64, 2, 2, 2>, attr_s64, 64, 64, 256,
-                            2 * (size_t)(64 + 64) * kChunks * sizeof(uint4), x, w, bias, res, y, M, N, K, epi, sp, s, ks)
-          : launch_tiles<E>(gemm_mfma_tile_kernel<E, 128, 128, 2, 2, 2>, attr_s128, 128, 128, 256,
-                            2 * (size_t)(128 + 128) * kChunks * sizeof(uint4), x, w, bias, res, y, M, N, K, epi, sp, s, ks);
-      if (e != hipSuccess) return e;
-      return launch_partial_reduce<E>(split_scratch, ks, bias, res, y, M, N, epi, s);
-    }
-  }
-  // Few 128x128 tiles leave most of the 256 CUs idle: 64x64 tiles give four times as many workgroups
-  // (measured: 593 x 1024 x 4096 44 -> 33 us, 128 x 15360 x 5120 60 -> 44 us).
-  const int64_t tiles128 = ((M + 127) / 128) * ((N + 127) / 128);
-  if (tiles128 < 128 && !wants_fold) {
-    static LdsAttrOnce attr_64;
-    return launch_tiles<E>(gemm_mfma_tile_kernel<E, 64, 64, 2, 2, 0>, attr_64, 64, 64, 256,
-                           2 * (size_t)(64 + 64) * kChunks * sizeof(uint4), x, w, bias, res, y, M, N, K, epi, lf, s);
-  }
-  if (wants_fold)
-    return launch_tiles<E>(gemm_mfma_tile_kernel<E, 128, 128, 2, 2, 1>, attr_small_fold, 128, 128, 256,
-                           2 * (size_t)(128 + 128) * kChunks * sizeof(uint4), x, w, bias, res, y, M, N, K, epi, lf, s);
-  return launch_tiles<E>(gemm_mfma_tile_kernel<E, 128, 128, 2, 2, 0>, attr_small, 128, 128, 256,
-                         2 * (size_t)(128 + 128) * kChunks * sizeof(uint4), x, w, bias, res, y, M, N, K, epi, lf, s);
+  // Shifted edge tiles of the 256x256 kernel overlap: not with the residual aliasing y (see takes_sched_kernel).
+  const bool overlap_safe = res != y || (M % 256 == 0 && N % 256 == 0);
+  const TilePlan t = tile_plan(M, N, K, overlap_safe, !wants_fold, scratch_bytes, wgs);
+  if (wants_fold) return launch_tile<E, 1>(t.kind, x, w, bias, res, y, M, N, K, epi, lf, s);
+  if (t.kind == kSplit) return launch_gemm_ksplit<E>(t.split, x, w, bias, res, y, M, N, K, epi, s);
+  if (t.kind == kPieces)
+    return launch_sched<E, kEpiPlain>(x, w, bias, res, y, M, N, K, epi, lf, s, pieces_plan(M, N, K, t.ks, wgs), scratch);
+  if (t.ks == 1) return launch_tile<E, 0>(t.kind, x, w, bias, res, y, M, N, K, epi, lf, s);
+  LnFold sp;
+  sp.partial = scratch;
+  const hipError_t e = launch_tile_cfg<E, kWideM, kWideN, 2, 4, 2>(x, w, bias, res, y, M, N, K, epi, sp, s, t.ks);
+  if (e != hipSuccess) return e;
+  return launch_partial_reduce<E>(scratch, t.ks, bias, res, y, M, N, epi, s);
 }
 
 hipError_t launch_gemm_bf16(const bf16_t* x, const bf16_t* w, const bf16_t* bias, const bf16_t* res, bf16_t* y,
                             int64_t M, int32_t N, int32_t K, int epi, hipStream_t s, const LnFold* fold,
-                            float* split_scratch) {
-  return launch_gemm_mfma<bf16_t>(x, w, bias, res, y, M, N, K, epi, s, fold, split_scratch);
+                            float* scratch, size_t scratch_bytes) {
+  return launch_gemm_mfma<bf16_t>(x, w, bias, res, y, M, N, K, epi, s, fold, scratch, scratch_bytes);
 }
 
 hipError_t launch_gemm_f16(const f16_t* x, const f16_t* w, const f16_t* bias, const f16_t* res, f16_t* y, int64_t M,
-                           int32_t N, int32_t K, int epi, hipStream_t s, const LnFold* fold, float* split_scratch) {
-  return launch_gemm_mfma<f16_t>(x, w, bias, res, y, M, N, K, epi, s, fold, split_scratch);
+                           int32_t N, int32_t K, int epi, hipStream_t s, const LnFold* fold, float* scratch,
+                           size_t scratch_bytes) {
+  return launch_gemm_mfma<f16_t>(x, w, bias, res, y, M, N, K, epi, s, fold, scratch, scratch_bytes);
 }
 
 }  // namespace energon
