@@ -189,8 +189,8 @@ size_t gemm_scratch_bytes(int64_t M, int32_t N, int32_t K);
 // the same for the shapes of whole rounds of the persistent 256x256 kernel, 0 for others (and where it would not
 // cut tiles along K): room for two pieces of 256x256 fp32 accumulators per workgroup
 size_t gemm_sched_scratch_bytes(int64_t M, int32_t N, int32_t K);
-// what a generation step's workspace holds for a contraction of more than 64 rows
-size_t gemm_decode_scratch_bytes(int64_t M, int32_t N, int32_t K);
+// the 256x256 kernel takes the shape in whole rounds of tiles
+bool gemm_takes_whole_rounds(int64_t M, int32_t N, int32_t K);
 // host-side replay of that kernel's work decomposition for one shape: 0 = every tile and slab covered once
 int gemm_sched_selfcheck(int64_t M, int32_t N, int32_t K, int32_t wgs, int32_t can_split, int32_t* pieces_out);
 hipError_t launch_gemm_bf16(const bf16_t* x, const bf16_t* w, const bf16_t* bias, const bf16_t* res, bf16_t* y,
@@ -204,20 +204,23 @@ enum class KsplitTile { k32x32, k64x32, k64x64 };
 template <typename E>
 hipError_t launch_gemm_ksplit(KsplitTile tile, const E* x, const E* w, const E* bias, const E* res, E* y, int64_t M,
                               int32_t N, int32_t K, int epi, hipStream_t s);
-// gemm_skinny.hip: M <= 64 rows (a generation step), bound by streaming W once.  With `partial`
-// (gemm_skinny_partial_bytes bytes of scratch) K may be cut over several workgroups.
+// gemm_skinny.hip: M <= 64 rows (a generation step), bound by streaming W once.  With `partial` (fp32 scratch;
+// gemm_skinny_partial_bytes is what the best plan takes) K may be cut over several workgroups.
 bool gemm_skinny_takes(int64_t M, int32_t N, int32_t K, int epi);
 size_t gemm_skinny_partial_bytes(int64_t M, int32_t N, int32_t K);
 template <typename E>
 hipError_t launch_gemm_skinny(const E* x, const E* w, const E* bias, const E* res, E* y, int64_t M, int32_t N,
-                              int32_t K, int epi, hipStream_t s, float* partial = nullptr);
+                              int32_t K, int epi, hipStream_t s, float* partial = nullptr, size_t partial_bytes = 0);
 // y = epilogue(sum over kz < KS of partial[kz][M][N] + b), the parts added in the order of kz
 template <typename E>
 hipError_t launch_partial_reduce(const float* partial, int32_t KS, const E* bias, const E* res, E* y, int64_t M,
                                  int32_t N, int epi, hipStream_t s);
-// decode_attention.hip, model_ends.hip (dtype 1 or 2 only)
+// decode_attention.hip, model_ends.hip (dtype 1 or 2 only).  scratch (optional, fp32): room for the states of keys cut
+// over workgroups, decode_attention_scratch_bytes for the most parts; what fits is used
+size_t decode_attention_scratch_bytes(int64_t B, int32_t nh, int32_t d);
 hipError_t launch_decode_attention(const void* qkv, void* k_cache, void* v_cache, const int32_t* lens, int32_t B,
-                                   int32_t S_cap, int32_t nh, int32_t d, int dtype, void* out, hipStream_t s);
+                                   int32_t S_cap, int32_t nh, int32_t d, int dtype, void* out, hipStream_t s,
+                                   float* scratch = nullptr, size_t scratch_bytes = 0);
 hipError_t launch_embed_packed(const int32_t* ids, const int32_t* cu, const int32_t* positions, int32_t B, int64_t T,
                                const void* wte, int32_t V, const void* wpe, int32_t P, int32_t H, int dtype, void* x,
                                hipStream_t s);

@@ -5,20 +5,22 @@
 // paper's padding elimination (Sec. 4.3), no position beyond a sequence's real length is touched.
 //
 // The work is one pass over the cached rows (2 * d * e bytes per key and head, each used once):
-// bound by HBM, so there is no MFMA here.  One workgroup (4 wavefronts) per (sequence, head); a
-// key's head slice (d elements) is spread over d / 8 lanes, 16 bytes each, so a wavefront takes
-// 64 / (d / 8) keys per step with fully coalesced loads and the workgroup four times that; each
-// lane group runs its own online softmax over the keys it sees, and the 4 * 64 / (d / 8) partial
-// states are merged through LDS at the end.  The new token's k and v are read from the qkv row and
-// written to the cache row at the sequence's length by the same workgroup.
+// bound by HBM, so there is no MFMA here.  One workgroup (8 wavefronts) per (sequence, head), or per part of its keys
+// where there are few of them; a key's head slice (d elements) is spread over d / 8 lanes, 16 bytes each, so a
+// wavefront takes 64 / (d / 8) keys per step with fully coalesced loads.  Each lane group runs its own online softmax
+// over the keys it sees, two steps' loads ahead of its arithmetic; the groups' states are merged by lane
+// exchanges, the wavefronts' through LDS, the parts' by a second small kernel, always in a fixed order.  The new
+// token's k and v are read from the qkv row and written to the cache row at the sequence's length.
+// Whole steps of a 13B-size layer (us; with 4 wavefronts, no loads ahead and no parts before): 2 sequences of 4096
+// 207 -> 170 (see dec_parts), 64 of 700 361 -> 357, 32 of up to 512 the same 41 us (4.2 TB/s); 1 of 4096 x 16 heads
+// 113 -> 91 before its keys were cut.
 #include "common.h"
+#include <algorithm>
 
 namespace energon {
 
 namespace {
 
-constexpr int kDecWaves = 4;
-constexpr int kDecUnroll = 4;   // key steps whose loads are in flight together
 constexpr float kDecLog2e = 1.4426950408889634f;
 
 // sum over the LPK consecutive lanes that hold one key (LPK = 8 or 16, inside one DPP row)
@@ -30,17 +32,19 @@ template <int LPK> __device__ __forceinline__ float key_sum(float v) {
   return v;
 }
 
-template <typename E, int D>
-__global__ __launch_bounds__(kDecWaves * 64) void decode_attention_kernel(const E* __restrict__ qkv, E* k_cache,
-                                                                         E* v_cache, const int32_t* __restrict__ lens,
-                                                                         int32_t nh, int32_t S_cap,
-                                                                         E* __restrict__ out) {
+// grid = (B * nh, parts): part y of a (sequence, head) takes the y-th of equal shares of its keys.  With parts == 1
+// the result goes to out, otherwise each part leaves its state (D sums, running max, running sum) in
+// part[(y * B * nh + x) * (D + 2)] for decode_merge_kernel.
+template <typename E, int D, int NW, int U>
+__global__ __launch_bounds__(NW * 64) void decode_attention_kernel(const E* __restrict__ qkv, E* k_cache, E* v_cache,
+                                                                  const int32_t* __restrict__ lens, int32_t nh,
+                                                                  int32_t S_cap, E* __restrict__ out,
+                                                                  float* __restrict__ part) {
   constexpr int LPK = D / 8;          // lanes per key
   constexpr int KPW = 64 / LPK;       // keys per wavefront step
-  constexpr int KPB = KPW * kDecWaves;
-  constexpr int NSTREAM = KPB;        // independent online-softmax states in the workgroup
-  __shared__ float st_m[NSTREAM], st_l[NSTREAM];
-  __shared__ float st_o[NSTREAM][D + 4];
+  constexpr int KPB = KPW * NW;       // keys per step of the workgroup
+  __shared__ float st_m[NW], st_l[NW];
+  __shared__ float st_o[NW][D];
 
   const int32_t b = blockIdx.x / nh, h = blockIdx.x % nh;
   const int32_t A = nh * D;
@@ -48,7 +52,8 @@ __global__ __launch_bounds__(kDecWaves * 64) void decode_attention_kernel(const 
   const int sub = lane % LPK, slot = wave * KPW + lane / LPK;   // which 8 elements of d; which key of a step
   int32_t p = lens[b];
   p = p < 0 ? 0 : (p > S_cap ? S_cap : p);     // cached keys; the new token is key p
-  const int32_t n_keys = p + 1;
+  const int32_t share = (p + (int32_t)gridDim.y) / (int32_t)gridDim.y;   // ceil((p + 1) / parts)
+  const int32_t first = (int32_t)blockIdx.y * share, end = min(first + share, p + 1);
 
   const E* qrow = qkv + (size_t)b * 3 * A + (size_t)h * D + sub * 8;
   const vec8<E> q8 = *reinterpret_cast<const vec8<E>*>(qrow);
@@ -64,7 +69,7 @@ __global__ __launch_bounds__(kDecWaves * 64) void decode_attention_kernel(const 
   const E* vc = v_cache + head_off;
 
   // append: the new token's k and v become cache row p (one wavefront's first LPK lanes)
-  if (wave == 0 && lane < LPK && p < S_cap) {
+  if (blockIdx.y == 0 && wave == 0 && lane < LPK && p < S_cap) {
     *reinterpret_cast<vec8<E>*>(k_cache + head_off + (size_t)p * A) = *reinterpret_cast<const vec8<E>*>(knew);
     *reinterpret_cast<vec8<E>*>(v_cache + head_off + (size_t)p * A) = *reinterpret_cast<const vec8<E>*>(vnew);
   }
@@ -73,76 +78,147 @@ __global__ __launch_bounds__(kDecWaves * 64) void decode_attention_kernel(const 
 #pragma unroll
   for (int e = 0; e < 8; ++e) o[e] = 0.f;
 
-  for (int32_t j0 = 0; j0 < n_keys; j0 += KPB * kDecUnroll) {
-    vec8<E> k8[kDecUnroll], v8[kDecUnroll];
+  // U steps' loads are in flight while the U steps before are worked on
+  vec8<E> k8[2][U], v8[2][U];
+  auto load = [&](int s, int32_t j0) {
 #pragma unroll
-    for (int u = 0; u < kDecUnroll; ++u) {
+    for (int u = 0; u < U; ++u) {
       const int32_t j = j0 + u * KPB + slot;
       // key p is the new token (read from the qkv row, never from the cache row written above);
       // keys past it are clamped to it and masked below
       const bool cached = j < p;
-      const E* kp = cached ? kc + (size_t)j * A : knew;
-      const E* vp = cached ? vc + (size_t)j * A : vnew;
-      k8[u] = *reinterpret_cast<const vec8<E>*>(kp);
-      v8[u] = *reinterpret_cast<const vec8<E>*>(vp);
+      k8[s][u] = *reinterpret_cast<const vec8<E>*>(cached ? kc + (size_t)j * A : knew);
+      v8[s][u] = *reinterpret_cast<const vec8<E>*>(cached ? vc + (size_t)j * A : vnew);
     }
+  };
+  auto step = [&](int s, int32_t j0) {
 #pragma unroll
-    for (int u = 0; u < kDecUnroll; ++u) {
+    for (int u = 0; u < U; ++u) {
       const int32_t j = j0 + u * KPB + slot;
-      float s = 0.f;
+      float x = 0.f;
 #pragma unroll
-      for (int e = 0; e < 8; ++e) s = fmaf(q[e], static_cast<float>(k8[u][e]), s);
-      s = key_sum<LPK>(s);                       // the key's score in log2 units, in all its lanes
-      if (j < n_keys) {
-        const float m_new = fmaxf(m_run, s);
+      for (int e = 0; e < 8; ++e) x = fmaf(q[e], static_cast<float>(k8[s][u][e]), x);
+      x = key_sum<LPK>(x);                       // the key's score in log2 units, in all its lanes
+      if (j < end) {
+        const float m_new = fmaxf(m_run, x);
         const float corr = __builtin_amdgcn_exp2f(m_run - m_new);   // first key: exp2(-inf) = 0
-        const float pw = __builtin_amdgcn_exp2f(s - m_new);
+        const float pw = __builtin_amdgcn_exp2f(x - m_new);
         l_run = fmaf(l_run, corr, pw);
 #pragma unroll
-        for (int e = 0; e < 8; ++e) o[e] = fmaf(o[e], corr, pw * static_cast<float>(v8[u][e]));
+        for (int e = 0; e < 8; ++e) o[e] = fmaf(o[e], corr, pw * static_cast<float>(v8[s][u][e]));
         m_run = m_new;
       }
     }
+  };
+  constexpr int kTrip = KPB * U;
+  if (first < end) load(0, first);
+  for (int32_t j0 = first; j0 < end; j0 += 2 * kTrip) {
+    if (j0 + kTrip < end) load(1, j0 + kTrip);
+    step(0, j0);
+    if (j0 + kTrip < end) {
+      if (j0 + 2 * kTrip < end) load(0, j0 + 2 * kTrip);
+      step(1, j0 + kTrip);
+    }
   }
 
-  // merge the NSTREAM partial states: weights 2^(m_i - M); a stream that saw no key has m = -inf, l = 0
-  if (sub == 0) { st_m[slot] = m_run; st_l[slot] = l_run; }
+  // Merge the wavefront's KPW states by lane exchanges, then the wavefronts' through LDS: weights 2^(m_i - M); a
+  // state that saw no key has m = -inf, l = 0, o = 0 (and M = -inf only if none of the merged ones saw any).
+  float M = m_run;
 #pragma unroll
-  for (int e = 0; e < 8; ++e) st_o[slot][sub * 8 + e] = o[e];
+  for (int off = LPK; off < 64; off <<= 1) M = fmaxf(M, __shfl_xor(M, off, 64));
+  const float wgt = m_run > -INFINITY ? __builtin_amdgcn_exp2f(m_run - M) : 0.f;
+  l_run *= wgt;
+#pragma unroll
+  for (int e = 0; e < 8; ++e) o[e] *= wgt;
+#pragma unroll
+  for (int off = LPK; off < 64; off <<= 1) {
+    l_run += __shfl_xor(l_run, off, 64);
+#pragma unroll
+    for (int e = 0; e < 8; ++e) o[e] += __shfl_xor(o[e], off, 64);
+  }
+  if (lane < LPK) {
+    if (lane == 0) { st_m[wave] = M; st_l[wave] = l_run; }
+#pragma unroll
+    for (int e = 0; e < 8; ++e) st_o[wave][sub * 8 + e] = o[e];
+  }
   __syncthreads();
   if (tid < D) {
-    float M = st_m[0];
+    M = st_m[0];
 #pragma unroll
-    for (int i = 1; i < NSTREAM; ++i) M = fmaxf(M, st_m[i]);   // finite: key 0 exists
+    for (int i = 1; i < NW; ++i) M = fmaxf(M, st_m[i]);
     float L = 0.f, acc = 0.f;
 #pragma unroll
-    for (int i = 0; i < NSTREAM; ++i) {
-      const float wgt = __builtin_amdgcn_exp2f(st_m[i] - M);
-      L = fmaf(st_l[i], wgt, L);
-      acc = fmaf(st_o[i][tid], wgt, acc);
+    for (int i = 0; i < NW; ++i) {
+      const float w = st_m[i] > -INFINITY ? __builtin_amdgcn_exp2f(st_m[i] - M) : 0.f;
+      L = fmaf(st_l[i], w, L);
+      acc = fmaf(st_o[i][tid], w, acc);
     }
-    out[(size_t)b * A + (size_t)h * D + tid] = static_cast<E>(acc / L);
+    if (part == nullptr) {
+      out[(size_t)b * A + (size_t)h * D + tid] = static_cast<E>(acc / L);   // key 0 exists: L > 0
+    } else {
+      float* dst = part + ((size_t)blockIdx.y * gridDim.x + blockIdx.x) * (D + 2);
+      dst[2 + tid] = acc;
+      if (tid == 0) { dst[0] = M; dst[1] = L; }
+    }
   }
 }
 
-template <typename E>
-hipError_t launch_dec(const E* qkv, E* kc, E* vc, const int32_t* lens, int32_t B, int32_t S_cap, int32_t nh, int32_t d,
-                      E* out, hipStream_t s) {
-  const dim3 grid((unsigned)((int64_t)B * nh)), block(kDecWaves * 64);
-  if (d == 128) decode_attention_kernel<E, 128><<<grid, block, 0, s>>>(qkv, kc, vc, lens, nh, S_cap, out);
-  else decode_attention_kernel<E, 64><<<grid, block, 0, s>>>(qkv, kc, vc, lens, nh, S_cap, out);
+// The parts of a (sequence, head) added in order.
+template <typename E, int D>
+__global__ __launch_bounds__(D) void decode_merge_kernel(const float* __restrict__ part, int32_t parts,
+                                                        E* __restrict__ out) {
+  const size_t stride = (size_t)gridDim.x * (D + 2);
+  const float* src = part + (size_t)blockIdx.x * (D + 2);
+  float M = src[0];
+  for (int32_t i = 1; i < parts; ++i) M = fmaxf(M, src[i * stride]);   // finite: part 0 holds key 0
+  float L = 0.f, acc = 0.f;
+  for (int32_t i = 0; i < parts; ++i) {
+    const float m = src[i * stride], w = m > -INFINITY ? __builtin_amdgcn_exp2f(m - M) : 0.f;
+    L = fmaf(src[i * stride + 1], w, L);
+    acc = fmaf(src[i * stride + 2 + threadIdx.x], w, acc);
+  }
+  out[(size_t)blockIdx.x * D + threadIdx.x] = static_cast<E>(acc / L);
+}
+
+// Parts of a (sequence, head)'s keys: as many as bring the launch to about 512 workgroups, each with at least 512 of
+// the cache's rows, if the scratch holds their states.  (2 sequences of 4096 x 40 heads, whole step: 209 us whole,
+// 185 in 6 parts; from 256 pairs on cutting only costs the second launch: 32 x 512 x 40 200 -> 207 in 4 parts.)
+int32_t dec_parts(int64_t pairs, int32_t S_cap) {
+  if (pairs >= 256) return 1;
+  return (int32_t)std::max<int64_t>(1, std::min<int64_t>({32, 512 / pairs, S_cap / 512}));
+}
+
+template <typename E, int D>
+hipError_t launch_dec(const E* qkv, E* kc, E* vc, const int32_t* lens, int32_t B, int32_t S_cap, int32_t nh, E* out,
+                      float* scratch, size_t scratch_bytes, hipStream_t s) {
+  const int64_t pairs = (int64_t)B * nh;
+  const size_t state = (size_t)pairs * (D + 2) * sizeof(float);
+  const int32_t fit = scratch != nullptr ? (int32_t)std::min<size_t>(scratch_bytes / state, 32) : 1;
+  const int32_t parts = std::max(1, std::min(dec_parts(pairs, S_cap), fit));
+  decode_attention_kernel<E, D, 8, 2><<<dim3((unsigned)pairs, (unsigned)parts), dim3(8 * 64), 0, s>>>(
+      qkv, kc, vc, lens, nh, S_cap, out, parts > 1 ? scratch : nullptr);
+  const hipError_t e = hipGetLastError();
+  if (e != hipSuccess || parts == 1) return e;
+  decode_merge_kernel<E, D><<<dim3((unsigned)pairs), dim3(D), 0, s>>>(scratch, parts, out);
   return hipGetLastError();
 }
 
 }  // namespace
 
+size_t decode_attention_scratch_bytes(int64_t B, int32_t nh, int32_t d) {
+  const int32_t parts = B > 0 ? dec_parts(B * nh, INT32_MAX) : 1;
+  return parts > 1 ? (size_t)(B * nh) * parts * (d + 2) * sizeof(float) : 0;
+}
+
 hipError_t launch_decode_attention(const void* qkv, void* k_cache, void* v_cache, const int32_t* lens, int32_t B,
-                                   int32_t S_cap, int32_t nh, int32_t d, int dtype, void* out, hipStream_t s) {
+                                   int32_t S_cap, int32_t nh, int32_t d, int dtype, void* out, hipStream_t s,
+                                   float* scratch, size_t scratch_bytes) {
   if (B <= 0) return hipSuccess;
-  return dtype == 1 ? launch_dec<bf16_t>((const bf16_t*)qkv, (bf16_t*)k_cache, (bf16_t*)v_cache, lens, B, S_cap, nh, d,
-                                         (bf16_t*)out, s)
-                    : launch_dec<f16_t>((const f16_t*)qkv, (f16_t*)k_cache, (f16_t*)v_cache, lens, B, S_cap, nh, d,
-                                        (f16_t*)out, s);
+#define DEC_CASE(E, D) \
+  launch_dec<E, D>((const E*)qkv, (E*)k_cache, (E*)v_cache, lens, B, S_cap, nh, (E*)out, scratch, scratch_bytes, s)
+  return dtype == 1 ? (d == 128 ? DEC_CASE(bf16_t, 128) : DEC_CASE(bf16_t, 64))
+                    : (d == 128 ? DEC_CASE(f16_t, 128) : DEC_CASE(f16_t, 64));
+#undef DEC_CASE
 }
 
 }  // namespace energon

@@ -2,6 +2,7 @@
 // the kernel launches of each stage, all on the caller's stream.  No allocation, no state.
 #include "../../include/energon.h"
 #include "common.h"
+#include <algorithm>
 #include <mutex>
 
 using namespace energon;
@@ -715,17 +716,45 @@ int energon_decode_attention(const void* qkv, void* k_cache, void* v_cache, cons
   return ENERGON_OK;
 }
 
-// scratch for the partial sums of the few-row contractions of a step (the largest of the four)
-static size_t decode_partial_bytes(const EnergonLayerConfig* c, int32_t B) {
+// A generation step's workspace beyond the six intermediates.  What a call is refused without: the partial sums that
+// the contractions have had room for since the entry points exist, a rule of its own, so that a workspace once sized
+// stays large enough.
+static size_t decode_scratch_needed(const EnergonLayerConfig* c, int32_t B) {
+  if (B < 1) return 0;
+  const int32_t H = c->hidden, A = c->n_heads * c->head_dim, F = c->ffn;
+  const int32_t shapes[4][2] = {{3 * A, H}, {H, A}, {F, H}, {H, F}};
+  size_t need = 0;
+  for (const auto& nk : shapes) {
+    const int32_t N = nk[0], KT = nk[1] / 64;
+    size_t parts = 1;
+    if (B <= 64 && N % 32 == 0) {
+      const int32_t bn = (N % 64 == 0 && N / 64 >= 200 && N / 64 <= 256) ? 64 : 32;
+      if (N / bn <= 256) {
+        while (parts < 8 && KT % (2 * parts) == 0 && KT / (2 * parts) >= 40) parts *= 2;
+        if (parts < 4) parts = 1;
+      }
+    } else if (gemm_takes_whole_rounds(B, N, nk[1])) {
+      need = std::max(need, gemm_sched_scratch_bytes(B, N, nk[1]));
+    } else {
+      const int64_t t = (int64_t)((B + 127) / 128) * ((N + 127) / 128) < 128 ? 64 : 128;
+      const int64_t tiles = ((B + t - 1) / t) * ((N + t - 1) / t);
+      while (parts < 16 && tiles * (int64_t)parts < 512 && KT % (2 * parts) == 0 && KT / (2 * parts) >= 16) parts *= 2;
+    }
+    if (parts > 1) need = std::max(need, parts * (size_t)B * N * sizeof(float));
+  }
+  return round256(need);
+}
+
+// What energon_decode_workspace_bytes asks for: room for the best plans of the contractions and for keys cut over
+// workgroups.  A call takes the best plans that fit what it is given.
+static size_t decode_scratch_wanted(const EnergonLayerConfig* c, int32_t B) {
   if (!is16(c->dtype) || B < 1) return 0;
   const int32_t H = c->hidden, A = c->n_heads * c->head_dim, F = c->ffn;
-  size_t m = 0;
   const int32_t shapes[4][2] = {{3 * A, H}, {H, A}, {F, H}, {H, F}};
-  for (const auto& nk : shapes) {
-    const size_t b = gemm_skinny_takes(B, nk[0], nk[1], EPI_BIAS) ? gemm_skinny_partial_bytes(B, nk[0], nk[1])
-                                                                  : gemm_decode_scratch_bytes(B, nk[0], nk[1]);
-    m = b > m ? b : m;
-  }
+  size_t m = std::max(decode_scratch_needed(c, B), decode_attention_scratch_bytes(B, c->n_heads, c->head_dim));
+  for (const auto& nk : shapes)
+    m = std::max(m, gemm_skinny_takes(B, nk[0], nk[1], EPI_BIAS) ? gemm_skinny_partial_bytes(B, nk[0], nk[1])
+                                                                : gemm_scratch_bytes(B, nk[0], nk[1]));
   return round256(m);
 }
 
@@ -744,7 +773,7 @@ int energon_cache_fill(const void* qkv_packed, const int32_t* cu, int64_t T, int
 
 size_t energon_decode_workspace_bytes(const EnergonLayerConfig* cfg, int32_t B) {
   if (check_cfg(cfg) != ENERGON_OK || B < 0) return 0;
-  const size_t t = ws_layout(cfg, B).total + decode_partial_bytes(cfg, B);
+  const size_t t = ws_layout(cfg, B).total + decode_scratch_wanted(cfg, B);
   return t ? t : 256;
 }
 
@@ -770,7 +799,8 @@ static int decode_layer_checked(const EnergonLayerConfig* cfg, const EnergonLaye
   for (const void* p : ptrs)
     if (!aligned16(p)) return ENERGON_ERR_ALIGN;
   if ((reinterpret_cast<uintptr_t>(cache_lens_dev) & 3u)) return ENERGON_ERR_ALIGN;
-  if (ws_bytes < energon_decode_workspace_bytes(cfg, B)) return ENERGON_ERR_CAPACITY;
+  const WsLayout l = ws_layout(cfg, B);
+  if (ws_bytes < std::max<size_t>(l.total + decode_scratch_needed(cfg, B), 256)) return ENERGON_ERR_CAPACITY;
   if (ws_is_static) {   // every argument has passed: now, and only now, touch the device
     st = static_scratch(&ws);
     if (st != ENERGON_OK) return st;
@@ -778,7 +808,6 @@ static int decode_layer_checked(const EnergonLayerConfig* cfg, const EnergonLaye
   if ((reinterpret_cast<uintptr_t>(ws) & 255u) != 0) return ENERGON_ERR_ALIGN;
   if (B == 0) return ENERGON_OK;
   hipStream_t s = static_cast<hipStream_t>(stream);
-  const WsLayout l = ws_layout(cfg, B);
   char* base = static_cast<char*>(ws);
   void* u = base + l.off[ENERGON_WS_U];
   void* qkv = base + l.off[ENERGON_WS_QKV];
@@ -788,12 +817,12 @@ static int decode_layer_checked(const EnergonLayerConfig* cfg, const EnergonLaye
   void* m = base + l.off[ENERGON_WS_M];
   const int32_t H = cfg->hidden, A = cfg->n_heads * cfg->head_dim, F = cfg->ffn, dt = cfg->dtype;
   float* const part = reinterpret_cast<float*>(base + l.total);
-  const size_t part_bytes = decode_partial_bytes(cfg, B);
+  const size_t part_bytes = ws_bytes - l.total;
 #define STEP(call) do { st = (call); if (st != ENERGON_OK) return st; } while (0)
   HIP_TRY(launch_layernorm(x, w->ln1_g, w->ln1_b, u, B, H, cfg->ln_eps, dt, s));
   STEP(linear_impl(u, w->w_qkv, w->b_qkv, nullptr, qkv, B, 3 * A, H, ENERGON_EPI_BIAS, dt, s, nullptr, part, part_bytes));
   HIP_TRY(launch_decode_attention(qkv, k_cache, v_cache, cache_lens_dev, B, S_cap, cfg->n_heads, cfg->head_dim, dt,
-                                  att, s));
+                                  att, s, part, part_bytes));
   STEP(linear_impl(att, w->w_o, w->b_o, x, y1, B, H, A, ENERGON_EPI_BIAS_RESIDUAL, dt, s, nullptr, part, part_bytes));
   HIP_TRY(launch_layernorm(y1, w->ln2_g, w->ln2_b, wn, B, H, cfg->ln_eps, dt, s));
   STEP(linear_impl(wn, w->w_fc1, w->b_fc1, nullptr, m, B, F, H, ENERGON_EPI_BIAS_GELU, dt, s, nullptr, part, part_bytes));

@@ -845,6 +845,8 @@ static bool takes_sched_kernel(int64_t M, int32_t N, int32_t K, bool res_aliases
   return M >= 256 && N >= 256 && K % 128 == 0 && big_tiles >= 192 && overlap_safe;
 }
 
+bool gemm_takes_whole_rounds(int64_t M, int32_t N, int32_t K) { return takes_sched_kernel(M, N, K, false); }
+
 // Row partials come from the 256x256 kernel's epilogue, one per 128-column segment, and a
 // shifted column tile would count its overlap twice: whole column tiles only.
 bool gemm_emits_row_partials(int64_t M, int32_t N, int32_t K, bool res_aliases_y) {
@@ -1008,19 +1010,6 @@ size_t gemm_scratch_bytes(int64_t M, int32_t N, int32_t K) {
   return tile_plan(M, N, K, true, true, SIZE_MAX, sched_wgs_per_xcd()).scratch;
 }
 
-// The scratch that a generation step's workspace has had for a contraction (part of what that entry point asks
-// its callers for): the plan above takes what fits in it.
-size_t gemm_decode_scratch_bytes(int64_t M, int32_t N, int32_t K) {
-  if (takes_sched_kernel(M, N, K, false)) return gemm_sched_scratch_bytes(M, N, K);
-  const int64_t tiles128 = ((M + 127) / 128) * ((N + 127) / 128);
-  const int32_t t = tiles128 < 128 ? 64 : 128;
-  const int64_t tiles = ((M + t - 1) / t) * ((N + t - 1) / t);
-  const int32_t KT = K / BK;
-  int32_t k = 1;
-  while (k < 16 && tiles * k < 512 && KT % (2 * k) == 0 && KT / (2 * k) >= 16) k *= 2;
-  return k > 1 ? (size_t)k * (size_t)M * N * sizeof(float) : 0;
-}
-
 // Host-side check of the decomposition for one shape (what the kernels would do, replayed with the
 // same functions): every tile is either finished whole by exactly one workgroup or cut into pieces
 // whose slab ranges are even, start where the previous one ended and add up to the tile; the pieces of
@@ -1146,7 +1135,7 @@ static hipError_t launch_gemm_mfma(const E* x, const E* w, const E* bias, const 
   if (lf.partial != nullptr && (epi != EPI_BIAS_RESIDUAL || !gemm_emits_row_partials(M, N, K, res == y)))
     return hipErrorInvalidValue;
   if (lf.partial == nullptr && gemm_skinny_takes(M, N, K, epi))
-    return launch_gemm_skinny<E>(x, w, bias, res, y, M, N, K, epi, s, scratch_bytes >= gemm_skinny_partial_bytes(M, N, K) ? scratch : nullptr);
+    return launch_gemm_skinny<E>(x, w, bias, res, y, M, N, K, epi, s, scratch, scratch_bytes);
   const int32_t wgs = sched_wgs_per_xcd();
   if (takes_sched_kernel(M, N, K, res == y)) {
     // the LayerNorm-folded epilogues and the row statistics live in the main kernel only: no cutting there

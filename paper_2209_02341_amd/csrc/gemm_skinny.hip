@@ -2,14 +2,14 @@
 // This is the shape of a generation step, one token per sequence: every weight is used M times
 // only, so the contraction is bound by streaming W from HBM once (N*K*e bytes), not by the
 // matrix cores.  Design for gfx950:
-//  * a workgroup owns 32 or 64 output columns (rows of W) and all of K, or 1/KS of it; its 4
+//  * a workgroup owns 16, 32, 64 or 80 output columns (rows of W) and all of K, or 1/KS of it; its 4
 //    wavefronts split that in interleaved slabs of 64 (wavefront w takes slabs w, w + 4, ...) and
 //    add their partial sums through LDS at the end, in a fixed order.  With K cut over KS
 //    workgroups (only where the caller provides room for KS fp32 partial results) a second small
 //    kernel adds the parts in a fixed order and applies the epilogue.  Deterministic, no atomics;
-//  * a slab of W (32 or 64 rows x 128 bytes) and the same slab of x (16 MT rows x 128 bytes) go
+//  * a slab of W (16 to 80 rows x 128 bytes) and the same slab of x (16 MT rows x 128 bytes) go
 //    from global memory straight to LDS (global_load_lds_dwordx4, whole 128-byte lines) into a
-//    ring that is private to the wavefront, 2 or 4 slabs deep (the depth made no measurable
+//    ring that is private to the wavefront, 2 to 4 slabs deep (the depth made no measurable
 //    difference): no barrier and no staging register in the streaming loop.  x is read again by every workgroup, from the L2; fetched as whole lines it
 //    costs the W stream 20 % (measured in a probe: 24.7 -> 29.6 us for a 157 MB matrix), as 64-byte
 //    operand gathers into registers 60 %.  The XOR swizzle of the 256x256 kernel keeps the operand
@@ -17,6 +17,7 @@
 //  * v_mfma_f32_16x16x32: x rows are the A operand (row tiles of 16, MT of them), W rows the B
 //    operand; at these sizes the matrix cores are idle most of the time by design.
 #include "common.h"
+#include <algorithm>
 
 namespace energon {
 
@@ -32,10 +33,10 @@ __device__ __forceinline__ int sk_swz(int row) {
 }
 
 // MT row tiles of x (16 rows each), NT row tiles of W (= 16 NT output columns per workgroup)
-template <int MT, int NT> struct SkCfg {
+template <int MT, int NT, int D> struct SkCfg {
   static constexpr int kBN = 16 * NT;
   static constexpr int kSlotVecs = (16 * NT + 16 * MT) * 8;      // uint4 per ring slot: W rows, then x rows
-  static constexpr int kDepth = kSlotVecs * 16 <= 6144 ? 4 : 2;  // slabs in flight per wavefront
+  static constexpr int kDepth = D;                               // slabs in flight per wavefront
   static constexpr int kRedLd = kBN + 4;                         // floats per row of the reduction buffer:
                                                                  // rows 4 apart land 16 banks apart
   static constexpr size_t kRing = (size_t)kSkWaves * kDepth * kSlotVecs * 16;
@@ -43,17 +44,16 @@ template <int MT, int NT> struct SkCfg {
   static constexpr size_t kLds = kRing > kRed ? kRing : kRed;
 };
 
-// grid = (N / BN, KS).  Workgroup (nb, kz) contracts slabs [kz * KT / KS, (kz + 1) * KT / KS) of K for
+// grid = (ceil(N / BN), KS).  Workgroup (nb, kz) contracts slabs [kz * KT / KS, (kz + 1) * KT / KS) of K for
 // columns 16 NT nb ..; with partial == nullptr (KS = 1) it applies the epilogue and writes y, otherwise
 // it writes its fp32 sums to partial[kz][M][N] and skinny_reduce_kernel finishes the job.
-template <typename E, int MT, int NT>
+template <typename E, int MT, int NT, int kD>
 __global__ __launch_bounds__(kSkWaves * 64) void gemm_skinny_kernel(const E* __restrict__ x, const E* __restrict__ w,
                                                                    const E* __restrict__ bias, const E* res, E* y,
                                                                    float* __restrict__ partial, int32_t M, int32_t N,
                                                                    int32_t K, int epi) {
   static_assert(MT == 1 || MT == 2 || MT == 4, "row tiles of x");
-  static_assert(NT == 2 || NT == 4, "row tiles of W");
-  using Cfg = SkCfg<MT, NT>;
+  using Cfg = SkCfg<MT, NT, kD>;
   constexpr int D = Cfg::kDepth, SV = Cfg::kSlotVecs, BN = Cfg::kBN, RLD = Cfg::kRedLd;
   constexpr int GW = 2 * NT, GX = 2 * MT;   // 8-row groups of W and x per slab
   constexpr int G = GW + GX;                // direct-to-LDS instructions per slab
@@ -78,6 +78,7 @@ __global__ __launch_bounds__(kSkWaves * 64) void gemm_skinny_kernel(const E* __r
   const uint32_t ch_odd = (uint32_t)(((lane & 7) ^ sk_swz((lane >> 3) | 8)) * 16);
   const uint32_t woff_even = (uint32_t)(lane >> 3) * row_b + ch_even, woff_odd = (uint32_t)(lane >> 3) * row_b + ch_odd;
   const char* wbase = reinterpret_cast<const char*>(w + (size_t)n0 * K) + (size_t)s0 * 128;   // uniform
+  const int32_t groups = (N - n0 + 7) >> 3;   // 8-row groups of W that exist (N % 8 == 0); those past the end repeat the last
   const char* xbase = reinterpret_cast<const char*>(x) + (size_t)s0 * 128;                    // uniform
   uint32_t xoff[GX];
 #pragma unroll
@@ -99,7 +100,7 @@ __global__ __launch_bounds__(kSkWaves * 64) void gemm_skinny_kernel(const E* __r
     uint4* dst = ring + slot * SV;
 #pragma unroll
     for (int j = 0; j < GW; ++j)
-      __builtin_amdgcn_global_load_lds((sk_gptr_t)(wbase + (size_t)(8 * j) * row_b + kb + ((j & 1) ? woff_odd : woff_even)),
+      __builtin_amdgcn_global_load_lds((sk_gptr_t)(wbase + (size_t)(8 * min(j, groups - 1)) * row_b + kb + ((j & 1) ? woff_odd : woff_even)),
                                        (sk_lptr_t)(dst + j * 64), 16, 0, 0);
 #pragma unroll
     for (int j = 0; j < GX; ++j)
@@ -149,15 +150,17 @@ __global__ __launch_bounds__(kSkWaves * 64) void gemm_skinny_kernel(const E* __r
       for (int e = 0; e < 4; ++e)
         red[wave * kRedWave + (16 * t + 4 * lq + e) * RLD + 16 * j + lrow] = acc[t][j][e];
   __syncthreads();
-  constexpr int TPR = BN / 4;   // threads per output row
-  const int32_t c4 = (tid % TPR) * 4;
-  for (int32_t m = tid / TPR; m < MT * 16 && m < M; m += kSkWaves * 64 / TPR) {
+  constexpr int TPR = BN / 4;   // vectors of 4 columns per output row
+  for (int32_t i = tid; i < MT * 16 * TPR; i += kSkWaves * 64) {
+    const int32_t m = i / TPR, c4 = (i - m * TPR) * 4;
+    if (m >= M) break;
     float v[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int wv = 0; wv < kSkWaves; ++wv) {
       const float4 p = *reinterpret_cast<const float4*>(&red[wv * kRedWave + m * RLD + c4]);
       v[0] += p.x; v[1] += p.y; v[2] += p.z; v[3] += p.w;
     }
+    if (n0 + c4 >= N) continue;
     const size_t off = (size_t)m * N + n0 + c4;
     if (partial != nullptr) {
       *reinterpret_cast<float4*>(partial + (size_t)blockIdx.y * M * N + off) = make_float4(v[0], v[1], v[2], v[3]);
@@ -184,7 +187,9 @@ __global__ __launch_bounds__(kSkWaves * 64) void gemm_skinny_kernel(const E* __r
   }
 }
 
-// y = epilogue(sum over kz of partial[kz] + b): the partial sums are added in the order of kz.
+// y = epilogue(sum over kz of partial[kz] + b): the partial sums are added in the order of kz.  A few hundred
+// kilobytes: what it takes is its launch and one memory latency, so bias, residual and the parts (four at a time) are
+// all requested before the first is used.
 template <typename E>
 __global__ __launch_bounds__(256) void skinny_reduce_kernel(const float* __restrict__ partial, int32_t KS,
                                                             const E* __restrict__ bias, const E* res, E* y, int32_t M,
@@ -192,56 +197,57 @@ __global__ __launch_bounds__(256) void skinny_reduce_kernel(const float* __restr
   const size_t i4 = (size_t)blockIdx.x * 256 + threadIdx.x;   // group of 4 columns
   const size_t total4 = (size_t)M * N / 4;
   if (i4 >= total4) return;
-  const size_t off = i4 * 4;
+  const size_t off = i4 * 4, stride = (size_t)M * N;
   const int32_t n = (int32_t)(off % N);
+  vec4<E> b4, r4;
+#pragma unroll
+  for (int q = 0; q < 4; ++q) b4[q] = r4[q] = static_cast<E>(0.f);
+  if (bias != nullptr) b4 = *reinterpret_cast<const vec4<E>*>(bias + n);
+  if (epi == EPI_BIAS_RESIDUAL) r4 = *reinterpret_cast<const vec4<E>*>(res + off);
   float v[4] = {0.f, 0.f, 0.f, 0.f};
-  for (int32_t kz = 0; kz < KS; ++kz) {
-    const float4 p = *reinterpret_cast<const float4*>(partial + (size_t)kz * M * N + off);
-    v[0] += p.x; v[1] += p.y; v[2] += p.z; v[3] += p.w;
-  }
-  if (bias != nullptr) {
-    const vec4<E> b4 = *reinterpret_cast<const vec4<E>*>(bias + n);
+  for (int32_t k0 = 0; k0 < KS; k0 += 4) {
+    float4 p[4];
 #pragma unroll
-    for (int q = 0; q < 4; ++q) v[q] += static_cast<float>(b4[q]);
-  }
-  if (epi == EPI_BIAS_GELU) {
+    for (int k = 0; k < 4; ++k) p[k] = *reinterpret_cast<const float4*>(partial + (size_t)min(k0 + k, KS - 1) * stride + off);
 #pragma unroll
-    for (int q = 0; q < 4; ++q) v[q] = gelu_erf(v[q]);
-  }
-  if (epi == EPI_BIAS_RESIDUAL) {
-    const vec4<E> r4 = *reinterpret_cast<const vec4<E>*>(res + off);
-#pragma unroll
-    for (int q = 0; q < 4; ++q) v[q] += static_cast<float>(r4[q]);
+    for (int k = 0; k < 4; ++k)
+      if (k0 + k < KS) { v[0] += p[k].x; v[1] += p[k].y; v[2] += p[k].z; v[3] += p[k].w; }
   }
   vec4<E> o;
 #pragma unroll
-  for (int q = 0; q < 4; ++q) o[q] = static_cast<E>(v[q]);
+  for (int q = 0; q < 4; ++q) {
+    float t = v[q];
+    if (bias != nullptr) t += static_cast<float>(b4[q]);
+    if (epi == EPI_BIAS_GELU) t = gelu_erf(t);
+    if (epi == EPI_BIAS_RESIDUAL) t += static_cast<float>(r4[q]);
+    o[q] = static_cast<E>(t);
+  }
   *reinterpret_cast<vec4<E>*>(y + off) = o;
 }
 
-template <typename E, int MT, int NT>
-hipError_t launch_cfg(const E* x, const E* w, const E* bias, const E* res, E* y, float* partial, int32_t KS, int32_t M,
-                      int32_t N, int32_t K, int epi, hipStream_t s) {
-  auto kern = gemm_skinny_kernel<E, MT, NT>;
-  constexpr size_t lds = SkCfg<MT, NT>::kLds;
+template <typename E, int MT, int NT, int kD>
+hipError_t launch_sk(const E* x, const E* w, const E* bias, const E* res, E* y, float* partial, int32_t KS, int32_t M,
+                     int32_t N, int32_t K, int epi, hipStream_t s) {
+  auto kern = gemm_skinny_kernel<E, MT, NT, kD>;
+  constexpr size_t lds = SkCfg<MT, NT, kD>::kLds;
   static LdsAttrOnce once;
   {
     hipError_t e = ensure_dynamic_lds(reinterpret_cast<const void*>(kern), lds, once);
     if (e != hipSuccess) return e;
   }
-  kern<<<dim3((unsigned)(N / (16 * NT)), (unsigned)KS), dim3(kSkWaves * 64), lds, s>>>(x, w, bias, res, y, partial, M, N,
+  kern<<<dim3((unsigned)((N + 16 * NT - 1) / (16 * NT)), (unsigned)KS), dim3(kSkWaves * 64), lds, s>>>(x, w, bias, res, y, partial, M, N,
                                                                                       K, epi);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || partial == nullptr) return e;
   return launch_partial_reduce<E>(partial, KS, bias, res, y, M, N, epi, s);
 }
 
-template <typename E, int NT>
+template <typename E, int NT, int D1, int D2, int D4>
 hipError_t launch_nt(const E* x, const E* w, const E* bias, const E* res, E* y, float* partial, int32_t KS, int32_t M,
                      int32_t N, int32_t K, int epi, hipStream_t s) {
-  if (M <= 16) return launch_cfg<E, 1, NT>(x, w, bias, res, y, partial, KS, M, N, K, epi, s);
-  if (M <= 32) return launch_cfg<E, 2, NT>(x, w, bias, res, y, partial, KS, M, N, K, epi, s);
-  return launch_cfg<E, 4, NT>(x, w, bias, res, y, partial, KS, M, N, K, epi, s);
+  if (M <= 16) return launch_sk<E, 1, NT, D1>(x, w, bias, res, y, partial, KS, M, N, K, epi, s);
+  if (M <= 32) return launch_sk<E, 2, NT, D2>(x, w, bias, res, y, partial, KS, M, N, K, epi, s);
+  return launch_sk<E, 4, NT, D4>(x, w, bias, res, y, partial, KS, M, N, K, epi, s);
 }
 
 }  // namespace
@@ -261,51 +267,59 @@ template hipError_t launch_partial_reduce<f16_t>(const float*, int32_t, const f1
                                                  int32_t, int, hipStream_t);
 
 bool gemm_skinny_takes(int64_t M, int32_t N, int32_t K, int epi) {
-  return M >= 1 && M <= 64 && N % 32 == 0 && K % 64 == 0 && epi >= EPI_BIAS && epi <= EPI_BIAS_RESIDUAL;
+  return M >= 1 && M <= 64 && N % 8 == 0 && K % 64 == 0 && epi >= EPI_BIAS && epi <= EPI_BIAS_RESIDUAL;
 }
 
-// Shape of the launch, from measurements on the 13B-shape matrices with M = 32 (W streamed at
-// 5.2-5.7 TB/s when x is not fetched at all; fetching x, which every workgroup reads again from
-// the L2, costs about x-bytes-fetched / 15 TB/s on top, and x-bytes-fetched = W bytes * M / BN):
-//  * 64 columns per workgroup when that gives one full round of workgroups (200..256), else 32;
-//  * K cut over 4 or 8 workgroups only where there are few column blocks and K is long (each part
-//    >= 40 slabs) and the caller has room for the fp32 partial sums: FC2's shape gains 14 %, shorter
-//    K loses to the second kernel and the partial traffic.
-void gemm_skinny_plan(int64_t M, int32_t N, int32_t K, bool can_split, int32_t* bn, int32_t* ks) {
-  (void)M;
-  const int32_t KT = K / 64;
-  const int32_t b = (N % 64 == 0 && N / 64 >= 200 && N / 64 <= 256) ? 64 : 32;
-  int32_t k = 1;
-  if (can_split && N / b <= 256) {
-    while (k < 8 && KT % (2 * k) == 0 && KT / (2 * k) >= 40) k *= 2;
-    if (k < 4) k = 1;
+// Columns per workgroup (16 nt) and parts of K (ks, their sums in at most `cap` bytes of scratch): the least expected
+// time, which is the longer of W from HBM (5.8 TB/s) and the busiest CU's share of W and x
+// (40 KB/us with all CUs at work, up to 65 with fewer and narrow blocks); cutting K costs 4 us for the second kernel.  Wide
+// blocks read x less often (a hundredth of those bytes decides a tie), so the best shape is the widest that still gives every CU one workgroup: 80 columns
+// x 4 parts = 256 workgroups for N = 5120.  Measured (us, weights from HBM, M = 2 / 32 / 64; before: 32 or 64 columns,
+// 8 parts or none):
+//   5120 x 20480  48 -> 39 / 50 -> 41 / 66 -> 45     20480 x 5120  40 -> 37 / 48 -> 39 / -
+//   5120 x 5120   12.3 -> 12.3 / 17.6 -> 16.2 / 22.5 -> 18.5     15360 x 5120 (64 columns as before) 29 / 31 / 36
+struct SkinnyPlan { int32_t nt, ks; size_t scratch; };
+static SkinnyPlan gemm_skinny_plan(int64_t M, int32_t N, int32_t K, size_t cap) {
+  const int32_t KT = K / 64, mt = M <= 16 ? 1 : M <= 32 ? 2 : 4;
+  const float hbm_us = (float)N * (float)K * (2.0f / 5.8e6f);
+  SkinnyPlan best{1, 1, 0};
+  float best_us = 1e30f;
+  for (const int32_t nt : {5, 4, 2, 1}) {
+    const int32_t blocks = (N + 16 * nt - 1) / (16 * nt);
+    const float slab_kb = 2.048f * (float)(nt + mt);   // of one workgroup
+    for (const int32_t ks : {1, 2, 4, 5, 8}) {
+      const int32_t wgs = blocks * ks;
+      if (ks > 1 && (wgs > 512 || KT % ks != 0 || KT / ks < 4)) continue;
+      const size_t scratch = ks > 1 ? (size_t)ks * (size_t)M * N * sizeof(float) : 0;
+      if (scratch > cap) continue;
+      const float rate = std::min(nt >= 4 ? 42.0f : 65.0f, std::max(40.0f, 7680.0f / (float)wgs));   // KB/us of one CU
+      const float cu_us = (float)((wgs + 255) >> 8) * (float)(KT / ks) * slab_kb / rate;
+      const float us = (ks > 1 ? 4.0f : 0.0f) + std::max(hbm_us, cu_us) + (float)blocks * (float)KT * slab_kb * 1.0e-5f;
+      if (us < best_us) { best_us = us; best = {nt, ks, scratch}; }
+    }
   }
-  *bn = b;
-  *ks = k;
+  return best;
 }
 
-size_t gemm_skinny_partial_bytes(int64_t M, int32_t N, int32_t K) {
-  int32_t bn, ks;
-  gemm_skinny_plan(M, N, K, true, &bn, &ks);
-  return ks > 1 ? (size_t)ks * (size_t)M * N * sizeof(float) : 0;
-}
+size_t gemm_skinny_partial_bytes(int64_t M, int32_t N, int32_t K) { return gemm_skinny_plan(M, N, K, SIZE_MAX).scratch; }
 
-// partial == nullptr: one launch, K not split.  Otherwise `partial` must hold
-// gemm_skinny_partial_bytes(M, N, K) bytes and the plan above decides.
 template <typename E>
 hipError_t launch_gemm_skinny(const E* x, const E* w, const E* bias, const E* res, E* y, int64_t M, int32_t N,
-                              int32_t K, int epi, hipStream_t s, float* partial) {
+                              int32_t K, int epi, hipStream_t s, float* partial, size_t partial_bytes) {
   if (!gemm_skinny_takes(M, N, K, epi)) return hipErrorInvalidValue;
-  int32_t bn, ks;
-  gemm_skinny_plan(M, N, K, partial != nullptr, &bn, &ks);
-  float* p = ks > 1 ? partial : nullptr;
-  if (bn == 64) return launch_nt<E, 4>(x, w, bias, res, y, p, ks, (int32_t)M, N, K, epi, s);
-  return launch_nt<E, 2>(x, w, bias, res, y, p, ks, (int32_t)M, N, K, epi, s);
+  const SkinnyPlan plan = gemm_skinny_plan(M, N, K, partial != nullptr ? partial_bytes : 0);
+  float* const p = plan.ks > 1 ? partial : nullptr;
+  switch (plan.nt) {   // slabs in flight per wavefront for up to 16, 32, 64 rows: what fits beside another workgroup
+    case 5: return launch_nt<E, 5, 2, 2, 2>(x, w, bias, res, y, p, plan.ks, (int32_t)M, N, K, epi, s);
+    case 4: return launch_nt<E, 4, 2, 2, 2>(x, w, bias, res, y, p, plan.ks, (int32_t)M, N, K, epi, s);
+    case 2: return launch_nt<E, 2, 4, 2, 2>(x, w, bias, res, y, p, plan.ks, (int32_t)M, N, K, epi, s);
+    default: return launch_nt<E, 1, 4, 4, 3>(x, w, bias, res, y, p, plan.ks, (int32_t)M, N, K, epi, s);
+  }
 }
 
 template hipError_t launch_gemm_skinny<bf16_t>(const bf16_t*, const bf16_t*, const bf16_t*, const bf16_t*, bf16_t*,
-                                               int64_t, int32_t, int32_t, int, hipStream_t, float*);
+                                               int64_t, int32_t, int32_t, int, hipStream_t, float*, size_t);
 template hipError_t launch_gemm_skinny<f16_t>(const f16_t*, const f16_t*, const f16_t*, const f16_t*, f16_t*, int64_t,
-                                              int32_t, int32_t, int, hipStream_t, float*);
+                                              int32_t, int32_t, int, hipStream_t, float*, size_t);
 
 }  // namespace energon

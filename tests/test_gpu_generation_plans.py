@@ -1,0 +1,74 @@
+"""The ways a generation step can run: the few-row linear in its column blocks (16, 32, 64, 80) with and without K cut over
+workgroups, ragged last blocks, one row to 64; the cached attention whole or with its keys cut over workgroups, at
+cached lengths on both sides of a part's, a trip's and the cache's end; workspaces of the least size that is accepted."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import energon_oracle as orc
+from paper_2209_02341_amd import binding as E
+from paper_2209_02341_amd import harness as hz
+from paper_2209_02341_amd import workloads as wl
+from tests.test_gpu_parity import assert_close, layer_noise
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("M,N,K,dtype", [
+    (1, 8, 64, wl.BF16), (16, 40, 192, wl.F16), (17, 1608, 1600, wl.BF16), (33, 4104, 512, wl.BF16), (64, 264, 3072, wl.F16),
+    (3, 20488, 256, wl.BF16), (2, 5128, 5120, wl.BF16), (32, 5120, 5120, wl.F16), (50, 2056, 4096, wl.BF16)])
+@pytest.mark.parametrize("epi", [E.EPI_BIAS, E.EPI_BIAS_GELU, E.EPI_BIAS_RESIDUAL])
+def test_few_row_linear(M, N, K, dtype, epi):
+    rng = np.random.default_rng(M + N + K + epi)
+    x = wl.round_to_dtype(rng.standard_normal((M, K), dtype=np.float32), dtype)
+    w = wl.round_to_dtype(rng.standard_normal((N, K), dtype=np.float32) / np.sqrt(K), dtype)
+    b = wl.round_to_dtype(rng.standard_normal(N) * 0.5, dtype)
+    r = wl.round_to_dtype(rng.standard_normal((M, N), dtype=np.float32), dtype)
+    xd, wd, bd, rd = (hz.to_device(a, dtype) for a in (x, w, b, r))
+    ref = orc.linear(x.astype(np.float64), w.astype(np.float64), b.astype(np.float64))
+    ref = orc.gelu(ref) if epi == E.EPI_BIAS_GELU else ref + r if epi == E.EPI_BIAS_RESIDUAL else ref
+    for nbytes in (0, 8 * M * N * 4):
+        outs = []
+        for fill in (0, 255):
+            scratch = torch.full((nbytes,), fill, dtype=torch.uint8, device="cuda") if nbytes else None
+            yd = torch.full((M + 1, N), 3.0, dtype=xd.dtype, device="cuda")
+            E.energon_linear_with_scratch(xd, wd, bd, rd if epi == E.EPI_BIAS_RESIDUAL else None, yd, epi, scratch)
+            assert torch.all(yd[M] == 3.0), "row past M was written"
+            outs.append(yd[:M])
+        assert torch.equal(outs[0].view(torch.int16), outs[1].view(torch.int16))
+        assert_close(hz.to_host(outs[0]), ref, dtype, f"few-row linear epi={epi} scratch={nbytes}")
+
+
+# 16 heads x 2 sequences of a cache of 1600: 3 parts; 3 sequences x 4 heads: 3 parts (the cache's length limits them)
+@pytest.mark.parametrize("nh,d,lens,S_cap,dtype", [(16, 64, [0, 1599], 1600, wl.BF16), (4, 128, [1, 63, 64], 1600, wl.F16),
+                                                    (4, 128, [1000, 1023, 1024], 2048, wl.BF16), (2, 64, [5, 1535], 1536, wl.F16)])
+def test_step_with_keys_in_parts(nh, d, lens, S_cap, dtype):
+    rng = np.random.default_rng(S_cap + nh)
+    H, F, B = 256, 512, len(lens)
+    A = nh * d
+    p = wl.random_small_layer(rng, H, nh, d, F, dtype, std=0.05)
+    kc, vc = (wl.round_to_dtype(rng.standard_normal((B, S_cap, A)), dtype) for _ in range(2))
+    x = wl.round_to_dtype(rng.standard_normal((B, H)), dtype)
+    cfg, layer = hz.layer_config(H, nh, d, F, dtype), hz.DeviceLayer(p, dtype)
+    lens = np.asarray(lens, np.int32)
+    caches = [(kc[b, :n].astype(np.float64), vc[b, :n].astype(np.float64)) for b, n in enumerate(lens)]
+    ref, k_new, v_new = orc.decode_layer(x, caches, p, nh, d, 1e-5)
+    whole = E.energon_decode_workspace_bytes(cfg, B)
+    least = E.energon_workspace_bytes(cfg, B)          # these shapes have had no partial sums: the six intermediates
+    assert least < whole
+    ys = []
+    for nbytes in (least, whole, whole + 4096):
+        kd, vd, xd = hz.to_device(kc, dtype), hz.to_device(vc, dtype), hz.to_device(x, dtype)
+        yd = torch.empty_like(xd)
+        args = (cfg, layer.struct, xd, yd, torch.from_numpy(lens).cuda(), lens, kd, vd)
+        E.energon_decode_layer_forward(*args, torch.full((nbytes,), 255, dtype=torch.uint8, device="cuda"))
+        ys.append(yd)
+        # weights of standard deviation 0.05 behind a LayerNorm of 256 features, cached keys of 1: logits of about 0.8
+        assert_close(hz.to_host(yd), ref, dtype, f"step, workspace {nbytes}", **layer_noise(1, 1.0))
+        for b, n in enumerate(lens):
+            assert_close(hz.to_host(kd[b, n]), k_new[b], dtype, "appended key", stages=2)
+            assert_close(hz.to_host(vd[b, n]), v_new[b], dtype, "appended value", stages=2)
+            assert torch.equal(kd[b, :n].view(torch.int16), hz.to_device(kc[b, :n], dtype).view(torch.int16))
+    assert torch.equal(ys[1].view(torch.int16), ys[2].view(torch.int16))
+    with pytest.raises(E.EnergonError):
+        E.energon_decode_layer_forward(*args, torch.empty(least - 256, dtype=torch.uint8, device="cuda"))
