@@ -150,7 +150,10 @@ def _stream(stream):
     if stream is not None:
         return stream
     import torch
-    return torch.cuda.current_stream().cuda_stream if torch.cuda.is_available() else None
+    if not torch.cuda.is_available():
+        return None
+    # the handle alone: building a Stream object for it costs as much as the rest of a call's marshalling
+    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
 
 
 def _lengths(lengths) -> np.ndarray:
