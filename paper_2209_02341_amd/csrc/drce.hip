@@ -3,65 +3,100 @@
 // with the head transpose.
 //   rebuild:  packed [T, 3A] (Q | K | V, head-major)  ->  q, k, v  [B, nh, S, d], zeros at pads
 //   remove :  padded [B, nh, S, d]                    ->  packed [T, A]
-// Both are plain copies in 16-byte vectors, one wavefront per padded position (b, s); a head's
-// d elements (128 or 256 bytes) stay contiguous on both sides.  HBM-bound:
-// rebuild moves T*3A*e + B*S*3A*e bytes, remove 2*T*A*e.
+// Both are plain copies in 16-byte vectors, HBM-bound: rebuild moves T*3A*e + B*S*3A*e bytes, remove 2*T*A*e.  Each
+// writes in long runs and reads in head slices (128 or 256 bytes); all loads of a lane are issued before its first store.
+//  * rebuild: a wavefront moves one head's slices of 32 (d = 128) or 64 consecutive positions, 8 KiB that are
+//    contiguous on the head-major side; the four wavefronts of a workgroup take neighbouring heads.  (One wavefront per
+//    position scattered a head's slice every S*d elements and found its head by two divisions per vector:
+//    32 x 512 positions, 40 heads of 128, 160 -> 132 us, 5.8 TB/s.)
+//  * remove: a wavefront writes one packed row.  (Moved the way rebuild is, scattering its stores, it takes twice as long.)
 #include "common.h"
 
 namespace energon {
 
-// hv = 16-byte vectors per head (d * e / 16)
+constexpr int kMoveVecs = 8;   // 16-byte vectors per lane
+
+// This workgroup's sequence, first position and group of four heads; ids walk the groups of heads fastest, so that
+// workgroups side by side read (or write) the same packed rows.
+struct DrceBlock { int32_t b, s0, head; };
+__device__ __forceinline__ DrceBlock drce_block(int32_t S, int32_t groups, int32_t positions) {
+  const int32_t chunks = (S + positions - 1) / positions;
+  const int32_t at = blockIdx.x / groups;
+  const int32_t b = at / chunks;
+  return {b, (at - b * chunks) * positions, (int32_t)(blockIdx.x - at * groups) * 4 + (int32_t)(threadIdx.x >> 6)};
+}
+
+// HV = 16-byte vectors per head
+template <int HV>
 __global__ __launch_bounds__(256) void rebuild_qkv_kernel(const uint4* __restrict__ qkv, uint4* __restrict__ q,
                                                           uint4* __restrict__ k, uint4* __restrict__ v,
-                                                          const int32_t* __restrict__ cu, int32_t B, int32_t S,
-                                                          int32_t nh, int32_t hv) {
-  const int64_t p = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);  // padded position
-  if (p >= (int64_t)B * S) return;
-  const int lane = threadIdx.x & 63;
-  const int32_t b = (int32_t)(p / S), s = (int32_t)(p % S);
-  const int32_t c0 = cu[b], len = cu[b + 1] - c0;
-  const int32_t third = nh * hv;  // vectors per third of a packed row
-  const uint4* src = qkv + (size_t)(c0 + s) * 3 * third;
-  const uint4 zero = make_uint4(0, 0, 0, 0);
-  for (int32_t i = lane; i < 3 * third; i += 64) {
-    const int32_t which = i / third, r = i - which * third, h = r / hv, c = r - h * hv;
-    uint4* dst = which == 0 ? q : which == 1 ? k : v;
-    dst[((size_t)(b * nh + h) * S + s) * hv + c] = s < len ? src[i] : zero;
+                                                          const int32_t* __restrict__ cu, int32_t S, int32_t nh,
+                                                          int32_t groups) {
+  constexpr int R = 64 / HV;   // positions per load of the wavefront
+  const DrceBlock at = drce_block(S, groups, kMoveVecs * R);
+  if (at.head >= 3 * nh) return;   // head of Q, K or V
+  const int lane = threadIdx.x & 63, sub = lane % HV;
+  const int32_t c0 = cu[at.b], len = cu[at.b + 1] - c0;
+  const int32_t which = at.head / nh, h = at.head - which * nh, s = at.s0 + lane / HV;
+  const uint4* src = qkv + ((size_t)(c0 + s) * 3 * nh + at.head) * HV + sub;
+  uint4* dst = (which == 0 ? q : which == 1 ? k : v) + (((size_t)at.b * nh + h) * S + s) * HV + sub;
+  uint4 r[kMoveVecs];
+#pragma unroll
+  for (int i = 0; i < kMoveVecs; ++i) {
+    r[i] = make_uint4(0, 0, 0, 0);
+    if (s + i * R < len) r[i] = src[(size_t)(i * R) * 3 * nh * HV];
   }
+#pragma unroll
+  for (int i = 0; i < kMoveVecs; ++i)
+    if (s + i * R < S) dst[i * 64] = r[i];
 }
 
+template <int HV>
 __global__ __launch_bounds__(256) void remove_padding_heads_kernel(const uint4* __restrict__ o, uint4* __restrict__ out,
                                                                    const int32_t* __restrict__ cu, int32_t B, int32_t S,
-                                                                   int32_t nh, int32_t hv) {
-  const int64_t p = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+                                                                   int32_t nh) {
+  const int64_t p = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);   // padded position
   if (p >= (int64_t)B * S) return;
   const int lane = threadIdx.x & 63;
-  const int32_t b = (int32_t)(p / S), s = (int32_t)(p % S);
+  const int32_t b = (int32_t)(p / S), s = (int32_t)(p - (int64_t)b * S);
   const int32_t c0 = cu[b], len = cu[b + 1] - c0;
   if (s >= len) return;
-  const int32_t rowv = nh * hv;
+  const int32_t rowv = nh * HV;
+  const uint4* src = o + ((size_t)b * nh * S + s) * HV;   // head h: S * HV vectors further on each
   uint4* dst = out + (size_t)(c0 + s) * rowv;
-  for (int32_t i = lane; i < rowv; i += 64) {
-    const int32_t h = i / hv, c = i - h * hv;
-    dst[i] = o[((size_t)(b * nh + h) * S + s) * hv + c];
+  for (int32_t i0 = lane; i0 < rowv; i0 += 64 * kMoveVecs) {
+    uint4 r[kMoveVecs];
+#pragma unroll
+    for (int j = 0; j < kMoveVecs; ++j) {
+      const int32_t i = min(i0 + 64 * j, rowv - 1);       // past the row's end: its last vector, dropped
+      r[j] = src[(size_t)(i / HV) * S * HV + i % HV];
+    }
+#pragma unroll
+    for (int j = 0; j < kMoveVecs; ++j)
+      if (i0 + 64 * j < rowv) dst[i0 + 64 * j] = r[j];
   }
 }
 
+static unsigned drce_grid(int32_t B, int32_t S, int32_t groups, int hv) {
+  const int32_t positions = kMoveVecs * (64 / hv);
+  return (unsigned)((int64_t)B * ((S + positions - 1) / positions) * groups);
+}
+
+// head_bytes = 128 or 256
 hipError_t launch_rebuild_qkv(const void* qkv, void* q, void* k, void* v, const int32_t* cu, int32_t B, int32_t S,
                               int32_t nh, int32_t head_bytes, hipStream_t s) {
-  const int64_t blocks = ((int64_t)B * S + 3) / 4;
-  rebuild_qkv_kernel<<<dim3((unsigned)blocks), dim3(256), 0, s>>>(static_cast<const uint4*>(qkv), static_cast<uint4*>(q),
-                                                                static_cast<uint4*>(k), static_cast<uint4*>(v), cu, B,
-                                                                S, nh, head_bytes / 16);
+  const int32_t groups = (3 * nh + 3) / 4;
+  const auto kern = head_bytes == 256 ? rebuild_qkv_kernel<16> : rebuild_qkv_kernel<8>;
+  kern<<<dim3(drce_grid(B, S, groups, head_bytes / 16)), dim3(256), 0, s>>>(
+      static_cast<const uint4*>(qkv), static_cast<uint4*>(q), static_cast<uint4*>(k), static_cast<uint4*>(v), cu, S, nh, groups);
   return hipGetLastError();
 }
 
 hipError_t launch_remove_padding_heads(const void* o, void* out, const int32_t* cu, int32_t B, int32_t S, int32_t nh,
                                        int32_t head_bytes, hipStream_t s) {
   const int64_t blocks = ((int64_t)B * S + 3) / 4;
-  remove_padding_heads_kernel<<<dim3((unsigned)blocks), dim3(256), 0, s>>>(static_cast<const uint4*>(o),
-                                                                         static_cast<uint4*>(out), cu, B, S, nh,
-                                                                         head_bytes / 16);
+  const auto kern = head_bytes == 256 ? remove_padding_heads_kernel<16> : remove_padding_heads_kernel<8>;
+  kern<<<dim3((unsigned)blocks), dim3(256), 0, s>>>(static_cast<const uint4*>(o), static_cast<uint4*>(out), cu, B, S, nh);
   return hipGetLastError();
 }
 
