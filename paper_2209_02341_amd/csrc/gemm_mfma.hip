@@ -972,7 +972,8 @@ static TilePlan tile_plan(int64_t M, int32_t N, int32_t K, bool overlap_safe, bo
   }
   consider({kSmall, KsplitTile::k64x64, 1, 0}, 3.5 + KT * std::max(0.27, 0.22 * std::ceil(tiles(kSmallTile, kSmallTile) / cus)));
   const int64_t wide = tiles(kWideM, kWideN);
-  for (int32_t ks = 1; ks <= 8 && (ks == 1 || (plain && wide * ks <= 1024 && KT / ks >= 4)); ++ks) {
+  const bool wide_fits = K < (1 << 23);   // 256 rows of K in 32-bit byte offsets
+  for (int32_t ks = 1; wide_fits && ks <= 8 && (ks == 1 || (plain && wide * ks <= 1024 && KT / ks >= 4)); ++ks) {
     if (KT % ks != 0) continue;
     const double sums = (double)ks * M * N * 4.0;
     consider({kWide, KsplitTile::k64x64, ks, ks > 1 ? (size_t)ks * (size_t)M * N * sizeof(float) : 0},
