@@ -388,7 +388,8 @@ size_t energon_decode_workspace_bytes(const EnergonLayerConfig* cfg, int32_t B);
  * kernel that streams each weight matrix from HBM once.  cache_lens_host may be NULL; if given
  * (a host copy of cache_lens_dev) every length is checked to be in [0, S_cap) before anything is
  * launched (ENERGON_ERR_LENGTH).  workspace: energon_decode_workspace_bytes(cfg, B), 256-byte
- * aligned.  B <= 65535. */
+ * aligned; with less, down to what the intermediates and the B <= 64 contractions need, the call runs
+ * the fastest kernels that fit.  B <= 65535. */
 int energon_decode_layer_forward(const EnergonLayerConfig* cfg, const EnergonLayerWeights* weights, const void* x,
                                  void* y, int32_t B, const int32_t* cache_lens_dev, const int32_t* cache_lens_host,
                                  void* k_cache, void* v_cache, int32_t S_cap, void* workspace_dev,
@@ -396,11 +397,11 @@ int energon_decode_layer_forward(const EnergonLayerConfig* cfg, const EnergonLay
 
 /* For callers that cannot allocate device memory or hand over a workspace: code under HIP graph
  * capture, tight serving loops, harnesses that forbid hipMalloc.  Same arguments, checks, kernels
- * and results as energon_decode_layer_forward, minus the workspace: the intermediates live in a
+ * and results as energon_decode_layer_forward with a workspace of the array's size: the intermediates live in a
  * fixed array of ENERGON_STATIC_SCRATCH_BYTES of device memory inside the library (one copy per GPU
  * that loads it, held until the process ends; its address is looked up once per device, on the
  * first call made with that device current).  The call allocates and frees nothing.
- * ENERGON_ERR_CAPACITY if energon_decode_workspace_bytes(cfg, B) exceeds the array (at the
+ * ENERGON_ERR_CAPACITY if the least workspace that the other entry accepts exceeds the array (at the
  * hidden-5120 layer of the benchmark: batches up to 160 rows).  All calls on one GPU share the array, which
  * keeps the previous call's contents (nothing in it needs clearing: every stage overwrites what the
  * next one reads): calls on the same GPU must be ordered on one stream or otherwise serialised;

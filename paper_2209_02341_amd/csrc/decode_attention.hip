@@ -181,8 +181,9 @@ __global__ __launch_bounds__(D) void decode_merge_kernel(const float* __restrict
 }
 
 // Parts of a (sequence, head)'s keys: as many as bring the launch to about 512 workgroups, each with at least 512 of
-// the cache's rows, if the scratch holds their states.  (2 sequences of 4096 x 40 heads, whole step: 209 us whole,
-// 185 in 6 parts; from 256 pairs on cutting only costs the second launch: 32 x 512 x 40 200 -> 207 in 4 parts.)
+// the cache's rows, if the scratch holds their states.  (2 sequences of 4096 x 40 heads: 66 us whole, 36 in 6
+// parts with the merge; from 256 pairs on cutting only costs the second launch: a step at 32 x 512 x 40 200 -> 207 us
+// in 4 parts.)
 int32_t dec_parts(int64_t pairs, int32_t S_cap) {
   if (pairs >= 256) return 1;
   return (int32_t)std::max<int64_t>(1, std::min<int64_t>({32, 512 / pairs, S_cap / 512}));
