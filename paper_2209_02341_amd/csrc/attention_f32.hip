@@ -63,7 +63,9 @@ __global__ __launch_bounds__(kAfWaves * 64, 2) void attention_f32_kernel(const f
     }
   };
 
-  float m_run = -INFINITY, l_run = 0.f;   // per query (column): running max, this lane's part of the sum
+  // per query (column): running max, this lane's part of the sum.  The max starts at the lowest finite value: where every
+  // score so far is -inf (products that overflow), the weights are exp(-inf) = 0 and not exp(-inf + inf) = NaN
+  float m_run = kLowest, l_run = 0.f;
   f32x4 o[U][4];
 #pragma unroll
   for (int u = 0; u < U; ++u)
@@ -97,7 +99,7 @@ __global__ __launch_bounds__(kAfWaves * 64, 2) void attention_f32_kernel(const f
     float mx = fmaxf(fmaxf(s[0], s[1]), fmaxf(s[2], s[3]));
     mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
     mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
-    const float m_new = fmaxf(m_run, mx);   // finite: a tile holds at least one allowed key of every query
+    const float m_new = fmaxf(m_run, mx);
     const float corr = expf(m_run - m_new);
     f32x4 p;
 #pragma unroll
@@ -146,7 +148,7 @@ __global__ __launch_bounds__(kAfWaves * 64, 2) void attention_f32_kernel(const f
     }
   }
 
-  // merge the four states: weights exp(m_w - M); a wavefront that saw no key has m = -inf, l = 0, o = 0
+  // merge the four states: weights exp(m_w - M); a wavefront that saw no key of weight has m = kLowest, l = 0, o = 0
   l_run += __shfl_xor(l_run, 16, 64);
   l_run += __shfl_xor(l_run, 32, 64);
   if (g == 0) { st_m[wave][lr] = m_run; st_l[wave][lr] = l_run; }
@@ -159,7 +161,7 @@ __global__ __launch_bounds__(kAfWaves * 64, 2) void attention_f32_kernel(const f
   for (int i = tid; i < kAfQ * (D / 4); i += kAfWaves * 64) {
     const int r = i / (D / 4), v = i % (D / 4);
     if (q0 + r >= len) break;   // rows ascend with i
-    float M = st_m[0][r];       // finite: wavefront 0 has tile 0
+    float M = st_m[0][r];
 #pragma unroll
     for (int w = 1; w < kAfWaves; ++w) M = fmaxf(M, st_m[w][r]);
     float L = 0.f;

@@ -89,6 +89,8 @@ template <> struct Mfma<f16_t> {
   }
 };
 
+constexpr float kLowest = -3.402823466e+38f;   // the lowest finite float: where a running max starts
+
 template <typename T> struct alignas(16) Vec16 { T v[Elem<T>::VEC]; };
 
 __device__ inline float wave_sum(float v) {

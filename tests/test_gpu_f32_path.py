@@ -85,3 +85,23 @@ def test_attention_f32_bad_token_reaches_later_tokens_only():
     out, _ = _attention(qkv, [n], nh, d)
     assert np.allclose(out[:bad], clean[:bad], rtol=0, atol=1e-6)   # same weights, another order of the sums
     assert not np.isfinite(out[bad:]).any()
+
+
+# scores of -inf (finite q and k whose products overflow) have weight 0 wherever they lie: a whole first tile of one of
+# the four wavefronts that share the keys, several, the first keys of all, single ones
+@pytest.mark.parametrize("hidden_keys", [range(16, 32), range(16, 64), [*range(16), *range(40, 48)], [0, 17, 33, 63, 64]])
+@pytest.mark.parametrize("d", [64, 128])
+def test_attention_f32_scores_of_minus_infinity(hidden_keys, d):
+    n, nh = 90, 2
+    A = nh * d
+    qkv = np.random.default_rng(d).standard_normal((n, 3 * A)).astype(np.float32)
+    qkv[:, :A] = 1e20
+    qkv[:, A:2 * A] *= 1e-22                       # scores of the other keys: around 0
+    qkv[list(hidden_keys), A:2 * A] = -1e20
+    out, _ = _attention(qkv, [n], nh, d)
+    blk = qkv.astype(np.float64)
+    ref = orc.masked_causal_attention(blk[:, :A], blk[:, A:2 * A], blk[:, 2 * A:], n, nh, d)
+    seen = np.array([any(j not in hidden_keys for j in range(i + 1)) for i in range(n)])
+    eps = (d + 4) * U * 1e20 * d * np.abs(np.delete(blk[:, A:2 * A], list(hidden_keys), 0)).max() / np.sqrt(d)
+    bound = (2 * eps + (n + 16) * U) * np.abs(blk[:, 2 * A:]).max(axis=0)
+    assert np.all(np.abs(out - ref)[seen] <= bound)
