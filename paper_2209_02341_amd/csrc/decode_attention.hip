@@ -74,7 +74,9 @@ __global__ __launch_bounds__(NW * 64) void decode_attention_kernel(const E* __re
     *reinterpret_cast<vec8<E>*>(v_cache + head_off + (size_t)p * A) = *reinterpret_cast<const vec8<E>*>(vnew);
   }
 
-  float m_run = -INFINITY, l_run = 0.f, o[8];
+  // the running max starts at the lowest finite value: where every score so far is -inf (products that overflow), the
+  // weights are 2^-inf = 0 and not 2^(-inf + inf) = NaN
+  float m_run = kLowest, l_run = 0.f, o[8];
 #pragma unroll
   for (int e = 0; e < 8; ++e) o[e] = 0.f;
 
@@ -101,7 +103,7 @@ __global__ __launch_bounds__(NW * 64) void decode_attention_kernel(const E* __re
       x = key_sum<LPK>(x);                       // the key's score in log2 units, in all its lanes
       if (j < end) {
         const float m_new = fmaxf(m_run, x);
-        const float corr = __builtin_amdgcn_exp2f(m_run - m_new);   // first key: exp2(-inf) = 0
+        const float corr = __builtin_amdgcn_exp2f(m_run - m_new);   // first key: 0 (times sums of 0)
         const float pw = __builtin_amdgcn_exp2f(x - m_new);
         l_run = fmaf(l_run, corr, pw);
 #pragma unroll
@@ -122,11 +124,11 @@ __global__ __launch_bounds__(NW * 64) void decode_attention_kernel(const E* __re
   }
 
   // Merge the wavefront's KPW states by lane exchanges, then the wavefronts' through LDS: weights 2^(m_i - M); a
-  // state that saw no key has m = -inf, l = 0, o = 0 (and M = -inf only if none of the merged ones saw any).
+  // state that saw no key of weight has m = kLowest, l = 0, o = 0.
   float M = m_run;
 #pragma unroll
   for (int off = LPK; off < 64; off <<= 1) M = fmaxf(M, __shfl_xor(M, off, 64));
-  const float wgt = m_run > -INFINITY ? __builtin_amdgcn_exp2f(m_run - M) : 0.f;
+  const float wgt = __builtin_amdgcn_exp2f(m_run - M);
   l_run *= wgt;
 #pragma unroll
   for (int e = 0; e < 8; ++e) o[e] *= wgt;
@@ -149,7 +151,7 @@ __global__ __launch_bounds__(NW * 64) void decode_attention_kernel(const E* __re
     float L = 0.f, acc = 0.f;
 #pragma unroll
     for (int i = 0; i < NW; ++i) {
-      const float w = st_m[i] > -INFINITY ? __builtin_amdgcn_exp2f(st_m[i] - M) : 0.f;
+      const float w = __builtin_amdgcn_exp2f(st_m[i] - M);
       L = fmaf(st_l[i], w, L);
       acc = fmaf(st_o[i][tid], w, acc);
     }
@@ -170,10 +172,10 @@ __global__ __launch_bounds__(D) void decode_merge_kernel(const float* __restrict
   const size_t stride = (size_t)gridDim.x * (D + 2);
   const float* src = part + (size_t)blockIdx.x * (D + 2);
   float M = src[0];
-  for (int32_t i = 1; i < parts; ++i) M = fmaxf(M, src[i * stride]);   // finite: part 0 holds key 0
+  for (int32_t i = 1; i < parts; ++i) M = fmaxf(M, src[i * stride]);
   float L = 0.f, acc = 0.f;
   for (int32_t i = 0; i < parts; ++i) {
-    const float m = src[i * stride], w = m > -INFINITY ? __builtin_amdgcn_exp2f(m - M) : 0.f;
+    const float w = __builtin_amdgcn_exp2f(src[i * stride] - M);
     L = fmaf(src[i * stride + 1], w, L);
     acc = fmaf(src[i * stride + 2 + threadIdx.x], w, acc);
   }

@@ -72,3 +72,58 @@ def test_step_with_keys_in_parts(nh, d, lens, S_cap, dtype):
     assert torch.equal(ys[1].view(torch.int16), ys[2].view(torch.int16))
     with pytest.raises(E.EnergonError):
         E.energon_decode_layer_forward(*args, torch.empty(least - 256, dtype=torch.uint8, device="cuda"))
+
+
+# scores of -inf (finite q and k whose products overflow) have weight 0 wherever they lie in the order the keys are taken:
+# the first keys of some wavefronts, whole shares of keys cut over workgroups, the new token
+HIDDEN = [range(16, 32), range(4, 60), [*range(3), 70, 200], range(370, 1100)]
+
+
+def _overflowing(rng, B, S_cap, A, hidden, dtype):
+    kc, vc = (rng.standard_normal((B, S_cap, A)) for _ in range(2))
+    kc *= 1e-17
+    kc[:, [j for j in hidden if j < S_cap]] = -1e25
+    return wl.round_to_dtype(kc, dtype), wl.round_to_dtype(vc, dtype)
+
+
+@pytest.mark.parametrize("hidden", HIDDEN)
+@pytest.mark.parametrize("nh,d", [(3, 128), (5, 64)])
+def test_cached_attention_scores_of_minus_infinity(hidden, nh, d):
+    rng = np.random.default_rng(nh)
+    B, S_cap, A = 2, 800, nh * d
+    kc, vc = _overflowing(rng, B, S_cap, A, hidden, wl.BF16)
+    qkv = rng.standard_normal((B, 3 * A))
+    qkv[:, :A] = 1e15
+    qkv[:, A:2 * A] *= 1e-17
+    qkv[1, A:2 * A] = -1e25                              # sequence 1: its own key too
+    qkv = wl.round_to_dtype(qkv, wl.BF16)
+    lens = np.asarray([90, 799], np.int32)
+    kd, vd = hz.to_device(kc, wl.BF16), hz.to_device(vc, wl.BF16)
+    out = torch.empty((B, A), dtype=torch.bfloat16, device="cuda")
+    E.energon_decode_attention(hz.to_device(qkv, wl.BF16), kd, vd, torch.from_numpy(lens).cuda(), nh, d, out)
+    q = qkv.astype(np.float64)
+    ref = np.stack([orc.decode_attention(q[b, :A], q[b, A:2 * A], q[b, 2 * A:], kc[b, :n].astype(np.float64),
+                                         vc[b, :n].astype(np.float64), nh, d) for b, n in enumerate(lens)])
+    assert_close(hz.to_host(out), ref, wl.BF16, "attention", stages=2)
+
+
+@pytest.mark.parametrize("hidden", HIDDEN)
+def test_step_with_keys_in_parts_and_scores_of_minus_infinity(hidden):
+    rng = np.random.default_rng(1)
+    H, F, nh, d, B, S_cap = 256, 512, 4, 128, 2, 2048
+    A = nh * d
+    p = wl.random_small_layer(rng, H, nh, d, F, wl.BF16, std=0.05)
+    p["w_qkv"][:2 * A] = 0.0                             # q = 1e15, k = 1e-17 times normal, for every token
+    p["b_qkv"] = wl.round_to_dtype(np.concatenate([np.full(A, 1e15), rng.standard_normal(A) * 1e-17,
+                                                   rng.standard_normal(A)]), wl.BF16)
+    kc, vc = _overflowing(rng, B, S_cap, A, hidden, wl.BF16)
+    x = wl.round_to_dtype(rng.standard_normal((B, H)), wl.BF16)
+    cfg, layer = hz.layer_config(H, nh, d, F, wl.BF16), hz.DeviceLayer(p, wl.BF16)
+    lens = np.asarray([1500, 2047], np.int32)
+    ref, _, _ = orc.decode_layer(x, [(kc[b, :n].astype(np.float64), vc[b, :n].astype(np.float64))
+                                     for b, n in enumerate(lens)], p, nh, d, 1e-5)
+    yd = torch.empty((B, H), dtype=torch.bfloat16, device="cuda")
+    ws = torch.full((E.energon_decode_workspace_bytes(cfg, B),), 255, dtype=torch.uint8, device="cuda")
+    E.energon_decode_layer_forward(cfg, layer.struct, hz.to_device(x, wl.BF16), yd, torch.from_numpy(lens).cuda(), lens,
+                                   hz.to_device(kc, wl.BF16), hz.to_device(vc, wl.BF16), ws)
+    assert_close(hz.to_host(yd), ref, wl.BF16, "step", **layer_noise(1, 1.0))
