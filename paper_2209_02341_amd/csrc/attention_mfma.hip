@@ -66,14 +66,20 @@ template <int G> __device__ __forceinline__ void attn_wait(int n) {
   else asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
 }
 
-// Which (sequence, head, query block) this workgroup computes; false: none.  Workgroups run on XCD id % 8.  The
-// (sequence, head) pairs are dealt to the XCDs in turn, heads fastest, and an XCD takes the query blocks of a pair
-// behind each other, the one with the most keys first: the blocks that share K and V meet in their XCD's L2
-// (8 x 2048 tokens x 40 heads: 2.85 -> 0.22 GB fetched), and the heads that run at a time are neighbours in
-// the rows, which the HBM pages like (64 sequences of 64 tokens: 31 us with whole heads per XCD, 26 this way).
-// n_qblocks = 0 (packed, up to kAttnScan sequences, where max_len leaves a good part of the blocks without queries):
-// only blocks that have queries are counted, from a scan of the lengths by every wavefront, and the host launches an
-// upper bound.
+// Which (sequence, head, query block) this workgroup computes; false: none.  Workgroups run on XCD id % 8, each XCD
+// in the order of its ids.  Three ways:
+//  * n_qblocks > 0, group = 0: the last query block (the one with the most keys) of all (sequence, head) pairs, heads
+//    fastest, then the blocks in front of it.  Longest first and dealt to the XCDs one by one, the chip stays
+//    balanced whatever the number of pairs;
+//  * n_qblocks > 0, group > 0: an XCD takes whole pairs, about kAttnGroup at a time in that order, so that the blocks that
+//    share K and V meet in its L2; the pairs that the XCDs do not share evenly go first, their blocks dealt one by one;
+//  * n_qblocks = 0 (packed, up to kAttnScan sequences, where max_len leaves a good part of the blocks without queries):
+//    only blocks that have queries are counted, from a scan of the lengths by every wavefront, and the host
+//    launches an upper bound.  A sequence's heads go to the XCDs in whole eights, the blocks of the others are dealt.
+// Measured (us; order by pairs throughout / longest first throughout / as it is): 1 sequence of 32768 x 4 heads x 128
+// 2056 / 1135 / 1135, 1 of 8192 x 12 heads 310 / 233 / 233, 32 of 512 x 40 heads 208 / 232 / 176, 8 of 2048 x 40
+// heads x 128 (padded) 470 / 450 / 427, 16 of 512 x 40 heads 105 / 92 / 88, 8 of 512 x 40 heads 52.5 / 47.0 / 47.0.
+constexpr int kAttnGroup = 8;
 constexpr int kAttnScan = 256;
 
 // Sum over lanes 0 .. l in every lane l: shifts inside rows of 16 lanes, then the last lane of the row (of the half)
@@ -88,21 +94,40 @@ __device__ __forceinline__ int32_t wave_inclusive_sum(int32_t v) {
   return v;
 }
 __device__ __forceinline__ bool attn_block(const int32_t* __restrict__ cu, int32_t B, int32_t nh, int32_t n_qblocks,
-                                           int lane, int32_t& b, int32_t& h, int32_t& qb, int32_t& c0, int32_t& len) {
+                                           int32_t group, int lane, int32_t& b, int32_t& h, int32_t& qb, int32_t& c0,
+                                           int32_t& len) {
   const int32_t xcd = blockIdx.x % kXcds, j = blockIdx.x / kXcds;
   if (n_qblocks > 0) {
-    const int32_t k = j / n_qblocks, pair = xcd + kXcds * k;
+    const int32_t pairs = B * nh, whole = pairs / kXcds, rest = pairs - whole * kXcds;   // pairs per XCD, left over
+    const int32_t dealt = (rest * n_qblocks + kXcds - 1) / kXcds;                         // their blocks per XCD
+    int32_t pair, k;   // k: blocks behind this one in the sequence
+    if (group == 0) {
+      k = (int32_t)blockIdx.x / pairs;
+      pair = (int32_t)blockIdx.x - k * pairs;
+    } else if (j < dealt) {
+      const int32_t u = xcd + kXcds * j;
+      k = u / rest;
+      pair = kXcds * whole + u - k * rest;
+    } else {
+      const int32_t per = group * n_qblocks, g = (j - dealt) / per, in = j - dealt - g * per;
+      const int32_t size = min(group, whole - g * group);
+      if (size <= 0) return false;
+      k = in / size;
+      pair = xcd + kXcds * (g * group + in - k * size);
+    }
+    if (k >= n_qblocks) return false;
     b = pair / nh;
-    if (b >= B) return false;
     h = pair - b * nh;
-    qb = n_qblocks - 1 - (j - k * n_qblocks);
+    qb = n_qblocks - 1 - k;
     c0 = cu[b];
     len = cu[b + 1] - c0;
     return true;
   }
-  // lane l: sequences per * l .. per * l + per - 1; a sequence counts its query blocks times its heads on this XCD
+  // lane l: sequences per * l .. per * l + per - 1; a sequence of n query blocks has n * (nh / 8) on every XCD and of the
+  // n * (nh % 8) others, numbered from the sequence's index times nh, those whose number is this XCD's modulo 8
   constexpr int kPer = kAttnScan / kWave;
   const int32_t per = (B + kWave - 1) / kWave, first = lane * per;
+  const int32_t eights = nh / kXcds, rest = nh - eights * kXcds;
   int32_t at[kPer + 1], nb[kPer], w[kPer], mine = 0;
   at[0] = cu[min(first, B)];
 #pragma unroll
@@ -110,8 +135,8 @@ __device__ __forceinline__ bool attn_block(const int32_t* __restrict__ cu, int32
 #pragma unroll
   for (int k = 0; k < kPer; ++k) {
     nb[k] = k < per ? (at[k + 1] - at[k] + kBQ - 1) / kBQ : 0;
-    const int32_t p = (first + k) * nh + kXcds - 1 - xcd;
-    w[k] = nb[k] * ((p + nh) / kXcds - p / kXcds);
+    const int32_t p = (((first + k) * rest) & (kXcds - 1)) + kXcds - 1 - xcd;
+    w[k] = nb[k] * eights + (p + nb[k] * rest) / kXcds - p / kXcds;
     mine += w[k];
   }
   const int32_t incl = wave_inclusive_sum(mine);
@@ -123,12 +148,20 @@ __device__ __forceinline__ bool attn_block(const int32_t* __restrict__ cu, int32
   for (int k = 0; k < kPer; ++k) {
     const int32_t n = __builtin_amdgcn_readlane(w[k], src);
     if (r < n) {
-      const int32_t blocks = __builtin_amdgcn_readlane(nb[k], src), i = r / blocks;
+      const int32_t blocks = __builtin_amdgcn_readlane(nb[k], src);
       b += k;
-      h = ((xcd - b * nh) & (kXcds - 1)) + kXcds * i;
-      qb = blocks - 1 - (r - i * blocks);
       c0 = __builtin_amdgcn_readlane(at[k], src);
       len = __builtin_amdgcn_readlane(at[k + 1], src) - c0;
+      const int32_t mixed = n - blocks * eights;   // this XCD's share of the dealt blocks comes first
+      if (r < mixed) {
+        const int32_t u = ((xcd - b * rest) & (kXcds - 1)) + kXcds * r, q = u / rest;
+        h = kXcds * eights + u - q * rest;
+        qb = blocks - 1 - q;
+      } else {
+        const int32_t i = (r - mixed) / blocks;
+        h = xcd + kXcds * i;
+        qb = blocks - 1 - (r - mixed - i * blocks);
+      }
       break;
     }
     r -= n;
@@ -143,7 +176,8 @@ __device__ __forceinline__ bool attn_block(const int32_t* __restrict__ cu, int32
 template <typename E, int D, bool PADDED>
 __global__ __launch_bounds__(kAttnWaves * 64, D == 128 ? 2 : 3) void attention_mfma_kernel(
     const E* __restrict__ qptr, const E* __restrict__ kptr, const E* __restrict__ vptr, E* __restrict__ out,
-    const int32_t* __restrict__ cu, int32_t B, int32_t nh, int32_t n_qblocks, int32_t S) {
+    const int32_t* __restrict__ cu, int32_t B, int32_t nh, int32_t n_qblocks, int32_t group,
+    int32_t S) {
   constexpr int KS = D / 16;                 // 16-wide steps of the head dimension (S^T contraction)
   constexpr int DB = D / 32;                 // 32-row blocks of O^T
   constexpr int KC = D / 8;                  // 16-byte chunks per row
@@ -159,7 +193,7 @@ __global__ __launch_bounds__(kAttnWaves * 64, D == 128 ? 2 : 3) void attention_m
 
   const int tid = threadIdx.x, lane = tid & 63;
   int32_t b, h, qb, c0, len;
-  if (!attn_block(cu, B, nh, n_qblocks, lane, b, h, qb, c0, len)) return;
+  if (!attn_block(cu, B, nh, n_qblocks, group, lane, b, h, qb, c0, len)) return;
   const int32_t q0 = qb * kBQ;
   const int32_t n_queries = PADDED ? S : len;   // queries of this sequence that are computed
   if (q0 >= n_queries) return;  // whole workgroup leaves before any barrier
@@ -400,13 +434,24 @@ static hipError_t launch_d(const E* q, const E* k, const E* v, E* out, const int
     if (e != hipSuccess) return e;
   }
   const int32_t n_qblocks = (max_len + kBQ - 1) / kBQ;
-  // blocks per XCD: pairs x blocks of max_len, or the bound sum of ceil(len / kBQ) <= T / kBQ + B per head where
-  // that is at least a fifth less (the scan costs a workgroup about half a microsecond)
-  const int64_t n_pairs = (int64_t)B * nh, all = (n_pairs + kXcds - 1) / kXcds * n_qblocks;
-  const int64_t bound = (T / kBQ + B) * ((nh + kXcds - 1) / kXcds);
-  const bool scan = !PADDED && B <= kAttnScan && 5 * bound <= 4 * all;
-  const int64_t grid = (scan ? bound : all) * kXcds;
-  kern<<<dim3((unsigned)grid), dim3(kAttnWaves * 64), lds, s>>>(q, k, v, out, cu, B, nh, scan ? 0 : n_qblocks, max_len);
+  const int64_t pairs = (int64_t)B * nh, whole = pairs / kXcds, rest = pairs % kXcds, all = pairs * n_qblocks;
+  // sum of ceil(len / kBQ) <= T / kBQ + B per head; where that is at least a fifth less than the blocks of max_len, the
+  // blocks are counted by a scan (which costs a workgroup about half a microsecond), unless the launch is small and
+  // at least half full, where balance is worth more: 8 sequences of up to 2048 x 25 heads x 64 103 against 80 us.
+  // Without a scan, groups pay from three tenths full (400 of up to 1000 x 16 heads x 128, 0.66: 1.71 ms longest first, 1.15 in
+  // groups; 300 x 12 heads x 64 with one of 4096 among short ones, 0.07: 135 and 200 us).
+  const int64_t filled = T / kBQ + B, most = (int64_t)B * n_qblocks;
+  const bool few = 2 * all <= 9 * 256 * (D == 128 ? 2 : 3);   // 4.5 rounds of 2 or 3 workgroups per CU
+  const bool sparse = !PADDED && 5 * filled <= 4 * most;
+  const bool scan = sparse && B <= kAttnScan && !(few && 2 * filled > most);
+  const bool grouped = !scan && !few && n_qblocks > 1 && whole > 0 && (PADDED || 10 * filled > 3 * most);
+  const int64_t groups = (whole + kAttnGroup - 1) / kAttnGroup;
+  const int32_t group = grouped ? (int32_t)((whole + groups - 1) / groups) : 0;
+  const int64_t per_xcd = scan ? filled * (nh / kXcds) + (filled * (nh % kXcds) + 7 * (int64_t)B) / kXcds
+                        : grouped ? whole * n_qblocks + (rest * n_qblocks + kXcds - 1) / kXcds
+                                  : (all + kXcds - 1) / kXcds;
+  kern<<<dim3((unsigned)(per_xcd * kXcds)), dim3(kAttnWaves * 64), lds, s>>>(q, k, v, out, cu, B, nh, scan ? 0 : n_qblocks,
+                                                                            group, max_len);
   return hipGetLastError();
 }
 

@@ -1,7 +1,8 @@
 """Which blocks the 16-bit attention kernel computes: batches whose padded length leaves most query blocks empty (the
 kernel then counts only the blocks that have queries, from a scan of up to 256 lengths), batches beyond that limit
-and dense ones (blocks straight from the workgroup id), head counts that the 8 XCDs do not share evenly, sequences
-at the edges of the 32-key tiles and 128-query blocks.  Against the oracle at the suite's bars."""
+and dense ones (blocks straight from the workgroup id, longest first, or in groups of (sequence, head) pairs per XCD where
+there are many), head counts that the 8 XCDs do not share evenly, sequences at the edges of the 32-key tiles and
+128-query blocks.  Against the oracle at the suite's bars."""
 import numpy as np
 import pytest
 import torch
@@ -43,3 +44,32 @@ def test_attention_blocks(lens, S, nh, d, dtype):
             blk = qkv[cu[b]:cu[b + 1]].astype(np.float64)
             ref = orc.masked_causal_attention(blk[:, :A], blk[:, A:2 * A], blk[:, 2 * A:], int(n), nh, d)
             assert_close(out[cu[b]:cu[b + 1]], ref, dtype, f"attention seq {b}", stages=2)   # P, then the output
+
+
+# more than 4.5 rounds of workgroups (2304 at width 128, 3456 at 64): pairs in groups per XCD, 4 pairs left over
+@pytest.mark.parametrize("B,nh,d,dtype", [(300, 5, 128, wl.BF16), (300, 7, 64, wl.F16)])
+@pytest.mark.parametrize("padded", [False, True])
+def test_attention_blocks_in_groups(B, nh, d, dtype, padded):
+    S, A = 257, nh * d
+    kinds = [130, 1, 129, 257, 256]                      # five sequences, over and over
+    lens = np.asarray((kinds * B)[:B], np.int32)
+    rng = np.random.default_rng(d)
+    blocks = [wl.round_to_dtype(rng.standard_normal((n, 3 * A)), dtype) for n in kinds]
+    refs = []
+    for n, blk in zip(kinds, (b.astype(np.float64) for b in blocks)):
+        refs.append(orc.masked_causal_attention(blk[:, :A], blk[:, A:2 * A], blk[:, 2 * A:], n, nh, d))
+    cu = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    cud, T = torch.from_numpy(cu).cuda(), int(cu[-1])
+    qkv = hz.to_device(np.concatenate([blocks[b % len(kinds)] for b in range(B)]), dtype)
+    out = torch.full((T + 1, A), 3.0, dtype=qkv.dtype, device="cuda")
+    if padded:
+        q, k, v, o = (torch.full((B, nh, S, d), 3.0, dtype=qkv.dtype, device="cuda") for _ in range(4))
+        E.energon_rebuild_qkv(qkv, cud, B, S, nh, d, q, k, v)
+        E.energon_attention_padded(q, k, v, cud, o)
+        E.energon_remove_attn_padding(o, cud, out[:T])
+    else:
+        E.energon_attention(qkv, out[:T], cud, B, S, nh, d)
+    out = hz.to_host(out)
+    assert np.all(out[T] == 3.0), "row past T was written"
+    for b in range(B):
+        assert_close(out[cu[b]:cu[b + 1]], refs[b % len(kinds)], dtype, f"attention seq {b}", stages=2)
