@@ -5,9 +5,9 @@
 // whole removal is ONE launch and no copy: the lengths travel in the kernel's argument block, the
 // first wavefront of every workgroup scans them with lane shuffles into LDS (a few hundred cycles,
 // hidden behind the other workgroups' row traffic), workgroup 0 also writes cu to global memory,
-// and every wavefront then gathers one packed row, finding its sequence by bisection in the LDS copy of cu (two
-// rows per wavefront left too few loads in flight: 8428 x 5120 40.0 -> 37.5 us, 3184 x 12288 39.4 -> 35.6).  Larger batches scan the lengths in launches of their own (896 per
-// launch, again from the argument block, each continuing from the previous one's last sum) and gather
+// and every wavefront then gathers one packed row, or two consecutive ones (pack_rows_per_wave), finding the first
+// one's sequence by bisection in the LDS copy of cu.  Larger batches scan the lengths in launches of their own
+// (896 per launch, again from the argument block, each continuing from the previous one's last sum) and gather
 // with cu in global memory.  The scatter walks the padded rows and either
 // copies a packed row or writes zeros.  All row traffic is 16-byte vectors, a wavefront per row, so
 // every access is a full contiguous line; a row moves in batches of eight vectors per lane, all
@@ -67,8 +67,8 @@ __device__ __forceinline__ void copy_row(const u32x4* __restrict__ src, u32x4* _
 }
 
 // SCAN: the lengths are in the argument block and cu is built here (see the file comment);
-// otherwise cu_global already holds the prefix sums.
-template <bool SCAN>
+// otherwise cu_global already holds the prefix sums.  ROWS: consecutive packed rows gathered by one wavefront.
+template <bool SCAN, int ROWS>
 __global__ __launch_bounds__(kPackWaves* kWave) void pack_rows_kernel(
     const u32x4* __restrict__ x_padded, u32x4* __restrict__ x_packed, const LensArg lens, int32_t* cu_global,
     int32_t* __restrict__ token_idx, int32_t B, int32_t S, int32_t row_vecs, int64_t T) {
@@ -96,17 +96,24 @@ __global__ __launch_bounds__(kPackWaves* kWave) void pack_rows_kernel(
       for (int32_t i = threadIdx.x; i <= B; i += kPackWaves * kWave) cu_global[i] = cu_s[i];
   }
   const int32_t* cu = SCAN ? cu_s : cu_global;
-  const int64_t t = (int64_t)blockIdx.x * kPackWaves + wave;
-  if (t >= T) return;
-  // largest b with cu[b] <= t; then cu[b] <= t < cu[b+1], so sequence b is not empty
-  int32_t lo = 0, hi = B;
-  while (hi - lo > 1) {
-    const int32_t mid = (lo + hi) >> 1;
-    if ((int64_t)cu[mid] <= t) lo = mid; else hi = mid;
+  const int64_t t0 = ((int64_t)blockIdx.x * kPackWaves + wave) * ROWS;
+  if (t0 >= T) return;
+  // largest b with cu[b] <= t0; then cu[b] <= t0 < cu[b+1], so sequence b is not empty
+  int32_t b = 0, hi = B;
+  while (hi - b > 1) {
+    const int32_t mid = (b + hi) >> 1;
+    if ((int64_t)cu[mid] <= t0) b = mid; else hi = mid;
   }
-  const int32_t src_row = lo * S + (int32_t)(t - cu[lo]);
-  if (lane == 0) token_idx[t] = src_row;
-  copy_row<false>(x_padded + (size_t)src_row * row_vecs, x_packed + (size_t)t * row_vecs, row_vecs, lane);
+#pragma unroll
+  for (int r = 0; r < ROWS; ++r) {
+    const int64_t t = t0 + r;
+    if (t >= T) break;
+    if (r > 0)
+      while (t >= (int64_t)cu[b + 1]) ++b;   // skips empty sequences; ends because t < T = cu[B]
+    const int32_t src_row = b * S + (int32_t)(t - cu[b]);
+    if (lane == 0) token_idx[t] = src_row;
+    copy_row<false>(x_padded + (size_t)src_row * row_vecs, x_packed + (size_t)t * row_vecs, row_vecs, lane);
+  }
 }
 
 __global__ __launch_bounds__(kRowsPerBlock* kWave) void unpack_rows_kernel(
@@ -149,8 +156,14 @@ hipError_t launch_scan_lengths_host(const int32_t* lengths_host, int32_t* cu, in
   return hipSuccess;
 }
 
-static unsigned pack_grid(int64_t T) {
-  const int64_t blocks = (T + kPackWaves - 1) / kPackWaves;   // T < 2^31
+// Two rows behind one another leave a wavefront of wide rows too few loads in flight; one narrow row does not pay for its
+// wavefront (us, one row / two: 8711 x 24 KB 86 / 92, 32383 x 16 KB 215 / 217, 63903 x 8 KB 211 / 214, 110424 x 5 KB
+// 245 / 234, 128911 x 4 KB 237 / 228, 254446 x 128 bytes 138 / 84).  Two also keep the launch within 2^32 threads for
+// 2^27 rows; 2^26 rows of 8 KB exceed the device's memory.
+static int pack_rows_per_wave(int64_t T, int64_t row_bytes) { return row_bytes < 8192 && T > 4096 ? 2 : 1; }
+
+static unsigned pack_grid(int64_t T, int rows) {
+  const int64_t per_block = kPackWaves * rows, blocks = (T + per_block - 1) / per_block;   // T < 2^31
   return (unsigned)(blocks > 0 ? blocks : 1);
 }
 
@@ -161,8 +174,10 @@ hipError_t launch_pack_scan_rows(const void* x_padded, void* x_packed, const int
   LensArg arg;
   for (int32_t b = 0; b < B; ++b) arg.v[b] = lengths_host[b];
   for (int32_t b = B; b < kLensArgMax; ++b) arg.v[b] = 0;
-  pack_rows_kernel<true><<<pack_grid(T), kPackWaves * kWave, 0, s>>>((const u32x4*)x_padded, (u32x4*)x_packed, arg, cu,
-                                                                     token_idx, B, S, (int32_t)(row_bytes / 16), T);
+  const int rows = pack_rows_per_wave(T, row_bytes);
+  const auto kern = rows == 2 ? pack_rows_kernel<true, 2> : pack_rows_kernel<true, 1>;
+  kern<<<pack_grid(T, rows), kPackWaves * kWave, 0, s>>>((const u32x4*)x_padded, (u32x4*)x_packed, arg, cu, token_idx, B, S,
+                                                         (int32_t)(row_bytes / 16), T);
   return hipGetLastError();
 }
 
@@ -170,9 +185,11 @@ hipError_t launch_pack_rows(const void* x_padded, void* x_packed, const int32_t*
                             int32_t S, int64_t row_bytes, int64_t T, hipStream_t s) {
   if (T <= 0) return hipSuccess;
   const LensArg none{};
-  pack_rows_kernel<false><<<pack_grid(T), kPackWaves * kWave, 0, s>>>(
-      (const u32x4*)x_padded, (u32x4*)x_packed, none, const_cast<int32_t*>(cu), token_idx, B, S,
-      (int32_t)(row_bytes / 16), T);
+  const int rows = pack_rows_per_wave(T, row_bytes);
+  const auto kern = rows == 2 ? pack_rows_kernel<false, 2> : pack_rows_kernel<false, 1>;
+  kern<<<pack_grid(T, rows), kPackWaves * kWave, 0, s>>>((const u32x4*)x_padded, (u32x4*)x_packed, none,
+                                                         const_cast<int32_t*>(cu), token_idx, B, S,
+                                                         (int32_t)(row_bytes / 16), T);
   return hipGetLastError();
 }
 
