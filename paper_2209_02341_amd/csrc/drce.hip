@@ -14,7 +14,7 @@
 
 namespace energon {
 
-constexpr int kMoveVecs = 8;   // 16-byte vectors per lane
+constexpr int kMoveVecs = 8;   // 16-byte vectors per lane and batch
 
 // This workgroup's sequence, first position and group of four heads; ids walk the groups of heads fastest, so that
 // workgroups side by side read (or write) the same packed rows.
@@ -26,29 +26,57 @@ __device__ __forceinline__ DrceBlock drce_block(int32_t S, int32_t groups, int32
   return {b, (at - b * chunks) * positions, (int32_t)(blockIdx.x - at * groups) * 4 + (int32_t)(threadIdx.x >> 6)};
 }
 
-// HV = 16-byte vectors per head
-template <int HV>
+// HV = 16-byte vectors per head, VECS = 16-byte vectors per lane
+template <int HV, int VECS>
 __global__ __launch_bounds__(256) void rebuild_qkv_kernel(const uint4* __restrict__ qkv, uint4* __restrict__ q,
                                                           uint4* __restrict__ k, uint4* __restrict__ v,
                                                           const int32_t* __restrict__ cu, int32_t S, int32_t nh,
                                                           int32_t groups) {
   constexpr int R = 64 / HV;   // positions per load of the wavefront
-  const DrceBlock at = drce_block(S, groups, kMoveVecs * R);
+  const DrceBlock at = drce_block(S, groups, VECS * R);
   if (at.head >= 3 * nh) return;   // head of Q, K or V
   const int lane = threadIdx.x & 63, sub = lane % HV;
   const int32_t c0 = cu[at.b], len = cu[at.b + 1] - c0;
   const int32_t which = at.head / nh, h = at.head - which * nh, s = at.s0 + lane / HV;
   const uint4* src = qkv + ((size_t)(c0 + s) * 3 * nh + at.head) * HV + sub;
   uint4* dst = (which == 0 ? q : which == 1 ? k : v) + (((size_t)at.b * nh + h) * S + s) * HV + sub;
-  uint4 r[kMoveVecs];
+  uint4 r[VECS];
 #pragma unroll
-  for (int i = 0; i < kMoveVecs; ++i) {
+  for (int i = 0; i < VECS; ++i) {
     r[i] = make_uint4(0, 0, 0, 0);
     if (s + i * R < len) r[i] = src[(size_t)(i * R) * 3 * nh * HV];
   }
 #pragma unroll
-  for (int i = 0; i < kMoveVecs; ++i)
+  for (int i = 0; i < VECS; ++i)
     if (s + i * R < S) dst[i * 64] = r[i];
+}
+
+// The same where a sequence has few positions: rows of a sequence's [nh, S] block, head after head, so that a wavefront's
+// 8 KiB still are one run.
+template <int HV>
+__global__ __launch_bounds__(256) void rebuild_short_kernel(const uint4* __restrict__ qkv, uint4* __restrict__ q,
+                                                            uint4* __restrict__ k, uint4* __restrict__ v,
+                                                            const int32_t* __restrict__ cu, int32_t B, int32_t S,
+                                                            int32_t nh, int32_t chunks) {
+  constexpr int R = 64 / HV;   // rows per load of the wavefront
+  const int32_t id = (int32_t)blockIdx.x * 4 + (int32_t)(threadIdx.x >> 6);
+  const int32_t b = id / (3 * chunks), at = id - b * 3 * chunks, which = at / chunks;
+  if (b >= B) return;
+  const int lane = threadIdx.x & 63, sub = lane % HV;
+  const int32_t c0 = cu[b], len = cu[b + 1] - c0, rows = nh * S;
+  const int32_t row0 = (at - which * chunks) * (kMoveVecs * R) + lane / HV;
+  const uint4* src = qkv + ((size_t)c0 * 3 + which) * nh * HV + sub;
+  uint4* dst = (which == 0 ? q : which == 1 ? k : v) + (size_t)b * rows * HV + sub;
+  uint4 r[kMoveVecs];
+#pragma unroll
+  for (int i = 0; i < kMoveVecs; ++i) {
+    const int32_t row = row0 + i * R, h = row / S, s = row - h * S;
+    r[i] = make_uint4(0, 0, 0, 0);
+    if (row < rows && s < len) r[i] = src[((size_t)s * 3 * nh + h) * HV];
+  }
+#pragma unroll
+  for (int i = 0; i < kMoveVecs; ++i)
+    if (row0 + i * R < rows) dst[(size_t)(row0 + i * R) * HV] = r[i];
 }
 
 template <int HV>
@@ -77,19 +105,34 @@ __global__ __launch_bounds__(256) void remove_padding_heads_kernel(const uint4* 
   }
 }
 
-static unsigned drce_grid(int32_t B, int32_t S, int32_t groups, int hv) {
-  const int32_t positions = kMoveVecs * (64 / hv);
-  return (unsigned)((int64_t)B * ((S + positions - 1) / positions) * groups);
+template <int HV>
+static hipError_t rebuild(const uint4* qkv, uint4* q, uint4* k, uint4* v, const int32_t* cu, int32_t B, int32_t S, int32_t nh,
+                          hipStream_t s) {
+  constexpr int32_t positions = kMoveVecs * (64 / HV);   // of one head, moved by a wavefront
+  const int32_t groups = (3 * nh + 3) / 4;
+  const auto blocks = [&](int32_t per) { return (int64_t)B * ((S + per - 1) / per) * groups; };
+  // Fewer than an eighth of them filled in a launch of many workgroups: heads behind one another instead (us, one position
+  // per wavefront / this / heads' positions: 2000 x 1 position x 40 x 128 24 / 23 / 56, 3000 x 3 x 12 x 64 15.4 / 13.5 / 24.8,
+  // 1000 x 4 x 40 x 128 42 / 38 / 37; but 1 x 3 x 40 x 128 5.8 / 3.4 / 2.2).
+  if (8 * S < positions && blocks(positions) > 2048) {
+    const int32_t chunks = (nh * S + positions - 1) / positions;
+    rebuild_short_kernel<HV><<<dim3((unsigned)(((int64_t)B * 3 * chunks + 3) / 4)), dim3(256), 0, s>>>(qkv, q, k, v, cu, B, S, nh,
+                                                                                                     chunks);
+    return hipGetLastError();
+  }
+  // Too few workgroups for the chip: a quarter of the vectors per lane, four times as many wavefronts
+  if (blocks(positions) < 256)
+    rebuild_qkv_kernel<HV, kMoveVecs / 4><<<dim3((unsigned)blocks(positions / 4)), dim3(256), 0, s>>>(qkv, q, k, v, cu, S, nh, groups);
+  else
+    rebuild_qkv_kernel<HV, kMoveVecs><<<dim3((unsigned)blocks(positions)), dim3(256), 0, s>>>(qkv, q, k, v, cu, S, nh, groups);
+  return hipGetLastError();
 }
 
 // head_bytes = 128 or 256
 hipError_t launch_rebuild_qkv(const void* qkv, void* q, void* k, void* v, const int32_t* cu, int32_t B, int32_t S,
                               int32_t nh, int32_t head_bytes, hipStream_t s) {
-  const int32_t groups = (3 * nh + 3) / 4;
-  const auto kern = head_bytes == 256 ? rebuild_qkv_kernel<16> : rebuild_qkv_kernel<8>;
-  kern<<<dim3(drce_grid(B, S, groups, head_bytes / 16)), dim3(256), 0, s>>>(
-      static_cast<const uint4*>(qkv), static_cast<uint4*>(q), static_cast<uint4*>(k), static_cast<uint4*>(v), cu, S, nh, groups);
-  return hipGetLastError();
+  const auto f = head_bytes == 256 ? rebuild<16> : rebuild<8>;
+  return f(static_cast<const uint4*>(qkv), static_cast<uint4*>(q), static_cast<uint4*>(k), static_cast<uint4*>(v), cu, B, S, nh, s);
 }
 
 hipError_t launch_remove_padding_heads(const void* o, void* out, const int32_t* cu, int32_t B, int32_t S, int32_t nh,

@@ -47,3 +47,22 @@ def test_pack_of_more_than_2_to_26_rows():
     assert cu.tolist() == [0, S, T]
     assert torch.equal(idx, torch.arange(T, dtype=torch.int32, device="cuda"))
     assert torch.equal(xp.view(torch.int16), x.view(torch.int16).view(2 * S, H)[:T])
+
+
+# sequences of few positions: heads' positions per wavefront, or (fewer than 4 positions at width 128, 8 at 64, many
+# workgroups) heads behind one another; launches of few workgroups with fewer vectors per lane
+@pytest.mark.parametrize("B,S,nh,d", [(700, 1, 5, 128), (1100, 3, 7, 128), (700, 4, 5, 128), (2100, 1, 1, 64), (900, 7, 3, 64),
+                                      (900, 8, 3, 64), (3, 3, 5, 128), (2, 7, 9, 64), (1, 70, 3, 64), (2, 33, 3, 128),
+                                      (90, 65, 5, 64), (90, 33, 5, 128)])
+def test_rebuild_of_short_sequences(B, S, nh, d):
+    rng = np.random.default_rng(B + S)
+    lens = rng.integers(0, S + 1, size=B).astype(np.int32)
+    lens[0], lens[-1] = S, S
+    T, A = int(lens.sum()), nh * d
+    qkv = wl.round_to_dtype(rng.standard_normal((T, 3 * A)), wl.BF16)
+    cu_ref, _ = orc.pack_indices(lens, S)
+    pads = [torch.full((B + 1, nh, S, d), 9.0, dtype=torch.bfloat16, device="cuda") for _ in range(3)]
+    E.energon_rebuild_qkv(hz.to_device(qkv, wl.BF16), torch.from_numpy(cu_ref).cuda(), B, S, nh, d, *(p[:B] for p in pads))
+    for got, want in zip(pads, orc.rebuild_qkv_heads(qkv, lens, S, nh, d)):
+        assert np.array_equal(_bits(got[:B]), _bits(torch.from_numpy(want.astype(np.float32)).to(torch.bfloat16)))
+        assert torch.all(got[B] == 9.0), "past the last sequence was written"
