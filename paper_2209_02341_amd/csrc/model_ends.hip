@@ -14,12 +14,19 @@ namespace energon {
 
 namespace {
 
-// Vectors per lane and source that are requested before the first is stored: a prompt of a few hundred tokens
-// gives a CU one workgroup, so its time is the number of memory latencies in a row (928 tokens x 5120: embedding
-// 10.5 -> 8.0 us, cache fill 11.0 -> 9.0, with one vector at a time before).
-constexpr int kEndsBatch = 5;
+// U = vectors per lane and source that are requested before the first is stored: a prompt of a few hundred tokens
+// gives a CU one workgroup, so its time is the number of memory latencies in a row.  Rows of fewer than four vectors per lane
+// go one at a time: batches cost registers there and gain nothing.
+static int ends_batch(int32_t vecs) {
+  const int32_t v = vecs / 64;   // full steps of a row's lanes
+  if (v < 4) return 1;
+  int best = 4;
+  for (const int u : {5, 8})
+    if (v >= u && v % u <= v % best) best = u;   // the fewest single steps behind the batches, then the longest batch
+  return best;
+}
 
-template <typename E>
+template <typename E, int U>
 __global__ __launch_bounds__(256) void embed_packed_kernel(const int32_t* __restrict__ ids,
                                                            const int32_t* __restrict__ cu,
                                                            const int32_t* __restrict__ positions, int32_t B, int64_t T,
@@ -54,15 +61,17 @@ __global__ __launch_bounds__(256) void embed_packed_kernel(const int32_t* __rest
     o[v] = r;
   };
   int32_t v = lane;
-  for (; v + 64 * (kEndsBatch - 1) < H / 8; v += 64 * kEndsBatch) {
-    vec8<E> a8[kEndsBatch], p8[kEndsBatch];
+  if constexpr (U > 1) {
+    for (; v + 64 * (U - 1) < H / 8; v += 64 * U) {
+      vec8<E> a8[U], p8[U];
 #pragma unroll
-    for (int u = 0; u < kEndsBatch; ++u) {
-      a8[u] = a[v + 64 * u];
-      p8[u] = p[v + 64 * u];
+      for (int u = 0; u < U; ++u) {
+        a8[u] = a[v + 64 * u];
+        p8[u] = p[v + 64 * u];
+      }
+#pragma unroll
+      for (int u = 0; u < U; ++u) put(v + 64 * u, a8[u], p8[u]);
     }
-#pragma unroll
-    for (int u = 0; u < kEndsBatch; ++u) put(v + 64 * u, a8[u], p8[u]);
   }
   for (; v < H / 8; v += 64) put(v, a[v], p[v]);
 }
@@ -79,6 +88,7 @@ __global__ __launch_bounds__(256) void last_rows_kernel(const uint4* __restrict_
 
 // K and V thirds of the packed QKV rows of a prefill -> rows 0 .. len-1 of each sequence's cache
 // [B, S_cap, A]; one wavefront per packed row, 16-byte vectors.
+template <int U>
 __global__ __launch_bounds__(256) void cache_fill_kernel(const uint4* __restrict__ qkv, const int32_t* __restrict__ cu,
                                                          int32_t B, int64_t T, int32_t a_vecs, int32_t S_cap,
                                                          uint4* __restrict__ kc, uint4* __restrict__ vc) {
@@ -95,17 +105,19 @@ __global__ __launch_bounds__(256) void cache_fill_kernel(const uint4* __restrict
   const uint4* src = qkv + (size_t)t * 3 * a_vecs;
   const size_t dst = ((size_t)lo * S_cap + pos) * a_vecs;
   int32_t v = lane;
-  for (; v + 64 * (kEndsBatch - 1) < a_vecs; v += 64 * kEndsBatch) {
-    uint4 k[kEndsBatch], w[kEndsBatch];
+  if constexpr (U > 1) {
+    for (; v + 64 * (U - 1) < a_vecs; v += 64 * U) {
+      uint4 k[U], w[U];
 #pragma unroll
-    for (int u = 0; u < kEndsBatch; ++u) {
-      k[u] = src[a_vecs + v + 64 * u];
-      w[u] = src[2 * a_vecs + v + 64 * u];
-    }
+      for (int u = 0; u < U; ++u) {
+        k[u] = src[a_vecs + v + 64 * u];
+        w[u] = src[2 * a_vecs + v + 64 * u];
+      }
 #pragma unroll
-    for (int u = 0; u < kEndsBatch; ++u) {
-      kc[dst + v + 64 * u] = k[u];
-      vc[dst + v + 64 * u] = w[u];
+      for (int u = 0; u < U; ++u) {
+        kc[dst + v + 64 * u] = k[u];
+        vc[dst + v + 64 * u] = w[u];
+      }
     }
   }
   for (; v < a_vecs; v += 64) {
@@ -119,8 +131,20 @@ __global__ __launch_bounds__(256) void cache_fill_kernel(const uint4* __restrict
 hipError_t launch_cache_fill(const void* qkv, const int32_t* cu, int32_t B, int64_t T, int64_t a_bytes, int32_t S_cap,
                              void* kc, void* vc, hipStream_t s) {
   if (T <= 0) return hipSuccess;
-  cache_fill_kernel<<<dim3((unsigned)((T + 3) / 4)), dim3(256), 0, s>>>((const uint4*)qkv, cu, B, T, (int32_t)(a_bytes / 16),
-                                                                       S_cap, (uint4*)kc, (uint4*)vc);
+  const int u = ends_batch((int32_t)(a_bytes / 16));
+  const auto kern = u == 1 ? cache_fill_kernel<1> : u == 4 ? cache_fill_kernel<4> : u == 5 ? cache_fill_kernel<5> : cache_fill_kernel<8>;
+  kern<<<dim3((unsigned)((T + 3) / 4)), dim3(256), 0, s>>>((const uint4*)qkv, cu, B, T, (int32_t)(a_bytes / 16), S_cap, (uint4*)kc,
+                                                         (uint4*)vc);
+  return hipGetLastError();
+}
+
+template <typename E>
+static hipError_t embed(const int32_t* ids, const int32_t* cu, const int32_t* positions, int32_t B, int64_t T, const void* wte,
+                        int32_t V, const void* wpe, int32_t P, int32_t H, void* x, hipStream_t s) {
+  const int u = ends_batch(H / 8);
+  const auto kern = u == 1 ? embed_packed_kernel<E, 1> : u == 4 ? embed_packed_kernel<E, 4>
+                  : u == 5 ? embed_packed_kernel<E, 5> : embed_packed_kernel<E, 8>;
+  kern<<<dim3((unsigned)((T + 3) / 4)), dim3(256), 0, s>>>(ids, cu, positions, B, T, (const E*)wte, V, (const E*)wpe, P, H, (E*)x);
   return hipGetLastError();
 }
 
@@ -129,15 +153,8 @@ hipError_t launch_embed_packed(const int32_t* ids, const int32_t* cu, const int3
                                const void* wte, int32_t V, const void* wpe, int32_t P, int32_t H, int dtype, void* x,
                                hipStream_t s) {
   if (T <= 0) return hipSuccess;
-  const dim3 grid((unsigned)((T + 3) / 4)), block(256);
-  if (dtype == 1)
-    embed_packed_kernel<bf16_t><<<grid, block, 0, s>>>(ids, cu, positions, B, T, (const bf16_t*)wte, V, (const bf16_t*)wpe, P,
-                                                       H,
-                                                       (bf16_t*)x);
-  else
-    embed_packed_kernel<f16_t><<<grid, block, 0, s>>>(ids, cu, positions, B, T, (const f16_t*)wte, V, (const f16_t*)wpe, P, H,
-                                                      (f16_t*)x);
-  return hipGetLastError();
+  return dtype == 1 ? embed<bf16_t>(ids, cu, positions, B, T, wte, V, wpe, P, H, x, s)
+                    : embed<f16_t>(ids, cu, positions, B, T, wte, V, wpe, P, H, x, s);
 }
 
 hipError_t launch_last_rows(const void* x, const int32_t* cu, int32_t B, int64_t row_bytes, void* out, hipStream_t s) {

@@ -66,3 +66,41 @@ def test_rebuild_of_short_sequences(B, S, nh, d):
     for got, want in zip(pads, orc.rebuild_qkv_heads(qkv, lens, S, nh, d)):
         assert np.array_equal(_bits(got[:B]), _bits(torch.from_numpy(want.astype(np.float32)).to(torch.bfloat16)))
         assert torch.all(got[B] == 9.0), "past the last sequence was written"
+
+
+# rows of one step of the lanes, of batches of 4, 5 and 8 vectors with and without single steps behind them, ragged ends
+WIDTHS = [2040, 2048, 2056, 2560, 3080, 4096, 4104, 5120, 5128, 12288]
+
+
+@pytest.mark.parametrize("H", WIDTHS)
+@pytest.mark.parametrize("dtype", [wl.BF16, wl.F16])
+def test_embedding_of_wide_rows(H, dtype):
+    rng = np.random.default_rng(H)
+    V, P, lens = 50, 40, [5, 0, 9]
+    T = sum(lens)
+    wte, wpe = (wl.round_to_dtype(rng.standard_normal((n, H)), dtype) for n in (V, P))
+    ids = rng.integers(0, V, size=T).astype(np.int32)
+    cu = torch.tensor(np.concatenate([[0], np.cumsum(lens)]), dtype=torch.int32, device="cuda")
+    wted, wped = hz.to_device(wte, dtype), hz.to_device(wpe, dtype)
+    x = torch.full((T + 1, H), 3.0, dtype=wted.dtype, device="cuda")
+    E.energon_embed_packed(torch.from_numpy(ids).cuda(), cu, wted, wped, x[:T])
+    pos = np.concatenate([np.arange(n) for n in lens])
+    want = (wted[torch.from_numpy(ids.astype(np.int64)).cuda()].float() + wped[torch.from_numpy(pos).cuda()].float()).to(wted.dtype)
+    assert torch.equal(x[:T].view(torch.int16), want.view(torch.int16))     # one rounding of an exact fp32 sum
+    assert torch.all(x[T] == 3.0), "row past T was written"
+
+
+@pytest.mark.parametrize("A", WIDTHS)
+def test_cache_fill_of_wide_rows(A):
+    lens, S_cap = [5, 0, 9], 11
+    T = sum(lens)
+    qkv = torch.randint(-2 ** 15, 2 ** 15, (T, 3 * A), dtype=torch.int16, device="cuda")
+    cu = torch.tensor(np.concatenate([[0], np.cumsum(lens)]), dtype=torch.int32, device="cuda")
+    caches = [torch.full((3, S_cap, A), 77, dtype=torch.int16, device="cuda") for _ in range(2)]
+    E.energon_cache_fill(qkv.view(torch.bfloat16), cu, *(c.view(torch.bfloat16) for c in caches))
+    for c, part in zip(caches, (1, 2)):
+        t = 0
+        for b, n in enumerate(lens):
+            assert torch.equal(c[b, :n], qkv[t:t + n, part * A:(part + 1) * A])
+            assert torch.all(c[b, n:] == 77)
+            t += n
