@@ -5,10 +5,10 @@
 // paper's padding elimination (Sec. 4.3), no position beyond a sequence's real length is touched.
 //
 // The work is one pass over the cached rows (2 * d * e bytes per key and head, each used once):
-// bound by HBM, so there is no MFMA here.  One workgroup (8 wavefronts) per (sequence, head), or per part of its keys
+// bound by HBM, so there is no MFMA here.  One workgroup (4 or 8 wavefronts) per (sequence, head), or per part of its keys
 // where there are few of them; a key's head slice (d elements) is spread over d / 8 lanes, 16 bytes each, so a
 // wavefront takes 64 / (d / 8) keys per step with fully coalesced loads.  Each lane group runs its own online softmax
-// over the keys it sees, two steps' loads ahead of its arithmetic; the groups' states are merged by lane
+// over the keys it sees, one or two steps' loads ahead of its arithmetic; the groups' states are merged by lane
 // exchanges, the wavefronts' through LDS, the parts' by a second small kernel, always in a fixed order.  The new
 // token's k and v are read from the qkv row and written to the cache row at the sequence's length.
 // Whole steps of a 13B-size layer (us; with 4 wavefronts, no loads ahead and no parts before): 2 sequences of 4096
@@ -32,6 +32,19 @@ template <int LPK> __device__ __forceinline__ float key_sum(float v) {
   return v;
 }
 
+// the same value of lane ^ off (off = 8, 16 or 32) combined with the own one, on the vector ALU
+template <typename F> __device__ __forceinline__ float with_lane_xor(float v, int off, F f) {
+  const unsigned u = __float_as_uint(v);
+  if (off == 8) return f(v, __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x128, 0xF, 0xF, true)));   // row_ror 8
+  if (off == 16) {
+    const auto r = __builtin_amdgcn_permlane16_swap(u, u, false, false);
+    return f(__uint_as_float(r[0]), __uint_as_float(r[1]));
+  }
+  const auto r = __builtin_amdgcn_permlane32_swap(u, u, false, false);
+  return f(__uint_as_float(r[0]), __uint_as_float(r[1]));
+}
+__device__ __forceinline__ float add2(float a, float b) { return a + b; }
+
 // grid = (B * nh, parts): part y of a (sequence, head) takes the y-th of equal shares of its keys.  With parts == 1
 // the result goes to out, otherwise each part leaves its state (D sums, running max, running sum) in
 // part[(y * B * nh + x) * (D + 2)] for decode_merge_kernel.
@@ -48,7 +61,7 @@ __global__ __launch_bounds__(NW * 64) void decode_attention_kernel(const E* __re
 
   const int32_t b = blockIdx.x / nh, h = blockIdx.x % nh;
   const int32_t A = nh * D;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int sub = lane % LPK, slot = wave * KPW + lane / LPK;   // which 8 elements of d; which key of a step
   int32_t p = lens[b];
   p = p < 0 ? 0 : (p > S_cap ? S_cap : p);     // cached keys; the new token is key p
@@ -113,12 +126,13 @@ __global__ __launch_bounds__(NW * 64) void decode_attention_kernel(const E* __re
     }
   };
   constexpr int kTrip = KPB * U;
-  if (first < end) load(0, first);
-  for (int32_t j0 = first; j0 < end; j0 += 2 * kTrip) {
-    if (j0 + kTrip < end) load(1, j0 + kTrip);
+  const int32_t last = end - wave * KPW;   // a wavefront whose keys of a trip all lie behind the end leaves
+  if (first < last) load(0, first);
+  for (int32_t j0 = first; j0 < last; j0 += 2 * kTrip) {
+    if (j0 + kTrip < last) load(1, j0 + kTrip);
     step(0, j0);
-    if (j0 + kTrip < end) {
-      if (j0 + 2 * kTrip < end) load(0, j0 + 2 * kTrip);
+    if (j0 + kTrip < last) {
+      if (j0 + 2 * kTrip < last) load(0, j0 + 2 * kTrip);
       step(1, j0 + kTrip);
     }
   }
@@ -127,16 +141,16 @@ __global__ __launch_bounds__(NW * 64) void decode_attention_kernel(const E* __re
   // state that saw no key of weight has m = kLowest, l = 0, o = 0.
   float M = m_run;
 #pragma unroll
-  for (int off = LPK; off < 64; off <<= 1) M = fmaxf(M, __shfl_xor(M, off, 64));
+  for (int off = LPK; off < 64; off <<= 1) M = with_lane_xor(M, off, fmaxf);
   const float wgt = __builtin_amdgcn_exp2f(m_run - M);
   l_run *= wgt;
 #pragma unroll
   for (int e = 0; e < 8; ++e) o[e] *= wgt;
 #pragma unroll
   for (int off = LPK; off < 64; off <<= 1) {
-    l_run += __shfl_xor(l_run, off, 64);
+    l_run = with_lane_xor(l_run, off, add2);
 #pragma unroll
-    for (int e = 0; e < 8; ++e) o[e] += __shfl_xor(o[e], off, 64);
+    for (int e = 0; e < 8; ++e) o[e] = with_lane_xor(o[e], off, add2);
   }
   if (lane < LPK) {
     if (lane == 0) { st_m[wave] = M; st_l[wave] = l_run; }
@@ -198,8 +212,16 @@ hipError_t launch_dec(const E* qkv, E* kc, E* vc, const int32_t* lens, int32_t B
   const size_t state = (size_t)pairs * (D + 2) * sizeof(float);
   const int32_t fit = scratch != nullptr ? (int32_t)std::min<size_t>(scratch_bytes / state, 32) : 1;
   const int32_t parts = std::max(1, std::min(dec_parts(pairs, S_cap), fit));
-  decode_attention_kernel<E, D, 8, 2><<<dim3((unsigned)pairs, (unsigned)parts), dim3(8 * 64), 0, s>>>(
-      qkv, kc, vc, lens, nh, S_cap, out, parts > 1 ? scratch : nullptr);
+  // With a workgroup per CU or less, eight wavefronts and two steps ahead: 40 heads of 4000 keys 60 us with four wavefronts,
+  // 43 with eight.  Beyond, four: where the keys are few, eight only take longer to start (us, eight / four: 4096 heads of
+  // 50 keys x 64 18.7 / 12.7, 768 of 100 5.4 / 4.6, 3840 x 128 of 500 178 / 181).  From two and a half to eight workgroups per CU
+  // their number hides the latency, and one step ahead leaves room for more of them (one / two: 400 x 128 of 2000 keys
+  // 112 / 81, 640 128 / 129, 1024 of 1000 94 / 99, 1280 of 300 30.8 / 31.2, 3840 of 500 184 / 181).
+  const bool few = pairs <= 256;
+  const auto kern = few ? decode_attention_kernel<E, D, 8, 2> : pairs >= 640 && pairs <= 2048 ? decode_attention_kernel<E, D, 4, 1>
+                                                                                              : decode_attention_kernel<E, D, 4, 2>;
+  kern<<<dim3((unsigned)pairs, (unsigned)parts), dim3(few ? 8 * 64 : 4 * 64), 0, s>>>(qkv, kc, vc, lens, nh, S_cap, out,
+                                                                                     parts > 1 ? scratch : nullptr);
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess || parts == 1) return e;
   decode_merge_kernel<E, D><<<dim3((unsigned)pairs), dim3(D), 0, s>>>(scratch, parts, out);

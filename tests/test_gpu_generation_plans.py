@@ -127,3 +127,24 @@ def test_step_with_keys_in_parts_and_scores_of_minus_infinity(hidden):
     E.energon_decode_layer_forward(cfg, layer.struct, hz.to_device(x, wl.BF16), yd, torch.from_numpy(lens).cuda(), lens,
                                    hz.to_device(kc, wl.BF16), hz.to_device(vc, wl.BF16), ws)
     assert_close(hz.to_host(yd), ref, wl.BF16, "step", **layer_noise(1, 1.0))
+
+
+# workgroups of four wavefronts, one step of loads ahead (640 to 2048 heads) and two, of eight (up to 256); lengths around a
+# trip of either
+@pytest.mark.parametrize("B,nh,d", [(64, 4, 64), (65, 4, 128), (160, 4, 128), (512, 4, 64), (513, 4, 64), (64, 10, 64)])
+def test_cached_attention_of_many_heads(B, nh, d):
+    rng = np.random.default_rng(B)
+    S_cap, A, dtype = 300, nh * d, wl.F16 if d == 64 else wl.BF16
+    kinds = [0, 1, 15, 16, 17, 31, 32, 33, 63, 64, 127, 128, 299]
+    lens = np.asarray((kinds * B)[:B], np.int32)
+    n = len(kinds)                                       # distinct sequences, over and over
+    kc, vc = (wl.round_to_dtype(rng.standard_normal((n, S_cap, A)), dtype) for _ in range(2))
+    qkv = wl.round_to_dtype(rng.standard_normal((n, 3 * A)), dtype)
+    at = torch.arange(B, device="cuda") % n
+    kd, vd, qd = (hz.to_device(t, dtype)[at].contiguous() for t in (kc, vc, qkv))
+    out = torch.empty((B, A), dtype=qd.dtype, device="cuda")
+    E.energon_decode_attention(qd, kd, vd, torch.from_numpy(lens).cuda(), nh, d, out)
+    q = qkv.astype(np.float64)
+    ref = np.stack([orc.decode_attention(q[b, :A], q[b, A:2 * A], q[b, 2 * A:], kc[b, :l].astype(np.float64),
+                                         vc[b, :l].astype(np.float64), nh, d) for b, l in enumerate(kinds)])
+    assert_close(hz.to_host(out), ref[np.arange(B) % n], dtype, "attention", stages=2)
