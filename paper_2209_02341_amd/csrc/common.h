@@ -178,8 +178,9 @@ hipError_t launch_unpack_rows(const void* y_packed, void* y_padded, const int32_
                               int64_t row_bytes, hipStream_t s);
 // layernorm.hip
 // dtype: 0 fp32, 1 bf16, 2 fp16 (the values of energon_dtype)
+// zero (optional): n_zero words that the launch sets to zero beside its own work
 hipError_t launch_layernorm(const void* x, const void* gamma, const void* beta, void* y, int64_t T, int32_t H,
-                            float eps, int dtype, hipStream_t s);
+                            float eps, int dtype, hipStream_t s, int32_t* zero = nullptr, int32_t n_zero = 0);
 // gemm_f32.hip / gemm_mfma.hip (16-bit element types on the matrix cores)
 hipError_t launch_gemm_f32(const float* x, const float* w, const float* bias, const float* res, float* y,
                            int64_t M, int32_t N, int32_t K, int epi, hipStream_t s);
@@ -218,11 +219,12 @@ template <typename E>
 hipError_t launch_partial_reduce(const float* partial, int32_t KS, const E* bias, const E* res, E* y, int64_t M,
                                  int32_t N, int epi, hipStream_t s);
 // decode_attention.hip, model_ends.hip (dtype 1 or 2 only).  scratch (optional, fp32): room for the states of keys cut
-// over workgroups, decode_attention_scratch_bytes for the most parts; what fits is used
+// over workgroups, decode_attention_scratch_bytes for the most parts; what fits is used.  arrived (with it): B * nh
+// counters that are zero when the launch starts
 size_t decode_attention_scratch_bytes(int64_t B, int32_t nh, int32_t d);
 hipError_t launch_decode_attention(const void* qkv, void* k_cache, void* v_cache, const int32_t* lens, int32_t B,
                                    int32_t S_cap, int32_t nh, int32_t d, int dtype, void* out, hipStream_t s,
-                                   float* scratch = nullptr, size_t scratch_bytes = 0);
+                                   float* scratch = nullptr, size_t scratch_bytes = 0, int32_t* arrived = nullptr);
 hipError_t launch_embed_packed(const int32_t* ids, const int32_t* cu, const int32_t* positions, int32_t B, int64_t T,
                                const void* wte, int32_t V, const void* wpe, int32_t P, int32_t H, int dtype, void* x,
                                hipStream_t s);

@@ -9,11 +9,9 @@
 // where there are few of them; a key's head slice (d elements) is spread over d / 8 lanes, 16 bytes each, so a
 // wavefront takes 64 / (d / 8) keys per step with fully coalesced loads.  Each lane group runs its own online softmax
 // over the keys it sees, one or two steps' loads ahead of its arithmetic; the groups' states are merged by lane
-// exchanges, the wavefronts' through LDS, the parts' by a second small kernel, always in a fixed order.  The new
+// exchanges, the wavefronts' through LDS, the parts' by the workgroup that finishes last, always in a fixed order.  The new
 // token's k and v are read from the qkv row and written to the cache row at the sequence's length.
-// Whole steps of a 13B-size layer (us; with 4 wavefronts, no loads ahead and no parts before): 2 sequences of 4096
-// 207 -> 170 (see dec_parts), 64 of 700 361 -> 357, 32 of up to 512 the same 41 us (4.2 TB/s); 1 of 4096 x 16 heads
-// 113 -> 91 before its keys were cut.
+// About 5.4 TB/s on long caches of many sequences (96 x 40 heads of 200 keys: 74 us).
 #include "common.h"
 #include <algorithm>
 
@@ -45,14 +43,28 @@ template <typename F> __device__ __forceinline__ float with_lane_xor(float v, in
 }
 __device__ __forceinline__ float add2(float a, float b) { return a + b; }
 
-// grid = (B * nh, parts): part y of a (sequence, head) takes the y-th of equal shares of its keys.  With parts == 1
-// the result goes to out, otherwise each part leaves its state (D sums, running max, running sum) in
-// part[(y * B * nh + x) * (D + 2)] for decode_merge_kernel.
-template <typename E, int D, int NW, int U>
+// A word that workgroups on other XCDs read in the same launch: written through, and read past, the caches that are
+// not shared.  (A release and an acquire fence around plain ones write back and drop a whole L2 each: 8 us.)
+__device__ __forceinline__ void put_shared(float* p, float v) {
+  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ float get_shared(const float* p) {
+  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// Keys of a part, at least: what is cached decides how many of the launch's parts a (sequence, head) uses.
+constexpr int kDecPartKeys = 256;
+
+// grid = (B * nh, parts): part y of a (sequence, head) takes the y-th of equal shares of its keys.  A share has
+// kDecPartKeys or more, so short sequences use fewer parts than were launched and the rest leaves at once.  With one
+// part the result goes straight to out; otherwise each leaves its state (running max, running sum, D sums) in
+// part[(y * B * nh + x) * (D + 2)], counts itself in arrived[x] (zero at the start of the launch), and the one that
+// counts last adds all of them in their order: no second launch, and nobody waits.
+template <typename E, int D, int NW, int U, bool PARTS>
 __global__ __launch_bounds__(NW * 64) void decode_attention_kernel(const E* __restrict__ qkv, E* k_cache, E* v_cache,
                                                                   const int32_t* __restrict__ lens, int32_t nh,
-                                                                  int32_t S_cap, E* __restrict__ out,
-                                                                  float* __restrict__ part) {
+                                                                  int32_t S_cap, E* __restrict__ out, float* part,
+                                                                  int32_t* arrived) {
   constexpr int LPK = D / 8;          // lanes per key
   constexpr int KPW = 64 / LPK;       // keys per wavefront step
   constexpr int KPB = KPW * NW;       // keys per step of the workgroup
@@ -65,8 +77,10 @@ __global__ __launch_bounds__(NW * 64) void decode_attention_kernel(const E* __re
   const int sub = lane % LPK, slot = wave * KPW + lane / LPK;   // which 8 elements of d; which key of a step
   int32_t p = lens[b];
   p = p < 0 ? 0 : (p > S_cap ? S_cap : p);     // cached keys; the new token is key p
-  const int32_t share = (p + (int32_t)gridDim.y) / (int32_t)gridDim.y;   // ceil((p + 1) / parts)
-  const int32_t first = (int32_t)blockIdx.y * share, end = min(first + share, p + 1);
+  const int32_t parts = PARTS ? min((int32_t)gridDim.y, p / kDecPartKeys + 1) : 1, y = PARTS ? (int32_t)blockIdx.y : 0;
+  if (y >= parts) return;
+  const int32_t share = (p + parts) / parts;   // ceil((p + 1) / parts)
+  const int32_t first = y * share, end = min(first + share, p + 1);
 
   const E* qrow = qkv + (size_t)b * 3 * A + (size_t)h * D + sub * 8;
   const vec8<E> q8 = *reinterpret_cast<const vec8<E>*>(qrow);
@@ -82,7 +96,7 @@ __global__ __launch_bounds__(NW * 64) void decode_attention_kernel(const E* __re
   const E* vc = v_cache + head_off;
 
   // append: the new token's k and v become cache row p (one wavefront's first LPK lanes)
-  if (blockIdx.y == 0 && wave == 0 && lane < LPK && p < S_cap) {
+  if (y == 0 && wave == 0 && lane < LPK && p < S_cap) {
     *reinterpret_cast<vec8<E>*>(k_cache + head_off + (size_t)p * A) = *reinterpret_cast<const vec8<E>*>(knew);
     *reinterpret_cast<vec8<E>*>(v_cache + head_off + (size_t)p * A) = *reinterpret_cast<const vec8<E>*>(vnew);
   }
@@ -158,6 +172,8 @@ __global__ __launch_bounds__(NW * 64) void decode_attention_kernel(const E* __re
     for (int e = 0; e < 8; ++e) st_o[wave][sub * 8 + e] = o[e];
   }
   __syncthreads();
+  E* const orow = out + (size_t)b * A + (size_t)h * D;
+  const size_t stride = (size_t)gridDim.x * (D + 2);   // of a part's states
   if (tid < D) {
     M = st_m[0];
 #pragma unroll
@@ -169,37 +185,51 @@ __global__ __launch_bounds__(NW * 64) void decode_attention_kernel(const E* __re
       L = fmaf(st_l[i], w, L);
       acc = fmaf(st_o[i][tid], w, acc);
     }
-    if (part == nullptr) {
-      out[(size_t)b * A + (size_t)h * D + tid] = static_cast<E>(acc / L);   // key 0 exists: L > 0
+    if (!PARTS || parts == 1) {
+      orow[tid] = static_cast<E>(acc / L);   // key 0 exists: L > 0
     } else {
-      float* dst = part + ((size_t)blockIdx.y * gridDim.x + blockIdx.x) * (D + 2);
-      dst[2 + tid] = acc;
-      if (tid == 0) { dst[0] = M; dst[1] = L; }
+      float* dst = part + y * stride + (size_t)blockIdx.x * (D + 2);
+      put_shared(dst + 2 + tid, acc);
+      if (tid == 0) { put_shared(dst, M); put_shared(dst + 1, L); }
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // they have arrived before the workgroup is counted
     }
   }
-}
-
-// The parts of a (sequence, head) added in order.
-template <typename E, int D>
-__global__ __launch_bounds__(D) void decode_merge_kernel(const float* __restrict__ part, int32_t parts,
-                                                        E* __restrict__ out) {
-  const size_t stride = (size_t)gridDim.x * (D + 2);
+  if (!PARTS || parts == 1) return;
+  __shared__ int32_t st_last;
+  __syncthreads();
+  if (tid == 0) st_last = __hip_atomic_fetch_add(arrived + blockIdx.x, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == parts - 1;
+  __syncthreads();
+  if (!st_last || tid >= D) return;
   const float* src = part + (size_t)blockIdx.x * (D + 2);
-  float M = src[0];
-  for (int32_t i = 1; i < parts; ++i) M = fmaxf(M, src[i * stride]);
+  M = kLowest;
   float L = 0.f, acc = 0.f;
-  for (int32_t i = 0; i < parts; ++i) {
-    const float w = __builtin_amdgcn_exp2f(src[i * stride] - M);
-    L = fmaf(src[i * stride + 1], w, L);
-    acc = fmaf(src[i * stride + 2 + threadIdx.x], w, acc);
+  for (int32_t i0 = 0; i0 < parts; i0 += 8) {   // eight states requested before the first is used
+    float m[8], l[8], a[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      const float* st = src + min(i0 + i, parts - 1) * stride;
+      m[i] = get_shared(st);
+      l[i] = get_shared(st + 1);
+      a[i] = get_shared(st + 2 + tid);
+    }
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      if (i0 + i >= parts) break;
+      const float m_new = fmaxf(M, m[i]);
+      const float corr = __builtin_amdgcn_exp2f(M - m_new), w = __builtin_amdgcn_exp2f(m[i] - m_new);
+      L = fmaf(L, corr, l[i] * w);
+      acc = fmaf(acc, corr, a[i] * w);
+      M = m_new;
+    }
   }
-  out[(size_t)blockIdx.x * D + threadIdx.x] = static_cast<E>(acc / L);
+  orow[tid] = static_cast<E>(acc / L);
 }
 
-// Parts of a (sequence, head)'s keys: as many as bring the launch to about 512 workgroups, each with at least 512 of
-// the cache's rows, if the scratch holds their states.  (2 sequences of 4096 x 40 heads: 66 us whole, 36 in 6
-// parts with the merge; from 256 pairs on cutting only costs the second launch: a step at 32 x 512 x 40 200 -> 207 us
-// in 4 parts.)
+// Parts that are launched for a (sequence, head)'s keys: as many as bring the launch to about 512 workgroups, each with
+// at least 512 of the cache's rows, if the scratch holds their states.  How many of them are used is decided by what is
+// cached (kDecPartKeys), so a short conversation in a long cache pays nothing.  Whole steps, us, uncut / cut: 2 of 4000
+// keys x 40 heads of 128 227 / 177, 1 of 4000 x 16 x 128 96 / 48; 2 of 100 in a cache of 16384 40.7 / 39.1 (with the parts
+// counted from the capacity and added by a second launch: 50.6).  From 256 pairs on nothing is cut.
 int32_t dec_parts(int64_t pairs, int32_t S_cap) {
   if (pairs >= 256) return 1;
   return (int32_t)std::max<int64_t>(1, std::min<int64_t>({32, 512 / pairs, S_cap / 512}));
@@ -207,10 +237,10 @@ int32_t dec_parts(int64_t pairs, int32_t S_cap) {
 
 template <typename E, int D>
 hipError_t launch_dec(const E* qkv, E* kc, E* vc, const int32_t* lens, int32_t B, int32_t S_cap, int32_t nh, E* out,
-                      float* scratch, size_t scratch_bytes, hipStream_t s) {
+                      float* scratch, size_t scratch_bytes, int32_t* arrived, hipStream_t s) {
   const int64_t pairs = (int64_t)B * nh;
   const size_t state = (size_t)pairs * (D + 2) * sizeof(float);
-  const int32_t fit = scratch != nullptr ? (int32_t)std::min<size_t>(scratch_bytes / state, 32) : 1;
+  const int32_t fit = scratch != nullptr && arrived != nullptr ? (int32_t)std::min<size_t>(scratch_bytes / state, 32) : 1;
   const int32_t parts = std::max(1, std::min(dec_parts(pairs, S_cap), fit));
   // With a workgroup per CU or less, eight wavefronts and two steps ahead: 40 heads of 4000 keys 60 us with four wavefronts,
   // 43 with eight.  Beyond, four: where the keys are few, eight only take longer to start (us, eight / four: 4096 heads of
@@ -218,13 +248,11 @@ hipError_t launch_dec(const E* qkv, E* kc, E* vc, const int32_t* lens, int32_t B
   // their number hides the latency, and one step ahead leaves room for more of them (one / two: 400 x 128 of 2000 keys
   // 112 / 81, 640 128 / 129, 1024 of 1000 94 / 99, 1280 of 300 30.8 / 31.2, 3840 of 500 184 / 181).
   const bool few = pairs <= 256;
-  const auto kern = few ? decode_attention_kernel<E, D, 8, 2> : pairs >= 640 && pairs <= 2048 ? decode_attention_kernel<E, D, 4, 1>
-                                                                                              : decode_attention_kernel<E, D, 4, 2>;
-  kern<<<dim3((unsigned)pairs, (unsigned)parts), dim3(few ? 8 * 64 : 4 * 64), 0, s>>>(qkv, kc, vc, lens, nh, S_cap, out,
-                                                                                     parts > 1 ? scratch : nullptr);
-  const hipError_t e = hipGetLastError();
-  if (e != hipSuccess || parts == 1) return e;
-  decode_merge_kernel<E, D><<<dim3((unsigned)pairs), dim3(D), 0, s>>>(scratch, parts, out);
+  const auto kern = few ? decode_attention_kernel<E, D, 8, 2, true>
+                  : pairs >= 640 && pairs <= 2048 ? decode_attention_kernel<E, D, 4, 1, false>
+                                                  : decode_attention_kernel<E, D, 4, 2, false>;
+  kern<<<dim3((unsigned)pairs, (unsigned)parts), dim3(few ? 8 * 64 : 4 * 64), 0, s>>>(qkv, kc, vc, lens, nh, S_cap, out, scratch,
+                                                                                     arrived);
   return hipGetLastError();
 }
 
@@ -237,10 +265,10 @@ size_t decode_attention_scratch_bytes(int64_t B, int32_t nh, int32_t d) {
 
 hipError_t launch_decode_attention(const void* qkv, void* k_cache, void* v_cache, const int32_t* lens, int32_t B,
                                    int32_t S_cap, int32_t nh, int32_t d, int dtype, void* out, hipStream_t s,
-                                   float* scratch, size_t scratch_bytes) {
+                                   float* scratch, size_t scratch_bytes, int32_t* arrived) {
   if (B <= 0) return hipSuccess;
 #define DEC_CASE(E, D) \
-  launch_dec<E, D>((const E*)qkv, (E*)k_cache, (E*)v_cache, lens, B, S_cap, nh, (E*)out, scratch, scratch_bytes, s)
+  launch_dec<E, D>((const E*)qkv, (E*)k_cache, (E*)v_cache, lens, B, S_cap, nh, (E*)out, scratch, scratch_bytes, arrived, s)
   return dtype == 1 ? (d == 128 ? DEC_CASE(bf16_t, 128) : DEC_CASE(bf16_t, 64))
                     : (d == 128 ? DEC_CASE(f16_t, 128) : DEC_CASE(f16_t, 64));
 #undef DEC_CASE

@@ -818,11 +818,16 @@ static int decode_layer_checked(const EnergonLayerConfig* cfg, const EnergonLaye
   const int32_t H = cfg->hidden, A = cfg->n_heads * cfg->head_dim, F = cfg->ffn, dt = cfg->dtype;
   float* const part = reinterpret_cast<float*>(base + l.total);
   const size_t part_bytes = ws_bytes - l.total;
+  // counters of the attention's parts, where keys may be cut: in the FFN's intermediate, which nothing else uses before FC1
+  const int64_t pairs = (int64_t)B * cfg->n_heads;
+  const bool counts = decode_attention_scratch_bytes(B, cfg->n_heads, cfg->head_dim) > 0 &&
+                      (size_t)F * esize(dt) >= cfg->n_heads * sizeof(int32_t);
+  int32_t* const arrived = counts ? static_cast<int32_t*>(m) : nullptr;
 #define STEP(call) do { st = (call); if (st != ENERGON_OK) return st; } while (0)
-  HIP_TRY(launch_layernorm(x, w->ln1_g, w->ln1_b, u, B, H, cfg->ln_eps, dt, s));
+  HIP_TRY(launch_layernorm(x, w->ln1_g, w->ln1_b, u, B, H, cfg->ln_eps, dt, s, arrived, counts ? (int32_t)pairs : 0));
   STEP(linear_impl(u, w->w_qkv, w->b_qkv, nullptr, qkv, B, 3 * A, H, ENERGON_EPI_BIAS, dt, s, nullptr, part, part_bytes));
   HIP_TRY(launch_decode_attention(qkv, k_cache, v_cache, cache_lens_dev, B, S_cap, cfg->n_heads, cfg->head_dim, dt,
-                                  att, s, part, part_bytes));
+                                  att, s, part, part_bytes, arrived));
   STEP(linear_impl(att, w->w_o, w->b_o, x, y1, B, H, A, ENERGON_EPI_BIAS_RESIDUAL, dt, s, nullptr, part, part_bytes));
   HIP_TRY(launch_layernorm(y1, w->ln2_g, w->ln2_b, wn, B, H, cfg->ln_eps, dt, s));
   STEP(linear_impl(wn, w->w_fc1, w->b_fc1, nullptr, m, B, F, H, ENERGON_EPI_BIAS_GELU, dt, s, nullptr, part, part_bytes));

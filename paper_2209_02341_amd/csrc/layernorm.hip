@@ -24,12 +24,15 @@ __device__ inline float block_sum(float v, float* red) {
 template <typename T, int VPT>
 __global__ __launch_bounds__(kLnThreads) void layernorm_kernel(const T* __restrict__ x, const T* __restrict__ gamma,
                                                                const T* __restrict__ beta, T* __restrict__ y,
-                                                               int32_t H, float eps) {
+                                                               int32_t H, float eps, int32_t* __restrict__ zero,
+                                                               int32_t n_zero) {
   constexpr int VEC = Elem<T>::VEC;
   __shared__ float red[kLnThreads / kWave];
   const int32_t row_vecs = H / VEC;
   const size_t row = blockIdx.x;
   const Vec16<T>* xr = reinterpret_cast<const Vec16<T>*>(x + row * H);
+  // words that a later kernel counts in, a share per row
+  for (int32_t i = blockIdx.x * kLnThreads + threadIdx.x; i < n_zero; i += gridDim.x * kLnThreads) zero[i] = 0;
   float v[VPT][VEC];
   float s = 0.f;
 #pragma unroll
@@ -75,12 +78,12 @@ __global__ __launch_bounds__(kLnThreads) void layernorm_kernel(const T* __restri
 
 template <typename T>
 static hipError_t dispatch(const void* x, const void* g, const void* b, void* y, int64_t T_, int32_t H, float eps,
-                           hipStream_t s) {
+                           hipStream_t s, int32_t* zero, int32_t n_zero) {
   const int32_t row_vecs = H / Elem<T>::VEC;
   const int vpt = (row_vecs + kLnThreads - 1) / kLnThreads;
   const dim3 grid((unsigned)T_), block(kLnThreads);
 #define LN_CASE(V)                                                                                       \
-  layernorm_kernel<T, V><<<grid, block, 0, s>>>((const T*)x, (const T*)g, (const T*)b, (T*)y, H, eps); \
+  layernorm_kernel<T, V><<<grid, block, 0, s>>>((const T*)x, (const T*)g, (const T*)b, (T*)y, H, eps, zero, n_zero); \
   break;
   switch (vpt <= 1 ? 1 : vpt <= 2 ? 2 : vpt <= 4 ? 4 : vpt <= 8 ? 8 : vpt <= 16 ? 16 : 0) {
     case 1: LN_CASE(1)
@@ -96,11 +99,11 @@ static hipError_t dispatch(const void* x, const void* g, const void* b, void* y,
 
 // Largest H one launch handles (16 vectors of 8 or 4 elements in each of 256 threads).
 hipError_t launch_layernorm(const void* x, const void* gamma, const void* beta, void* y, int64_t T, int32_t H,
-                            float eps, int dtype, hipStream_t s) {
+                            float eps, int dtype, hipStream_t s, int32_t* zero, int32_t n_zero) {
   if (T <= 0) return hipSuccess;
-  return dtype == 1 ? dispatch<bf16_t>(x, gamma, beta, y, T, H, eps, s)
-       : dtype == 2 ? dispatch<f16_t>(x, gamma, beta, y, T, H, eps, s)
-                    : dispatch<float>(x, gamma, beta, y, T, H, eps, s);
+  return dtype == 1 ? dispatch<bf16_t>(x, gamma, beta, y, T, H, eps, s, zero, n_zero)
+       : dtype == 2 ? dispatch<f16_t>(x, gamma, beta, y, T, H, eps, s, zero, n_zero)
+                    : dispatch<float>(x, gamma, beta, y, T, H, eps, s, zero, n_zero);
 }
 
 }  // namespace energon
