@@ -46,8 +46,9 @@ template <int MT, int NT, int D> struct SkCfg {
 
 // grid = (ceil(N / BN), KS).  Workgroup (nb, kz) contracts slabs [kz * KT / KS, (kz + 1) * KT / KS) of K for
 // columns 16 NT nb ..; with partial == nullptr (KS = 1) it applies the epilogue and writes y, otherwise
-// it writes its fp32 sums to partial[kz][M][N] and skinny_reduce_kernel finishes the job.
-template <typename E, int MT, int NT, int kD>
+// it writes its fp32 sums to partial[kz][M][N] and skinny_reduce_kernel finishes the job.  RAGGED: the last block has
+// fewer columns than BN (N % 8 == 0); an instance of its own, because the address of every load would pay for it.
+template <typename E, int MT, int NT, int kD, bool RAGGED>
 __global__ __launch_bounds__(kSkWaves * 64) void gemm_skinny_kernel(const E* __restrict__ x, const E* __restrict__ w,
                                                                    const E* __restrict__ bias, const E* res, E* y,
                                                                    float* __restrict__ partial, int32_t M, int32_t N,
@@ -78,7 +79,7 @@ __global__ __launch_bounds__(kSkWaves * 64) void gemm_skinny_kernel(const E* __r
   const uint32_t ch_odd = (uint32_t)(((lane & 7) ^ sk_swz((lane >> 3) | 8)) * 16);
   const uint32_t woff_even = (uint32_t)(lane >> 3) * row_b + ch_even, woff_odd = (uint32_t)(lane >> 3) * row_b + ch_odd;
   const char* wbase = reinterpret_cast<const char*>(w + (size_t)n0 * K) + (size_t)s0 * 128;   // uniform
-  const int32_t groups = (N - n0 + 7) >> 3;   // 8-row groups of W that exist (N % 8 == 0); those past the end repeat the last
+  const int32_t groups = (N - n0 + 7) >> 3;   // 8-row groups of W that exist; those past the end repeat the last
   const char* xbase = reinterpret_cast<const char*>(x) + (size_t)s0 * 128;                    // uniform
   uint32_t xoff[GX];
 #pragma unroll
@@ -100,7 +101,8 @@ __global__ __launch_bounds__(kSkWaves * 64) void gemm_skinny_kernel(const E* __r
     uint4* dst = ring + slot * SV;
 #pragma unroll
     for (int j = 0; j < GW; ++j)
-      __builtin_amdgcn_global_load_lds((sk_gptr_t)(wbase + (size_t)(8 * min(j, groups - 1)) * row_b + kb + ((j & 1) ? woff_odd : woff_even)),
+      __builtin_amdgcn_global_load_lds((sk_gptr_t)(wbase + (size_t)(8 * (RAGGED ? min(j, groups - 1) : j)) * row_b + kb +
+                                                   ((j & 1) ? woff_odd : woff_even)),
                                        (sk_lptr_t)(dst + j * 64), 16, 0, 0);
 #pragma unroll
     for (int j = 0; j < GX; ++j)
@@ -150,17 +152,17 @@ __global__ __launch_bounds__(kSkWaves * 64) void gemm_skinny_kernel(const E* __r
       for (int e = 0; e < 4; ++e)
         red[wave * kRedWave + (16 * t + 4 * lq + e) * RLD + 16 * j + lrow] = acc[t][j][e];
   __syncthreads();
-  constexpr int TPR = BN / 4;   // vectors of 4 columns per output row
-  for (int32_t i = tid; i < MT * 16 * TPR; i += kSkWaves * 64) {
-    const int32_t m = i / TPR, c4 = (i - m * TPR) * 4;
-    if (m >= M) break;
+  constexpr int TPR = BN / 4;   // threads per output row
+  constexpr int RPT = kSkWaves * 64 / TPR;   // rows at a time; the threads left over (80 columns) have none
+  const int32_t c4 = (tid % TPR) * 4;
+  if (tid / TPR >= RPT || (RAGGED && n0 + c4 >= N)) return;
+  for (int32_t m = tid / TPR; m < MT * 16 && m < M; m += RPT) {
     float v[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int wv = 0; wv < kSkWaves; ++wv) {
       const float4 p = *reinterpret_cast<const float4*>(&red[wv * kRedWave + m * RLD + c4]);
       v[0] += p.x; v[1] += p.y; v[2] += p.z; v[3] += p.w;
     }
-    if (n0 + c4 >= N) continue;
     const size_t off = (size_t)m * N + n0 + c4;
     if (partial != nullptr) {
       *reinterpret_cast<float4*>(partial + (size_t)blockIdx.y * M * N + off) = make_float4(v[0], v[1], v[2], v[3]);
@@ -228,15 +230,16 @@ __global__ __launch_bounds__(256) void skinny_reduce_kernel(const float* __restr
 template <typename E, int MT, int NT, int kD>
 hipError_t launch_sk(const E* x, const E* w, const E* bias, const E* res, E* y, float* partial, int32_t KS, int32_t M,
                      int32_t N, int32_t K, int epi, hipStream_t s) {
-  auto kern = gemm_skinny_kernel<E, MT, NT, kD>;
   constexpr size_t lds = SkCfg<MT, NT, kD>::kLds;
-  static LdsAttrOnce once;
+  const bool ragged = N % (16 * NT) != 0;
+  const auto kern = ragged ? gemm_skinny_kernel<E, MT, NT, kD, true> : gemm_skinny_kernel<E, MT, NT, kD, false>;
+  static LdsAttrOnce once[2];
   {
-    hipError_t e = ensure_dynamic_lds(reinterpret_cast<const void*>(kern), lds, once);
+    hipError_t e = ensure_dynamic_lds(reinterpret_cast<const void*>(kern), lds, once[ragged]);
     if (e != hipSuccess) return e;
   }
-  kern<<<dim3((unsigned)((N + 16 * NT - 1) / (16 * NT)), (unsigned)KS), dim3(kSkWaves * 64), lds, s>>>(x, w, bias, res, y, partial, M, N,
-                                                                                      K, epi);
+  kern<<<dim3((unsigned)((N + 16 * NT - 1) / (16 * NT)), (unsigned)KS), dim3(kSkWaves * 64), lds, s>>>(x, w, bias, res, y,
+                                                                                                     partial, M, N, K, epi);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || partial == nullptr) return e;
   return launch_partial_reduce<E>(partial, KS, bias, res, y, M, N, epi, s);
@@ -271,16 +274,24 @@ bool gemm_skinny_takes(int64_t M, int32_t N, int32_t K, int epi) {
 }
 
 // Columns per workgroup (16 nt) and parts of K (ks, their sums in at most `cap` bytes of scratch): the least expected
-// time, which is the longer of W from HBM (5.8 TB/s) and the busiest CU's share of W and x
-// (40 KB/us with all CUs at work, up to 65 with fewer and narrow blocks); cutting K costs 4 us for the second kernel.  Wide
-// blocks read x less often (a hundredth of those bytes decides a tie), so the best shape is the widest that still gives every CU one workgroup: 80 columns
-// x 4 parts = 256 workgroups for N = 5120.  Measured (us, weights from HBM, M = 2 / 32 / 64; before: 32 or 64 columns,
-// 8 parts or none):
+// time, which is the longer of W from HBM (5.8 TB/s) and the busiest CU's share of W and x (40 KB/us with all CUs at work, up
+// to 65 with fewer and narrow blocks); cutting K costs 4 us for the second kernel.  Wide blocks read x less often (a
+// hundredth of the bytes read decides a tie).  Two cases lie outside that model:
+//  * K of less than about 1800, where the latency of a workgroup's few slabs counts: 16 columns as long as each CU gets
+//    one such block (us, 32 columns / 16: 64 x 3072 x 768 4.6 / 3.9, 16 x 4096 x 1024 3.7 / 3.4);
+//  * 17 to 32 rows and 512 or more blocks of 32 columns, of which two share a CU, so that one's first loads and sums hide
+//    behind the other: 32 columns up to K = 3072 (us, 64 or 80 columns / 32: 32 x 50304 x 1024 23.6 / 18.6, 32 x 32000 x
+//    3072 32.0 / 30.0).  Not where K is a multiple of 2048, whose rows meet in the same memory channels (32 x 32000 x 2048
+//    23.3 / 27.9);
+//  * 80 columns not up to K = 3072 where 64 still are one block per CU: the longer prologue and epilogue are not repaid (us,
+//    80 / 64 columns: 16 x 16384 x 768 5.5 / 4.2, 16 x 12288 x 1536 8.0 / 7.3; at K = 4096 16 x 16384 21.7 / 22.1).
+// Measured (us, weights from HBM, M = 2 / 32 / 64; before: 32 or 64 columns, 8 parts or none):
 //   5120 x 20480  48 -> 39 / 50 -> 41 / 66 -> 45     20480 x 5120  40 -> 37 / 48 -> 39 / -
-//   5120 x 5120   12.3 -> 12.3 / 17.6 -> 16.2 / 22.5 -> 18.5     15360 x 5120 (64 columns as before) 29 / 31 / 36
+//   5120 x 5120   12.3 -> 12.3 / 17.6 -> 16.2 / 22.5 -> 18.5     15360 x 5120 29 / 31 / 36 (80 columns at M = 2, else 64 as before)
 struct SkinnyPlan { int32_t nt, ks; size_t scratch; };
 static SkinnyPlan gemm_skinny_plan(int64_t M, int32_t N, int32_t K, size_t cap) {
   const int32_t KT = K / 64, mt = M <= 16 ? 1 : M <= 32 ? 2 : 4;
+  if (mt == 2 && (N + 31) / 32 >= 512 && K <= 3072 && K % 2048 != 0) return {2, 1, 0};
   const float hbm_us = (float)N * (float)K * (2.0f / 5.8e6f);
   SkinnyPlan best{1, 1, 0};
   float best_us = 1e30f;
@@ -290,9 +301,11 @@ static SkinnyPlan gemm_skinny_plan(int64_t M, int32_t N, int32_t K, size_t cap) 
     for (const int32_t ks : {1, 2, 4, 5, 8}) {
       const int32_t wgs = blocks * ks;
       if (ks > 1 && (wgs > 512 || KT % ks != 0 || KT / ks < 4)) continue;
+      if (nt == 5 && ks == 1 && KT <= 48 && N <= 256 * 64) continue;
       const size_t scratch = ks > 1 ? (size_t)ks * (size_t)M * N * sizeof(float) : 0;
       if (scratch > cap) continue;
-      const float rate = std::min(nt >= 4 ? 42.0f : 65.0f, std::max(40.0f, 7680.0f / (float)wgs));   // KB/us of one CU
+      const bool latency = nt == 1 && ks == 1 && blocks <= 256 && KT <= 28;
+      const float rate = latency ? 60.0f : std::min(nt >= 4 ? 42.0f : 65.0f, std::max(40.0f, 7680.0f / (float)wgs));   // KB/us of one CU
       const float cu_us = (float)((wgs + 255) >> 8) * (float)(KT / ks) * slab_kb / rate;
       const float us = (ks > 1 ? 4.0f : 0.0f) + std::max(hbm_us, cu_us) + (float)blocks * (float)KT * slab_kb * 1.0e-5f;
       if (us < best_us) { best_us = us; best = {nt, ks, scratch}; }

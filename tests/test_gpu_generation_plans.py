@@ -16,7 +16,10 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("M,N,K,dtype", [
     (1, 8, 64, wl.BF16), (16, 40, 192, wl.F16), (17, 1608, 1600, wl.BF16), (33, 4104, 512, wl.BF16), (64, 264, 3072, wl.F16),
-    (3, 20488, 256, wl.BF16), (2, 5128, 5120, wl.BF16), (32, 5120, 5120, wl.F16), (50, 2056, 4096, wl.BF16)])
+    (3, 20488, 256, wl.BF16), (2, 5128, 5120, wl.BF16), (32, 5120, 5120, wl.F16), (50, 2056, 4096, wl.BF16),
+    # both instances (whole and ragged last block) of 64, 32 and 16 columns at K of a few slabs, where the rule of that case decides
+    (16, 16384, 768, wl.BF16), (9, 16376, 768, wl.F16), (20, 16384, 256, wl.BF16), (32, 16392, 320, wl.F16), (64, 3072, 768, wl.F16),
+    (40, 3080, 768, wl.BF16)])
 @pytest.mark.parametrize("epi", [E.EPI_BIAS, E.EPI_BIAS_GELU, E.EPI_BIAS_RESIDUAL])
 def test_few_row_linear(M, N, K, dtype, epi):
     rng = np.random.default_rng(M + N + K + epi)
