@@ -235,6 +235,15 @@ int energon_linear_with_scratch(const void* x_dev, const void* w_dev, const void
 int energon_linear_plan_selfcheck(int64_t M, int32_t N, int32_t K, int32_t workgroups_per_xcd,
                                   int32_t with_scratch, int32_t* pieces_out);
 
+/* Host only: how a 16-bit linear of this shape runs, given scratch_bytes of scratch (0: none).  epilogue as in
+ * energon_linear; ln_folded != 0: as energon_linear_ln_folded (ENERGON_EPI_BIAS or _GELU); in_place != 0: the residual is y.
+ * plan: [0] the kernel: 0 few rows (W streamed once), 1 small tiles with K over the wavefronts, 2 tiles of 64x64, 128x128 or
+ * 128x256, 3 persistent 256x256 tiles; [1], [2] rows and columns of an output tile; [3] parts that K is cut into (for
+ * kernel 3: pieces per cut tile).  For tests and for reading a profile: results do not depend on it beyond the order of sums.
+ * SHAPE and UNSUPPORTED as energon_linear refuses. */
+int energon_linear_plan(int64_t M, int32_t N, int32_t K, int32_t epilogue, int32_t ln_folded, int32_t in_place,
+                        size_t scratch_bytes, int32_t plan[4]);
+
 /* Causal attention of every sequence over its real length, on packed rows.
  *   qkv_dev [T, 3A]  (row t: Q | K | V, head h at columns h*d .. (h+1)*d-1 of each third)
  *   out_dev [T, A];  cu_seqlens_dev [B+1];  max_len >= every sequence length.

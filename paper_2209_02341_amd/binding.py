@@ -81,6 +81,8 @@ def lib() -> C.CDLL:
         l.energon_linear_with_scratch.restype = C.c_int
         l.energon_linear_plan_selfcheck.argtypes = [i64, i32, i32, i32, i32, C.POINTER(i32)]
         l.energon_linear_plan_selfcheck.restype = C.c_int
+        l.energon_linear_plan.argtypes = [i64, i32, i32, i32, i32, i32, sz, C.POINTER(i32)]
+        l.energon_linear_plan.restype = C.c_int
         l.energon_attention.argtypes = [vp, vp, vp, i64, i32, i32, i32, i32, i32, vp]
         l.energon_rebuild_qkv.argtypes = [vp, vp, i64, i32, i32, i32, i32, i32, vp, vp, vp, vp]
         l.energon_attention_padded.argtypes = [vp, vp, vp, vp, i32, i32, i32, i32, i32, vp, vp]
@@ -286,6 +288,16 @@ def energon_linear_plan_selfcheck(M: int, N: int, K: int, workgroups_per_xcd: in
     st = lib().energon_linear_plan_selfcheck(int(M), int(N), int(K), int(workgroups_per_xcd), int(bool(with_scratch)),
                                              C.byref(pieces))
     return int(st), int(pieces.value)
+
+
+def energon_linear_plan(M: int, N: int, K: int, epilogue: int = EPI_BIAS, ln_folded: bool = False, in_place: bool = False,
+                        scratch_bytes: int = 0) -> tuple:
+    """(kernel, tile rows, tile columns, parts of K) of a 16-bit linear; kernel 0 few rows, 1 K over wavefronts, 2 tiles,
+    3 persistent."""
+    plan = (C.c_int32 * 4)()
+    _check(lib().energon_linear_plan(int(M), int(N), int(K), int(epilogue), int(ln_folded), int(in_place),
+                                     int(scratch_bytes), plan), "energon_linear_plan")
+    return tuple(plan)
 
 
 def energon_attention(qkv, out, cu_seqlens, B: int, max_len: int, n_heads: int, head_dim: int,

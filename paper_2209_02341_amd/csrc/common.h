@@ -144,6 +144,9 @@ inline hipError_t ensure_dynamic_lds(const void* kern, size_t bytes, LdsAttrOnce
   return e;
 }
 
+// A launch holds fewer than 2^32 threads along a dimension of its grid; HIP does not report more, it drops the high bits.
+constexpr int64_t kMaxGridThreads = 0xFFFFFFFFll;
+
 enum Epilogue { EPI_BIAS = 0, EPI_BIAS_GELU = 1, EPI_BIAS_RESIDUAL = 2, EPI_LNFOLD = 3, EPI_LNFOLD_GELU = 4 };
 
 // LayerNorm folded into a 16-bit linear (the fusion of Sec. 5.5's comparison system, in algebraic
@@ -196,6 +199,12 @@ size_t gemm_sched_scratch_bytes(int64_t M, int32_t N, int32_t K);
 bool gemm_takes_whole_rounds(int64_t M, int32_t N, int32_t K);
 // host-side replay of that kernel's work decomposition for one shape: 0 = every tile and slab covered once
 int gemm_sched_selfcheck(int64_t M, int32_t N, int32_t K, int32_t wgs, int32_t can_split, int32_t* pieces_out);
+// how a 16-bit linear runs: whose kernel, the output tile of a workgroup, parts or pieces that K is cut into
+struct LinearPlan {
+  enum Kernel { kFewRows, kWaves, kTiles, kPersistent };   // gemm_skinny, gemm_ksplit, gemm_mfma_tile, gemm_mfma_sched
+  int32_t kernel, tile_rows, tile_columns, parts;
+};
+LinearPlan gemm_plan(int64_t M, int32_t N, int32_t K, int epi, bool res_aliases_y, size_t scratch_bytes);
 hipError_t launch_gemm_bf16(const bf16_t* x, const bf16_t* w, const bf16_t* bias, const bf16_t* res, bf16_t* y,
                             int64_t M, int32_t N, int32_t K, int epi, hipStream_t s, const LnFold* fold = nullptr,
                             float* scratch = nullptr, size_t scratch_bytes = 0);
@@ -211,6 +220,7 @@ hipError_t launch_gemm_ksplit(KsplitTile tile, const E* x, const E* w, const E* 
 // gemm_skinny_partial_bytes is what the best plan takes) K may be cut over several workgroups.
 bool gemm_skinny_takes(int64_t M, int32_t N, int32_t K, int epi);
 size_t gemm_skinny_partial_bytes(int64_t M, int32_t N, int32_t K);
+LinearPlan gemm_skinny_plan_of(int64_t M, int32_t N, int32_t K, size_t scratch_bytes);
 template <typename E>
 hipError_t launch_gemm_skinny(const E* x, const E* w, const E* bias, const E* res, E* y, int64_t M, int32_t N,
                               int32_t K, int epi, hipStream_t s, float* partial = nullptr, size_t partial_bytes = 0);

@@ -592,6 +592,18 @@ int energon_linear_plan_selfcheck(int64_t M, int32_t N, int32_t K, int32_t workg
   return gemm_sched_selfcheck(M, N, K, workgroups_per_xcd, with_scratch, pieces_out);
 }
 
+int energon_linear_plan(int64_t M, int32_t N, int32_t K, int32_t epilogue, int32_t ln_folded, int32_t in_place,
+                        size_t scratch_bytes, int32_t plan[4]) {
+  if (!plan) return ENERGON_ERR_NULL;
+  if (M <= 0 || M >= ((int64_t)1 << 31) || N <= 0 || K <= 0 || K % 64 != 0 || N % 8 != 0) return ENERGON_ERR_SHAPE;
+  if (epilogue < EPI_BIAS || epilogue > (ln_folded ? EPI_BIAS_GELU : EPI_BIAS_RESIDUAL)) return ENERGON_ERR_UNSUPPORTED;
+  if (K >= kMaxReduction) return ENERGON_ERR_UNSUPPORTED;
+  const int epi = !ln_folded ? epilogue : epilogue == EPI_BIAS_GELU ? EPI_LNFOLD_GELU : EPI_LNFOLD;
+  const LinearPlan p = gemm_plan(M, N, K, epi, in_place != 0, scratch_bytes);
+  plan[0] = p.kernel; plan[1] = p.tile_rows; plan[2] = p.tile_columns; plan[3] = p.parts;
+  return ENERGON_OK;
+}
+
 int energon_attention(const void* qkv, void* out, const int32_t* cu, int64_t T, int32_t B, int32_t max_len,
                       int32_t n_heads, int32_t head_dim, int32_t dtype, void* stream) {
   if (!qkv || !out || !cu) return ENERGON_ERR_NULL;

@@ -5,7 +5,7 @@
 // Design for gfx950:
 //  * both operands are contiguous along K, so x rows feed the MFMA A operand and W rows the
 //    B operand with the same 16-byte chunks; fp32 accumulators;
-//  * a BM x BN output tile per workgroup, K walked in slabs of 64 (128 bytes per row), two
+//  * a BM x BN output tile per workgroup, K walked in slabs of 64 (128 bytes per row), two or three
 //    slab buffers in LDS, filled straight from global memory (global_load_lds_dwordx4);
 //  * an LDS row is 8 chunks of 16 bytes; chunk c of row r is stored in slot c ^ swizzle(r), chosen
 //    per MFMA form so that a wavefront's operand read meets no bank conflict (measured).  Slabs
@@ -22,7 +22,7 @@
 //    inwards, so nothing is clamped or predicated; the epilogue goes through LDS and leaves as
 //    16-byte non-temporal stores;
 //  * gemm_mfma_tile_kernel, compiler-scheduled, v_mfma_f32_32x32x16, clamped loads and predicated
-//    stores, three slabs in LDS: 64x64 and 128x256 tiles for problems that do not give the first kernel whole rounds
+//    stores: 64x64, 128x128 and 128x256 tiles for problems that do not give the first kernel whole rounds
 //    of tiles, or that it cannot take (odd slab counts, fewer than 256 rows or columns).
 // tile_plan chooses between these, the first kernel with its tiles cut along K, and gemm_ksplit.hip.
 #include "common.h"
@@ -242,9 +242,10 @@ __device__ __forceinline__ void store_tile_coalesced(const f32x4 (&acc)[8][8], c
 }
 
 // ---- compiler-scheduled tile kernel ---------------------------------------------------------
-// S slab buffers: S - 1 slabs are on their way while one is worked on, one barrier per slab.  (Two buffers with a wait
-// for the only slab in flight and a full barrier per slab left every load's latency exposed: 387 x 1024 x 4096
-// 36 us on 64x64 tiles, 20 us with three buffers; five take the place of other workgroups and win nothing.)
+// S slab buffers: S - 1 slabs are on their way while one is worked on, one barrier per slab.  Three where a workgroup has
+// to hide its own latency (387 x 1024 x 4096 on 64x64 tiles: 36 us with two buffers, 20 us with three; five take the place
+// of other workgroups and win nothing); two for 128x128 tiles, whose 64 KiB then leave room for a second workgroup on the
+// CU that does it (658 x 5120 x 5120: 60 us).
 // MODE 0: plain epilogues; 1: the LayerNorm-folded epilogues; 2: split K, gridDim.y parts, fp32 sums
 // of part blockIdx.y to lf.partial + blockIdx.y * M * N (lf.partial is the caller's scratch here).
 template <typename E, int BM, int BN, int WM, int WN, int S, int MODE>
@@ -254,6 +255,7 @@ __global__ __launch_bounds__(WM* WN * 64) void gemm_mfma_tile_kernel(const E* __
                                                                      const E* res, E* y, int64_t M,
                                                                      int32_t N, int32_t K, int epi, int32_t tiles_m,
                                                                      int32_t tiles_n, LnFold lf) {
+  static_assert(S == 2 || S == 3, "the wait below covers one slab in flight behind the awaited one, or none");
   constexpr int NW = WM * WN;
   constexpr int WTM = BM / WM, WTN = BN / WN;
   constexpr int TM = WTM / 32, TN = WTN / 32;
@@ -330,10 +332,7 @@ __global__ __launch_bounds__(WM* WN * 64) void gemm_mfma_tile_kernel(const E* __
     if (u < KT) issue(u, u);
   int stage = 0;
   for (int kt = 0; kt < KT; ++kt) {
-    const int behind = min(S - 2, KT - 1 - kt);
-    if (behind >= 3) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(3 * G) : "memory");
-    else if (behind == 2) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(2 * G) : "memory");
-    else if (behind == 1) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(G) : "memory");
+    if (S == 3 && kt + 1 < KT) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(G) : "memory");
     else asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
     __builtin_amdgcn_s_barrier();
     const uint4* cur = smem + stage * kStage;
@@ -830,6 +829,7 @@ static hipError_t launch_tiles(Kern kern, LdsAttrOnce& attr_set, int BM, int BN,
   const int32_t tiles_m = (int32_t)((M + BM - 1) / BM), tiles_n = (N + BN - 1) / BN;
   const int64_t total = (int64_t)tiles_m * tiles_n;
   const int64_t grid = (total + kXcds - 1) / kXcds * kXcds;
+  if (grid * threads > kMaxGridThreads) return hipErrorInvalidConfiguration;
   kern<<<dim3((unsigned)grid, (unsigned)ks), dim3(threads), lds, s>>>(x, w, bias, res, y, M, N, K, epi, tiles_m, tiles_n,
                                                                        lf);
   return hipGetLastError();
@@ -940,21 +940,64 @@ size_t gemm_sched_scratch_bytes(int64_t M, int32_t N, int32_t K) {
 // How a shape that is too small for the 256x256 kernel's whole rounds runs, given `cap` bytes of scratch:
 //   kSplit   32x32, 64x32 or 64x64 tiles, K cut over the four wavefronts of the workgroup (gemm_ksplit.hip);
 //   kSmall   64x64 tiles shared by four wavefronts, three workgroups per CU;
+//   kSquare  128x128 tiles, 4 wavefronts, two slab buffers so that two workgroups share a CU;
 //   kWide    128x256 tiles, 8 wavefronts, one workgroup per CU, K cut over ks workgroups (sums in the scratch);
 //   kPieces  the 256x256 kernel with every tile cut into pieces (needs M, N >= 256 and K % 128 == 0).
-// The one with the least expected time; the times are fits of a sweep over 35 shapes.  Measured (us, with scratch;
-// in brackets the former rule: 64x64 and 128x128 tiles, one slab in flight, K cut for generation steps only):
-//   79 x 768 x 768 3.6 [7]          387 x 1024 x 4096 10.6 [36]      387 x 3072 x 1024 9.7 [12.4]    333 x 5120 x 5120 34 [56]
-//   96 x 2048 x 8192 15 [38]        120 x 5120 x 20480 58 [219]      333 x 5120 x 20480 95 [223]     928 x 5120 x 5120 64 [85]
-//   928 x 5120 x 20480 174 [317]    1500 x 4096 x 16384 183 [265]    600 x 8192 x 2048 36 [38]       2000 x 1600 x 6400 60 [78]
+// The one with the least expected time.  Each tile's time is fitted to a sweep of 440 shapes on it, 65 to 4600 rows of
+// every layer width, K of 64 to 20480: launch and prologue, the epilogue's share, and per slab a piecewise linear
+// function of the tiles per CU, which has a step wherever another round of workgroups begins.  The choice costs 0.5 % over
+// the best of them in the mean.  Measured (us, without scratch; in brackets the next larger or smaller tile):
+//   79 x 768 x 768 3.6 kSplit [7 kSmall]           387 x 3072 x 1024 9.7 kSmall [20 kSquare]     100000 x 192 x 768 61 kSmall [88 kWide]
+//   658 x 5120 x 5120 57 kSquare [92 kSmall]       533 x 6144 x 12288 133 kSquare [192 kWide]    600 x 15360 x 5120 136 kSquare [160 kWide]
+//   3000 x 4096 x 4160 126 kSquare [141 kWide]     8428 x 5120 x 5184 491 kSquare [547 kWide]    250 x 12288 x 4096 42 kWide [51 kSquare]
+// and with scratch: 515 x 2056 x 4096 + residual 26.3 kWide in parts [30.0 kSmall]   879 x 5120 x 20480 177 kPieces [283 kSquare]
 // What bounds them is latency and idle CUs below a few hundred tiles, the L2 above: 128 x 256 tiles ask it for 48 KiB
 // per slab and CU, about 1 us at the 10-11 TB/s that it gives all CUs together; smaller tiles ask for more per flop but
-// fill the chip; the parts of a K cut over workgroups cost their way to memory and back (6 TB/s) and a second launch.
-enum TileKind { kSplit, kSmall, kWide, kPieces };
+// fill the chip, and two on a CU hide each other's barriers; the parts of a K cut over workgroups cost their way to memory
+// and back and a second launch.
+enum TileKind { kSplit, kSmall, kSquare, kWide, kPieces };
 struct TilePlan { TileKind kind; KsplitTile split; int32_t ks; size_t scratch; };   // ks: parts of K (kPieces: pieces per tile)
-constexpr int kSmallTile = 64, kWideM = 128, kWideN = 256, kTileStages = 3;
+constexpr int kSmallTile = 64, kSquareTile = 128, kWideM = 128, kWideN = 256;
 
-static TilePlan tile_plan(int64_t M, int32_t N, int32_t K, bool overlap_safe, bool plain, size_t cap, int32_t wgs) {
+// us = base + gelu + residual + n (round + residual_round) + steps * slab(n), n = tiles per CU; slab(n) through the given
+// points, in proportion beyond the last.  The epilogue that reads row statistics has base and round of its own.
+struct TileTime {
+  double base, gelu, residual, round, residual_round, fold_base, fold_round;
+  struct { double n, us; } slab[11];
+  double slab_us(double n) const {
+    int i = 1;
+    while (i < 10 && n > slab[i].n && slab[i + 1].n > 0) ++i;
+    if (n > slab[i].n) return slab[i].us * n / slab[i].n;
+    return slab[i - 1].us + (slab[i].us - slab[i - 1].us) * (n - slab[i - 1].n) / (slab[i].n - slab[i - 1].n);
+  }
+  double us(double n, int epi) const {   // without the slabs
+    const bool fold = epi == EPI_LNFOLD || epi == EPI_LNFOLD_GELU;
+    return (fold ? fold_base + n * fold_round : base + n * round) + (epi == EPI_BIAS_GELU || epi == EPI_LNFOLD_GELU ? gelu : 0.0) +
+           (epi == EPI_BIAS_RESIDUAL ? residual + n * residual_round : 0.0);
+  }
+};
+constexpr TileTime kSmallTime{3.56, 0.78, 1.04, 0.53, 1.22, 6.12, 1.01,
+    {{0, 0.247}, {1, 0.261}, {1.003, 0.339}, {2, 0.378}, {2.003, 0.539}, {3, 0.580}, {3.003, 0.750}, {4, 0.824}, {4.003, 0.880},
+     {6, 1.170}, {10, 1.991}}};
+constexpr TileTime kSquareTime{7.67, 3.18, 4.97, 1.79, 6.08, 17.46, 1.99,
+    {{0, 0.564}, {1, 0.631}, {1.003, 0.780}, {1.5, 0.902}, {2, 1.040}, {2.003, 1.550}, {3, 1.720}, {4, 2.100}, {4.5, 2.800}, {10, 5.700}}};
+constexpr TileTime kWideTime{7.97, 2.70, 5.47, 3.53, 11.73, 17.42, 4.04,
+    {{0, 0.805}, {0.5, 0.848}, {1, 0.985}, {1.003, 1.903}, {1.5, 1.996}, {2, 2.805}}};
+constexpr TileTime kSplitTime[3] = {   // steps of four slabs, one per wavefront
+    {2.18, 0.23, 0.27, 0.46, 0.08, 0, 0,
+     {{0, 0.298}, {1, 0.345}, {1.003, 0.573}, {2, 0.662}, {2.003, 0.888}, {4, 1.261}, {4.003, 1.456}, {6, 1.934}, {16, 5.175}, {40, 12.477}}},
+    {2.38, 0.43, 0.23, 1.69, 0.39, 0, 0,
+     {{0, 0.454}, {1, 0.451}, {1.003, 1.050}, {2, 0.944}, {2.003, 1.580}, {3, 1.469}, {3.003, 1.969}, {4, 2.081}, {8, 4.395}, {20, 11.016}}},
+    {3.54, 0.41, 0.18, 3.07, 1.05, 0, 0,
+     {{0, 0.684}, {1, 0.645}, {1.003, 1.471}, {2, 1.345}, {2.003, 2.141}, {3, 2.174}, {3.003, 2.709}, {5, 3.701}, {10, 8.146}}}};
+static_assert((int)KsplitTile::k32x32 == 0 && (int)KsplitTile::k64x32 == 1 && (int)KsplitTile::k64x64 == 2, "order of kSplitTime");
+
+// Slabs of 128x256 tiles, whole rounds of them beyond two.
+static double wide_slab_us(double n) { return n <= 2.0 ? kWideTime.slab_us(n) : std::ceil(n) * kWideTime.slab_us(1.0); }
+
+// epi: one of EPI_BIAS, EPI_BIAS_GELU, EPI_BIAS_RESIDUAL (all plans) or the folded ones (kSmall, kSquare and whole kWide only).
+static TilePlan tile_plan(int64_t M, int32_t N, int32_t K, bool overlap_safe, int epi, size_t cap, int32_t wgs) {
+  const bool plain = epi != EPI_LNFOLD && epi != EPI_LNFOLD_GELU;
   const int32_t KT = K / BK;
   const double cus = 8.0 * wgs;
   TilePlan best{kSmall, KsplitTile::k64x64, 1, 0};
@@ -963,21 +1006,30 @@ static TilePlan tile_plan(int64_t M, int32_t N, int32_t K, bool overlap_safe, bo
     if (t.scratch <= cap && us < best_us) { best = t; best_us = us; }
   };
   const auto tiles = [&](int64_t bm, int64_t bn) { return ((M + bm - 1) / bm) * ((N + bn - 1) / bn); };
+  const auto fits = [](int64_t tiles, int64_t threads) { return tiles * threads <= kMaxGridThreads; };
+  // What the small tiles lose to the larger ones where their reads come from farther away: W of more than the last cache's
+  // 256 MB (151 x 24576 x 8192 159 us on 64x64 tiles, 145 on 128x128; but 338 x 8192 x 32768 378 on 64x64 with K over the
+  // wavefronts, 463), and the shared ones at rows of 24 KiB and more (539 x 4608 x 12288 115 % of the fit to shorter rows).
+  const double far = (double)N * K * sizeof(uint16_t) > 268.0e6 ? 1.06 : 1.0, far_shared = std::max(far, K >= 12288 ? 1.08 : 1.0);
   if (plain) {
-    const int32_t steps = (KT + 3) / 4;   // slabs of the longest wavefront
-    const double w = tiles(32, 32) / cus;
-    consider({kSplit, KsplitTile::k32x32, 1, 0}, 3.0 + 0.5 * std::ceil(w / 2) + steps * (w <= 1 ? 0.3 : w <= 2 ? 0.5 : 0.42 * w));
-    consider({kSplit, KsplitTile::k64x32, 1, 0}, 3.0 + std::ceil(tiles(64, 32) / cus) * (1.0 + 0.45 * steps));
-    consider({kSplit, KsplitTile::k64x64, 1, 0}, 3.0 + std::ceil(tiles(64, 64) / cus) * (1.5 + 0.85 * steps));
+    const KsplitTile split[3] = {KsplitTile::k32x32, KsplitTile::k64x32, KsplitTile::k64x64};
+    const int64_t n[3] = {tiles(32, 32), tiles(64, 32), tiles(64, 64)};
+    for (int i = 0; i < 3; ++i)
+      if (fits(n[i], 256)) consider({kSplit, split[i], 1, 0}, kSplitTime[i].us(n[i] / cus, epi) + (KT + 3) / 4 * far * kSplitTime[i].slab_us(n[i] / cus));
   }
-  consider({kSmall, KsplitTile::k64x64, 1, 0}, 3.5 + KT * std::max(0.27, 0.22 * std::ceil(tiles(kSmallTile, kSmallTile) / cus)));
+  if (const int64_t n = tiles(kSmallTile, kSmallTile); fits(n, 256))
+    consider({kSmall, KsplitTile::k64x64, 1, 0}, kSmallTime.us(n / cus, epi) + KT * far_shared * kSmallTime.slab_us(n / cus));
+  if (const int64_t n = tiles(kSquareTile, kSquareTile); K < (1 << 24) && fits(n, 256))   // a tile's rows in 32-bit byte offsets
+    consider({kSquare, KsplitTile::k64x64, 1, 0}, kSquareTime.us(n / cus, epi) + KT * kSquareTime.slab_us(n / cus));
   const int64_t wide = tiles(kWideM, kWideN);
-  const bool wide_fits = K < (1 << 23);   // 256 rows of K in 32-bit byte offsets
-  for (int32_t ks = 1; wide_fits && ks <= 8 && (ks == 1 || (plain && wide * ks <= 1024 && KT / ks >= 4)); ++ks) {
+  const double elems = (double)M * N, res = epi == EPI_BIAS_RESIDUAL ? 1.0 : 0.0;
+  if (K < (1 << 23) && fits(wide, 512))
+    consider({kWide, KsplitTile::k64x64, 1, 0}, kWideTime.us(wide / cus, epi) + KT * wide_slab_us(wide / cus));
+  for (int32_t ks = 2; plain && K < (1 << 23) && ks <= 8 && wide * ks <= 1024 && KT / ks >= 4; ++ks) {
     if (KT % ks != 0) continue;
-    const double sums = (double)ks * M * N * 4.0;
-    consider({kWide, KsplitTile::k64x64, ks, ks > 1 ? (size_t)ks * (size_t)M * N * sizeof(float) : 0},
-             3.5 + KT / ks * std::ceil(wide * ks / cus) + (ks > 1 ? 2.0 + 2.0 * sums / 6.0e6 : 0.0));
+    const double n = wide * ks / cus;   // then the sums' way to memory and back, and the second launch
+    consider({kWide, KsplitTile::k64x64, ks, (size_t)ks * (size_t)M * N * sizeof(float)},
+             8.0 + 2.1 * n + KT / ks * wide_slab_us(n) + (0.233 * 4.0 * ks + 0.236 * res) * elems / 1.0e6);
   }
   if (plain && M >= 256 && N >= 256 && K % 128 == 0 && overlap_safe) {
     const int64_t big = tiles(256, 256);
@@ -988,7 +1040,7 @@ static TilePlan tile_plan(int64_t M, int32_t N, int32_t K, bool overlap_safe, bo
       if (rem >= wgs || rem * P > 2 * wgs || (KT + chunk - 1) / chunk != P || chunk < 8) continue;
       const double rounds = std::ceil((double)rem * P / wgs);
       consider({kPieces, KsplitTile::k64x64, P, sched_scratch_bytes(wgs)},
-               12.0 + rounds * (chunk * 1.25 + 6.0) + big * P * (kPartFloats * 4.0) / 3.0e6);
+               8.2 + rounds * (1.1 + 1.228 * chunk) + (0.388 * big * P * kPartFloats * 4.0 + 0.394 * res * elems) / 1.0e6);
     }
   }
   return best;
@@ -1008,7 +1060,10 @@ static SchedPlan pieces_plan(int64_t M, int32_t N, int32_t K, int32_t pieces, in
 size_t gemm_scratch_bytes(int64_t M, int32_t N, int32_t K) {
   if (takes_sched_kernel(M, N, K, false)) return gemm_sched_scratch_bytes(M, N, K);
   if (M <= 0 || gemm_skinny_takes(M, N, K, EPI_BIAS)) return 0;   // few rows: planned for by the generation step only
-  return tile_plan(M, N, K, true, true, SIZE_MAX, sched_wgs_per_xcd()).scratch;
+  size_t need = 0;   // of whichever epilogue the call turns out to have
+  for (const int epi : {EPI_BIAS, EPI_BIAS_GELU, EPI_BIAS_RESIDUAL})
+    need = std::max(need, tile_plan(M, N, K, true, epi, SIZE_MAX, sched_wgs_per_xcd()).scratch);
+  return need;
 }
 
 // Host-side check of the decomposition for one shape (what the kernels would do, replayed with the
@@ -1024,7 +1079,7 @@ int gemm_sched_selfcheck(int64_t M, int32_t N, int32_t K, int32_t wgs, int32_t c
     p = sched_plan(M, N, K, can_split != 0, wgs);
   } else {
     if (!can_split) return -1;
-    const TilePlan t = tile_plan(M, N, K, true, true, SIZE_MAX, wgs);
+    const TilePlan t = tile_plan(M, N, K, true, EPI_BIAS, SIZE_MAX, wgs);
     if (t.kind != kPieces) return -1;
     p = pieces_plan(M, N, K, t.ks, wgs);
   }
@@ -1109,19 +1164,22 @@ static hipError_t launch_sched(const E* x, const E* w, const E* bias, const E* r
   return hipGetLastError();
 }
 
-template <typename E, int BM, int BN, int WM, int WN, int MODE>
+template <typename E, int BM, int BN, int WM, int WN, int S, int MODE>
 static hipError_t launch_tile_cfg(const E* x, const E* w, const E* bias, const E* res, E* y, int64_t M, int32_t N,
                                   int32_t K, int epi, const LnFold& lf, hipStream_t s, int32_t ks = 1) {
   static LdsAttrOnce once;   // per element type and configuration
-  return launch_tiles<E>(gemm_mfma_tile_kernel<E, BM, BN, WM, WN, kTileStages, MODE>, once, BM, BN, WM * WN * 64,
-                         kTileStages * (size_t)(BM + BN) * kChunks * sizeof(uint4), x, w, bias, res, y, M, N, K, epi, lf, s, ks);
+  return launch_tiles<E>(gemm_mfma_tile_kernel<E, BM, BN, WM, WN, S, MODE>, once, BM, BN, WM * WN * 64,
+                         S * (size_t)(BM + BN) * kChunks * sizeof(uint4), x, w, bias, res, y, M, N, K, epi, lf, s, ks);
 }
 
 template <typename E, int MODE>
 static hipError_t launch_tile(TileKind kind, const E* x, const E* w, const E* bias, const E* res, E* y, int64_t M,
-                              int32_t N, int32_t K, int epi, const LnFold& lf, hipStream_t s, int32_t ks = 1) {
-  if (kind == kWide) return launch_tile_cfg<E, kWideM, kWideN, 2, 4, MODE>(x, w, bias, res, y, M, N, K, epi, lf, s, ks);
-  return launch_tile_cfg<E, kSmallTile, kSmallTile, 2, 2, MODE>(x, w, bias, res, y, M, N, K, epi, lf, s, ks);
+                              int32_t N, int32_t K, int epi, const LnFold& lf, hipStream_t s) {
+  switch (kind) {
+    case kWide: return launch_tile_cfg<E, kWideM, kWideN, 2, 4, 3, MODE>(x, w, bias, res, y, M, N, K, epi, lf, s);
+    case kSquare: return launch_tile_cfg<E, kSquareTile, kSquareTile, 2, 2, 2, MODE>(x, w, bias, res, y, M, N, K, epi, lf, s);
+    default: return launch_tile_cfg<E, kSmallTile, kSmallTile, 2, 2, 3, MODE>(x, w, bias, res, y, M, N, K, epi, lf, s);
+  }
 }
 
 template <typename E>
@@ -1148,7 +1206,7 @@ static hipError_t launch_gemm_mfma(const E* x, const E* w, const E* bias, const 
   }
   // Shifted edge tiles of the 256x256 kernel overlap: not with the residual aliasing y (see takes_sched_kernel).
   const bool overlap_safe = res != y || (M % 256 == 0 && N % 256 == 0);
-  const TilePlan t = tile_plan(M, N, K, overlap_safe, !wants_fold, scratch_bytes, wgs);
+  const TilePlan t = tile_plan(M, N, K, overlap_safe, epi, scratch_bytes, wgs);
   if (wants_fold) return launch_tile<E, 1>(t.kind, x, w, bias, res, y, M, N, K, epi, lf, s);
   if (t.kind == kSplit) return launch_gemm_ksplit<E>(t.split, x, w, bias, res, y, M, N, K, epi, s);
   if (t.kind == kPieces)
@@ -1156,9 +1214,25 @@ static hipError_t launch_gemm_mfma(const E* x, const E* w, const E* bias, const 
   if (t.ks == 1) return launch_tile<E, 0>(t.kind, x, w, bias, res, y, M, N, K, epi, lf, s);
   LnFold sp;
   sp.partial = scratch;
-  const hipError_t e = launch_tile_cfg<E, kWideM, kWideN, 2, 4, 2>(x, w, bias, res, y, M, N, K, epi, sp, s, t.ks);
+  const hipError_t e = launch_tile_cfg<E, kWideM, kWideN, 2, 4, 3, 2>(x, w, bias, res, y, M, N, K, epi, sp, s, t.ks);
   if (e != hipSuccess) return e;
   return launch_partial_reduce<E>(scratch, t.ks, bias, res, y, M, N, epi, s);
+}
+
+LinearPlan gemm_plan(int64_t M, int32_t N, int32_t K, int epi, bool res_aliases_y, size_t scratch_bytes) {
+  if (gemm_skinny_takes(M, N, K, epi)) return gemm_skinny_plan_of(M, N, K, scratch_bytes);
+  const bool plain = epi != EPI_LNFOLD && epi != EPI_LNFOLD_GELU;
+  const int32_t wgs = sched_wgs_per_xcd();
+  if (takes_sched_kernel(M, N, K, res_aliases_y))
+    return {LinearPlan::kPersistent, 256, 256, sched_plan(M, N, K, plain && scratch_bytes >= sched_scratch_bytes(wgs), wgs).pieces};
+  const TilePlan t = tile_plan(M, N, K, !res_aliases_y || (M % 256 == 0 && N % 256 == 0), epi, scratch_bytes, wgs);
+  switch (t.kind) {
+    case kSplit: return {LinearPlan::kWaves, t.split == KsplitTile::k32x32 ? 32 : 64, t.split == KsplitTile::k64x64 ? 64 : 32, 1};
+    case kPieces: return {LinearPlan::kPersistent, 256, 256, t.ks};
+    case kWide: return {LinearPlan::kTiles, kWideM, kWideN, t.ks};
+    case kSquare: return {LinearPlan::kTiles, kSquareTile, kSquareTile, 1};
+    default: return {LinearPlan::kTiles, kSmallTile, kSmallTile, 1};
+  }
 }
 
 hipError_t launch_gemm_bf16(const bf16_t* x, const bf16_t* w, const bf16_t* bias, const bf16_t* res, bf16_t* y,

@@ -314,6 +314,11 @@ static SkinnyPlan gemm_skinny_plan(int64_t M, int32_t N, int32_t K, size_t cap) 
   return best;
 }
 
+LinearPlan gemm_skinny_plan_of(int64_t M, int32_t N, int32_t K, size_t scratch_bytes) {
+  const SkinnyPlan p = gemm_skinny_plan(M, N, K, scratch_bytes);
+  return {LinearPlan::kFewRows, M <= 16 ? 16 : M <= 32 ? 32 : 64, 16 * p.nt, p.ks};
+}
+
 size_t gemm_skinny_partial_bytes(int64_t M, int32_t N, int32_t K) { return gemm_skinny_plan(M, N, K, SIZE_MAX).scratch; }
 
 template <typename E>

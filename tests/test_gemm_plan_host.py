@@ -58,3 +58,12 @@ def test_shapes_the_kernel_does_not_take():
     assert E.energon_linear_plan_selfcheck(577, 1024, 1024)[0] == -1      # too few tiles
     assert E.energon_linear_plan_selfcheck(8428, 5120, 5184)[0] == -1     # odd number of slabs
     assert E.energon_linear_plan_selfcheck(8428, 5120, 5100)[0] == -1
+
+
+def test_linear_plan_refusals_and_one_shape_per_kernel():
+    for args in ((0, 64, 64), (8, 12, 64), (8, 64, 100), (8, 64, 1 << 24)):
+        with pytest.raises(E.EnergonError):
+            E.energon_linear_plan(*args)
+    with pytest.raises(E.EnergonError):
+        E.energon_linear_plan(100, 64, 64, E.EPI_BIAS_RESIDUAL, ln_folded=True)   # no such epilogue
+    assert [E.energon_linear_plan(*s)[0] for s in ((4, 512, 512), (100, 512, 512), (658, 5120, 5120), (8428, 5120, 5120))] == [0, 1, 2, 3]

@@ -1,5 +1,5 @@
 """16-bit linears too small for whole rounds of the 256x256 kernel, one shape per way they can run: K cut over the
-wavefronts of a small tile (three tile sizes), 64x64 and 128x256 tiles, K cut over workgroups, the 256x256 kernel in
+wavefronts of a small tile (three tile sizes), 64x64, 128x128 and 128x256 tiles, K cut over workgroups, the 256x256 kernel in
 pieces; with and without scratch, ragged rows and columns, all epilogues, the residual also in place (which rules out
 overlapping edge tiles).  Against the oracle at the suite's bars; the same bits on a second run over other scratch."""
 import numpy as np
@@ -16,14 +16,14 @@ pytestmark = pytest.mark.gpu
 
 SHAPES = [
     # M, N, K, dtype, scratch that the plan takes
-    (65, 40, 64, wl.BF16, False),          # 64x64 tiles, one slab
+    (65, 40, 64, wl.BF16, False),          # 32x32, one slab
     (130, 264, 192, wl.BF16, False),       # 32x32, fewer slabs than wavefronts
     (515, 1032, 1024, wl.F16, False),      # 32x32
     (131, 2056, 4096, wl.BF16, False),     # 64x32
-    (513, 1032, 2048, wl.BF16, False),     # 64x64 along K
+    (513, 1032, 2048, wl.BF16, False),     # 32x32, more than one round
     (1025, 2056, 1024, wl.F16, False),     # 64x64 shared
-    (2600, 2056, 192, wl.BF16, False),     # 128x256
-    (515, 2056, 4096, wl.BF16, True),      # 128x256, K cut four ways
+    (2600, 2056, 192, wl.BF16, False),     # 64x64 shared, many rounds
+    (515, 2056, 4096, wl.BF16, True),      # bias + residual: 128x256, K cut four ways
     (900, 5128, 5120, wl.BF16, True),      # pieces
 ]
 
@@ -70,3 +70,23 @@ def test_scratch_below_the_plans_need_is_not_refused():
     ref = x.double() @ w.double().t()
     for y in ys:   # one rounding of the result (2^-9 of it) and of sums of K fp32 products
         assert float((y.double() - ref).abs().max()) <= 2.0 ** -8 * float(ref.abs().max())
+
+
+# M, N, K, dtype, what runs with bias / bias + GeLU / bias + residual: rows and columns of the tile, last ones ragged
+SQUARE, WIDE, SHARED = (2, 128, 128, 1), (2, 128, 256, 1), (2, 64, 64, 1)
+TILES = [
+    (650, 5128, 4096, wl.BF16, (SQUARE, SQUARE, SQUARE)),
+    (1000, 15368, 192, wl.F16, (SQUARE, SHARED, SHARED)),     # three slabs on two buffers
+    (2000, 20488, 64, wl.BF16, (SQUARE, SHARED, SHARED)),     # one slab
+    (515, 12296, 2560, wl.F16, (WIDE, WIDE, WIDE)),
+    (650, 1032, 1600, wl.BF16, ((1, 64, 64, 1), (1, 64, 64, 1), (1, 32, 32, 1))),
+    (900, 264, 1600, wl.F16, ((1, 64, 32, 1),) * 3),
+]
+
+
+@pytest.mark.parametrize("M,N,K,dtype,plans", TILES)
+@pytest.mark.parametrize("epi", [E.EPI_BIAS, E.EPI_BIAS_GELU, E.EPI_BIAS_RESIDUAL])
+def test_linear_tiles(M, N, K, dtype, plans, epi):
+    assert E.energon_linear_plan(M, N, K, epi) == plans[epi]
+    nbytes = E.energon_linear_scratch_bytes(M, N, K, E.BF16 if dtype == wl.BF16 else E.F16)
+    test_linear_plans(M, N, K, dtype, nbytes > 0, epi)

@@ -104,6 +104,17 @@ def test_linear_ln_folded_matches_layernorm_then_linear(M, N, K, dtype, gelu):
     assert np.all(out[M] == 3.0), "row past M was written"
 
 
+# the 128x128 and 128x256 tiles of the folded epilogues, ragged in both directions, one slab and an odd number of them
+@pytest.mark.parametrize("M,N,K,dtype,gelu,tile", [
+    (2000, 12296, 64, wl.BF16, False, (128, 128)), (2600, 12296, 64, wl.F16, True, (128, 128)),
+    (650, 5128, 4096, wl.F16, False, (128, 128)),
+    (1300, 15368, 192, wl.F16, False, (128, 256)), (1300, 20488, 64, wl.BF16, True, (128, 256)),
+])
+def test_linear_ln_folded_tiles(M, N, K, dtype, gelu, tile):
+    assert E.energon_linear_plan(M, N, K, E.EPI_BIAS_GELU if gelu else E.EPI_BIAS, ln_folded=True) == (2,) + tile + (1,)
+    test_linear_ln_folded_matches_layernorm_then_linear(M, N, K, dtype, gelu)
+
+
 @pytest.mark.parametrize("M,N,K,dtype", [
     (300, 264, 192, wl.BF16),        # predicated kernel: statistics by a pass over y
     (3333, 3592, 128, wl.BF16),      # 256x256 kernel but a ragged column tile: pass over y
