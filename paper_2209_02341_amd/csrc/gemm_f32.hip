@@ -21,6 +21,7 @@
 // 214 -> 41 us, 387 x 1024 x 4096 596 -> 40 us, 76 x 256 x 1024 149 -> 4.1 us; 2048 x 2048 x 8192 runs at
 // 125 TFLOP/s.
 #include "common.h"
+#include <cmath>
 
 namespace energon {
 
@@ -185,6 +186,7 @@ hipError_t launch_cfg(const float* x, const float* w, const float* bias, const f
   if (e != hipSuccess) return e;
   const int32_t tiles_m = (int32_t)((M + BM - 1) / BM), tiles_n = (N + BN - 1) / BN;
   const int64_t grid = ((int64_t)tiles_m * tiles_n + kXcds - 1) / kXcds * kXcds;
+  if (grid * WK * 64 > kMaxGridThreads) return hipErrorInvalidConfiguration;
   kern<<<dim3((unsigned)grid), dim3(WK * 64), lds, s>>>(x, w, bias, res, y, M, N, K, epi, tiles_m, tiles_n);
   return hipGetLastError();
 }
@@ -195,19 +197,30 @@ hipError_t launch_gemm_f32(const float* x, const float* w, const float* bias, co
                            int32_t N, int32_t K, int epi, hipStream_t s) {
   if (M <= 0) return hipSuccess;
   const auto tiles = [&](int bm, int bn) { return ((M + bm - 1) / bm) * ((N + bn - 1) / bn); };
+  const int64_t t16 = tiles(16, 16), t32 = tiles(32, 32), t64 = tiles(64, 64);
+  const auto fits = [](int64_t n) { return n * 256 <= kMaxGridThreads; };
   // Large tiles move fewer bytes, small ones make more workgroups; where the lines lie (measured, us):
-  //   64 x 64 from 448 tiles: 600 x 4800 x 1600 (750) 94 against 97 with 32 x 32, 2048 x 2048 x 8192 (1024)
-  //     552 / 693; but 387 x 3072 x 1024 (336, a second round nearly empty) 42 / 31;
+  //   16 x 16 where a side has no more than that, whatever the other: 100000 x 4 x 4 10 against 29 with 64 x 64 (15 with
+  //     32 x 32), 300000 x 16 x 16 36 / 84 (47), 4 x 100000 x 64 11 / 33 (16);
   //   32 x 32 from 168 tiles: 130 x 1600 x 6400 (250) 34 against 48 with 16 x 16; 37 x 1600 x 1600 (100) 10.6 / 7.3;
   //   in between, where 32 x 32 would be one to two rounds of 256 CUs, 32 x 64 is one: 387 x 1024 x 1024
   //     (416) 12.8 against 14.4;
+  //   64 x 64 where its whole rounds are expected to take less time than the smaller tiles' (fits to 181 shapes): 64 x 64
+  //     against the smaller, 655 x 3072 x 1024 (528) 73 / 58, 700 x 3072 x 1024 73 / 60, 100000 x 64 x 64 38 / 34, but
+  //     600 x 4800 x 1600 (750) 98 / 103, 724 x 1024 x 4096 (192) 73 / 84, 2048 x 2048 x 8192 (1024) 571 / 663;
   //   16 x 16 with eight wavefronts along a long K while every CU has at most one tile: 17 x 2048 x 8192
   //     15.7 against 20.0 with four.
-  if (tiles(64, 64) >= 448) return launch_cfg<4, 4, 4, 2>(x, w, bias, res, y, M, N, K, epi, s);
-  const int64_t t32 = tiles(32, 32);
-  if (t32 > 256 && t32 <= 512) return launch_cfg<2, 4, 4, 2>(x, w, bias, res, y, M, N, K, epi, s);
-  if (t32 >= 168) return launch_cfg<2, 2, 4, 2>(x, w, bias, res, y, M, N, K, epi, s);
-  if (tiles(16, 16) <= 256 && K >= 2048) return launch_cfg<1, 1, 8, 2>(x, w, bias, res, y, M, N, K, epi, s);
+  const bool narrow = (M <= 16 || N <= 16) && fits(t16);
+  if (!narrow && t32 >= 168) {
+    const double k = K;
+    const double us64 = std::ceil(t64 / 256.0) * (9.0 + 0.0155 * k);
+    const bool halves = t32 > 256 && t32 <= 512;
+    const double us = halves ? std::ceil(tiles(32, 64) / 256.0) * (3.5 + 0.0088 * k) : 2.0 + t32 / 256.0 * (1.6 + 0.0049 * k);
+    if (us64 < us || !fits(t32)) return launch_cfg<4, 4, 4, 2>(x, w, bias, res, y, M, N, K, epi, s);
+    if (halves) return launch_cfg<2, 4, 4, 2>(x, w, bias, res, y, M, N, K, epi, s);
+    return launch_cfg<2, 2, 4, 2>(x, w, bias, res, y, M, N, K, epi, s);
+  }
+  if (t16 <= 256 && K >= 2048) return launch_cfg<1, 1, 8, 2>(x, w, bias, res, y, M, N, K, epi, s);
   return launch_cfg<1, 1, 4, 2>(x, w, bias, res, y, M, N, K, epi, s);
 }
 

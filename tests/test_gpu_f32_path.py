@@ -23,7 +23,9 @@ U = 2.0 ** -24
 # 16 x 16 tiles with four and with eight wavefronts, 32 x 32, 32 x 64, 64 x 64; K with fewer slabs than wavefronts,
 # a partial last slab, ragged rows and columns
 LINEAR = [(17, 20, 4), (16, 16, 100), (33, 68, 132), (5, 260, 2052), (250, 644, 36), (257, 1028, 64), (387, 1036, 92),
-          (1403, 1412, 68)]
+          (1403, 1412, 68),
+          # narrow sides take 16 x 16 however long the other is, the next wider 32 x 32; 64 x 64 from a longer K on
+          (5409, 16, 36), (9, 5412, 36), (5409, 20, 36), (1021, 1020, 1092)]
 
 
 @pytest.mark.parametrize("M,N,K", LINEAR)
