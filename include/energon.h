@@ -107,10 +107,14 @@ enum {
 const char* energon_strerror(int status);
 
 /* Bytes of workspace energon_layer_forward needs for up to max_tokens packed rows: the six
- * intermediates below plus, where the 16-bit contractions would cut K over workgroups (see
- * energon_linear_with_scratch), room for the sums behind them.  A smaller workspace that still
- * holds the intermediates of the actual T is accepted; the contractions then take the plans that fit.
- * Returns 0 if cfg is NULL/invalid or max_tokens < 0. */
+ * intermediates below plus, where the 16-bit contractions of max_tokens rows would cut K over workgroups
+ * (see energon_linear_with_scratch), room for the sums behind them.  Any workspace that holds the
+ * intermediates of the actual T is accepted; the contractions take the fastest plan whose sums fit in
+ * the rest of it.  Fewer rows may have use for more sums than max_tokens does (hidden 2048, FFN 8192: 5888
+ * rows 381 MiB in all, 5895 rows 253 MiB), so a workspace sized once for max_tokens is enough for every T, but for the
+ * fastest plan at T it takes energon_workspace_bytes(cfg, T) bytes.  The plan decides the order of
+ * fp32 sums: results are run-to-run identical for the same T and workspace size, and may differ in the last bits
+ * between sizes.  Returns 0 if cfg is NULL/invalid or max_tokens < 0. */
 size_t energon_workspace_bytes(const EnergonLayerConfig* cfg, int64_t max_tokens);
 
 /* Byte offsets (offsets_out[ENERGON_WS_COUNT], host) at which a call of
@@ -214,9 +218,11 @@ int energon_linear(const void* x_dev, const void* w_dev, const void* bias_dev,
  * busy, so, given scratch, they are cut along K into equal shares, one per workgroup, the fp32 pieces meet in the
  * scratch, and a second kernel adds them in a fixed order and applies the epilogue.  Smaller problems with a long
  * K are cut likewise where that is expected to be faster.  Same rounding points, a different but fixed order of the
- * fp32 sums; run-to-run identical.  energon_linear_scratch_bytes returns what the best plan for a shape needs
- * (0: none; then scratch may be NULL).  With less (scratch_bytes) the best plan that fits is taken; only a shape of
- * the first kind refuses less than it needs.  scratch_dev: 256-byte aligned, contents undefined afterwards.
+ * fp32 sums; run-to-run identical.  energon_linear_scratch_bytes returns what the best plan for a shape of more than 64
+ * rows needs (0: none; then scratch may be NULL); for up to 64 rows it returns 0, though scratch that is given is
+ * used there too (energon_decode_workspace_bytes counts it in).  With less (scratch_bytes) the best plan that fits
+ * is taken; only a shape of the first kind refuses less than it needs.  scratch_dev: 256-byte aligned, contents
+ * undefined afterwards.
  * energon_layer_forward does the same inside its workspace.  Other arguments and errors as energon_linear, plus
  * CAPACITY (scratch too small). */
 size_t energon_linear_scratch_bytes(int64_t M, int32_t N, int32_t K, int32_t dtype);

@@ -207,7 +207,7 @@ hipError_t launch_gemm_f32(const float* x, const float* w, const float* bias, co
   //     (416) 12.8 against 14.4;
   //   64 x 64 where its whole rounds are expected to take less time than the smaller tiles' (fits to 181 shapes): 64 x 64
   //     against the smaller, 655 x 3072 x 1024 (528) 73 / 58, 700 x 3072 x 1024 73 / 60, 100000 x 64 x 64 38 / 34, but
-  //     600 x 4800 x 1600 (750) 98 / 103, 724 x 1024 x 4096 (192) 73 / 84, 2048 x 2048 x 8192 (1024) 571 / 663;
+  //     600 x 4800 x 1600 (750) 98 / 103, 2048 x 2048 x 8192 (1024) 571 / 663;
   //   16 x 16 with eight wavefronts along a long K while every CU has at most one tile: 17 x 2048 x 8192
   //     15.7 against 20.0 with four.
   const bool narrow = (M <= 16 || N <= 16) && fits(t16);
