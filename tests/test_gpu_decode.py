@@ -280,7 +280,7 @@ def test_embed_packed_and_last_rows(dtype):
 @pytest.mark.parametrize("dtype", [wl.BF16, wl.F16])
 def test_decode_layer_with_split_contraction(dtype):
     """A long FFN (10240 = 160 slabs) with few output columns: the FC2 contraction of the step is cut
-    over 4 workgroups along K and finished by the second kernel.  Also run-to-run identical."""
+    over 8 workgroups along K and finished by the second kernel.  Also run-to-run identical."""
     w = wl.Workload("dec_split", dtype, 1, 256, 4, 64, 10240, 5, 24, "uniform", 0, 24)
     lens = np.array([0, 23, 7, 1, 12], dtype=np.int32)
     rng = np.random.default_rng(21)
@@ -292,7 +292,8 @@ def test_decode_layer_with_split_contraction(dtype):
     cfg = hz.layer_config(w.hidden, w.n_heads, w.head_dim, w.ffn, dtype, w.ln_eps)
     layer = hz.DeviceLayer(p, dtype)
     ws = torch.empty(E.energon_decode_workspace_bytes(cfg, B), dtype=torch.uint8, device="cuda")
-    assert ws.numel() > E.energon_workspace_bytes(cfg, B), "no room for partial sums was planned"
+    room = ws.numel() - E.energon_workspace_bytes(cfg, B)   # behind the intermediates
+    assert E.energon_linear_plan(B, w.hidden, w.ffn, E.EPI_BIAS_RESIDUAL, scratch_bytes=room) == (0, 16, 16, 8)
     outs = []
     for _ in range(2):
         xd, kd, vd = (hz.to_device(a, dtype) for a in (x, kc, vc))
@@ -456,14 +457,15 @@ def test_generation_steps_replayed_from_a_hip_graph():
         assert torch.equal(st.v[i].view(torch.int16), eager.v[i].view(torch.int16))
 
 
-def test_decode_layer_batch_above_the_few_row_kernel():
-    """96 sequences: more rows than the few-row kernel takes, few enough that the tiled kernel would
-    leave most CUs idle; with the step's scratch its K is cut over workgroups (QKV, out-proj, FC1
-    and FC2 all qualify at this shape).  Against the oracle, and run-to-run identical."""
+@pytest.mark.parametrize("B,ffn,S_cap,fc2", [(96, 8192, 24, (1, 32, 32, 1)), (300, 16384, 8, (2, 128, 256, 8))])
+def test_decode_layer_batch_above_the_few_row_kernel(B, ffn, S_cap, fc2):
+    """More sequences than the few-row kernel takes rows.  96: K is cut over the wavefronts of small tiles, no scratch.
+    300 and a long FFN: FC2's K is cut over workgroups, with sums in the step's workspace.  Against the oracle, and
+    run-to-run identical."""
     dtype = wl.BF16
-    w = wl.Workload("dec_b96", dtype, 1, 2048, 16, 128, 8192, 96, 24, "uniform", 0, 24)
+    w = wl.Workload("dec_b96", dtype, 1, 2048, 16, 128, ffn, B, S_cap, "uniform", 0, S_cap)
     rng = np.random.default_rng(31)
-    B, S_cap, A = 96, 24, w.attn_width
+    A = w.attn_width
     lens = rng.integers(0, S_cap, B).astype(np.int32)
     p = wl.sample_layer(w, 0)
     kc = wl.round_to_dtype(rng.standard_normal((B, S_cap, A)), dtype)
@@ -472,7 +474,8 @@ def test_decode_layer_batch_above_the_few_row_kernel():
     cfg = hz.layer_config(w.hidden, w.n_heads, w.head_dim, w.ffn, dtype, w.ln_eps)
     layer = hz.DeviceLayer(p, dtype)
     ws = torch.empty(E.energon_decode_workspace_bytes(cfg, B), dtype=torch.uint8, device="cuda")
-    assert ws.numel() > E.energon_workspace_bytes(cfg, B), "no room for partial sums was planned"
+    assert E.energon_linear_plan(B, w.hidden, w.ffn, E.EPI_BIAS_RESIDUAL,
+                                 scratch_bytes=E.energon_linear_scratch_bytes(B, w.hidden, w.ffn, E.BF16)) == fc2
     outs = []
     for _ in range(2):
         xd, kd, vd = (hz.to_device(a, dtype) for a in (x, kc, vc))

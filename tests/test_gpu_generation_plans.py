@@ -1,5 +1,5 @@
-"""The ways a generation step can run: the few-row linear in its column blocks (16, 32, 64, 80) with and without K cut over
-workgroups, ragged last blocks, one row to 64; the cached attention whole or with its keys cut over workgroups, at
+"""The ways a generation step can run: the few-row linear at edges of its rules and in every instance (rows, block columns, K
+whole or cut over workgroups, ragged last block), asserted to be the one that the plan takes; the cached attention whole or with its keys cut over workgroups, at
 cached lengths on both sides of a part's, a trip's and the cache's end; workspaces of the least size that is accepted."""
 import numpy as np
 import pytest
@@ -42,7 +42,33 @@ def test_few_row_linear(M, N, K, dtype, epi):
         assert_close(hz.to_host(outs[0]), ref, dtype, f"few-row linear epi={epi} scratch={nbytes}")
 
 
-# 16 heads x 2 sequences of a cache of 1600: 3 parts; 3 sequences x 4 heads: 3 parts (the cache's length limits them)
+# every instance of the few-row kernel: rows of the tile x columns of a block x K whole or in parts x whole and ragged last
+# block, at the smallest shape whose plan takes it
+INSTANCES = [   # M, N, K, tile rows, block columns, parts of K
+    (2, 16, 5120, 16, 16, 8), (2, 8, 5120, 16, 16, 8), (2, 16, 64, 16, 16, 1), (2, 8, 64, 16, 16, 1),
+    (2, 352, 5120, 16, 32, 8), (2, 344, 5120, 16, 32, 8), (2, 4800, 64, 16, 32, 1), (2, 4104, 64, 16, 32, 1),
+    (2, 1280, 8192, 16, 64, 8), (2, 1608, 10240, 16, 64, 8), (2, 10240, 64, 16, 64, 1), (2, 8200, 64, 16, 64, 1),
+    (2, 2560, 8192, 16, 80, 8), (2, 2048, 10240, 16, 80, 8), (2, 17600, 64, 16, 80, 1), (2, 16392, 64, 16, 80, 1),
+    (17, 16, 4096, 32, 16, 8), (17, 8, 4096, 32, 16, 8), (17, 16, 64, 32, 16, 1), (17, 8, 64, 32, 16, 1),
+    (17, 320, 4096, 32, 32, 8), (17, 312, 4096, 32, 32, 8), (17, 4800, 64, 32, 32, 1), (17, 4104, 64, 32, 32, 1),
+    (17, 1280, 5120, 32, 64, 8), (17, 1608, 5120, 32, 64, 8), (17, 10240, 64, 32, 64, 1), (17, 8200, 64, 32, 64, 1),
+    (17, 2560, 4096, 32, 80, 8), (17, 2048, 5120, 32, 80, 8), (17, 17600, 2048, 32, 80, 1), (17, 16392, 2048, 32, 80, 1),
+    (33, 16, 2048, 64, 16, 8), (33, 8, 2048, 64, 16, 8), (33, 16, 64, 64, 16, 1), (33, 8, 64, 64, 16, 1),
+    (33, 288, 2048, 64, 32, 8), (33, 280, 2048, 64, 32, 8), (33, 4800, 64, 64, 32, 1), (33, 4104, 64, 64, 32, 1),
+    (33, 1280, 2560, 64, 64, 8), (33, 1032, 2560, 64, 64, 8), (33, 10240, 64, 64, 64, 1), (33, 8200, 64, 64, 64, 1),
+    (33, 2560, 2048, 64, 80, 8), (33, 2056, 2560, 64, 80, 8), (33, 17600, 64, 64, 80, 1), (33, 16392, 64, 64, 80, 1),
+]
+
+
+@pytest.mark.parametrize("M,N,K,rows,columns,parts", INSTANCES)
+def test_few_row_instances(M, N, K, rows, columns, parts):
+    room = 8 * M * N * 4 if parts > 1 else 0
+    assert E.energon_linear_plan(M, N, K, scratch_bytes=room) == (0, rows, columns, parts)
+    for epi in (E.EPI_BIAS, E.EPI_BIAS_GELU, E.EPI_BIAS_RESIDUAL):
+        test_few_row_linear(M, N, K, wl.F16 if N % 16 else wl.BF16, epi)
+
+
+# a part for every 256 cached keys, up to what is launched: 1 and 3 or more, 1 each, 4 and (1024 keys and the new one) 5, 1 and 6
 @pytest.mark.parametrize("nh,d,lens,S_cap,dtype", [(16, 64, [0, 1599], 1600, wl.BF16), (4, 128, [1, 63, 64], 1600, wl.F16),
                                                     (4, 128, [1000, 1023, 1024], 2048, wl.BF16), (2, 64, [5, 1535], 1536, wl.F16)])
 def test_step_with_keys_in_parts(nh, d, lens, S_cap, dtype):
