@@ -38,7 +38,6 @@ constexpr int kAttnWaves = 4, kWQ = 32, kBQ = kAttnWaves * kWQ;   // queries per
 constexpr int kBKV = 32, kStages = 4;                             // keys per tile, tiles in LDS
 constexpr float kLog2e = 1.4426950408889634f;
 
-typedef __attribute__((address_space(1))) const void* attn_gptr_t;
 typedef __attribute__((address_space(3))) void* attn_lptr_t;
 
 // 16-byte slot of chunk c of row r inside an LDS row: c ^ kswz(r) for rows read as 32-row operand tiles (lane l:

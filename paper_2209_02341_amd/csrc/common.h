@@ -98,11 +98,21 @@ __device__ inline float wave_sum(float v) {
   for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
   return v;
 }
-__device__ inline float wave_max(float v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, 64));
-  return v;
+
+// LDS rows of 128 bytes read as 16-row MFMA operands (lane l: row l % 16, chunk 4 h + l / 16 of 16 bytes): chunk c of row r
+// lies in slot c ^ swz16(r), row bits 1, 2, 3 going to slot bits 0, 2, 1; such a read then meets no bank conflict (measured).
+__device__ __forceinline__ int swz16(int row) {
+  return ((row >> 1) & 1) | (((row >> 2) & 1) << 2) | (((row >> 3) & 1) << 1);
 }
+
+// LDS of a workgroup whose WK wavefronts cut K: each has a ring of kDepth slabs of 128 bytes of 16 TN rows of W and 16 TM of x,
+// in whose place the fp32 sums of all of them meet at the end.
+template <int TM, int TN, int WK, int kDepth> struct WaveRings {
+  static constexpr int kSlotVecs = (TM + TN) * 16 * 8;   // 16-byte vectors per slab: W rows, then x rows
+  static constexpr size_t kRing = (size_t)WK * kDepth * kSlotVecs * 16;
+  static constexpr size_t kRed = (size_t)WK * TN * TM * 1024;
+  static constexpr size_t kLds = kRing > kRed ? kRing : kRed;
+};
 
 // GeLU in its erf form, z * Phi(z) = 0.5 z (1 + erf(z / sqrt 2)), in fp32, written without the
 // cancellation of 1 + erf for negative z:

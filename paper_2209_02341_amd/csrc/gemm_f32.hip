@@ -30,26 +30,13 @@ namespace {
 typedef __attribute__((address_space(1))) const void* f32_gptr_t;
 typedef __attribute__((address_space(3))) void* f32_lptr_t;
 
-// 16-byte slot of chunk c of row r inside a 128-byte LDS row: c ^ f32_swz(r) (row bits 1, 2, 3 to slot bits
-// 0, 2, 1: the 16-row operand reads below then meet no bank conflict).
-__device__ __forceinline__ int f32_swz(int row) {
-  return ((row >> 1) & 1) | (((row >> 2) & 1) << 2) | (((row >> 3) & 1) << 1);
-}
-
-template <int TM, int TN, int WK, int kDepth> struct F32Cfg {
-  static constexpr int kSlotVecs = (TM + TN) * 16 * 8;   // 16-byte vectors per slab: W rows, then x rows
-  static constexpr size_t kRing = (size_t)WK * kDepth * kSlotVecs * 16;
-  static constexpr size_t kRed = (size_t)WK * TN * TM * 1024;
-  static constexpr size_t kLds = kRing > kRed ? kRing : kRed;
-};
-
 // TN x TM tiles of 16 x 16 (columns x rows of y) per workgroup, WK wavefronts along K, kDepth slabs in flight each.
 template <int TM, int TN, int WK, int kDepth>
 __global__ __launch_bounds__(WK * 64) void gemm_f32_kernel(const float* __restrict__ x, const float* __restrict__ w,
                                                           const float* __restrict__ bias, const float* res, float* y,
                                                           int64_t M, int32_t N, int32_t K, int epi, int32_t tiles_m,
                                                           int32_t tiles_n) {
-  using Cfg = F32Cfg<TM, TN, WK, kDepth>;
+  using Cfg = WaveRings<TM, TN, WK, kDepth>;
   constexpr int G = 2 * (TM + TN);   // 1 KiB loads (8 rows x 128 bytes) per slab
   extern __shared__ f32x4 lds[];
   int64_t m0;
@@ -70,7 +57,7 @@ __global__ __launch_bounds__(WK * 64) void gemm_f32_kernel(const float* __restri
   const char *pw[2 * TN], *px[2 * TM];
   uint32_t chunk[2];
 #pragma unroll
-  for (int p = 0; p < 2; ++p) chunk[p] = (uint32_t)((lane & 7) ^ f32_swz((lane >> 3) + 8 * p));
+  for (int p = 0; p < 2; ++p) chunk[p] = (uint32_t)((lane & 7) ^ swz16((lane >> 3) + 8 * p));
 #pragma unroll
   for (int g = 0; g < 2 * TN; ++g) {
     const int32_t n = n0 + 8 * g + (lane >> 3);
@@ -103,7 +90,7 @@ __global__ __launch_bounds__(WK * 64) void gemm_f32_kernel(const float* __restri
     for (int j = 0; j < TM; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
   uint32_t foff[2];   // operand reads: row l % 16 of a 16-row tile, chunk 4 h + l / 16
 #pragma unroll
-  for (int h = 0; h < 2; ++h) foff[h] = (uint32_t)(lrow * 8 + ((4 * h + lq) ^ f32_swz(lrow)));
+  for (int h = 0; h < 2; ++h) foff[h] = (uint32_t)(lrow * 8 + ((4 * h + lq) ^ swz16(lrow)));
 
   for (int32_t u = 0; u < kDepth && u < ns; ++u) issue(u, u);
   int32_t slot = 0;
@@ -178,7 +165,7 @@ template <int TM, int TN, int WK, int kDepth>
 hipError_t launch_cfg(const float* x, const float* w, const float* bias, const float* res, float* y, int64_t M,
                       int32_t N, int32_t K, int epi, hipStream_t s) {
   constexpr int BM = 16 * TM, BN = 16 * TN;
-  constexpr size_t lds = F32Cfg<TM, TN, WK, kDepth>::kLds;
+  constexpr size_t lds = WaveRings<TM, TN, WK, kDepth>::kLds;
   static_assert(lds <= 160 * 1024, "LDS of a CU");
   auto kern = gemm_f32_kernel<TM, TN, WK, kDepth>;
   static LdsAttrOnce once;

@@ -18,25 +18,13 @@ namespace {
 typedef __attribute__((address_space(1))) const void* kp_gptr_t;
 typedef __attribute__((address_space(3))) void* kp_lptr_t;
 
-// 16-byte slot of chunk c of row r inside a 128-byte LDS row: c ^ kp_swz(r) (no bank conflict in the operand reads)
-__device__ __forceinline__ int kp_swz(int row) {
-  return ((row >> 1) & 1) | (((row >> 2) & 1) << 2) | (((row >> 3) & 1) << 1);
-}
-
 // TN x TM tiles of 16 x 16 (columns x rows of y) per workgroup, WK wavefronts along K, kDepth slabs in flight each.
-template <int TM, int TN, int WK, int kDepth> struct KpCfg {
-  static constexpr int kSlotVecs = (TM + TN) * 16 * 8;   // 16-byte vectors per slab: W rows, then x rows
-  static constexpr size_t kRing = (size_t)WK * kDepth * kSlotVecs * 16;
-  static constexpr size_t kRed = (size_t)WK * TN * TM * 1024;
-  static constexpr size_t kLds = kRing > kRed ? kRing : kRed;
-};
-
 template <typename E, int TM, int TN, int WK, int kDepth>
 __global__ __launch_bounds__(WK * 64) void gemm_ksplit_kernel(const E* __restrict__ x, const E* __restrict__ w,
                                                              const E* __restrict__ bias, const E* res, E* y, int64_t M,
                                                              int32_t N, int32_t K, int epi, int32_t tiles_m,
                                                              int32_t tiles_n) {
-  using Cfg = KpCfg<TM, TN, WK, kDepth>;
+  using Cfg = WaveRings<TM, TN, WK, kDepth>;
   constexpr int G = 2 * (TM + TN);   // 1 KiB loads (8 rows x 128 bytes) per slab
   extern __shared__ uint4 lds[];
   int64_t m0;
@@ -55,13 +43,13 @@ __global__ __launch_bounds__(WK * 64) void gemm_ksplit_kernel(const E* __restric
 #pragma unroll
   for (int g = 0; g < 2 * TN; ++g) {
     const int row = 8 * g + (lane >> 3);
-    ow[g] = ((uint32_t)min(row, N - 1 - n0) * (uint32_t)K + (uint32_t)((lane & 7) ^ kp_swz(row & 15)) * 8u) * 2u;
+    ow[g] = ((uint32_t)min(row, N - 1 - n0) * (uint32_t)K + (uint32_t)((lane & 7) ^ swz16(row & 15)) * 8u) * 2u;
   }
   const int64_t lim = M - 1 - m0;
 #pragma unroll
   for (int g = 0; g < 2 * TM; ++g) {
     const int row = 8 * g + (lane >> 3);
-    ox[g] = ((uint32_t)(row < lim ? row : lim) * (uint32_t)K + (uint32_t)((lane & 7) ^ kp_swz(row & 15)) * 8u) * 2u;
+    ox[g] = ((uint32_t)(row < lim ? row : lim) * (uint32_t)K + (uint32_t)((lane & 7) ^ swz16(row & 15)) * 8u) * 2u;
   }
   const char* const wbase = reinterpret_cast<const char*>(w + (size_t)n0 * K);
   const char* const xbase = reinterpret_cast<const char*>(x + (size_t)m0 * K);
@@ -83,7 +71,7 @@ __global__ __launch_bounds__(WK * 64) void gemm_ksplit_kernel(const E* __restric
     for (int b = 0; b < TM; ++b) acc[a][b] = f32x4{0.f, 0.f, 0.f, 0.f};
   uint32_t foff[2];   // operand reads: row l % 16 of a 16-row tile, chunk 4 ks + l / 16
 #pragma unroll
-  for (int ks = 0; ks < 2; ++ks) foff[ks] = (uint32_t)(lrow * 8 + ((4 * ks + lq) ^ kp_swz(lrow)));
+  for (int ks = 0; ks < 2; ++ks) foff[ks] = (uint32_t)(lrow * 8 + ((4 * ks + lq) ^ swz16(lrow)));
 
   for (int32_t u = 0; u < kDepth && u < ns; ++u) issue(u, u);
   int32_t slot = 0;
@@ -159,7 +147,7 @@ template <typename E, int TM, int TN, int WK, int kDepth>
 hipError_t launch_cfg(const E* x, const E* w, const E* bias, const E* res, E* y, int64_t M, int32_t N, int32_t K,
                       int epi, hipStream_t s) {
   constexpr int BM = 16 * TM, BN = 16 * TN;
-  constexpr size_t lds = KpCfg<TM, TN, WK, kDepth>::kLds;
+  constexpr size_t lds = WaveRings<TM, TN, WK, kDepth>::kLds;
   static_assert(lds <= 160 * 1024, "LDS of a CU");
   auto kern = gemm_ksplit_kernel<E, TM, TN, WK, kDepth>;
   static LdsAttrOnce once;

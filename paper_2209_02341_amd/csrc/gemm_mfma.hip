@@ -38,13 +38,8 @@ constexpr int kChunks = BK / 8;   // 16-byte chunks per LDS row
 typedef __attribute__((address_space(1))) const void* gptr_t;
 typedef __attribute__((address_space(3))) void* lptr_t;
 
+// Swizzle for the 32-row operand tiles of the 32x32x16 form (the 16-row ones: swz16, two passes per read with this one).
 __device__ __forceinline__ int swz(int row) { return (row & 7) ^ ((row >> 3) & 1); }
-// The same for the 16-row operand tiles of the 16x16x32 form, where lane l reads row l % 16, chunk
-// 4 ks + l / 16: row bits 1, 2, 3 go to slot bits 0, 2, 1 (measured: zero bank conflicts; with the
-// function above every such read takes two passes).
-__device__ __forceinline__ int swz16(int row) {
-  return ((row >> 1) & 1) | (((row >> 2) & 1) << 2) | (((row >> 3) & 1) << 1);
-}
 
 // Epilogue of one wavefront: TM x TN accumulator tiles of 32x32 whose top-left element is
 // (mw, nw).  In each tile the lane holds column (lane & 31), rows 8*(e/4) + 4*(lane/32) + e%4.

@@ -28,10 +28,6 @@ typedef __attribute__((address_space(3))) void* sk_lptr_t;
 
 constexpr int kSkWaves = 4;     // a workgroup's share of K is split over this many wavefronts
 
-__device__ __forceinline__ int sk_swz(int row) {
-  return ((row >> 1) & 1) | (((row >> 2) & 1) << 2) | (((row >> 3) & 1) << 1);
-}
-
 // MT row tiles of x (16 rows each), NT row tiles of W (= 16 NT output columns per workgroup)
 template <int MT, int NT, int D> struct SkCfg {
   static constexpr int kBN = 16 * NT;
@@ -75,8 +71,8 @@ __global__ __launch_bounds__(kSkWaves * 64) void gemm_skinny_kernel(const E* __r
   // workgroup's first slab) plus a 32-bit per-lane offset, so that advancing along K is scalar
   // arithmetic.  x rows are clamped to M - 1: rows past M are computed and dropped.
   const uint32_t row_b = (uint32_t)K * (uint32_t)sizeof(E);
-  const uint32_t ch_even = (uint32_t)(((lane & 7) ^ sk_swz(lane >> 3)) * 16);
-  const uint32_t ch_odd = (uint32_t)(((lane & 7) ^ sk_swz((lane >> 3) | 8)) * 16);
+  const uint32_t ch_even = (uint32_t)(((lane & 7) ^ swz16(lane >> 3)) * 16);
+  const uint32_t ch_odd = (uint32_t)(((lane & 7) ^ swz16((lane >> 3) | 8)) * 16);
   const uint32_t woff_even = (uint32_t)(lane >> 3) * row_b + ch_even, woff_odd = (uint32_t)(lane >> 3) * row_b + ch_odd;
   const char* wbase = reinterpret_cast<const char*>(w + (size_t)n0 * K) + (size_t)s0 * 128;   // uniform
   const int32_t groups = (N - n0 + 7) >> 3;   // 8-row groups of W that exist; those past the end repeat the last
@@ -87,7 +83,7 @@ __global__ __launch_bounds__(kSkWaves * 64) void gemm_skinny_kernel(const E* __r
   // operand reads from a ring slot: row l % 16 of a 16-row tile, chunk (4 ks + l / 16) ^ swizzle
   uint32_t foff[2];
 #pragma unroll
-  for (int ks = 0; ks < 2; ++ks) foff[ks] = (uint32_t)(lrow * 8 + ((ks * 4 + lq) ^ sk_swz(lrow)));
+  for (int ks = 0; ks < 2; ++ks) foff[ks] = (uint32_t)(lrow * 8 + ((ks * 4 + lq) ^ swz16(lrow)));
 
   f32x4 acc[MT][NT];
 #pragma unroll

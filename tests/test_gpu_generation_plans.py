@@ -68,7 +68,7 @@ def test_few_row_instances(M, N, K, rows, columns, parts):
         test_few_row_linear(M, N, K, wl.F16 if N % 16 else wl.BF16, epi)
 
 
-# a part for every 256 cached keys, up to what is launched: 1 and 3 or more, 1 each, 4 and (1024 keys and the new one) 5, 1 and 6
+# a part for every 256 cached keys, up to the launched one for every 512 of the cache: 1 and 3, 1 each, 4 each, 1 and 3
 @pytest.mark.parametrize("nh,d,lens,S_cap,dtype", [(16, 64, [0, 1599], 1600, wl.BF16), (4, 128, [1, 63, 64], 1600, wl.F16),
                                                     (4, 128, [1000, 1023, 1024], 2048, wl.BF16), (2, 64, [5, 1535], 1536, wl.F16)])
 def test_step_with_keys_in_parts(nh, d, lens, S_cap, dtype):
