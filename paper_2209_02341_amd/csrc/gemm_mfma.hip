@@ -403,6 +403,7 @@ struct SchedPlan {
   int32_t wgs;                    // workgroups per XCD
   int32_t raster;                 // 0 / 1, see above
   int32_t pieces;                 // P: 1 = remainder tiles run whole
+  int32_t slots;                  // room for pieces in the scratch, per XCD
 };
 struct XcdShare { int32_t n_tiles, dp_rounds, rem, chunk; };   // chunk: slabs per piece
 
@@ -467,7 +468,7 @@ __host__ __device__ inline void sched_tile(const SchedPlan& p, int32_t x, int32_
 
 // The work of workgroup `wg` of XCD `xcd`, in the order it is done: whole tiles first, then pieces of
 // the XCD's cut tiles.  next() yields tile l of the XCD's sequence, the slabs [kb, kb + n) of it, and
-// the scratch slot of the piece inside the XCD's 2 * wgs slots (-1: the whole tile, finished by this
+// the scratch slot of the piece inside the XCD's slots (-1: the whole tile, finished by this
 // workgroup).  Shared by the kernel and the host-side check of the decomposition.
 struct SchedWalker {
   XcdShare share;
@@ -562,7 +563,7 @@ __global__ __launch_bounds__(WM* WN * 64) void gemm_mfma_sched_kernel(const E* _
     int32_t l, kb, KT, slot;
     if (!walk.next(l, kb, KT, slot)) break;
     // non-null: the piece does not cover its tile
-    float* const piece_out = slot < 0 ? nullptr : part + ((size_t)xcd * (2 * plan.wgs) + (size_t)slot) * kPartFloats;
+    float* const piece_out = slot < 0 ? nullptr : part + ((size_t)xcd * plan.slots + (size_t)slot) * kPartFloats;
     int32_t tm, tn;
     sched_tile(plan, xcd, l, tm, tn);
     int64_t m0 = (int64_t)tm * BM;
@@ -767,7 +768,7 @@ __global__ __launch_bounds__(512) void gemm_mfma_fixup_kernel(const float* __res
   const int32_t n_chunks = (plan.kt + share.chunk - 1) / share.chunk;
   const int tid = threadIdx.x;
   const int r = strip * 16 + (tid >> 5), c8 = (tid & 31) * 8;   // row and first column inside the tile
-  const float* src = part + ((size_t)xcd * (2 * plan.wgs) + (size_t)t * plan.pieces) * kPartFloats + (size_t)r * 256 + c8;
+  const float* src = part + ((size_t)xcd * plan.slots + (size_t)t * plan.pieces) * kPartFloats + (size_t)r * 256 + c8;
   float v[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
   for (int32_t c0 = 0; c0 < n_chunks; c0 += 4) {   // four pieces' loads in flight at a time
     float4 lo[4], hi[4];
@@ -877,6 +878,7 @@ static SchedPlan sched_plan(int64_t M, int32_t N, int32_t K, bool can_split, int
   p.wgs = wgs;
   p.raster = p.tiles_m >= 2 * kXcds ? 1 : 0;
   p.pieces = 1;
+  p.slots = 2 * wgs;
   if (!can_split) return p;
   // per XCD: full rounds and remainder tiles (they differ by a tile between XCDs)
   int32_t full[kXcds], rem[kXcds], rem_max = 0;
@@ -924,7 +926,11 @@ static int32_t sched_max_rem(const SchedPlan& p) {
   return m;
 }
 
-static size_t sched_scratch_bytes(int32_t wgs) { return (size_t)2 * kXcds * wgs * kPartFloats * sizeof(float); }
+static size_t slots_bytes(int32_t per_xcd) { return (size_t)kXcds * per_xcd * kPartFloats * sizeof(float); }
+static int32_t pieces_slots(int64_t M, int32_t N, int32_t pieces) {   // every tile of an XCD is cut
+  return (int32_t)((((M + 255) / 256) * ((N + 255) / 256) + kXcds - 1) / kXcds) * pieces;
+}
+static size_t sched_scratch_bytes(int32_t wgs) { return slots_bytes(2 * wgs); }
 
 size_t gemm_sched_scratch_bytes(int64_t M, int32_t N, int32_t K) {
   if (!takes_sched_kernel(M, N, K, false)) return 0;
@@ -1034,7 +1040,7 @@ static TilePlan tile_plan(int64_t M, int32_t N, int32_t K, bool overlap_safe, in
       // one round at most of every XCD's workgroups, and slots for it (two per workgroup)
       if (rem >= wgs || rem * P > 2 * wgs || (KT + chunk - 1) / chunk != P || chunk < 8) continue;
       const double rounds = std::ceil((double)rem * P / wgs);
-      consider({kPieces, KsplitTile::k64x64, P, sched_scratch_bytes(wgs)},
+      consider({kPieces, KsplitTile::k64x64, P, slots_bytes(pieces_slots(M, N, P))},
                8.2 + rounds * (1.1 + 1.228 * chunk) + (0.388 * big * P * kPartFloats * 4.0 + 0.394 * res * elems) / 1.0e6);
     }
   }
@@ -1049,6 +1055,7 @@ static SchedPlan pieces_plan(int64_t M, int32_t N, int32_t K, int32_t pieces, in
   p.wgs = wgs;
   p.raster = 0;
   p.pieces = pieces;
+  p.slots = pieces_slots(M, N, pieces);
   return p;
 }
 
@@ -1065,7 +1072,7 @@ size_t gemm_scratch_bytes(int64_t M, int32_t N, int32_t K) {
 // same functions): every tile is either finished whole by exactly one workgroup or cut into pieces
 // whose slab ranges are even, start where the previous one ended and add up to the tile; the pieces of
 // a tile occupy the slots its second-kernel workgroups read, in ascending K order; no slot is used
-// twice or lies outside the XCD's 2 * wgs.  0 if all of that holds, else a positive code naming the
+// twice or lies outside the XCD's.  0 if all of that holds, else a positive code naming the
 // first violation; -1 if the 256x256 kernel does not take the shape.
 int gemm_sched_selfcheck(int64_t M, int32_t N, int32_t K, int32_t wgs, int32_t can_split, int32_t* pieces_out) {
   if (wgs < 1) return -1;
@@ -1084,7 +1091,7 @@ int gemm_sched_selfcheck(int64_t M, int32_t N, int32_t K, int32_t wgs, int32_t c
   std::vector<int8_t> whole(tiles, 0);
   for (int32_t x = 0; x < kXcds; ++x) {
     const XcdShare sh = xcd_share(p, x);
-    std::vector<int8_t> slot_used(2 * (size_t)wgs, 0);
+    std::vector<int8_t> slot_used(p.slots, 0);
     // pieces of one tile are produced by different workgroups: collect (tile, kb, n, slot) and sort by kb
     struct Piece { int64_t tile; int32_t kb, n, slot; };
     std::vector<Piece> pieces;
@@ -1104,7 +1111,7 @@ int gemm_sched_selfcheck(int64_t M, int32_t N, int32_t K, int32_t wgs, int32_t c
           whole[tile] = 1;
           covered[tile] = p.kt;
         } else {
-          if (slot >= 2 * wgs || slot_used[slot]) return 5;
+          if (slot >= p.slots || slot_used[slot]) return 5;
           slot_used[slot] = 1;
           pieces.push_back({tile, kb, n, slot});
         }
@@ -1131,7 +1138,7 @@ int gemm_sched_selfcheck(int64_t M, int32_t N, int32_t K, int32_t wgs, int32_t c
       }
       if (kb != p.kt) return 8;
     }
-    if (sh.rem > wgs || (p.pieces > 1 && sh.rem * p.pieces > 2 * wgs)) return 9;
+    if (sh.rem > wgs || (p.pieces > 1 && sh.rem * p.pieces > p.slots)) return 9;
     (void)seen;
   }
   for (int64_t t = 0; t < tiles; ++t)

@@ -67,3 +67,14 @@ def test_linear_plan_refusals_and_one_shape_per_kernel():
     with pytest.raises(E.EnergonError):
         E.energon_linear_plan(100, 64, 64, E.EPI_BIAS_RESIDUAL, ln_folded=True)   # no such epilogue
     assert [E.energon_linear_plan(*s)[0] for s in ((4, 512, 512), (100, 512, 512), (658, 5120, 5120), (8428, 5120, 5120))] == [0, 1, 2, 3]
+
+
+def test_tiles_in_pieces_ask_for_their_pieces_room_only():
+    for M, N, K in ((928, 5120, 20480), (928, 5120, 5120), (400, 5120, 20480)):
+        need = E.energon_linear_scratch_bytes(M, N, K, E.BF16)
+        kernel, rows, columns, pieces = E.energon_linear_plan(M, N, K, E.EPI_BIAS, scratch_bytes=need)
+        assert (kernel, rows, columns) == (3, 256, 256) and pieces > 1
+        tiles = -(-M // rows) * -(-N // columns)
+        per_xcd = -(-tiles // 8)
+        assert need == 8 * per_xcd * pieces * rows * columns * 4
+        assert E.energon_linear_plan_selfcheck(M, N, K)[0] == 0
