@@ -977,12 +977,12 @@ struct TileTime {
            (epi == EPI_BIAS_RESIDUAL ? residual + n * residual_round : 0.0);
   }
 };
-constexpr TileTime kSmallTime{3.56, 0.78, 1.04, 0.53, 1.22, 6.12, 1.01,
+constexpr TileTime kSmallTime{3.56, 0.78, 1.04, 0.53, 1.22, 5.34, 1.01,
     {{0, 0.247}, {1, 0.261}, {1.003, 0.339}, {2, 0.378}, {2.003, 0.539}, {3, 0.580}, {3.003, 0.750}, {4, 0.824}, {4.003, 0.880},
      {6, 1.170}, {10, 1.991}}};
-constexpr TileTime kSquareTime{7.67, 3.18, 4.97, 1.79, 6.08, 17.46, 1.99,
+constexpr TileTime kSquareTime{7.67, 3.18, 4.97, 1.79, 6.08, 11.90, 4.50,
     {{0, 0.564}, {1, 0.631}, {1.003, 0.780}, {1.5, 0.902}, {2, 1.040}, {2.003, 1.550}, {3, 1.720}, {4, 2.100}, {4.5, 2.800}, {10, 5.700}}};
-constexpr TileTime kWideTime{7.97, 2.70, 5.47, 3.53, 11.73, 17.42, 4.04,
+constexpr TileTime kWideTime{7.97, 2.70, 5.47, 3.53, 11.73, 14.72, 4.04,
     {{0, 0.805}, {0.5, 0.848}, {1, 0.985}, {1.003, 1.903}, {1.5, 1.996}, {2, 2.805}}};
 constexpr TileTime kSplitTime[3] = {   // steps of four slabs, one per wavefront
     {2.18, 0.23, 0.27, 0.46, 0.08, 0, 0,
