@@ -255,7 +255,9 @@ __global__ __launch_bounds__(kAttnWaves * 64, D == 128 ? 2 : 3) void attention_m
   for (int i = 0; i < DB; ++i)
 #pragma unroll
     for (int e = 0; e < 16; ++e) oacc[i][e] = 0.f;
-  float m_run = -INFINITY, l_run = 0.f;        // reference in log2 units (already scaled), running sum
+  // reference in log2 units (already scaled), running sum.  The reference starts at the lowest finite value: where every
+  // score so far is -inf (products that overflow), a difference of two -inf would be NaN; so weights are 0 and nothing is lost.
+  float m_run = kLowest, l_run = 0.f;
   const float sc = rsqrtf((float)D) * kLog2e;  // raw score -> log2 units
 
   uint32_t koff[KS], voff[DB];   // this lane's operand reads: 16-byte vectors of the K tile, bytes of the V tile
@@ -349,7 +351,7 @@ __global__ __launch_bounds__(kAttnWaves * 64, D == 128 ? 2 : 3) void attention_m
       const auto o = __builtin_amdgcn_permlane32_swap(__float_as_uint(mx), __float_as_uint(mx), false, false);
       mx = fmaxf(__uint_as_float(o[0]), __uint_as_float(o[1]));
     }
-    const float m_new = fmaxf(m_run, mx * sc);   // finite from tile 0 on: key 0 <= every query (sc > 0)
+    const float m_new = fmaxf(m_run, mx * sc);
     const float corr = __builtin_amdgcn_exp2f(m_run - m_new);
     float psum[2] = {0.f, 0.f};
     vec8<E> pf[N][2];

@@ -73,3 +73,21 @@ def test_attention_blocks_in_groups(B, nh, d, dtype, padded):
     assert np.all(out[T] == 3.0), "row past T was written"
     for b in range(B):
         assert_close(out[cu[b]:cu[b + 1]], refs[b % len(kinds)], dtype, f"attention seq {b}", stages=2)
+
+
+# finite q and k whose product is -inf in fp32 (bf16 reaches 1e38) have weight 0 wherever they lie, also as the first tiles of a query
+@pytest.mark.parametrize("hidden", [range(64), range(200), [*range(16), *range(32, 160)], range(70, 140)])
+@pytest.mark.parametrize("d", [64, 128])
+def test_attention_scores_of_minus_infinity(hidden, d):
+    n, nh = 300, 2
+    A = nh * d
+    qkv = wl.round_to_dtype(np.random.default_rng(d).standard_normal((n, 3 * A)), wl.BF16)
+    qkv[:, :A], qkv[:, A:2 * A] = 2.0 ** 66, 0.0     # the other keys score 0: equal weights
+    qkv[list(hidden), A:2 * A] = -2.0 ** 66
+    out = torch.empty((n, A), dtype=torch.bfloat16, device="cuda")
+    cu = torch.tensor([0, n], dtype=torch.int32, device="cuda")
+    E.energon_attention(hz.to_device(qkv, wl.BF16), out, cu, 1, n, nh, d)
+    seen = np.array([any(j not in hidden for j in range(i + 1)) for i in range(n)])
+    blk = qkv.astype(np.float64)
+    ref = orc.masked_causal_attention(blk[:, :A], blk[:, A:2 * A], blk[:, 2 * A:], n, nh, d)
+    assert_close(hz.to_host(out)[seen], ref[seen], wl.BF16, "attention past scores of -inf", stages=2)
