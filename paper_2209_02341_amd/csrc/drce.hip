@@ -120,7 +120,8 @@ static hipError_t rebuild(const uint4* qkv, uint4* q, uint4* k, uint4* v, const 
                                                                                                      chunks);
     return hipGetLastError();
   }
-  // Too few workgroups for the chip: a quarter of the vectors per lane, four times as many wavefronts
+  // Too few workgroups for the chip: a quarter of the vectors per lane, four times as many wavefronts (1 x 64 positions x 4
+  // heads of 64: 3.2 -> 2.4 us)
   if (blocks(positions) < 256)
     rebuild_qkv_kernel<HV, kMoveVecs / 4><<<dim3((unsigned)blocks(positions / 4)), dim3(256), 0, s>>>(qkv, q, k, v, cu, S, nh, groups);
   else

@@ -951,7 +951,8 @@ size_t gemm_sched_scratch_bytes(int64_t M, int32_t N, int32_t K) {
 //   79 x 768 x 768 3.6 kSplit [7 kSmall]           387 x 3072 x 1024 9.7 kSmall [20 kSquare]     100000 x 192 x 768 61 kSmall [88 kWide]
 //   658 x 5120 x 5120 57 kSquare [92 kSmall]       533 x 6144 x 12288 133 kSquare [192 kWide]    600 x 15360 x 5120 136 kSquare [160 kWide]
 //   3000 x 4096 x 4160 126 kSquare [141 kWide]     8428 x 5120 x 5184 491 kSquare [547 kWide]    250 x 12288 x 4096 42 kWide [51 kSquare]
-// and with scratch: 515 x 2056 x 4096 + residual 26.3 kWide in parts [30.0 kSmall]   879 x 5120 x 20480 177 kPieces [283 kSquare]
+// and with scratch: 515 x 2056 x 4096 + residual 26.3 kWide in parts [30.0 kSmall]   333 x 5120 x 20480 96 kPieces [157 kSquare]
+//   928 x 5120 x 20480 179 kPieces [302 kSquare]
 // What bounds them is latency and idle CUs below a few hundred tiles, the L2 above: 128 x 256 tiles ask it for 48 KiB
 // per slab and CU, about 1 us at the 10-11 TB/s that it gives all CUs together; smaller tiles ask for more per flop but
 // fill the chip, and two on a CU hide each other's barriers; the parts of a K cut over workgroups cost their way to memory
