@@ -2,7 +2,7 @@
 // Sec. 4.3, keeps attention on the padded layout; here no padding is rebuilt inside a layer), on the
 // fp32 matrix instructions.
 //
-// One workgroup = (sequence, head, 16 queries); its 4 wavefronts take the key tiles of 16 in turn, each with
+// One workgroup = (sequence, head, 16 queries); its 4 wavefronts (1 where no sequence has more than one tile) take the key tiles of 16 in turn, each with
 // an online softmax of its own, and merge their four states through LDS at the end.  The path serves short
 // sequences of small models, so what bounds it is the chain of dependent loads, not arithmetic: cutting
 // the keys over wavefronts shortens the chain and a wavefront requests its next tile before it works on
@@ -22,16 +22,17 @@ namespace energon {
 
 namespace {
 
-constexpr int kAfWaves = 4, kAfQ = 16;
+constexpr int kAfQ = 16;
 
-template <int D>
-__global__ __launch_bounds__(kAfWaves * 64, 2) void attention_f32_kernel(const float* __restrict__ qkv,
+// WK = 4, or 1 for sequences of one tile at most, where there is nothing to cut
+template <int D, int WK>
+__global__ __launch_bounds__(WK * 64, 2) void attention_f32_kernel(const float* __restrict__ qkv,
                                                                         float* __restrict__ out,
                                                                         const int32_t* __restrict__ cu, int32_t nh) {
   constexpr int KC = D / 16;   // 16-element chunks of a K / Q row
   constexpr int U = D / 64;    // 64-element parts of a V row: one vector per lane each, four blocks of O^T
-  __shared__ float st_m[kAfWaves][kAfQ], st_l[kAfWaves][kAfQ];
-  __shared__ f32x4 st_o[kAfWaves][kAfQ][D / 4 + 1];   // rows padded by 16 bytes
+  __shared__ float st_m[WK][kAfQ], st_l[WK][kAfQ];
+  __shared__ f32x4 st_o[WK][kAfQ][D / 4 + 1];   // rows padded by 16 bytes
   const int32_t b = blockIdx.z, h = blockIdx.y;
   const int32_t c0 = cu[b], len = cu[b + 1] - c0;
   const int32_t q0 = ((int32_t)gridDim.x - 1 - (int32_t)blockIdx.x) * kAfQ;   // most keys first
@@ -49,7 +50,7 @@ __global__ __launch_bounds__(kAfWaves * 64, 2) void attention_f32_kernel(const f
 #pragma unroll
   for (int c = 0; c < KC; ++c) q[c] = *reinterpret_cast<const f32x4*>(qrow + 16 * c);
 
-  const int32_t n_tiles = q0 / 16 + 1;   // keys 0 .. q0 + 15, the last tile on the diagonal
+  const int32_t n_tiles = WK == 1 ? 1 : q0 / 16 + 1;   // keys 0 .. q0 + 15, the last tile on the diagonal
   f32x4 k4[KC], v4[4][U];
   auto load = [&](int32_t t) {   // keys past the end read the last row: they lie above the diagonal
     const float* kr = base + A + (size_t)min(16 * t + lr, len - 1) * ld + 4 * g;
@@ -73,7 +74,7 @@ __global__ __launch_bounds__(kAfWaves * 64, 2) void attention_f32_kernel(const f
     for (int j = 0; j < 4; ++j) o[u][j] = f32x4{0.f, 0.f, 0.f, 0.f};
 
   if (wave < n_tiles) load(wave);
-  for (int32_t t = wave; t < n_tiles; t += kAfWaves) {
+  for (int32_t t = wave; t < n_tiles; t += WK) {
     f32x4 kc[KC], vc[4][U];
 #pragma unroll
     for (int c = 0; c < KC; ++c) kc[c] = k4[c];
@@ -81,7 +82,7 @@ __global__ __launch_bounds__(kAfWaves * 64, 2) void attention_f32_kernel(const f
     for (int e = 0; e < 4; ++e)
 #pragma unroll
       for (int u = 0; u < U; ++u) vc[e][u] = v4[e][u];
-    if (t + kAfWaves < n_tiles) load(t + kAfWaves);
+    if (t + WK < n_tiles) load(t + WK);
     f32x4 s0 = f32x4{0.f, 0.f, 0.f, 0.f}, s1 = s0;   // two chains
 #pragma unroll
     for (int c = 0; c < KC; c += 2)
@@ -158,16 +159,16 @@ __global__ __launch_bounds__(kAfWaves * 64, 2) void attention_f32_kernel(const f
     for (int e = 0; e < 4; ++e)   // rows 4 g + e of blocks j = dd 64 u + 4 (4 g + e) + j
       st_o[wave][lr][16 * u + 4 * g + e] = f32x4{o[u][0][e], o[u][1][e], o[u][2][e], o[u][3][e]};
   __syncthreads();
-  for (int i = tid; i < kAfQ * (D / 4); i += kAfWaves * 64) {
+  for (int i = tid; i < kAfQ * (D / 4); i += WK * 64) {
     const int r = i / (D / 4), v = i % (D / 4);
     if (q0 + r >= len) break;   // rows ascend with i
     float M = st_m[0][r];
 #pragma unroll
-    for (int w = 1; w < kAfWaves; ++w) M = fmaxf(M, st_m[w][r]);
+    for (int w = 1; w < WK; ++w) M = fmaxf(M, st_m[w][r]);
     float L = 0.f;
     f32x4 acc = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int w = 0; w < kAfWaves; ++w) {
+    for (int w = 0; w < WK; ++w) {
       const float wgt = expf(st_m[w][r] - M);
       L += st_l[w][r] * wgt;
       acc += st_o[w][r][v] * wgt;
@@ -181,9 +182,13 @@ __global__ __launch_bounds__(kAfWaves * 64, 2) void attention_f32_kernel(const f
 hipError_t launch_attention_f32(const float* qkv, float* out, const int32_t* cu, int32_t B, int32_t max_len,
                                 int32_t nh, int32_t d, hipStream_t s) {
   if (B <= 0 || max_len <= 0) return hipSuccess;
-  const dim3 grid((unsigned)((max_len + kAfQ - 1) / kAfQ), (unsigned)nh, (unsigned)B), block(kAfWaves * 64);
-  if (d == 128) attention_f32_kernel<128><<<grid, block, 0, s>>>(qkv, out, cu, nh);
-  else attention_f32_kernel<64><<<grid, block, 0, s>>>(qkv, out, cu, nh);
+  const dim3 grid((unsigned)((max_len + kAfQ - 1) / kAfQ), (unsigned)nh, (unsigned)B);
+  // One tile of keys: three of four wavefronts would only take up registers (us, four / one; 5000 x 1 token x 4 heads of 64
+  // 60 / 25, 1000 x 16 x 12 60 / 41; but 8 of up to 128 tokens x 16 heads, cut over one, 8.0 / 10.9).
+  const bool one = max_len <= kAfQ;
+  const dim3 block(one ? 64 : 256);
+  if (d == 128) (one ? attention_f32_kernel<128, 1> : attention_f32_kernel<128, 4>)<<<grid, block, 0, s>>>(qkv, out, cu, nh);
+  else (one ? attention_f32_kernel<64, 1> : attention_f32_kernel<64, 4>)<<<grid, block, 0, s>>>(qkv, out, cu, nh);
   return hipGetLastError();
 }
 

@@ -62,7 +62,9 @@ def _attention(qkv, lens, nh, d):
     return out[:T], cu
 
 
-@pytest.mark.parametrize("lens,nh,d", [([1, 15, 16, 17, 0, 64, 65], 3, 64), ([129, 2, 80], 2, 128)])
+# the last two: one tile of keys at most, one wavefront
+@pytest.mark.parametrize("lens,nh,d", [([1, 15, 16, 17, 0, 64, 65], 3, 64), ([129, 2, 80], 2, 128), ([1, 15, 0, 16, 3], 3, 64),
+                                       ([2] * 70 + [16, 1], 2, 128)])
 def test_attention_f32(lens, nh, d):
     A = nh * d
     qkv = np.random.default_rng(d).standard_normal((sum(lens), 3 * A)).astype(np.float32)
@@ -78,8 +80,9 @@ def test_attention_f32(lens, nh, d):
         assert np.all(np.abs(out[cu[b]:cu[b + 1]] - ref) <= bound)
 
 
-def test_attention_f32_bad_token_reaches_later_tokens_only():
-    n, nh, d, bad = 40, 2, 64, 37
+@pytest.mark.parametrize("n,bad", [(40, 37), (14, 9)])
+def test_attention_f32_bad_token_reaches_later_tokens_only(n, bad):
+    nh, d = 2, 64
     A = nh * d
     qkv = np.random.default_rng(0).standard_normal((n, 3 * A)).astype(np.float32)
     clean, _ = _attention(qkv, [n], nh, d)
