@@ -197,7 +197,13 @@ hipError_t launch_gemm_f32(const float* x, const float* w, const float* bias, co
   //     600 x 4800 x 1600 (750) 98 / 103, 2048 x 2048 x 8192 (1024) 571 / 663;
   //   16 x 16 with eight wavefronts along a long K while every CU has at most one tile: 17 x 2048 x 8192
   //     15.7 against 20.0 with four.
+  //   K of two slabs at most: one wavefront, nothing to cut and no sums to meet: 32 x 32 8000 x 8000 x 4 104 against 263 (and 139 with
+  //     64 x 64), 2000 x 2000 x 64 14 / 22, 300000 x 20 x 16 19 / 40; 16 x 16 1000000 x 4 x 4 37 / 81, 300 x 300 x 16 2.6 / 2.8.
   const bool narrow = (M <= 16 || N <= 16) && fits(t16);
+  if (K <= 64) {
+    if (narrow || t32 < 168) return launch_cfg<1, 1, 1, 2>(x, w, bias, res, y, M, N, K, epi, s);
+    if (fits(t32)) return launch_cfg<2, 2, 1, 2>(x, w, bias, res, y, M, N, K, epi, s);
+  }
   if (!narrow && t32 >= 168) {
     const double k = K;
     const double us64 = std::ceil(t64 / 256.0) * (9.0 + 0.0155 * k);

@@ -24,8 +24,9 @@ U = 2.0 ** -24
 # a partial last slab, ragged rows and columns
 LINEAR = [(17, 20, 4), (16, 16, 100), (33, 68, 132), (5, 260, 2052), (250, 644, 36), (257, 1028, 64), (387, 1036, 92),
           (1403, 1412, 68),
-          # narrow sides take 16 x 16 however long the other is, the next wider 32 x 32; 64 x 64 from a longer K on
-          (5409, 16, 36), (9, 5412, 36), (5409, 20, 36), (1021, 1020, 1092)]
+          # narrow sides take 16 x 16 however long the other is, the next wider 32 x 32, each with one wavefront up to K = 64
+          # and with four beyond; 64 x 64 from a longer K on
+          (5409, 16, 36), (9, 5412, 64), (5409, 20, 36), (5409, 16, 68), (9, 5412, 100), (5409, 20, 68), (1021, 1020, 1092)]
 
 
 @pytest.mark.parametrize("M,N,K", LINEAR)
@@ -62,9 +63,9 @@ def _attention(qkv, lens, nh, d):
     return out[:T], cu
 
 
-# the last two: one tile of keys at most, one wavefront
+# from the third on one wavefront: one tile of keys at most, up to four of them in many workgroups
 @pytest.mark.parametrize("lens,nh,d", [([1, 15, 16, 17, 0, 64, 65], 3, 64), ([129, 2, 80], 2, 128), ([1, 15, 0, 16, 3], 3, 64),
-                                       ([2] * 70 + [16, 1], 2, 128)])
+                                       ([2] * 70 + [16, 1], 2, 128), ([64, 0, 17, 33, 1] * 60, 1, 64), ([50, 1, 64] * 50, 2, 128)])
 def test_attention_f32(lens, nh, d):
     A = nh * d
     qkv = np.random.default_rng(d).standard_normal((sum(lens), 3 * A)).astype(np.float32)
