@@ -2,7 +2,7 @@
 // Sec. 4.3, keeps attention on the padded layout; here no padding is rebuilt inside a layer), on the
 // fp32 matrix instructions.
 //
-// One workgroup = (sequence, head, 16 queries); its 4 wavefronts (1 where no sequence has more than one tile) take the key tiles of 16 in turn, each with
+// One workgroup = (sequence, head, 16 queries); its 4 wavefronts (1 where the tiles are few) take the key tiles of 16 in turn, each with
 // an online softmax of its own, and merge their four states through LDS at the end.  The path serves short
 // sequences of small models, so what bounds it is the chain of dependent loads, not arithmetic: cutting
 // the keys over wavefronts shortens the chain and a wavefront requests its next tile before it works on
@@ -24,8 +24,8 @@ namespace {
 
 constexpr int kAfQ = 16;
 
-// WK = 4, or 1 for sequences of one tile at most, where there is nothing to cut
-template <int D, int WK>
+// WK = 4 or 1; ONE: no sequence has more than one tile of keys
+template <int D, int WK, bool ONE>
 __global__ __launch_bounds__(WK * 64, 2) void attention_f32_kernel(const float* __restrict__ qkv,
                                                                         float* __restrict__ out,
                                                                         const int32_t* __restrict__ cu, int32_t nh) {
@@ -50,7 +50,7 @@ __global__ __launch_bounds__(WK * 64, 2) void attention_f32_kernel(const float* 
 #pragma unroll
   for (int c = 0; c < KC; ++c) q[c] = *reinterpret_cast<const f32x4*>(qrow + 16 * c);
 
-  const int32_t n_tiles = WK == 1 ? 1 : q0 / 16 + 1;   // keys 0 .. q0 + 15, the last tile on the diagonal
+  const int32_t n_tiles = ONE ? 1 : q0 / 16 + 1;   // keys 0 .. q0 + 15, the last tile on the diagonal
   f32x4 k4[KC], v4[4][U];
   auto load = [&](int32_t t) {   // keys past the end read the last row: they lie above the diagonal
     const float* kr = base + A + (size_t)min(16 * t + lr, len - 1) * ld + 4 * g;
@@ -183,13 +183,17 @@ hipError_t launch_attention_f32(const float* qkv, float* out, const int32_t* cu,
                                 int32_t nh, int32_t d, hipStream_t s) {
   if (B <= 0 || max_len <= 0) return hipSuccess;
   const dim3 grid((unsigned)((max_len + kAfQ - 1) / kAfQ), (unsigned)nh, (unsigned)B);
-  // One tile of keys: three of four wavefronts would only take up registers (us, four / one; 5000 x 1 token x 4 heads of 64
-  // 60 / 25, 1000 x 16 x 12 60 / 41; but 8 of up to 128 tokens x 16 heads, cut over one, 8.0 / 10.9).
-  const bool one = max_len <= kAfQ;
-  const dim3 block(one ? 64 : 256);
-  if (d == 128) (one ? attention_f32_kernel<128, 1> : attention_f32_kernel<128, 4>)<<<grid, block, 0, s>>>(qkv, out, cu, nh);
-  else (one ? attention_f32_kernel<64, 1> : attention_f32_kernel<64, 4>)<<<grid, block, 0, s>>>(qkv, out, cu, nh);
-  return hipGetLastError();
+  // Few tiles of keys in many workgroups: three of four wavefronts would mostly take up registers (us, four / one: 5000 x 1
+  // token x 4 heads of 64 60 / 23, 1000 x 17 x 12 105 / 64, 64 x 64 x 40 x 128 154 / 121; but 8 of up to 128 tokens x 16 heads
+  // 8.0 / 10.9, 4 of up to 32 x 4 3.7 / 4.4, one of 4096 81 / 272).
+  const auto launch = [&](auto kernel, int wavefronts) {
+    kernel<<<grid, dim3((unsigned)wavefronts * 64), 0, s>>>(qkv, out, cu, nh);
+    return hipGetLastError();
+  };
+  if (max_len <= kAfQ) return d == 128 ? launch(attention_f32_kernel<128, 1, true>, 1) : launch(attention_f32_kernel<64, 1, true>, 1);
+  if (max_len <= 4 * kAfQ && (int64_t)grid.x * nh * B >= 1024)
+    return d == 128 ? launch(attention_f32_kernel<128, 1, false>, 1) : launch(attention_f32_kernel<64, 1, false>, 1);
+  return d == 128 ? launch(attention_f32_kernel<128, 4, false>, 4) : launch(attention_f32_kernel<64, 4, false>, 4);
 }
 
 }  // namespace energon
