@@ -24,7 +24,7 @@
 // 4 us of dependent memory latencies (lengths, first rows, last stores) and 2 us between two workgroups of a slot.
 // Measured (bf16, d = 128, before -> now): 8 sequences of 1536 .. 2047 tokens x 40 heads 524 -> 403 us, 8 of 2048 582 -> 450,
 // 64 of very unequal length x 64 heads 734 -> 500, 32 of up to 512 x 40 94 -> 84, 64 of up to 64 x 40 29.1 -> 24.7;
-// d = 64: 8 long x 25 165 -> 133, 50 of up to 200 x 16 16.6 -> 13.6 (profiles/cases_kernel_stats.md).  Before, 8
+// d = 64: 8 long x 25 165 -> 133, 50 of up to 200 x 16 16.6 -> 13.6.  Before, 8
 // wavefronts of 16 queries read every operand from LDS twice as often and copied V into a transposed tile, with two
 // barriers per 64 keys.  Following the running max only when it had moved by a factor of 2^8 saves the rescaling and
 // another 10 %, but then the largest weight of a row is no longer exactly 1 and the error grows by a twentieth: not done.
