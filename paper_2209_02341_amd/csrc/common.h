@@ -257,9 +257,9 @@ hipError_t launch_fold_weights(const void* w, const void* b, const void* gamma, 
 hipError_t launch_row_stats(const void* x, int64_t M, int32_t K, float eps, int dtype, float* stats, hipStream_t s);
 hipError_t launch_merge_partials(const float* partial, int64_t M, int32_t P, float eps, float* stats, hipStream_t s);
 // attention_f32.hip / attention_mfma.hip
-hipError_t launch_attention_f32(const float* qkv, float* out, const int32_t* cu, int32_t B, int32_t max_len,
+// T: rows of qkv (>= cu[B]; bounds or shapes the launch, the work follows cu)
+hipError_t launch_attention_f32(const float* qkv, float* out, const int32_t* cu, int64_t T, int32_t B, int32_t max_len,
                                 int32_t nh, int32_t d, hipStream_t s);
-// T: rows of qkv (>= cu[B]; bounds the launch, the work follows cu)
 hipError_t launch_attention_bf16(const bf16_t* qkv, bf16_t* out, const int32_t* cu, int64_t T, int32_t B,
                                  int32_t max_len, int32_t nh, int32_t d, hipStream_t s);
 hipError_t launch_attention_f16(const f16_t* qkv, f16_t* out, const int32_t* cu, int64_t T, int32_t B,

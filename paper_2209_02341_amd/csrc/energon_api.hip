@@ -97,7 +97,7 @@ int attention_impl(const void* qkv, void* out, const int32_t* cu, int64_t T, int
   else if (dt == ENERGON_F16)
     HIP_TRY(launch_attention_f16((const f16_t*)qkv, (f16_t*)out, cu, T, B, max_len, nh, d, s));
   else
-    HIP_TRY(launch_attention_f32((const float*)qkv, (float*)out, cu, B, max_len, nh, d, s));
+    HIP_TRY(launch_attention_f32((const float*)qkv, (float*)out, cu, T, B, max_len, nh, d, s));
   return ENERGON_OK;
 }
 

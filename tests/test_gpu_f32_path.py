@@ -63,9 +63,11 @@ def _attention(qkv, lens, nh, d):
     return out[:T], cu
 
 
-# from the third on one wavefront: one tile of keys at most, up to four of them in many workgroups
+# from the third on one wavefront: one tile of keys at most, up to four of them in many workgroups, the last
+# two with a workgroup for all blocks of a (sequence, head)
 @pytest.mark.parametrize("lens,nh,d", [([1, 15, 16, 17, 0, 64, 65], 3, 64), ([129, 2, 80], 2, 128), ([1, 15, 0, 16, 3], 3, 64),
-                                       ([2] * 70 + [16, 1], 2, 128), ([64, 0, 17, 33, 1] * 60, 1, 64), ([50, 1, 64] * 50, 2, 128)])
+                                       ([2] * 70 + [16, 1], 2, 128), ([64, 0, 17, 33, 1] * 60, 1, 64), ([50, 1, 64] * 50, 2, 128),
+                                       ([1, 2, 0, 33, 1, 1] * 230, 2, 64), ([1] * 600 + [64, 17], 4, 128)])
 def test_attention_f32(lens, nh, d):
     A = nh * d
     qkv = np.random.default_rng(d).standard_normal((sum(lens), 3 * A)).astype(np.float32)
