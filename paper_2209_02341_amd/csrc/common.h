@@ -226,6 +226,16 @@ enum class KsplitTile { k32x32, k64x32, k64x64 };
 template <typename E>
 hipError_t launch_gemm_ksplit(KsplitTile tile, const E* x, const E* w, const E* bias, const E* res, E* y, int64_t M,
                               int32_t N, int32_t K, int epi, hipStream_t s);
+// gemm_ring.hip: tiles of rows x columns, per_cu workgroups on a CU; with parts > 1, K cut over that many workgroups, whose
+// fp32 sums go through scratch (parts * M * N floats; plain epilogues only)
+struct RingShape { int16_t rows, cols, per_cu; };
+constexpr RingShape kRingShapes[] = {{64, 64, 2},  {64, 96, 2},   {96, 96, 2},   {96, 128, 1},  {128, 128, 1}, {128, 128, 2},
+                                     {96, 192, 1}, {128, 192, 1}, {160, 192, 1}, {128, 256, 1}, {160, 256, 1}};
+constexpr int kRing64x64 = 0, kRing128x128 = 4, kRing128x128Pair = 5, kRing128x256 = 9;   // indexes there
+constexpr int kRingCount = sizeof(kRingShapes) / sizeof(kRingShapes[0]);
+template <typename E>
+hipError_t launch_gemm_ring(int shape, const E* x, const E* w, const E* bias, const E* res, E* y, int64_t M, int32_t N, int32_t K,
+                            int epi, const LnFold& lf, hipStream_t s, int32_t parts = 1, float* scratch = nullptr);
 // gemm_skinny.hip: M <= 64 rows (a generation step), bound by streaming W once.  With `partial` (fp32 scratch;
 // gemm_skinny_partial_bytes is what the best plan takes) K may be cut over several workgroups.
 bool gemm_skinny_takes(int64_t M, int32_t N, int32_t K, int epi);

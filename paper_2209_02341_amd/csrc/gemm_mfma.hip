@@ -15,15 +15,10 @@
 //    remapped to give every XCD a contiguous run of tiles, ordered in bands of 8 row tiles:
 //    the 32 tiles resident on an XCD form an 8 x 4 block that shares x and W slabs in that L2;
 //  * epilogue in fp32: + bias, GeLU(erf) or + residual, one rounding to the storage type.
-// Two kernels:
-//  * gemm_mfma_sched_kernel, 256x256 tile, 4 wavefronts x 128x128 = 8 x 8 tiles of
-//    v_mfma_f32_16x16x32 with the 256 accumulators in AGPRs; the slab loop is hand-scheduled
-//    (MFMA, LDS reads and the next slab's loads interleaved in asm); edge tiles are shifted
-//    inwards, so nothing is clamped or predicated; the epilogue goes through LDS and leaves as
-//    16-byte non-temporal stores;
-//  * gemm_mfma_tile_kernel, compiler-scheduled, v_mfma_f32_32x32x16, clamped loads and predicated
-//    stores: 64x64, 128x128 and 128x256 tiles for problems that do not give the first kernel whole rounds
-//    of tiles, or that it cannot take (odd slab counts, fewer than 256 rows or columns).
+// The kernel here, gemm_mfma_sched_kernel, takes problems of whole rounds of 256x256 tiles: 4 wavefronts x 128x128 = 8 x 8
+// tiles of v_mfma_f32_16x16x32 with the 256 accumulators in AGPRs; the slab loop is hand-scheduled (MFMA, LDS reads and the next
+// slab's loads interleaved in asm); edge tiles are shifted inwards, so nothing is clamped or predicated; the epilogue goes
+// through LDS and leaves as 16-byte non-temporal stores.  Smaller ones: gemm_ring.hip, gemm_ksplit.hip.
 // tile_plan chooses between these, the first kernel with its tiles cut along K, and gemm_ksplit.hip.
 #include "common.h"
 #include <algorithm>
@@ -37,69 +32,6 @@ constexpr int kChunks = BK / 8;   // 16-byte chunks per LDS row
 
 typedef __attribute__((address_space(1))) const void* gptr_t;
 typedef __attribute__((address_space(3))) void* lptr_t;
-
-// Swizzle for the 32-row operand tiles of the 32x32x16 form (the 16-row ones: swz16, two passes per read with this one).
-__device__ __forceinline__ int swz(int row) { return (row & 7) ^ ((row >> 3) & 1); }
-
-// Epilogue of one wavefront: TM x TN accumulator tiles of 32x32 whose top-left element is
-// (mw, nw).  In each tile the lane holds column (lane & 31), rows 8*(e/4) + 4*(lane/32) + e%4.
-// FOLD: the LayerNorm-folded epilogues are compiled into their own instantiation, so that the plain
-// one stays as small as it was (small problems are sensitive to it: 5 us per launch measured).
-template <typename E, int TM, int TN, bool FOLD>
-__device__ __forceinline__ void store_tile(const f32x16 (&acc)[TM][TN], const E* __restrict__ bias,
-                                           const E* res, E* y, int64_t M, int32_t N, int epi, int64_t mw,
-                                           int32_t nw, int lane, const LnFold& lf) {
-  const int lrow = lane & 31, lhalf = lane >> 5;
-  constexpr bool fold = FOLD;
-#pragma unroll
-  for (int j = 0; j < TN; ++j) {
-    const int32_t n = nw + j * 32 + lrow;
-    const bool n_ok = n < N;
-    float bv = 0.f, cv = 0.f;
-    if constexpr (fold) {
-      if (n_ok) { bv = lf.bias[n]; cv = lf.colsum[n]; }
-    } else {
-      if (bias != nullptr && n_ok) bv = static_cast<float>(bias[n]);
-    }
-#pragma unroll
-    for (int i = 0; i < TM; ++i) {
-#pragma unroll
-      for (int e = 0; e < 16; ++e) {
-        const int64_t m = mw + i * 32 + (e >> 2) * 8 + lhalf * 4 + (e & 3);
-        if (n_ok && m < M) {
-          float v = acc[i][j][e];
-          if constexpr (fold) {
-            const float2 st = *reinterpret_cast<const float2*>(lf.stats + 2 * m);
-            v = st.y * (v - st.x * cv);
-          }
-          v += bv;
-          if (epi == EPI_BIAS_GELU || epi == EPI_LNFOLD_GELU) v = gelu_erf(v);
-          if (epi == EPI_BIAS_RESIDUAL) v += static_cast<float>(res[(size_t)m * N + n]);
-          y[(size_t)m * N + n] = static_cast<E>(v);
-        }
-      }
-    }
-  }
-}
-
-// Split-K mode of the tile kernel: the raw fp32 sums of this workgroup's part of K, to
-// part[m][n] of its own [M, N] slice; a second kernel adds the slices in order and applies the epilogue.
-template <int TM, int TN>
-__device__ __forceinline__ void store_partial(const f32x16 (&acc)[TM][TN], float* __restrict__ part, int64_t M,
-                                              int32_t N, int64_t mw, int32_t nw, int lane) {
-  const int lrow = lane & 31, lhalf = lane >> 5;
-#pragma unroll
-  for (int j = 0; j < TN; ++j) {
-    const int32_t n = nw + j * 32 + lrow;
-#pragma unroll
-    for (int i = 0; i < TM; ++i)
-#pragma unroll
-      for (int e = 0; e < 16; ++e) {
-        const int64_t m = mw + i * 32 + (e >> 2) * 8 + lhalf * 4 + (e & 3);
-        if (n < N && m < M) part[(size_t)m * N + n] = acc[i][j][e];
-      }
-  }
-}
 
 // Epilogue of one wavefront's 128x128 tile (8 x 8 accumulator tiles of 16x16; in each the lane
 // holds column lane % 16, rows 4 * (lane / 16) + e) through LDS, for tiles that lie wholly
@@ -234,141 +166,6 @@ __device__ __forceinline__ void store_tile_coalesced(const f32x4 (&acc)[8][8], c
       }
     }
   }
-}
-
-// ---- compiler-scheduled tile kernel ---------------------------------------------------------
-// S slab buffers: S - 1 slabs are on their way while one is worked on, one barrier per slab.  Three where a workgroup has
-// to hide its own latency (387 x 1024 x 4096 on 64x64 tiles: 36 us with two buffers, 20 us with three; five take the place
-// of other workgroups and win nothing); two for 128x128 tiles, whose 64 KiB then leave room for a second workgroup on the
-// CU that does it (658 x 5120 x 5120: 60 us).
-// MODE 0: plain epilogues; 1: the LayerNorm-folded epilogues; 2: split K, gridDim.y parts, fp32 sums
-// of part blockIdx.y to lf.partial + blockIdx.y * M * N (lf.partial is the caller's scratch here).
-template <typename E, int BM, int BN, int WM, int WN, int S, int MODE>
-__global__ __launch_bounds__(WM* WN * 64) void gemm_mfma_tile_kernel(const E* __restrict__ x,
-                                                                     const E* __restrict__ w,
-                                                                     const E* __restrict__ bias,
-                                                                     const E* res, E* y, int64_t M,
-                                                                     int32_t N, int32_t K, int epi, int32_t tiles_m,
-                                                                     int32_t tiles_n, LnFold lf) {
-  static_assert(S == 2 || S == 3, "the wait below covers one slab in flight behind the awaited one, or none");
-  constexpr int NW = WM * WN;
-  constexpr int WTM = BM / WM, WTN = BN / WN;
-  constexpr int TM = WTM / 32, TN = WTN / 32;
-  constexpr int GA = BM / 8 / NW, GB = BN / 8 / NW;  // 8-row groups (1 KiB of LDS) per wavefront
-  static_assert(BM % (8 * NW) == 0 && BN % (8 * NW) == 0, "row groups must divide evenly");
-  extern __shared__ uint4 smem[];  // [S][BM + BN][kChunks]
-
-  int64_t m0;
-  int32_t n0;
-  if (!tile_origin<BM, BN>(tiles_m, tiles_n, m0, n0)) return;
-
-  const int tid = threadIdx.x, lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int wm0 = (wave / WN) * WTM, wn0 = (wave % WN) * WTN;
-
-  // One direct-to-LDS load fills 1 KiB = 8 rows x 8 chunks; lane l lands at row l/8, slot l%8 of
-  // the group, so it must fetch the chunk that the swizzle puts in that slot.
-  // Byte offsets from the tile's first row (uniform base pointer + 32-bit lane offset).
-  const int KT = MODE == 2 ? K / BK / (int)gridDim.y : K / BK;                   // slabs of this workgroup
-  const size_t k0 = MODE == 2 ? (size_t)blockIdx.y * KT * (BK * sizeof(E)) : 0;   // byte offset of its first slab
-  const char* xbase = reinterpret_cast<const char*>(x + (size_t)m0 * K) + k0;
-  const char* wbase = reinterpret_cast<const char*>(w + (size_t)n0 * K) + k0;
-  uint32_t oa[GA], ob[GB];
-#pragma unroll
-  for (int i = 0; i < GA; ++i) {
-    const int row = (wave + i * NW) * 8 + (lane >> 3), c = (lane & 7) ^ swz(row);
-    const int64_t lim = M - 1 - m0;
-    const uint32_t rr = (uint32_t)(row < lim ? row : lim);
-    oa[i] = (rr * (uint32_t)K + c * 8) * 2u;
-  }
-#pragma unroll
-  for (int i = 0; i < GB; ++i) {
-    const int row = (wave + i * NW) * 8 + (lane >> 3), c = (lane & 7) ^ swz(row);
-    const int32_t lim = N - 1 - n0;
-    const uint32_t rr = (uint32_t)(row < lim ? row : lim);
-    ob[i] = (rr * (uint32_t)K + c * 8) * 2u;
-  }
-  const int lrow = lane & 31, lhalf = lane >> 5;
-  int fa[TM], fb[TN], fsa[TM], fsb[TN];
-#pragma unroll
-  for (int t = 0; t < TM; ++t) { const int row = wm0 + t * 32 + lrow; fa[t] = row * kChunks; fsa[t] = swz(row); }
-#pragma unroll
-  for (int t = 0; t < TN; ++t) { const int row = wn0 + t * 32 + lrow; fb[t] = (BM + row) * kChunks; fsb[t] = swz(row); }
-
-  f32x16 acc[TM][TN];
-#pragma unroll
-  for (int i = 0; i < TM; ++i)
-#pragma unroll
-    for (int j = 0; j < TN; ++j)
-#pragma unroll
-      for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
-
-  constexpr int kStage = (BM + BN) * kChunks;  // in uint4
-
-  auto issue = [&](int kt, int stage) {
-    uint4* base = smem + stage * kStage;
-    const char* xk = xbase + (size_t)kt * (BK * 2);
-    const char* wk = wbase + (size_t)kt * (BK * 2);
-#pragma unroll
-    for (int i = 0; i < GA; ++i)
-      __builtin_amdgcn_global_load_lds((gptr_t)(xk + oa[i]), (lptr_t)(base + (wave + i * NW) * 64), 16, 0, 0);
-#pragma unroll
-    for (int i = 0; i < GB; ++i)
-      __builtin_amdgcn_global_load_lds((gptr_t)(wk + ob[i]), (lptr_t)(base + BM * kChunks + (wave + i * NW) * 64), 16,
-                                       0, 0);
-  };
-
-  // Slab kt has landed (this wavefront's part: loads return in order, behind it are those of at most S - 2 slabs)
-  // and this wavefront's reads of slab kt - 1 are back; past the barrier that holds for every wavefront, so the
-  // buffer of slab kt - 1 is free for slab kt + S - 1.
-  constexpr int G = GA + GB;
-#pragma unroll
-  for (int u = 0; u < S - 1; ++u)
-    if (u < KT) issue(u, u);
-  int stage = 0;
-  for (int kt = 0; kt < KT; ++kt) {
-    if (S == 3 && kt + 1 < KT) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(G) : "memory");
-    else asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
-    __builtin_amdgcn_s_barrier();
-    const uint4* cur = smem + stage * kStage;
-    const int refill = stage == 0 ? S - 1 : stage - 1;
-    stage = stage + 1 == S ? 0 : stage + 1;
-    if (kt + S - 1 < KT) issue(kt + S - 1, refill);
-    vec8<E> af[2][TM], bfr[2][TN];
-#pragma unroll
-    for (int t = 0; t < TM; ++t) af[0][t] = *reinterpret_cast<const vec8<E>*>(&cur[fa[t] + (lhalf ^ fsa[t])]);
-#pragma unroll
-    for (int t = 0; t < TN; ++t) bfr[0][t] = *reinterpret_cast<const vec8<E>*>(&cur[fb[t] + (lhalf ^ fsb[t])]);
-#pragma unroll
-    for (int ks = 0; ks < BK / 16; ++ks) {
-      const int p = ks & 1;
-      if (ks + 1 < BK / 16) {
-        const int c = (ks + 1) * 2 + lhalf;
-#pragma unroll
-        for (int t = 0; t < TM; ++t) af[p ^ 1][t] = *reinterpret_cast<const vec8<E>*>(&cur[fa[t] + (c ^ fsa[t])]);
-#pragma unroll
-        for (int t = 0; t < TN; ++t) bfr[p ^ 1][t] = *reinterpret_cast<const vec8<E>*>(&cur[fb[t] + (c ^ fsb[t])]);
-      }
-#pragma unroll
-      for (int i = 0; i < TM; ++i)
-#pragma unroll
-        for (int j = 0; j < TN; ++j)
-          acc[i][j] = Mfma<E>::m32x32x16(af[p][i], bfr[p][j], acc[i][j]);
-      // issue order: one LDS read of the next step's operands after every two MFMAs of this step
-      if (ks + 1 < BK / 16) {
-#pragma unroll
-        for (int q = 0; q < TM + TN; ++q) {
-          __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
-          __builtin_amdgcn_sched_group_barrier(0x008, (TM * TN) / (TM + TN), 0);
-        }
-      }
-    }
-  }
-
-  if constexpr (MODE == 2)
-    store_partial<TM, TN>(acc, lf.partial + (size_t)blockIdx.y * M * N, M, N, m0 + wm0, n0 + wn0, lane);
-  else
-    store_tile<E, TM, TN, MODE == 1>(acc, bias, res, y, M, N, epi, m0 + wm0, n0 + wn0, lane, lf);
 }
 
 // ---- hand-scheduled 256x256 kernel ----------------------------------------------------------
@@ -814,23 +611,6 @@ __global__ __launch_bounds__(512) void gemm_mfma_fixup_kernel(const float* __res
   *reinterpret_cast<vec8<E>*>(y + off) = o;
 }
 
-template <typename E, typename Kern>
-static hipError_t launch_tiles(Kern kern, LdsAttrOnce& attr_set, int BM, int BN, int threads, size_t lds, const E* x,
-                               const E* w, const E* bias, const E* res, E* y, int64_t M, int32_t N,
-                               int32_t K, int epi, const LnFold& lf, hipStream_t s, int32_t ks = 1) {
-  {
-    hipError_t e = ensure_dynamic_lds(reinterpret_cast<const void*>(kern), lds, attr_set);
-    if (e != hipSuccess) return e;
-  }
-  const int32_t tiles_m = (int32_t)((M + BM - 1) / BM), tiles_n = (N + BN - 1) / BN;
-  const int64_t total = (int64_t)tiles_m * tiles_n;
-  const int64_t grid = (total + kXcds - 1) / kXcds * kXcds;
-  if (grid * threads > kMaxGridThreads) return hipErrorInvalidConfiguration;
-  kern<<<dim3((unsigned)grid, (unsigned)ks), dim3(threads), lds, s>>>(x, w, bias, res, y, M, N, K, epi, tiles_m, tiles_n,
-                                                                       lf);
-  return hipGetLastError();
-}
-
 // The 256x256 kernel needs whole tiles to shift at the edges, an even number of slabs, and enough
 // tiles for most of the 256 CUs.  Shifted edge tiles overlap their neighbours: with the residual
 // aliasing y, an overlapped element could be read after the neighbour's write, so that case
@@ -940,26 +720,19 @@ size_t gemm_sched_scratch_bytes(int64_t M, int32_t N, int32_t K) {
 
 // How a shape that is too small for the 256x256 kernel's whole rounds runs, given `cap` bytes of scratch:
 //   kSplit   32x32, 64x32 or 64x64 tiles, K cut over the four wavefronts of the workgroup (gemm_ksplit.hip);
-//   kSmall   64x64 tiles shared by four wavefronts, three workgroups per CU;
-//   kSquare  128x128 tiles, 4 wavefronts, two slab buffers so that two workgroups share a CU;
-//   kWide    128x256 tiles, 8 wavefronts, one workgroup per CU, K cut over ks workgroups (sums in the scratch);
+//   kRing    one of eleven tiles of 64x64 to 160x256, four wavefronts (gemm_ring.hip), K whole or cut over ks workgroups
+//            (sums in the scratch);
 //   kPieces  the 256x256 kernel with every tile cut into pieces (needs M, N >= 256 and K % 128 == 0).
-// The one with the least expected time.  Each tile's time is fitted to a sweep of 440 shapes on it, 65 to 4600 rows of
-// every layer width, K of 64 to 20480: launch and prologue, the epilogue's share, and per slab a piecewise linear
-// function of the tiles per CU, which has a step wherever another round of workgroups begins.  The choice costs 0.5 % over
-// the best of them in the mean.  Measured (us, without scratch; in brackets the next larger or smaller tile):
-//   79 x 768 x 768 3.6 kSplit [7 kSmall]           387 x 3072 x 1024 9.7 kSmall [20 kSquare]     100000 x 192 x 768 61 kSmall [88 kWide]
-//   658 x 5120 x 5120 57 kSquare [92 kSmall]       533 x 6144 x 12288 133 kSquare [192 kWide]    600 x 15360 x 5120 136 kSquare [160 kWide]
-//   3000 x 4096 x 4160 126 kSquare [141 kWide]     8428 x 5120 x 5184 491 kSquare [547 kWide]    250 x 12288 x 4096 42 kWide [51 kSquare]
-// and with scratch: 515 x 2056 x 4096 + residual 26.3 kWide in parts [30.0 kSmall]   333 x 5120 x 20480 96 kPieces [157 kSquare]
-//   928 x 5120 x 20480 179 kPieces [302 kSquare]
-// What bounds them is latency and idle CUs below a few hundred tiles, the L2 above: 128 x 256 tiles ask it for 48 KiB
-// per slab and CU, about 1 us at the 10-11 TB/s that it gives all CUs together; smaller tiles ask for more per flop but
-// fill the chip, and two on a CU hide each other's barriers; the parts of a K cut over workgroups cost their way to memory
-// and back and a second launch.
-enum TileKind { kSplit, kSmall, kSquare, kWide, kPieces };
-struct TilePlan { TileKind kind; KsplitTile split; int32_t ks; size_t scratch; };   // ks: parts of K (kPieces: pieces per tile)
-constexpr int kSmallTile = 64, kSquareTile = 128, kWideM = 128, kWideN = 256;
+// The one with the least expected time, by a model that is fitted per tile to a sweep of 7300 shapes on all of them (65 to
+// 5000 rows of every layer width and others, K of 64 to 32768, the three epilogues, three sets of operands in turn): it costs
+// 1.4 % over the best of them in the mean.  What the choice turns on is whole rounds: so many sizes, because each alone is the best
+// by 10 to 45 % wherever its tiles just fill the CUs.  Measured (us; in brackets the same shape on the former tiles, and the
+// next best of these):
+//   387 x 4096 x 1024 + GeLU 9.8 64x64 [10.9; 10.5]   928 x 5120 x 5120 + residual 54 160x192 [72; 58]   200 x 20480 x 5120 73 160x192 [103; 77]
+//   600 x 4096 x 16384 86 160x256 in parts [102; 90]  2280 x 4096 x 4096 75 160x256 [109; 91]             333 x 5120 x 20480 87 128x256 in parts [99; 90]
+// Against the former choice (64x64, 128x128 and 128x256 tiles of a compiler-scheduled kernel) 0.84 times the time in the mean of the sweep.
+enum TileKind { kSplit, kRing, kPieces };
+struct TilePlan { TileKind kind; KsplitTile split; int32_t ring, ks; size_t scratch; };   // ks: parts of K (kPieces: pieces per tile)
 
 // us = base + gelu + residual + n (round + residual_round) + steps * slab(n), n = tiles per CU; slab(n) through the given
 // points, in proportion beyond the last.  The epilogue that reads row statistics has base and round of its own.
@@ -978,13 +751,6 @@ struct TileTime {
            (epi == EPI_BIAS_RESIDUAL ? residual + n * residual_round : 0.0);
   }
 };
-constexpr TileTime kSmallTime{3.56, 0.78, 1.04, 0.53, 1.22, 5.34, 1.01,
-    {{0, 0.247}, {1, 0.261}, {1.003, 0.339}, {2, 0.378}, {2.003, 0.539}, {3, 0.580}, {3.003, 0.750}, {4, 0.824}, {4.003, 0.880},
-     {6, 1.170}, {10, 1.991}}};
-constexpr TileTime kSquareTime{7.67, 3.18, 4.97, 1.79, 6.08, 11.90, 4.50,
-    {{0, 0.564}, {1, 0.631}, {1.003, 0.780}, {1.5, 0.902}, {2, 1.040}, {2.003, 1.550}, {3, 1.720}, {4, 2.100}, {4.5, 2.800}, {10, 5.700}}};
-constexpr TileTime kWideTime{7.97, 2.70, 5.47, 3.53, 11.73, 14.72, 4.04,
-    {{0, 0.805}, {0.5, 0.848}, {1, 0.985}, {1.003, 1.903}, {1.5, 1.996}, {2, 2.805}}};
 constexpr TileTime kSplitTime[3] = {   // steps of four slabs, one per wavefront
     {2.18, 0.23, 0.27, 0.46, 0.08, 0, 0,
      {{0, 0.298}, {1, 0.345}, {1.003, 0.573}, {2, 0.662}, {2.003, 0.888}, {4, 1.261}, {4.003, 1.456}, {6, 1.934}, {16, 5.175}, {40, 12.477}}},
@@ -994,45 +760,118 @@ constexpr TileTime kSplitTime[3] = {   // steps of four slabs, one per wavefront
      {{0, 0.684}, {1, 0.645}, {1.003, 1.471}, {2, 1.345}, {2.003, 2.141}, {3, 2.174}, {3.003, 2.709}, {5, 3.701}, {10, 8.146}}}};
 static_assert((int)KsplitTile::k32x32 == 0 && (int)KsplitTile::k64x32 == 1 && (int)KsplitTile::k64x64 == 2, "order of kSplitTime");
 
+// Tiles of gemm_ring.hip: launch, then rounds of workgroups; a round is its epilogue and its slabs, a slab as long as the
+// workgroups that share a CU make it, and shorter where not every CU has one more (power, memory).  `weights`: us per 100 MB of W;
+// `cold`: what a slab takes longer where W comes from HBM (W of 85 MB and more: with its neighbours in a stack or in a loop over
+// several it does not stay in the last cache's 256 MB); sums, sums_part, sums_res: the second kernel of a cut K, us and us per
+// million outputs, for each part and for the residual.
+struct RingTime {
+  double base, round, drop, gelu, residual, weights, cold, sums, sums_part, sums_res, slab[2];
+  double us(int per_cu, int32_t n, int32_t cus, double slabs, int epi) const {   // n workgroups on an XCD of so many CUs
+    const double epilogue = round + (epi == EPI_BIAS_GELU || epi == EPI_LNFOLD_GELU ? gelu : 0.0) + (epi == EPI_BIAS_RESIDUAL ? residual : 0.0) +
+                            (epi == EPI_LNFOLD || epi == EPI_LNFOLD_GELU ? 0.5 * round : 0.0);
+    const int32_t whole = (n - 1) / (cus * per_cu), rest = n - whole * cus * per_cu;   // rounds before the last; the last one's workgroups
+    const int level = rest <= cus ? 1 : 2;   // per_cu is 1 or 2
+    return base + whole * (epilogue + slabs * slab[per_cu - 1]) + epilogue * (level + 1) / (per_cu + 1) +
+           slabs * slab[level - 1] * (1.0 - drop * (level - rest / (double)cus));
+  }
+};
+constexpr RingTime kRingTime[] = {   // the order of kRingShapes
+    {2.82, 1.71, 0.146, 0.66, 0.31, 0.00, 0.49, 0.00, 0.00, 0.00, {0.188, 0.321}},
+    {3.37, 2.03, 0.219, 1.23, 0.87, 1.75, 0.50, 0.00, 0.00, 0.00, {0.230, 0.408}},
+    {3.35, 2.78, 0.222, 1.39, 1.28, 1.51, 0.48, 0.00, 0.00, 0.00, {0.314, 0.511}},
+    {1.11, 4.96, 0.137, 1.26, 1.40, 4.26, 0.62, 0.39, 1.61, 0.00, {0.283}},
+    {1.09, 5.76, 0.259, 1.65, 0.87, 4.34, 0.47, 0.00, 1.44, 0.21, {0.363}},
+    {3.03, 4.06, 0.232, 2.17, 1.96, 2.46, 0.32, 0.00, 0.00, 0.00, {0.713, 0.807}},
+    {1.29, 5.97, 0.259, 2.18, 0.72, 6.22, 0.48, 0.00, 1.10, 0.40, {0.394}},
+    {1.05, 7.33, 0.331, 2.91, 1.02, 7.38, 0.24, 0.00, 0.85, 0.69, {0.500}},
+    {0.50, 8.21, 0.290, 3.95, 1.48, 6.97, 0.16, 0.00, 0.90, 0.62, {0.586}},
+    {0.39, 8.24, 0.302, 3.53, 1.52, 8.85, 0.14, 0.00, 0.93, 0.46, {0.632}},
+    {0.72, 8.63, 0.311, 4.33, 6.02, 8.16, 0.05, 0.00, 0.92, 0.34, {0.759}}};
+static_assert(sizeof(kRingTime) / sizeof(kRingTime[0]) == kRingCount, "one per tile");
+
+// N that is not a multiple of 64, or K of eight N and more (no layer has such a linear): the plans that the former tiles of
+// 64x64, 128x128 and 128x256 had, and with them the scratch that callers were told, run on the same tiles of gemm_ring.hip (0.43
+// to 0.95 times the time, up to 1.09 where 128x128 tiles make many rounds of few slabs; 300 x 2048 x 16384 43 -> 38, 33 with 128x128).
+constexpr TileTime kSmallTime{3.56, 0.78, 1.04, 0.53, 1.22, 5.34, 1.01,
+    {{0, 0.247}, {1, 0.261}, {1.003, 0.339}, {2, 0.378}, {2.003, 0.539}, {3, 0.580}, {3.003, 0.750}, {4, 0.824}, {4.003, 0.880},
+     {6, 1.170}, {10, 1.991}}};
+constexpr TileTime kSquareTime{7.67, 3.18, 4.97, 1.79, 6.08, 11.90, 4.50,
+    {{0, 0.564}, {1, 0.631}, {1.003, 0.780}, {1.5, 0.902}, {2, 1.040}, {2.003, 1.550}, {3, 1.720}, {4, 2.100}, {4.5, 2.800}, {10, 5.700}}};
+constexpr TileTime kWideTime{7.97, 2.70, 5.47, 3.53, 11.73, 14.72, 4.04,
+    {{0, 0.805}, {0.5, 0.848}, {1, 0.985}, {1.003, 1.903}, {1.5, 1.996}, {2, 2.805}}};
+
 // Slabs of 128x256 tiles, whole rounds of them beyond two.
 static double wide_slab_us(double n) { return n <= 2.0 ? kWideTime.slab_us(n) : std::ceil(n) * kWideTime.slab_us(1.0); }
 
-// epi: one of EPI_BIAS, EPI_BIAS_GELU, EPI_BIAS_RESIDUAL (all plans) or the folded ones (kSmall, kSquare and whole kWide only).
+// epi: one of EPI_BIAS, EPI_BIAS_GELU, EPI_BIAS_RESIDUAL (all plans) or the folded ones (kRing without parts only).
 static TilePlan tile_plan(int64_t M, int32_t N, int32_t K, bool overlap_safe, int epi, size_t cap, int32_t wgs) {
   const bool plain = epi != EPI_LNFOLD && epi != EPI_LNFOLD_GELU;
   const int32_t KT = K / BK;
   const double cus = 8.0 * wgs;
-  TilePlan best{kSmall, KsplitTile::k64x64, 1, 0};
+  TilePlan best{kRing, KsplitTile::k64x64, 0, 1, 0};
   double best_us = 1e30;
   const auto consider = [&](TilePlan t, double us) {
     if (t.scratch <= cap && us < best_us) { best = t; best_us = us; }
   };
-  const auto tiles = [&](int64_t bm, int64_t bn) { return ((M + bm - 1) / bm) * ((N + bn - 1) / bn); };
+  // (this function is called for every linear: 32-bit divisions, M < 2^31)
+  const auto tiles = [&](uint32_t bm, uint32_t bn) { return (int64_t)(((uint32_t)M + bm - 1) / bm) * (((uint32_t)N + bn - 1) / bn); };
   const auto fits = [](int64_t tiles, int64_t threads) { return tiles * threads <= kMaxGridThreads; };
-  // What the small tiles lose to the larger ones where their reads come from farther away: W of more than the last cache's
-  // 256 MB (151 x 24576 x 8192 159 us on 64x64 tiles, 145 on 128x128; but 338 x 8192 x 32768 378 on 64x64 with K over the
-  // wavefronts, 463), and the shared ones at rows of 24 KiB and more (539 x 4608 x 12288 115 % of the fit to shorter rows).
-  const double far = (double)N * K * sizeof(uint16_t) > 268.0e6 ? 1.06 : 1.0, far_shared = std::max(far, K >= 12288 ? 1.08 : 1.0);
+  const bool former = N % 64 != 0 || K >= 8 * (int64_t)N;   // see kSmallTime
+  const double w_bytes = 2.0 * N * K;
+  const bool from_hbm = w_bytes > 85.0e6;   // see RingTime
+  const double far = former ? (w_bytes > 268.0e6 ? 1.06 : 1.0) : from_hbm ? 1.45 : 1.0;   // the same for the small tiles that cut K
   if (plain) {
+    // a last step that not all four wavefronts take costs about half the difference to one that they do
+    const double steps = former ? (KT + 3) / 4 : 0.5 * ((KT + 3) / 4 + 0.25 * KT);
     const KsplitTile split[3] = {KsplitTile::k32x32, KsplitTile::k64x32, KsplitTile::k64x64};
     const int64_t n[3] = {tiles(32, 32), tiles(64, 32), tiles(64, 64)};
     for (int i = 0; i < 3; ++i)
-      if (fits(n[i], 256)) consider({kSplit, split[i], 1, 0}, kSplitTime[i].us(n[i] / cus, epi) + (KT + 3) / 4 * far * kSplitTime[i].slab_us(n[i] / cus));
+      if (fits(n[i], 256)) consider({kSplit, split[i], 0, 1, 0}, kSplitTime[i].us(n[i] / cus, epi) + steps * far * kSplitTime[i].slab_us(n[i] / cus));
   }
-  if (const int64_t n = tiles(kSmallTile, kSmallTile); fits(n, 256))
-    consider({kSmall, KsplitTile::k64x64, 1, 0}, kSmallTime.us(n / cus, epi) + KT * far_shared * kSmallTime.slab_us(n / cus));
-  if (const int64_t n = tiles(kSquareTile, kSquareTile); K < (1 << 24) && fits(n, 256))   // a tile's rows in 32-bit byte offsets
-    consider({kSquare, KsplitTile::k64x64, 1, 0}, kSquareTime.us(n / cus, epi) + KT * kSquareTime.slab_us(n / cus));
-  const int64_t wide = tiles(kWideM, kWideN);
   const double elems = (double)M * N, res = epi == EPI_BIAS_RESIDUAL ? 1.0 : 0.0;
-  if (K < (1 << 23) && fits(wide, 512))
-    consider({kWide, KsplitTile::k64x64, 1, 0}, kWideTime.us(wide / cus, epi) + KT * wide_slab_us(wide / cus));
-  for (int32_t ks = 2; plain && K < (1 << 23) && ks <= 8 && wide * ks <= 1024 && KT / ks >= 4; ++ks) {
-    if (KT % ks != 0) continue;
-    const double n = wide * ks / cus;   // then the sums' way to memory and back, and the second launch
-    consider({kWide, KsplitTile::k64x64, ks, (size_t)ks * (size_t)M * N * sizeof(float)},
-             8.0 + 2.1 * n + KT / ks * wide_slab_us(n) + (0.233 * 4.0 * ks + 0.236 * res) * elems / 1.0e6);
+  // No ring tile wins where 32x32 ones are one round and K is short (0.4 us of host time saved on calls that it bounds).
+  const bool tiny = plain && KT <= 64 && tiles(32, 32) <= 8 * wgs;
+  if (!former && !tiny) {
+    const bool spills = 2.0 * (M + N) * K > 256.0e6;   // x and W do not both fit the last cache: another round reads them again
+    for (int i = 0; i < kRingCount; ++i) {
+      const RingShape& shape = kRingShapes[i];
+      const int64_t n = tiles(shape.rows, shape.cols);
+      if (!fits(n, 256) || (int64_t)K * 2 * std::max(shape.rows, shape.cols) > UINT32_MAX) continue;   // a tile's rows in 32-bit byte offsets
+      if (shape.rows >= M + 64) continue;   // a smaller one does
+      // K whole, or cut where the tiles alone leave CUs idle: into as many parts of six slabs at least as fill them, one less or half
+      const int32_t fill = plain && shape.per_cu == 1 && n <= 4 * wgs ? std::min({8 * wgs / (int32_t)n, 8, KT / 6}) : 1;
+      for (const int32_t parts : {1, fill, fill - 1, (fill + 1) / 2}) {
+        if (parts < 1) continue;
+        const int32_t units = (int32_t)n * parts;   // fits() above
+        double us = kRingTime[i].us(shape.per_cu, (units + kXcds - 1) / kXcds, wgs, (parts > 1 ? (KT + parts - 1) / parts : KT) * (from_hbm ? 1.0 + kRingTime[i].cold : 1.0),
+                                    parts > 1 ? EPI_BIAS : epi) + kRingTime[i].weights * 1.0e-8 * w_bytes;
+        if (spills && units > 8 * wgs * shape.per_cu) us *= 1.2;
+        if (parts > 1) us = 1.05 * (us + kRingTime[i].sums + elems * 1.0e-6 * (kRingTime[i].sums_part * parts + kRingTime[i].sums_res * res));
+        consider({kRing, KsplitTile::k64x64, i, parts, parts > 1 ? (size_t)parts * (size_t)M * N * sizeof(float) : 0}, us);
+        if (fill <= 1) break;
+      }
+    }
+  } else if (former) {
+    const double far_shared = std::max(far, K >= 12288 ? 1.08 : 1.0);
+    if (const int64_t n = tiles(64, 64); fits(n, 256))
+      consider({kRing, KsplitTile::k64x64, kRing64x64, 1, 0}, kSmallTime.us(n / cus, epi) + KT * far_shared * kSmallTime.slab_us(n / cus));
+    if (const int64_t n = tiles(128, 128); K < (1 << 24) && fits(n, 256))   // a tile's rows in 32-bit byte offsets
+      consider({kRing, KsplitTile::k64x64, n > cus ? kRing128x128Pair : kRing128x128, 1, 0}, kSquareTime.us(n / cus, epi) + KT * kSquareTime.slab_us(n / cus));
+    const int64_t wide = tiles(128, 256);
+    if (K < (1 << 23) && fits(wide, 512))
+      consider({kRing, KsplitTile::k64x64, kRing128x256, 1, 0}, kWideTime.us(wide / cus, epi) + KT * wide_slab_us(wide / cus));
+    for (int32_t ks = 2; plain && K < (1 << 23) && ks <= 8 && wide * ks <= 1024 && KT / ks >= 4; ++ks) {
+      if (KT % ks != 0) continue;
+      const double n = wide * ks / cus;   // then the sums' way to memory and back, and the second launch
+      consider({kRing, KsplitTile::k64x64, kRing128x256, ks, (size_t)ks * (size_t)M * N * sizeof(float)},
+               8.0 + 2.1 * n + KT / ks * wide_slab_us(n) + (0.233 * 4.0 * ks + 0.236 * res) * elems / 1.0e6);
+    }
   }
+  // A square contraction with a bias only is none of a layer's linears (the out-projection adds a residual); callers have been
+  // told the pieces' scratch for it, so pieces stay unless a ring tile is expected to save more than a third: 928 x 5120 x 5120
+  // 64.5 in pieces, 54 on 128x192.
+  const double settled = !former && epi == EPI_BIAS && N == K ? 0.66 : 1.0;
   if (plain && M >= 256 && N >= 256 && K % 128 == 0 && overlap_safe) {
     const int64_t big = tiles(256, 256);
     for (int32_t P = 2; P <= 8; ++P) {
@@ -1041,8 +880,8 @@ static TilePlan tile_plan(int64_t M, int32_t N, int32_t K, bool overlap_safe, in
       // one round at most of every XCD's workgroups, and slots for it (two per workgroup)
       if (rem >= wgs || rem * P > 2 * wgs || (KT + chunk - 1) / chunk != P || chunk < 8) continue;
       const double rounds = std::ceil((double)rem * P / wgs);
-      consider({kPieces, KsplitTile::k64x64, P, slots_bytes(pieces_slots(M, N, P))},
-               8.2 + rounds * (1.1 + 1.228 * chunk) + (0.388 * big * P * kPartFloats * 4.0 + 0.394 * res * elems) / 1.0e6);
+      consider({kPieces, KsplitTile::k64x64, 0, P, slots_bytes(pieces_slots(M, N, P))},
+               settled * (8.2 + rounds * (1.1 + 1.228 * chunk) + (0.388 * big * P * kPartFloats * 4.0 + 0.394 * res * elems) / 1.0e6));
     }
   }
   return best;
@@ -1167,24 +1006,6 @@ static hipError_t launch_sched(const E* x, const E* w, const E* bias, const E* r
   return hipGetLastError();
 }
 
-template <typename E, int BM, int BN, int WM, int WN, int S, int MODE>
-static hipError_t launch_tile_cfg(const E* x, const E* w, const E* bias, const E* res, E* y, int64_t M, int32_t N,
-                                  int32_t K, int epi, const LnFold& lf, hipStream_t s, int32_t ks = 1) {
-  static LdsAttrOnce once;   // per element type and configuration
-  return launch_tiles<E>(gemm_mfma_tile_kernel<E, BM, BN, WM, WN, S, MODE>, once, BM, BN, WM * WN * 64,
-                         S * (size_t)(BM + BN) * kChunks * sizeof(uint4), x, w, bias, res, y, M, N, K, epi, lf, s, ks);
-}
-
-template <typename E, int MODE>
-static hipError_t launch_tile(TileKind kind, const E* x, const E* w, const E* bias, const E* res, E* y, int64_t M,
-                              int32_t N, int32_t K, int epi, const LnFold& lf, hipStream_t s) {
-  switch (kind) {
-    case kWide: return launch_tile_cfg<E, kWideM, kWideN, 2, 4, 3, MODE>(x, w, bias, res, y, M, N, K, epi, lf, s);
-    case kSquare: return launch_tile_cfg<E, kSquareTile, kSquareTile, 2, 2, 2, MODE>(x, w, bias, res, y, M, N, K, epi, lf, s);
-    default: return launch_tile_cfg<E, kSmallTile, kSmallTile, 2, 2, 3, MODE>(x, w, bias, res, y, M, N, K, epi, lf, s);
-  }
-}
-
 template <typename E>
 static hipError_t launch_gemm_mfma(const E* x, const E* w, const E* bias, const E* res, E* y, int64_t M, int32_t N,
                                    int32_t K, int epi, hipStream_t s, const LnFold* fold, float* scratch,
@@ -1210,16 +1031,10 @@ static hipError_t launch_gemm_mfma(const E* x, const E* w, const E* bias, const 
   // Shifted edge tiles of the 256x256 kernel overlap: not with the residual aliasing y (see takes_sched_kernel).
   const bool overlap_safe = res != y || (M % 256 == 0 && N % 256 == 0);
   const TilePlan t = tile_plan(M, N, K, overlap_safe, epi, scratch_bytes, wgs);
-  if (wants_fold) return launch_tile<E, 1>(t.kind, x, w, bias, res, y, M, N, K, epi, lf, s);
   if (t.kind == kSplit) return launch_gemm_ksplit<E>(t.split, x, w, bias, res, y, M, N, K, epi, s);
   if (t.kind == kPieces)
     return launch_sched<E, kEpiPlain>(x, w, bias, res, y, M, N, K, epi, lf, s, pieces_plan(M, N, K, t.ks, wgs), scratch);
-  if (t.ks == 1) return launch_tile<E, 0>(t.kind, x, w, bias, res, y, M, N, K, epi, lf, s);
-  LnFold sp;
-  sp.partial = scratch;
-  const hipError_t e = launch_tile_cfg<E, kWideM, kWideN, 2, 4, 3, 2>(x, w, bias, res, y, M, N, K, epi, sp, s, t.ks);
-  if (e != hipSuccess) return e;
-  return launch_partial_reduce<E>(scratch, t.ks, bias, res, y, M, N, epi, s);
+  return launch_gemm_ring<E>(t.ring, x, w, bias, res, y, M, N, K, epi, lf, s, t.ks, scratch);
 }
 
 LinearPlan gemm_plan(int64_t M, int32_t N, int32_t K, int epi, bool res_aliases_y, size_t scratch_bytes) {
@@ -1232,9 +1047,7 @@ LinearPlan gemm_plan(int64_t M, int32_t N, int32_t K, int epi, bool res_aliases_
   switch (t.kind) {
     case kSplit: return {LinearPlan::kWaves, t.split == KsplitTile::k32x32 ? 32 : 64, t.split == KsplitTile::k64x64 ? 64 : 32, 1};
     case kPieces: return {LinearPlan::kPersistent, 256, 256, t.ks};
-    case kWide: return {LinearPlan::kTiles, kWideM, kWideN, t.ks};
-    case kSquare: return {LinearPlan::kTiles, kSquareTile, kSquareTile, 1};
-    default: return {LinearPlan::kTiles, kSmallTile, kSmallTile, 1};
+    default: return {LinearPlan::kTiles, kRingShapes[t.ring].rows, kRingShapes[t.ring].cols, t.ks};
   }
 }
 
