@@ -197,6 +197,10 @@ hipError_t launch_layernorm(const void* x, const void* gamma, const void* beta, 
 // gemm_f32.hip / gemm_mfma.hip (16-bit element types on the matrix cores)
 hipError_t launch_gemm_f32(const float* x, const float* w, const float* bias, const float* res, float* y,
                            int64_t M, int32_t N, int32_t K, int epi, hipStream_t s);
+// u = LayerNorm(x) and y = epilogue(u W^T + b) in one launch, for the shapes that gemm_f32_takes_ln says (EPI_BIAS, EPI_BIAS_GELU)
+bool gemm_f32_takes_ln(int64_t M, int32_t N, int32_t K);
+hipError_t launch_gemm_f32_ln(const float* x, const float* gamma, const float* beta, float eps, float* u, const float* w,
+                              const float* bias, float* y, int64_t M, int32_t N, int32_t K, int epi, hipStream_t s);
 // true if the launch for this shape can fill LnFold::partial (else the caller takes the statistics itself)
 bool gemm_emits_row_partials(int64_t M, int32_t N, int32_t K, bool res_aliases_y);
 // scratch (optional, 256-byte aligned): room for fp32 sums where K is cut over workgroups.  What is used of it is

@@ -161,9 +161,20 @@ int layer_impl(const EnergonLayerConfig* cfg, const EnergonLayerWeights* w, cons
 #define MARK(i) do { if (ev) HIP_TRY(hipEventRecord(ev[i], s)); } while (0)
 #define STEP(call) do { st = (call); if (st != ENERGON_OK) return st; } while (0)
   MARK(0);
-  HIP_TRY(launch_layernorm(x, w->ln1_g, w->ln1_b, u, T, H, cfg->ln_eps, dt, s));
-  MARK(1);
-  STEP(linear_impl(u, w->w_qkv, w->b_qkv, nullptr, qkv, T, 3 * A, H, ENERGON_EPI_BIAS, dt, s, nullptr, gs, gs_bytes));
+  // a small fp32 linear normalises its rows itself (not where the stages are timed apart)
+  const auto normalised_linear = [&](const void* in, const void* g, const void* b, void* norm, const void* wt, const void* bias, void* out,
+                                     int32_t N, int32_t epi, int mark) -> int {
+    if (dt == ENERGON_F32 && !ev && gemm_f32_takes_ln(T, N, H)) {
+      HIP_TRY(launch_gemm_f32_ln(static_cast<const float*>(in), static_cast<const float*>(g), static_cast<const float*>(b), cfg->ln_eps,
+                                 static_cast<float*>(norm), static_cast<const float*>(wt), static_cast<const float*>(bias),
+                                 static_cast<float*>(out), T, N, H, epi, s));
+      return ENERGON_OK;
+    }
+    HIP_TRY(launch_layernorm(in, g, b, norm, T, H, cfg->ln_eps, dt, s));
+    MARK(mark);
+    return linear_impl(norm, wt, bias, nullptr, out, T, N, H, epi, dt, s, nullptr, gs, gs_bytes);
+  };
+  STEP(normalised_linear(x, w->ln1_g, w->ln1_b, u, w->w_qkv, w->b_qkv, qkv, 3 * A, ENERGON_EPI_BIAS, 1));
   MARK(2);
   if (T > 0 && padws == nullptr) {
     STEP(attention_impl(qkv, att, cu, T, B, max_len, cfg->n_heads, cfg->head_dim, dt, s));
@@ -179,9 +190,7 @@ int layer_impl(const EnergonLayerConfig* cfg, const EnergonLayerWeights* w, cons
   MARK(3);
   STEP(linear_impl(att, w->w_o, w->b_o, x, y1, T, H, A, ENERGON_EPI_BIAS_RESIDUAL, dt, s, nullptr, gs, gs_bytes));
   MARK(4);
-  HIP_TRY(launch_layernorm(y1, w->ln2_g, w->ln2_b, wn, T, H, cfg->ln_eps, dt, s));
-  MARK(5);
-  STEP(linear_impl(wn, w->w_fc1, w->b_fc1, nullptr, m, T, F, H, ENERGON_EPI_BIAS_GELU, dt, s, nullptr, gs, gs_bytes));
+  STEP(normalised_linear(y1, w->ln2_g, w->ln2_b, wn, w->w_fc1, w->b_fc1, m, F, ENERGON_EPI_BIAS_GELU, 5));
   MARK(6);
   STEP(linear_impl(m, w->w_fc2, w->b_fc2, y1, y, T, H, F, ENERGON_EPI_BIAS_RESIDUAL, dt, s, nullptr, gs, gs_bytes));
   MARK(7);

@@ -28,12 +28,73 @@ namespace {
 typedef __attribute__((address_space(1))) const void* f32_gptr_t;
 typedef __attribute__((address_space(3))) void* f32_lptr_t;
 
+// LayerNorm of the x rows on their way into a linear: gain, offset, and where the normalised rows go as well
+struct LnRows {
+  const float *gamma, *beta;
+  float eps;
+  float* u;
+};
+constexpr int kLnMaxK = 512;   // of a row: a wavefront holds it in registers, gain and offset lie in LDS
+
+// Rows m0 .. m0 + 15 of x normalised as layernorm_kernel does it (two passes over a row in registers): a row per wavefront at a
+// time.  Mean and 1 / deviation to st, gain and offset to gb; with `write` the normalised rows to ln.u.
+template <int WK>
+__device__ __forceinline__ void ln_rows(const float* __restrict__ x, const LnRows& ln, int64_t m0, int64_t M, int32_t K, bool write,
+                                        int wave, int lane, float2* st, f32x4* gb) {
+  constexpr int V = kLnMaxK / 256;
+  const int32_t vecs = K / 4;   // K % 4 == 0
+  for (int32_t c = wave * 64 + lane; c < vecs; c += WK * 64) {
+    gb[c] = reinterpret_cast<const f32x4*>(ln.gamma)[c];
+    gb[kLnMaxK / 4 + c] = reinterpret_cast<const f32x4*>(ln.beta)[c];
+  }
+  constexpr int R = 16 / WK;
+  f32x4 v[R][V];
+#pragma unroll
+  for (int r = 0; r < R; ++r) {   // all rows requested before the first is summed
+    const int64_t m = m0 + wave * R + r;
+    const f32x4* row = reinterpret_cast<const f32x4*>(x + (size_t)(m < M ? m : M - 1) * K);
+#pragma unroll
+    for (int i = 0; i < V; ++i) v[r][i] = lane + 64 * i < vecs ? row[lane + 64 * i] : f32x4{0.f, 0.f, 0.f, 0.f};
+  }
+  const float inv = 1.0f / (float)K;
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    float sum = 0.f, sq = 0.f;
+#pragma unroll
+    for (int i = 0; i < V; ++i) sum += (v[r][i][0] + v[r][i][1]) + (v[r][i][2] + v[r][i][3]);
+    const float mean = wave_sum(sum) * inv;
+#pragma unroll
+    for (int i = 0; i < V; ++i)
+      if (lane + 64 * i < vecs) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) sq += (v[r][i][e] - mean) * (v[r][i][e] - mean);
+      }
+    const float rstd = rsqrtf(wave_sum(sq) * inv + ln.eps);
+    if (lane == 0) st[wave * R + r] = make_float2(mean, rstd);
+    const int64_t m = m0 + wave * R + r;
+    if (write && m < M) {
+      f32x4* out = reinterpret_cast<f32x4*>(ln.u + (size_t)m * K);
+#pragma unroll
+      for (int i = 0; i < V; ++i) {
+        const int32_t c = lane + 64 * i;
+        if (c < vecs) {
+          const f32x4 g = reinterpret_cast<const f32x4*>(ln.gamma)[c], b = reinterpret_cast<const f32x4*>(ln.beta)[c];
+          out[c] = (v[r][i] - mean) * rstd * g + b;
+        }
+      }
+    }
+  }
+}
+
 // TN x TM tiles of 16 x 16 (columns x rows of y) per workgroup, WK wavefronts along K, kDepth slabs in flight each.
-template <int TM, int TN, int WK, int kDepth>
+// LN: the x rows are normalised on the way (a launch of its own costs 3 to 4 us, of which the work is a fraction): every
+// workgroup takes the statistics of its 16 rows while its first slabs are on their way, and the operands as they leave LDS.
+template <int TM, int TN, int WK, int kDepth, bool LN = false>
 __global__ __launch_bounds__(WK * 64) void gemm_f32_kernel(const float* __restrict__ x, const float* __restrict__ w,
                                                           const float* __restrict__ bias, const float* res, float* y,
                                                           int64_t M, int32_t N, int32_t K, int epi, int32_t tiles_m,
-                                                          int32_t tiles_n) {
+                                                          int32_t tiles_n, LnRows ln) {
+  static_assert(!LN || TM == 1, "16 rows of statistics");
   using Cfg = WaveRings<TM, TN, WK, kDepth>;
   constexpr int G = 2 * (TM + TN);   // 1 KiB loads (8 rows x 128 bytes) per slab
   extern __shared__ f32x4 lds[];
@@ -91,6 +152,15 @@ __global__ __launch_bounds__(WK * 64) void gemm_f32_kernel(const float* __restri
   for (int h = 0; h < 2; ++h) foff[h] = (uint32_t)(lrow * 8 + ((4 * h + lq) ^ swz16(lrow)));
 
   for (int32_t u = 0; u < kDepth && u < ns; ++u) issue(u, u);
+  __shared__ float2 ln_st[LN ? 16 : 1];
+  __shared__ f32x4 ln_gb[LN ? kLnMaxK / 2 : 1];
+  float mean = 0.f, rstd = 0.f;
+  if constexpr (LN) {
+    ln_rows<WK>(x, ln, m0, M, K, n0 == 0, wave, lane, ln_st, ln_gb);
+    __syncthreads();
+    mean = ln_st[lrow].x;
+    rstd = ln_st[lrow].y;
+  }
   int32_t slot = 0;
   for (int32_t i = 0; i < ns; ++i) {
     // loads return in order; behind slab i's are those of the next kDepth - 1 slabs while they all exist
@@ -105,6 +175,13 @@ __global__ __launch_bounds__(WK * 64) void gemm_f32_kernel(const float* __restri
       for (int t = 0; t < TN; ++t) wb[h][t] = slab[t * 128 + foff[h]];
 #pragma unroll
       for (int t = 0; t < TM; ++t) xa[h][t] = slab[(TN + t) * 128 + foff[h]];
+    }
+    if constexpr (LN) {
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        const int32_t c = min((wave + i * WK) * 8 + 4 * h + lq, K / 4 - 1);   // past K: zeros below
+        xa[h][0] = (xa[h][0] - mean) * rstd * ln_gb[c] + ln_gb[kLnMaxK / 4 + c];
+      }
     }
     if (left < 32) {
 #pragma unroll
@@ -387,20 +464,20 @@ hipError_t launch_split(const float* x, const float* w, const float* bias, const
   return hipGetLastError();
 }
 
-template <int TM, int TN, int WK, int kDepth>
+template <int TM, int TN, int WK, int kDepth, bool LN = false>
 hipError_t launch_cfg(const float* x, const float* w, const float* bias, const float* res, float* y, int64_t M,
-                      int32_t N, int32_t K, int epi, hipStream_t s) {
+                      int32_t N, int32_t K, int epi, hipStream_t s, const LnRows& ln = {}) {
   constexpr int BM = 16 * TM, BN = 16 * TN;
   constexpr size_t lds = WaveRings<TM, TN, WK, kDepth>::kLds;
   static_assert(lds <= 160 * 1024, "LDS of a CU");
-  auto kern = gemm_f32_kernel<TM, TN, WK, kDepth>;
+  auto kern = gemm_f32_kernel<TM, TN, WK, kDepth, LN>;
   static LdsAttrOnce once;
   hipError_t e = ensure_dynamic_lds(reinterpret_cast<const void*>(kern), lds, once);
   if (e != hipSuccess) return e;
   const int32_t tiles_m = (int32_t)((M + BM - 1) / BM), tiles_n = (N + BN - 1) / BN;
   const int64_t grid = ((int64_t)tiles_m * tiles_n + kXcds - 1) / kXcds * kXcds;
   if (grid * WK * 64 > kMaxGridThreads) return hipErrorInvalidConfiguration;
-  kern<<<dim3((unsigned)grid), dim3(WK * 64), lds, s>>>(x, w, bias, res, y, M, N, K, epi, tiles_m, tiles_n);
+  kern<<<dim3((unsigned)grid), dim3(WK * 64), lds, s>>>(x, w, bias, res, y, M, N, K, epi, tiles_m, tiles_n, ln);
   return hipGetLastError();
 }
 
@@ -448,6 +525,20 @@ hipError_t launch_split_tile(const float* x, const float* w, const float* bias, 
 }
 
 }  // namespace
+
+// Where the linear runs on 16 x 16 tiles and four wavefronts, at most two of them per CU, and rows are short: every workgroup reads
+// its 16 rows once more and normalises them for itself.  77 rows, 256 / 768 / 1024 wide: the step 41 -> 33.5 us; but 40 rows,
+// 1024 / 3072 / 4096 wide, with 576 and 768 workgroups: 40 -> 48.5.
+bool gemm_f32_takes_ln(int64_t M, int32_t N, int32_t K) {
+  return M > 0 && N > 16 && K > 64 && K <= kLnMaxK && ((M + 15) / 16) * ((N + 15) / 16) <= 512 &&
+         (M <= 16 || ((M + 31) / 32) * ((N + 31) / 32) < 168);
+}
+
+hipError_t launch_gemm_f32_ln(const float* x, const float* gamma, const float* beta, float eps, float* u, const float* w,
+                              const float* bias, float* y, int64_t M, int32_t N, int32_t K, int epi, hipStream_t s) {
+  if (!gemm_f32_takes_ln(M, N, K) || epi == EPI_BIAS_RESIDUAL) return hipErrorInvalidValue;
+  return launch_cfg<1, 1, 4, 2, true>(x, w, bias, nullptr, y, M, N, K, epi, s, LnRows{gamma, beta, eps, u});
+}
 
 hipError_t launch_gemm_f32(const float* x, const float* w, const float* bias, const float* res, float* y, int64_t M,
                            int32_t N, int32_t K, int epi, hipStream_t s) {

@@ -1,0 +1,46 @@
+"""A small fp32 layer, whose linears normalise their rows themselves: ragged row tiles, one row, the widest and the next wider
+hidden size (which takes launches of its own), against the oracle; the normalised rows are left in the workspace as before."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import energon_oracle as orc
+from paper_2209_02341_amd import binding as E
+from paper_2209_02341_amd import harness as hz
+from paper_2209_02341_amd import workloads as wl
+
+pytestmark = pytest.mark.gpu
+U = 2.0 ** -24
+
+
+@pytest.mark.parametrize("lens,H,nh,F", [([1], 128, 2, 512), ([17, 3, 13], 256, 4, 1024), ([5, 11], 512, 8, 1024), ([16, 33], 68, 1, 260),
+                                         ([9, 4], 576, 9, 640), ([40, 31, 1], 256, 4, 300)])
+def test_small_f32_layer(lens, H, nh, F):
+    w = wl.Workload("small_ln", wl.F32, 1, H, nh, 64, F, len(lens), max(lens), "uniform", 0, max(lens))
+    lens = np.asarray(lens, np.int32)
+    T, A = int(lens.sum()), nh * 64
+    rng = np.random.default_rng(H + T)
+    p = wl.random_small_layer(rng, H, nh, 64, F)   # gain around 1, an offset
+    x = rng.normal(1.0, 2.0, (T, H)).astype(np.float32)   # a mean far from zero
+    cfg = hz.layer_config(H, nh, 64, F, wl.F32, w.ln_eps)
+    layer = hz.DeviceLayer(p, wl.F32)
+    cu = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    ws = torch.full((E.energon_workspace_bytes(cfg, T),), 255, dtype=torch.uint8, device="cuda")
+    y = torch.full((T + 1, H), 3.0, device="cuda")
+    E.energon_layer_forward(cfg, layer.struct, hz.to_device(x, wl.F32), y[:T], T, torch.from_numpy(cu).cuda(), lens, int(lens.max()), ws)
+    assert torch.all(y[T] == 3.0), "row past T was written"
+    off = E.energon_workspace_layout(cfg, T)
+    f32 = lambda slot, n: hz.to_host(ws[off[slot]: off[slot] + T * n * 4].view(torch.float32).view(T, n))
+    d = {k: None if v is None else np.asarray(v, np.float64) for k, v in p.items()}
+    # LayerNorm: sums of H terms, the deviation's root, four roundings; gain and offset of order one
+    u = orc.layer_norm(x.astype(np.float64), d["ln1_g"], d["ln1_b"], w.ln_eps)
+    assert np.abs(f32(E.WS_U, H) - u).max() <= (H + 16) * U * np.abs(u).max()
+    qkv = orc.linear(u, d["w_qkv"], d["b_qkv"])
+    bound = (2 * H + 32) * U * (np.abs(u).max() * np.abs(d["w_qkv"]).sum(1).max() + np.abs(d["b_qkv"]).max())
+    assert np.abs(f32(E.WS_QKV, 3 * A) - qkv).max() <= bound
+    y1 = f32(E.WS_Y1, H).astype(np.float64)
+    wn = orc.layer_norm(y1, d["ln2_g"], d["ln2_b"], w.ln_eps)
+    assert np.abs(f32(E.WS_W, H) - wn).max() <= (H + 16) * U * np.abs(wn).max()
+    m = orc.gelu(orc.linear(wn, d["w_fc1"], d["b_fc1"]))
+    bound = 1.13 * (2 * H + 32) * U * (np.abs(wn).max() * np.abs(d["w_fc1"]).sum(1).max() + np.abs(d["b_fc1"]).max()) + 1.3e-7
+    assert np.abs(f32(E.WS_M, F) - m).max() <= bound + 8 * U * np.abs(m).max()
