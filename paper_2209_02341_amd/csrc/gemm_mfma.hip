@@ -732,7 +732,7 @@ size_t gemm_sched_scratch_bytes(int64_t M, int32_t N, int32_t K) {
 //   600 x 4096 x 16384 86 160x256 in parts [102; 90]  2280 x 4096 x 4096 75 160x256 [109; 91]             333 x 5120 x 20480 87 128x256 in parts [99; 90]
 // Against the former choice (64x64, 128x128 and 128x256 tiles of a compiler-scheduled kernel) 0.84 times the time in the mean of the sweep.
 enum TileKind { kSplit, kRing, kPieces };
-struct TilePlan { TileKind kind; KsplitTile split; int32_t ring, ks; size_t scratch; };   // ks: parts of K (kPieces: pieces per tile)
+struct TilePlan { TileKind kind; KsplitTile split; int32_t ring, ks; size_t scratch; double us; };   // ks: parts of K (kPieces: pieces per tile)
 
 // us = base + gelu + residual + n (round + residual_round) + steps * slab(n), n = tiles per CU; slab(n) through the given
 // points, in proportion beyond the last.  The epilogue that reads row statistics has base and round of its own.
@@ -809,10 +809,9 @@ static TilePlan tile_plan(int64_t M, int32_t N, int32_t K, bool overlap_safe, in
   const bool plain = epi != EPI_LNFOLD && epi != EPI_LNFOLD_GELU;
   const int32_t KT = K / BK;
   const double cus = 8.0 * wgs;
-  TilePlan best{kRing, KsplitTile::k64x64, 0, 1, 0};
-  double best_us = 1e30;
+  TilePlan best{kRing, KsplitTile::k64x64, 0, 1, 0, 1e30};
   const auto consider = [&](TilePlan t, double us) {
-    if (t.scratch <= cap && us < best_us) { best = t; best_us = us; }
+    if (t.scratch <= cap && us < best.us) { best = t; best.us = us; }
   };
   // (this function is called for every linear: 32-bit divisions, M < 2^31)
   const auto tiles = [&](uint32_t bm, uint32_t bn) { return (int64_t)(((uint32_t)M + bm - 1) / bm) * (((uint32_t)N + bn - 1) / bn); };
@@ -885,6 +884,36 @@ static TilePlan tile_plan(int64_t M, int32_t N, int32_t K, bool overlap_safe, in
     }
   }
   return best;
+}
+
+// The persistent kernel takes what gives it 192 tiles, but up to some 400 of them are one or two rounds with much of the last one
+// empty, and a ring tile can fill its own better: expected times of both, the persistent kernel's fitted to 1100 shapes of 192
+// to 420 tiles.  Taken where the ring kernel is expected to need under 0.87 of the time: a quarter of the shapes, 0.97 of the time in
+// the mean of all, 0.91 for 257 to 330 tiles (3074 x 5120 x 1280 + residual 75 -> 53 us, 306 x 24576 x 8192 195 -> 134); between that
+// and 1 the two come out as they may (0.97: a sixth of all shapes more than 3 % slower).
+static double sched_us(const SchedPlan& p, int64_t M, int32_t N, int epi) {
+  const double slab = 1.47, epilogue = 9.26 + (epi == EPI_BIAS_GELU ? 6.1 : 0.0) + (epi == EPI_BIAS_RESIDUAL ? 4.43 : 0.0);
+  double worst = 0;
+  int32_t cut = 0;
+  for (int32_t x = 0; x < kXcds; ++x) {
+    const XcdShare s = xcd_share(p, x);
+    const int32_t full = s.n_tiles / p.wgs, rem = s.n_tiles - full * p.wgs;
+    double t = full * (epilogue + p.kt * slab);
+    if (p.pieces > 1) {
+      t += (rem * p.pieces + p.wgs - 1) / p.wgs * (s.chunk * slab + 5.32);
+      cut += rem;
+    } else if (rem > 0) {
+      t += epilogue + p.kt * slab * (1.0 - 0.452 * (1.0 - rem / (double)p.wgs));
+    }
+    worst = t > worst ? t : worst;
+  }
+  const double second = p.pieces > 1 ? 0.349e-6 * cut * p.pieces * (kPartFloats * 4.0) + (epi == EPI_BIAS_RESIDUAL ? 0.202e-6 * M * N : 0.0) : 0.0;
+  return 1.15 + worst + second;
+}
+static bool ring_instead(int64_t M, int32_t N, int32_t K, int epi, const SchedPlan& p, TilePlan& t) {
+  if ((int64_t)p.tiles_m * p.tiles_n >= 420 || N % 64 != 0) return false;
+  t = tile_plan(M, N, K, true, epi, 0, p.wgs);
+  return t.kind == kRing && t.us < 0.87 * sched_us(p, M, N, epi);
 }
 
 static SchedPlan pieces_plan(int64_t M, int32_t N, int32_t K, int32_t pieces, int32_t wgs) {
@@ -1026,6 +1055,8 @@ static hipError_t launch_gemm_mfma(const E* x, const E* w, const E* bias, const 
     const SchedPlan plan = sched_plan(M, N, K, plain && scratch_bytes >= sched_scratch_bytes(wgs), wgs);
     if (wants_fold) return launch_sched<E, kEpiFolded>(x, w, bias, res, y, M, N, K, epi, lf, s, plan, nullptr);
     if (!plain) return launch_sched<E, kEpiResidualStats>(x, w, bias, res, y, M, N, K, epi, lf, s, plan, nullptr);
+    TilePlan t;
+    if (ring_instead(M, N, K, epi, plan, t)) return launch_gemm_ring<E>(t.ring, x, w, bias, res, y, M, N, K, epi, lf, s);
     return launch_sched<E, kEpiPlain>(x, w, bias, res, y, M, N, K, epi, lf, s, plan, scratch);
   }
   // Shifted edge tiles of the 256x256 kernel overlap: not with the residual aliasing y (see takes_sched_kernel).
@@ -1041,8 +1072,12 @@ LinearPlan gemm_plan(int64_t M, int32_t N, int32_t K, int epi, bool res_aliases_
   if (gemm_skinny_takes(M, N, K, epi)) return gemm_skinny_plan_of(M, N, K, scratch_bytes);
   const bool plain = epi != EPI_LNFOLD && epi != EPI_LNFOLD_GELU;
   const int32_t wgs = sched_wgs_per_xcd();
-  if (takes_sched_kernel(M, N, K, res_aliases_y))
-    return {LinearPlan::kPersistent, 256, 256, sched_plan(M, N, K, plain && scratch_bytes >= sched_scratch_bytes(wgs), wgs).pieces};
+  if (takes_sched_kernel(M, N, K, res_aliases_y)) {
+    const SchedPlan p = sched_plan(M, N, K, plain && scratch_bytes >= sched_scratch_bytes(wgs), wgs);
+    TilePlan t;
+    if (plain && ring_instead(M, N, K, epi, p, t)) return {LinearPlan::kTiles, kRingShapes[t.ring].rows, kRingShapes[t.ring].cols, 1};
+    return {LinearPlan::kPersistent, 256, 256, p.pieces};
+  }
   const TilePlan t = tile_plan(M, N, K, !res_aliases_y || (M % 256 == 0 && N % 256 == 0), epi, scratch_bytes, wgs);
   switch (t.kind) {
     case kSplit: return {LinearPlan::kWaves, t.split == KsplitTile::k32x32 ? 32 : 64, t.split == KsplitTile::k64x64 ? 64 : 32, 1};

@@ -78,3 +78,11 @@ FOLDED = [(1127, 4160, 64, wl.BF16, True, (128, 128, 1)), (2289, 1024, 128, wl.F
 def test_ring_tiles_ln_folded(M, N, K, dtype, gelu, tile):
     assert E.energon_linear_plan(M, N, K, GELU if gelu else BIAS, ln_folded=True) == (2,) + tile
     folded.test_linear_ln_folded_matches_layernorm_then_linear(M, N, K, dtype, gelu)
+
+
+# shapes of 192 and more tiles of 256 x 256 that the ring kernel is expected to finish well before the persistent one
+@pytest.mark.parametrize("M,N,K,dtype,epi,tile", [(260, 24832, 256, wl.BF16, BIAS, (96, 96, 1)),
+                                                     (303, 24576, 1024, wl.F16, BIAS, (160, 192, 1))])
+def test_ring_tiles_instead_of_the_persistent_kernel(M, N, K, dtype, epi, tile):
+    assert E.energon_linear_plan(M, N, K, epi, ln_folded=True)[0] == 3   # folded linears stay there
+    test_ring_tiles(M, N, K, dtype, epi, tile)
