@@ -51,7 +51,7 @@ typedef enum {
 } energon_status;
 
 typedef enum {
-  ENERGON_F32 = 0,  /* fp32 storage, fp32 arithmetic (vector ALU)                        */
+  ENERGON_F32 = 0,  /* fp32 storage, fp32 sums of products exact to 24 bits              */
   ENERGON_BF16 = 1, /* bf16 storage, MFMA with fp32 accumulation, fp32 epilogues         */
   ENERGON_F16 = 2   /* fp16 storage (the paper's precision, Sec. 5.1), otherwise as bf16 */
 } energon_dtype;
@@ -243,8 +243,8 @@ int energon_linear_plan_selfcheck(int64_t M, int32_t N, int32_t K, int32_t workg
 
 /* Host only: how a 16-bit linear of this shape runs, given scratch_bytes of scratch (0: none).  epilogue as in
  * energon_linear; ln_folded != 0: as energon_linear_ln_folded (ENERGON_EPI_BIAS or _GELU); in_place != 0: the residual is y.
- * plan: [0] the kernel: 0 few rows (W streamed once), 1 small tiles with K over the wavefronts, 2 tiles of 64x64, 128x128 or
- * 128x256, 3 persistent 256x256 tiles; [1], [2] rows and columns of an output tile; [3] parts that K is cut into (for
+ * plan: [0] the kernel: 0 few rows (W streamed once), 1 small tiles with K over the wavefronts, 2 tiles of 64x64 to 160x256,
+ * 3 persistent 256x256 tiles; [1], [2] rows and columns of an output tile; [3] parts that K is cut into (for
  * kernel 3: pieces per cut tile).  For tests and for reading a profile: results do not depend on it beyond the order of sums.
  * SHAPE and UNSUPPORTED as energon_linear refuses. */
 int energon_linear_plan(int64_t M, int32_t N, int32_t K, int32_t epilogue, int32_t ln_folded, int32_t in_place,

@@ -215,7 +215,7 @@ bool gemm_takes_whole_rounds(int64_t M, int32_t N, int32_t K);
 int gemm_sched_selfcheck(int64_t M, int32_t N, int32_t K, int32_t wgs, int32_t can_split, int32_t* pieces_out);
 // how a 16-bit linear runs: whose kernel, the output tile of a workgroup, parts or pieces that K is cut into
 struct LinearPlan {
-  enum Kernel { kFewRows, kWaves, kTiles, kPersistent };   // gemm_skinny, gemm_ksplit, gemm_mfma_tile, gemm_mfma_sched
+  enum Kernel { kFewRows, kWaves, kTiles, kPersistent };   // gemm_skinny, gemm_ksplit, gemm_ring, gemm_mfma_sched
   int32_t kernel, tile_rows, tile_columns, parts;
 };
 LinearPlan gemm_plan(int64_t M, int32_t N, int32_t K, int epi, bool res_aliases_y, size_t scratch_bytes);

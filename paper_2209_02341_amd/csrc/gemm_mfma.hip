@@ -5,7 +5,7 @@
 // Design for gfx950:
 //  * both operands are contiguous along K, so x rows feed the MFMA A operand and W rows the
 //    B operand with the same 16-byte chunks; fp32 accumulators;
-//  * a BM x BN output tile per workgroup, K walked in slabs of 64 (128 bytes per row), two or three
+//  * a BM x BN output tile per workgroup, K walked in slabs of 64 (128 bytes per row), two
 //    slab buffers in LDS, filled straight from global memory (global_load_lds_dwordx4);
 //  * an LDS row is 8 chunks of 16 bytes; chunk c of row r is stored in slot c ^ swizzle(r), chosen
 //    per MFMA form so that a wavefront's operand read meets no bank conflict (measured).  Slabs
@@ -19,7 +19,7 @@
 // tiles of v_mfma_f32_16x16x32 with the 256 accumulators in AGPRs; the slab loop is hand-scheduled (MFMA, LDS reads and the next
 // slab's loads interleaved in asm); edge tiles are shifted inwards, so nothing is clamped or predicated; the epilogue goes
 // through LDS and leaves as 16-byte non-temporal stores.  Smaller ones: gemm_ring.hip, gemm_ksplit.hip.
-// tile_plan chooses between these, the first kernel with its tiles cut along K, and gemm_ksplit.hip.
+// tile_plan chooses between those and this kernel with every tile cut along K, ring_instead between it and the ring for one or two rounds.
 #include "common.h"
 #include <algorithm>
 #include <cmath>
