@@ -51,7 +51,7 @@ typedef enum {
 } energon_status;
 
 typedef enum {
-  ENERGON_F32 = 0,  /* fp32 storage, fp32 sums of products exact to 24 bits              */
+  ENERGON_F32 = 0,  /* fp32 storage, fp32 arithmetic (exact products, fp32 sums)         */
   ENERGON_BF16 = 1, /* bf16 storage, MFMA with fp32 accumulation, fp32 epilogues         */
   ENERGON_F16 = 2   /* fp16 storage (the paper's precision, Sec. 5.1), otherwise as bf16 */
 } energon_dtype;
