@@ -813,8 +813,12 @@ static TilePlan tile_plan(int64_t M, int32_t N, int32_t K, bool overlap_safe, in
   const auto consider = [&](TilePlan t, double us) {
     if (t.scratch <= cap && us < best.us) { best = t; best.us = us; }
   };
-  // (this function is called for every linear: 32-bit divisions, M < 2^31)
-  const auto tiles = [&](uint32_t bm, uint32_t bn) { return (int64_t)(((uint32_t)M + bm - 1) / bm) * (((uint32_t)N + bn - 1) / bn); };
+  // (this function is called for every linear: 32-bit divisions where M allows; callers that only ask for a size may give any M)
+  const bool narrow = M < ((int64_t)1 << 31);
+  const auto tiles = [&](uint32_t bm, uint32_t bn) {
+    const int64_t rows = narrow ? ((uint32_t)M + bm - 1) / bm : (M + bm - 1) / bm;
+    return rows * (((uint32_t)N + bn - 1) / bn);
+  };
   const auto fits = [](int64_t tiles, int64_t threads) { return tiles * threads <= kMaxGridThreads; };
   const bool former = N % 64 != 0 || K >= 8 * (int64_t)N;   // see kSmallTime
   const double w_bytes = 2.0 * N * K;

@@ -6,6 +6,7 @@ import numpy as np
 import pytest
 
 from paper_2209_02341_amd import binding as E
+from paper_2209_02341_amd import harness as hz
 from paper_2209_02341_amd import workloads as wl
 
 
@@ -78,3 +79,16 @@ def test_tiles_in_pieces_ask_for_their_pieces_room_only():
         per_xcd = -(-tiles // 8)
         assert need == 8 * per_xcd * pieces * rows * columns * 4
         assert E.energon_linear_plan_selfcheck(M, N, K)[0] == 0
+
+
+@pytest.mark.parametrize("M", [2 ** 31 - 1, 2 ** 31, 2 ** 32 - 100, 2 ** 32, 2 ** 32 + 5, 2 ** 40])
+def test_sizes_may_be_asked_for_any_number_of_rows(M):
+    """No such call could run, but the sizes are host arithmetic: no plan cuts K for so many rows, so no room for sums."""
+    for N, K in ((128, 192), (128, 4096), (4096, 192), (64, 16384), (1032, 4096)):
+        assert E.energon_linear_scratch_bytes(M, N, K, E.BF16) == 0
+        st, pieces = E.energon_linear_plan_selfcheck(M, N, K)
+        assert (st, pieces) in ((-1, 0), (0, 1))
+    H, A, F = 256, 256, 1024
+    cfg = hz.layer_config(H, 4, 64, F, wl.BF16, 1e-5)
+    r256 = lambda n: -(-n // 256) * 256
+    assert E.energon_workspace_bytes(cfg, M) == sum(r256(2 * M * n) for n in (H, 3 * A, A, H, H, F))
