@@ -871,10 +871,6 @@ static TilePlan tile_plan(int64_t M, int32_t N, int32_t K, bool overlap_safe, in
                8.0 + 2.1 * n + KT / ks * wide_slab_us(n) + (0.233 * 4.0 * ks + 0.236 * res) * elems / 1.0e6);
     }
   }
-  // A square contraction with a bias only is none of a layer's linears (the out-projection adds a residual); callers have been
-  // told the pieces' scratch for it, so pieces stay unless a ring tile is expected to save more than a third: 928 x 5120 x 5120
-  // 64.5 in pieces, 54 on 128x192.
-  const double settled = !former && epi == EPI_BIAS && N == K ? 0.66 : 1.0;
   if (plain && M >= 256 && N >= 256 && K % 128 == 0 && overlap_safe) {
     const int64_t big = tiles(256, 256);
     for (int32_t P = 2; P <= 8; ++P) {
@@ -884,7 +880,7 @@ static TilePlan tile_plan(int64_t M, int32_t N, int32_t K, bool overlap_safe, in
       if (rem >= wgs || rem * P > 2 * wgs || (KT + chunk - 1) / chunk != P || chunk < 8) continue;
       const double rounds = std::ceil((double)rem * P / wgs);
       consider({kPieces, KsplitTile::k64x64, 0, P, slots_bytes(pieces_slots(M, N, P))},
-               settled * (8.2 + rounds * (1.1 + 1.228 * chunk) + (0.388 * big * P * kPartFloats * 4.0 + 0.394 * res * elems) / 1.0e6));
+               8.2 + rounds * (1.1 + 1.228 * chunk) + (0.388 * big * P * kPartFloats * 4.0 + 0.394 * res * elems) / 1.0e6);
     }
   }
   return best;
