@@ -235,7 +235,6 @@ hipError_t launch_gemm_ksplit(KsplitTile tile, const E* x, const E* w, const E* 
 struct RingShape { int16_t rows, cols, per_cu; };
 constexpr RingShape kRingShapes[] = {{64, 64, 2},  {64, 96, 2},   {96, 96, 2},   {96, 128, 1},  {128, 128, 1}, {128, 128, 2},
                                      {96, 192, 1}, {128, 192, 1}, {160, 192, 1}, {128, 256, 1}, {160, 256, 1}};
-constexpr int kRing64x64 = 0, kRing128x128 = 4, kRing128x128Pair = 5, kRing128x256 = 9;   // indexes there
 constexpr int kRingCount = sizeof(kRingShapes) / sizeof(kRingShapes[0]);
 template <typename E>
 hipError_t launch_gemm_ring(int shape, const E* x, const E* w, const E* bias, const E* res, E* y, int64_t M, int32_t N, int32_t K,

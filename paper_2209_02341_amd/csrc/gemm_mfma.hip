@@ -724,20 +724,25 @@ size_t gemm_sched_scratch_bytes(int64_t M, int32_t N, int32_t K) {
 //            (sums in the scratch);
 //   kPieces  the 256x256 kernel with every tile cut into pieces (needs M, N >= 256 and K % 128 == 0).
 // The one with the least expected time, by a model that is fitted per tile to a sweep of 7300 shapes on all of them (65 to
-// 5000 rows of every layer width and others, K of 64 to 32768, the three epilogues, three sets of operands in turn): it costs
-// 1.4 % over the best of them in the mean.  What the choice turns on is whole rounds: so many sizes, because each alone is the best
-// by 10 to 45 % wherever its tiles just fill the CUs.  Measured (us; in brackets the same shape on the former tiles, and the
-// next best of these):
+// 5000 rows of every layer width and others, K of 64 to 32768, the three epilogues, three sets of operands in turn).  On 11200
+// others of up to 9000 rows, a fifth of them of ragged widths and a sixth with K of eight N and more (up to 65536), it costs 1.3 %
+// over the best of them in the mean.  What the choice turns on is whole rounds: so many sizes, because each alone is the best
+// by 10 to 45 % wherever its tiles just fill the CUs.  Measured (us; in brackets the same shape on the tiles of the kernel before
+// this one, and the next best of these):
 //   387 x 4096 x 1024 + GeLU 9.8 64x64 [10.9; 10.5]   928 x 5120 x 5120 + residual 54 160x192 [72; 58]   200 x 20480 x 5120 73 160x192 [103; 77]
 //   600 x 4096 x 16384 86 160x256 in parts [102; 90]  2280 x 4096 x 4096 75 160x256 [109; 91]             333 x 5120 x 20480 87 128x256 in parts [99; 90]
-// Against the former choice (64x64, 128x128 and 128x256 tiles of a compiler-scheduled kernel) 0.84 times the time in the mean of the sweep.
+//   692 x 30536 x 192 21.3 128x128 [29.9]             5239 x 2840 x 192 + GeLU 20.2 128x128 [26.4]        369 x 1096 x 11456 + GeLU 19.2 96x128 in parts [25.2]
+// Against the choice before (64x64, 128x128 and 128x256 tiles of a compiler-scheduled kernel), over shapes that take 8 us and more:
+// widths that are multiples of 64 0.77 times the time in the mean, others 0.71, K of eight N and more 0.69.  What stayed on 64x64 tiles
+// at K of 320 and less and some 500 to 800 tiles loses up to 1.1 (8881 x 320 x 320 7.6 -> 8.4): three workgroups of that kernel
+// shared a CU, two of this one do.
 enum TileKind { kSplit, kRing, kPieces };
 struct TilePlan { TileKind kind; KsplitTile split; int32_t ring, ks; size_t scratch; double us; };   // ks: parts of K (kPieces: pieces per tile)
 
 // us = base + gelu + residual + n (round + residual_round) + steps * slab(n), n = tiles per CU; slab(n) through the given
-// points, in proportion beyond the last.  The epilogue that reads row statistics has base and round of its own.
+// points, in proportion beyond the last.
 struct TileTime {
-  double base, gelu, residual, round, residual_round, fold_base, fold_round;
+  double base, gelu, residual, round, residual_round;
   struct { double n, us; } slab[11];
   double slab_us(double n) const {
     int i = 1;
@@ -746,17 +751,15 @@ struct TileTime {
     return slab[i - 1].us + (slab[i].us - slab[i - 1].us) * (n - slab[i - 1].n) / (slab[i].n - slab[i - 1].n);
   }
   double us(double n, int epi) const {   // without the slabs
-    const bool fold = epi == EPI_LNFOLD || epi == EPI_LNFOLD_GELU;
-    return (fold ? fold_base + n * fold_round : base + n * round) + (epi == EPI_BIAS_GELU || epi == EPI_LNFOLD_GELU ? gelu : 0.0) +
-           (epi == EPI_BIAS_RESIDUAL ? residual + n * residual_round : 0.0);
+    return base + n * round + (epi == EPI_BIAS_GELU ? gelu : 0.0) + (epi == EPI_BIAS_RESIDUAL ? residual + n * residual_round : 0.0);
   }
 };
 constexpr TileTime kSplitTime[3] = {   // steps of four slabs, one per wavefront
-    {2.18, 0.23, 0.27, 0.46, 0.08, 0, 0,
+    {2.18, 0.23, 0.27, 0.46, 0.08,
      {{0, 0.298}, {1, 0.345}, {1.003, 0.573}, {2, 0.662}, {2.003, 0.888}, {4, 1.261}, {4.003, 1.456}, {6, 1.934}, {16, 5.175}, {40, 12.477}}},
-    {2.38, 0.43, 0.23, 1.69, 0.39, 0, 0,
+    {2.38, 0.43, 0.23, 1.69, 0.39,
      {{0, 0.454}, {1, 0.451}, {1.003, 1.050}, {2, 0.944}, {2.003, 1.580}, {3, 1.469}, {3.003, 1.969}, {4, 2.081}, {8, 4.395}, {20, 11.016}}},
-    {3.54, 0.41, 0.18, 3.07, 1.05, 0, 0,
+    {3.54, 0.41, 0.18, 3.07, 1.05,
      {{0, 0.684}, {1, 0.645}, {1.003, 1.471}, {2, 1.345}, {2.003, 2.141}, {3, 2.174}, {3.003, 2.709}, {5, 3.701}, {10, 8.146}}}};
 static_assert((int)KsplitTile::k32x32 == 0 && (int)KsplitTile::k64x32 == 1 && (int)KsplitTile::k64x64 == 2, "order of kSplitTime");
 
@@ -790,20 +793,6 @@ constexpr RingTime kRingTime[] = {   // the order of kRingShapes
     {0.72, 8.63, 0.311, 4.33, 6.02, 8.16, 0.05, 0.00, 0.92, 0.34, {0.759}}};
 static_assert(sizeof(kRingTime) / sizeof(kRingTime[0]) == kRingCount, "one per tile");
 
-// N that is not a multiple of 64, or K of eight N and more (no layer has such a linear): the plans that the former tiles of
-// 64x64, 128x128 and 128x256 had, and with them the scratch that callers were told, run on the same tiles of gemm_ring.hip (0.43
-// to 0.95 times the time, up to 1.09 where 128x128 tiles make many rounds of few slabs; 300 x 2048 x 16384 43 -> 38, 33 with 128x128).
-constexpr TileTime kSmallTime{3.56, 0.78, 1.04, 0.53, 1.22, 5.34, 1.01,
-    {{0, 0.247}, {1, 0.261}, {1.003, 0.339}, {2, 0.378}, {2.003, 0.539}, {3, 0.580}, {3.003, 0.750}, {4, 0.824}, {4.003, 0.880},
-     {6, 1.170}, {10, 1.991}}};
-constexpr TileTime kSquareTime{7.67, 3.18, 4.97, 1.79, 6.08, 11.90, 4.50,
-    {{0, 0.564}, {1, 0.631}, {1.003, 0.780}, {1.5, 0.902}, {2, 1.040}, {2.003, 1.550}, {3, 1.720}, {4, 2.100}, {4.5, 2.800}, {10, 5.700}}};
-constexpr TileTime kWideTime{7.97, 2.70, 5.47, 3.53, 11.73, 14.72, 4.04,
-    {{0, 0.805}, {0.5, 0.848}, {1, 0.985}, {1.003, 1.903}, {1.5, 1.996}, {2, 2.805}}};
-
-// Slabs of 128x256 tiles, whole rounds of them beyond two.
-static double wide_slab_us(double n) { return n <= 2.0 ? kWideTime.slab_us(n) : std::ceil(n) * kWideTime.slab_us(1.0); }
-
 // epi: one of EPI_BIAS, EPI_BIAS_GELU, EPI_BIAS_RESIDUAL (all plans) or the folded ones (kRing without parts only).
 static TilePlan tile_plan(int64_t M, int32_t N, int32_t K, bool overlap_safe, int epi, size_t cap, int32_t wgs) {
   const bool plain = epi != EPI_LNFOLD && epi != EPI_LNFOLD_GELU;
@@ -820,13 +809,12 @@ static TilePlan tile_plan(int64_t M, int32_t N, int32_t K, bool overlap_safe, in
     return rows * (((uint32_t)N + bn - 1) / bn);
   };
   const auto fits = [](int64_t tiles, int64_t threads) { return tiles * threads <= kMaxGridThreads; };
-  const bool former = N % 64 != 0 || K >= 8 * (int64_t)N;   // see kSmallTime
   const double w_bytes = 2.0 * N * K;
   const bool from_hbm = w_bytes > 85.0e6;   // see RingTime
-  const double far = former ? (w_bytes > 268.0e6 ? 1.06 : 1.0) : from_hbm ? 1.45 : 1.0;   // the same for the small tiles that cut K
+  const double far = from_hbm ? 1.45 : 1.0;   // the same for the small tiles that cut K
   if (plain) {
     // a last step that not all four wavefronts take costs about half the difference to one that they do
-    const double steps = former ? (KT + 3) / 4 : 0.5 * ((KT + 3) / 4 + 0.25 * KT);
+    const double steps = 0.5 * ((KT + 3) / 4 + 0.25 * KT);
     const KsplitTile split[3] = {KsplitTile::k32x32, KsplitTile::k64x32, KsplitTile::k64x64};
     const int64_t n[3] = {tiles(32, 32), tiles(64, 32), tiles(64, 64)};
     for (int i = 0; i < 3; ++i)
@@ -835,7 +823,7 @@ static TilePlan tile_plan(int64_t M, int32_t N, int32_t K, bool overlap_safe, in
   const double elems = (double)M * N, res = epi == EPI_BIAS_RESIDUAL ? 1.0 : 0.0;
   // No ring tile wins where 32x32 ones are one round and K is short (0.4 us of host time saved on calls that it bounds).
   const bool tiny = plain && KT <= 64 && tiles(32, 32) <= 8 * wgs;
-  if (!former && !tiny) {
+  if (!tiny) {
     const bool spills = 2.0 * (M + N) * K > 256.0e6;   // x and W do not both fit the last cache: another round reads them again
     for (int i = 0; i < kRingCount; ++i) {
       const RingShape& shape = kRingShapes[i];
@@ -854,21 +842,6 @@ static TilePlan tile_plan(int64_t M, int32_t N, int32_t K, bool overlap_safe, in
         consider({kRing, KsplitTile::k64x64, i, parts, parts > 1 ? (size_t)parts * (size_t)M * N * sizeof(float) : 0}, us);
         if (fill <= 1) break;
       }
-    }
-  } else if (former) {
-    const double far_shared = std::max(far, K >= 12288 ? 1.08 : 1.0);
-    if (const int64_t n = tiles(64, 64); fits(n, 256))
-      consider({kRing, KsplitTile::k64x64, kRing64x64, 1, 0}, kSmallTime.us(n / cus, epi) + KT * far_shared * kSmallTime.slab_us(n / cus));
-    if (const int64_t n = tiles(128, 128); K < (1 << 24) && fits(n, 256))   // a tile's rows in 32-bit byte offsets
-      consider({kRing, KsplitTile::k64x64, n > cus ? kRing128x128Pair : kRing128x128, 1, 0}, kSquareTime.us(n / cus, epi) + KT * kSquareTime.slab_us(n / cus));
-    const int64_t wide = tiles(128, 256);
-    if (K < (1 << 23) && fits(wide, 512))
-      consider({kRing, KsplitTile::k64x64, kRing128x256, 1, 0}, kWideTime.us(wide / cus, epi) + KT * wide_slab_us(wide / cus));
-    for (int32_t ks = 2; plain && K < (1 << 23) && ks <= 8 && wide * ks <= 1024 && KT / ks >= 4; ++ks) {
-      if (KT % ks != 0) continue;
-      const double n = wide * ks / cus;   // then the sums' way to memory and back, and the second launch
-      consider({kRing, KsplitTile::k64x64, kRing128x256, ks, (size_t)ks * (size_t)M * N * sizeof(float)},
-               8.0 + 2.1 * n + KT / ks * wide_slab_us(n) + (0.233 * 4.0 * ks + 0.236 * res) * elems / 1.0e6);
     }
   }
   if (plain && M >= 256 && N >= 256 && K % 128 == 0 && overlap_safe) {
@@ -911,7 +884,7 @@ static double sched_us(const SchedPlan& p, int64_t M, int32_t N, int epi) {
   return 1.15 + worst + second;
 }
 static bool ring_instead(int64_t M, int32_t N, int32_t K, int epi, const SchedPlan& p, TilePlan& t) {
-  if ((int64_t)p.tiles_m * p.tiles_n >= 420 || N % 64 != 0) return false;
+  if ((int64_t)p.tiles_m * p.tiles_n >= 420 || N % 64 != 0) return false;   // the sweep behind it had multiples of 64 only
   t = tile_plan(M, N, K, true, epi, 0, p.wgs);
   return t.kind == kRing && t.us < 0.87 * sched_us(p, M, N, epi);
 }

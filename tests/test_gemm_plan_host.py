@@ -91,6 +91,19 @@ def test_square_linears_with_a_bias_only_are_not_held_in_pieces(M, N):
     assert need == max([4 * p[3] * M * N for p in plans if p[3] > 1], default=0) + 255 & ~255
 
 
+@pytest.mark.parametrize("M,N,K,epi,plan", [
+    # measured on the tiles that these shapes were held on and on these (us): 64x64 38.0 / 23.1, 59.2 / 43.5, 25.8 / 17.1,
+    # 29.2 / 20.0, 30.0 / 19.7; K over the wavefronts of small tiles 25.4 / 20.1, 36.5 / 23.5, 55.1 / 27.8; 128x256 in parts 38.6 / 33.6
+    (692, 30536, 192, E.EPI_BIAS, (2, 128, 128, 1)), (1033, 30536, 192, E.EPI_BIAS_GELU, (2, 96, 96, 1)),
+    (251, 50256, 256, E.EPI_BIAS, (2, 128, 128, 1)), (944, 18016, 192, E.EPI_BIAS, (2, 96, 96, 1)),
+    (5239, 2840, 192, E.EPI_BIAS_GELU, (2, 128, 128, 1)),
+    (369, 1096, 11456, E.EPI_BIAS_GELU, (2, 96, 128, 7)), (1186, 128, 25024, E.EPI_BIAS_GELU, (2, 96, 128, 8)),
+    (720, 72, 40576, E.EPI_BIAS_GELU, (2, 96, 128, 8)), (300, 2048, 16384, E.EPI_BIAS_RESIDUAL, (2, 96, 128, 4)),
+])
+def test_ragged_widths_and_long_k_run_on_the_tiles_that_every_shape_has(M, N, K, epi, plan):
+    assert E.energon_linear_plan(M, N, K, epi, scratch_bytes=E.energon_linear_scratch_bytes(M, N, K, E.BF16)) == plan
+
+
 @pytest.mark.parametrize("M", [2 ** 31 - 1, 2 ** 31, 2 ** 32 - 100, 2 ** 32, 2 ** 32 + 5, 2 ** 40])
 def test_sizes_may_be_asked_for_any_number_of_rows(M):
     """No such call could run, but the sizes are host arithmetic: no plan cuts K for so many rows, so no room for sums."""

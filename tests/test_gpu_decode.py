@@ -457,7 +457,7 @@ def test_generation_steps_replayed_from_a_hip_graph():
         assert torch.equal(st.v[i].view(torch.int16), eager.v[i].view(torch.int16))
 
 
-@pytest.mark.parametrize("B,ffn,S_cap,fc2", [(96, 8192, 24, (1, 32, 32, 1)), (300, 16384, 8, (2, 128, 256, 8))])
+@pytest.mark.parametrize("B,ffn,S_cap,fc2", [(96, 8192, 24, (1, 32, 32, 1)), (300, 16384, 8, (2, 96, 128, 4))])
 def test_decode_layer_batch_above_the_few_row_kernel(B, ffn, S_cap, fc2):
     """More sequences than the few-row kernel takes rows.  96: K is cut over the wavefronts of small tiles, no scratch.
     300 and a long FFN: FC2's K is cut over workgroups, with sums in the step's workspace.  Against the oracle, and

@@ -1,6 +1,5 @@
 """16-bit linears too small for whole rounds of the 256x256 kernel, one shape per way they can run: K cut over the
-wavefronts of a small tile (three tile sizes), 64x64, 128x128 and 128x256 tiles, K cut over workgroups, the 256x256 kernel in
-pieces; with and without scratch, ragged rows and columns, all epilogues, the residual also in place (which rules out
+wavefronts of a small tile (three tile sizes), tiles with all of K, K cut over workgroups, the 256x256 kernel in pieces; with and without scratch, ragged rows and columns, all epilogues, the residual also in place (which rules out
 overlapping edge tiles).  Against the oracle at the suite's bars; the same bits on a second run over other scratch."""
 import numpy as np
 import pytest
@@ -18,13 +17,16 @@ SHAPES = [
     # M, N, K, dtype, scratch that the plan takes
     (65, 40, 64, wl.BF16, False),          # 32x32, one slab
     (130, 264, 192, wl.BF16, False),       # 32x32, fewer slabs than wavefronts
-    (515, 1032, 1024, wl.F16, False),      # 32x32
+    (515, 1032, 1024, wl.F16, False),      # 64x64, with GeLU 32x32
     (131, 2056, 4096, wl.BF16, False),     # 64x32
-    (513, 1032, 2048, wl.BF16, False),     # 32x32, more than one round
-    (1025, 2056, 1024, wl.F16, False),     # 64x64 shared
-    (2600, 2056, 192, wl.BF16, False),     # 64x64 shared, many rounds
-    (515, 2056, 4096, wl.BF16, True),      # bias + residual: 128x256, K cut four ways
-    (900, 5128, 5120, wl.BF16, True),      # pieces
+    (513, 1032, 2048, wl.BF16, False),     # 64x64
+    (1025, 2056, 1024, wl.F16, False),     # 96x96
+    (2600, 2056, 192, wl.BF16, False),     # 128x128, with a residual 128x192
+    (515, 2056, 4096, wl.BF16, False),     # 64x96
+    (900, 5128, 5120, wl.BF16, False),     # 128x192
+    (300, 1032, 8192, wl.BF16, True),      # 96x128, K cut seven ways
+    (1300, 264, 8192, wl.F16, True),       # 96x128, K cut six ways
+    (500, 6584, 7680, wl.BF16, True),      # pieces
 ]
 
 
@@ -59,7 +61,7 @@ def test_linear_plans(M, N, K, dtype, cuts, epi):
 
 
 def test_scratch_below_the_plans_need_is_not_refused():
-    M, N, K = 515, 2056, 4096
+    M, N, K = 300, 1032, 8192
     x, w = torch.randn((M, K), device="cuda").bfloat16(), (torch.randn((N, K), device="cuda") * 0.02).bfloat16()
     need = E.energon_linear_scratch_bytes(M, N, K, E.BF16)
     ys = []
@@ -73,14 +75,16 @@ def test_scratch_below_the_plans_need_is_not_refused():
 
 
 # M, N, K, dtype, what runs with bias / bias + GeLU / bias + residual: rows and columns of the tile, last ones ragged
-SQUARE, WIDE, SHARED = (2, 128, 128, 1), (2, 128, 256, 1), (2, 64, 64, 1)
+SQUARE, WIDE, SHARED, CUT = (2, 128, 128, 1), (2, 128, 256, 1), (2, 64, 64, 1), (1, 64, 64, 1)
 TILES = [
     (650, 5128, 4096, wl.BF16, (SQUARE, SQUARE, SQUARE)),
-    (1000, 15368, 192, wl.F16, (SQUARE, SHARED, SHARED)),     # three slabs on two buffers
-    (2000, 20488, 64, wl.BF16, (SQUARE, SHARED, SHARED)),     # one slab
-    (515, 12296, 2560, wl.F16, (WIDE, WIDE, WIDE)),
-    (650, 1032, 1600, wl.BF16, ((1, 64, 64, 1), (1, 64, 64, 1), (1, 32, 32, 1))),
-    (900, 264, 1600, wl.F16, ((1, 64, 32, 1),) * 3),
+    (1000, 15368, 192, wl.F16, (SQUARE, SQUARE, SQUARE)),     # three slabs on two buffers
+    (2000, 20488, 64, wl.BF16, (SQUARE, SQUARE, SQUARE)),     # one slab
+    (515, 12296, 2560, wl.F16, (WIDE, SQUARE, WIDE)),
+    (1463, 4920, 1600, wl.BF16, (WIDE, WIDE, WIDE)),
+    (650, 1032, 1600, wl.BF16, (SHARED, SHARED, SHARED)),
+    (123, 7544, 5696, wl.F16, (CUT, CUT, CUT)),
+    (900, 264, 1600, wl.F16, ((1, 64, 32, 1), (1, 32, 32, 1), (1, 64, 32, 1))),
 ]
 
 

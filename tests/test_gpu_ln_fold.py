@@ -108,7 +108,8 @@ def test_linear_ln_folded_matches_layernorm_then_linear(M, N, K, dtype, gelu):
 @pytest.mark.parametrize("M,N,K,dtype,gelu,tile", [
     (2401, 5128, 832, wl.BF16, False, (128, 128)), (1106, 12296, 832, wl.F16, True, (128, 128)),
     (650, 5128, 4096, wl.F16, False, (128, 128)),
-    (1300, 15368, 192, wl.F16, False, (128, 256)), (1300, 20488, 64, wl.BF16, True, (128, 256)),
+    (1300, 15368, 192, wl.F16, False, (128, 128)), (1300, 20488, 64, wl.BF16, True, (128, 128)),
+    (515, 12296, 4160, wl.F16, False, (128, 256)), (327, 17296, 2624, wl.BF16, True, (128, 256)),
 ])
 def test_linear_ln_folded_tiles(M, N, K, dtype, gelu, tile):
     assert E.energon_linear_plan(M, N, K, E.EPI_BIAS_GELU if gelu else E.EPI_BIAS, ln_folded=True) == (2,) + tile + (1,)
