@@ -161,10 +161,11 @@ int layer_impl(const EnergonLayerConfig* cfg, const EnergonLayerWeights* w, cons
 #define MARK(i) do { if (ev) HIP_TRY(hipEventRecord(ev[i], s)); } while (0)
 #define STEP(call) do { st = (call); if (st != ENERGON_OK) return st; } while (0)
   MARK(0);
-  // a small fp32 linear normalises its rows itself (not where the stages are timed apart)
+  // a small fp32 linear normalises its rows itself: one launch, timed as the linear's stage
   const auto normalised_linear = [&](const void* in, const void* g, const void* b, void* norm, const void* wt, const void* bias, void* out,
                                      int32_t N, int32_t epi, int mark) -> int {
-    if (dt == ENERGON_F32 && !ev && gemm_f32_takes_ln(T, N, H)) {
+    if (dt == ENERGON_F32 && gemm_f32_takes_ln(T, N, H)) {
+      MARK(mark);
       HIP_TRY(launch_gemm_f32_ln(static_cast<const float*>(in), static_cast<const float*>(g), static_cast<const float*>(b), cfg->ln_eps,
                                  static_cast<float*>(norm), static_cast<const float*>(wt), static_cast<const float*>(bias),
                                  static_cast<float*>(out), T, N, H, epi, s));

@@ -44,3 +44,24 @@ def test_small_f32_layer(lens, H, nh, F):
     m = orc.gelu(orc.linear(wn, d["w_fc1"], d["b_fc1"]))
     bound = 1.13 * (2 * H + 32) * U * (np.abs(wn).max() * np.abs(d["w_fc1"]).sum(1).max() + np.abs(d["b_fc1"]).max()) + 1.3e-7
     assert np.abs(f32(E.WS_M, F) - m).max() <= bound + 8 * U * np.abs(m).max()
+
+
+@pytest.mark.parametrize("lens,H,nh,F", [([17, 3, 13], 256, 4, 1024), ([9, 4], 576, 9, 640)])
+def test_the_timed_layer_is_the_one_that_runs(lens, H, nh, F):
+    """energon_layer_forward_profiled makes the same launches: the same bits of everything, in a layer whose linears normalise their
+    rows themselves and in one that has launches for it."""
+    lens = np.asarray(lens, np.int32)
+    T = int(lens.sum())
+    rng = np.random.default_rng(H)
+    layer = hz.DeviceLayer(wl.random_small_layer(rng, H, nh, 64, F), wl.F32)
+    cfg = hz.layer_config(H, nh, 64, F, wl.F32, 1e-5)
+    x = hz.to_device(rng.normal(1.0, 2.0, (T, H)).astype(np.float32), wl.F32)
+    cu = torch.from_numpy(np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)).cuda()
+    left = []
+    for call in (E.energon_layer_forward, E.energon_layer_forward_profiled):
+        ws, y = torch.zeros(E.energon_workspace_bytes(cfg, T), dtype=torch.uint8, device="cuda"), torch.empty_like(x)
+        ms = call(cfg, layer.struct, x, y, T, cu, lens, int(lens.max()), ws)
+        left.append((y, ws))
+    assert list(ms) == list(E.STAGE_NAMES) and all(v >= 0.0 for v in ms.values())
+    for a, b in zip(*left):
+        assert torch.equal(a.view(torch.uint8), b.view(torch.uint8))
