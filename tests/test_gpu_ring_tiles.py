@@ -1,7 +1,8 @@
 """16-bit linears on the tiles of the ring kernel: every tile size, with ragged last rows and columns, fewer slabs of K than
 the ring holds and more, K cut over workgroups into parts of unequal length; the plain epilogues (the residual also in
 place) and the LayerNorm-folded ones.  Against the oracle at the suite's bars; the same bits on a second run over other
-scratch."""
+scratch.  The plan names the tile but not which of two kernels runs 128 x 128: up to 256 tiles, one per CU, it is the one with
+five slabs in the ring, beyond that and up to 512 the one with two, of which two share a CU."""
 import numpy as np
 import pytest
 import torch
@@ -27,7 +28,7 @@ SHAPES = [
     (833, 3520, 320, wl.F16, BIAS, (96, 128, 1)),
     (161, 2752, 4096, wl.BF16, RESIDUAL, (96, 128, 5)),    # 64 slabs in five parts
     (1154, 2624, 320, wl.BF16, RESIDUAL, (128, 128, 1)),
-    (780, 5696, 64, wl.BF16, BIAS, (128, 128, 1)),         # two workgroups on a CU
+    (780, 5696, 64, wl.BF16, BIAS, (128, 128, 1)),         # 315 tiles
     (97, 10688, 4096, wl.F16, GELU, (128, 128, 3)),
     (1753, 2432, 384, wl.BF16, RESIDUAL, (96, 192, 1)),
     (70, 11584, 4096, wl.F16, BIAS, (96, 192, 4)),
@@ -38,6 +39,19 @@ SHAPES = [
     (1958, 3776, 576, wl.F16, RESIDUAL, (128, 256, 1)),
     (645, 10944, 320, wl.BF16, BIAS, (160, 256, 1)),
     (264, 12480, 4096, wl.F16, GELU, (160, 256, 2)),
+    # the ring filled more than twice, an odd number of slabs, widths that are no multiple of any tile's
+    (68, 5776, 704, wl.BF16, RESIDUAL, (64, 64, 1)),
+    (66, 9800, 576, wl.F16, BIAS, (64, 96, 1)),
+    (133, 10912, 448, wl.BF16, BIAS, (96, 96, 1)),
+    (197, 9768, 704, wl.F16, BIAS, (96, 128, 1)),
+    (195, 12584, 704, wl.BF16, BIAS, (128, 128, 1)),
+    (329, 12432, 320, wl.F16, BIAS, (128, 128, 1)),        # 294 tiles
+    (789, 4624, 576, wl.BF16, RESIDUAL, (96, 192, 1)),
+    (336, 12408, 576, wl.F16, RESIDUAL, (128, 192, 1)),
+    (1422, 4408, 448, wl.BF16, RESIDUAL, (160, 192, 1)),
+    (1458, 5048, 576, wl.F16, RESIDUAL, (128, 256, 1)),
+    (516, 13208, 448, wl.BF16, BIAS, (160, 256, 1)),
+    (129, 7016, 6080, wl.F16, BIAS, (160, 192, 6)),        # 95 slabs in six parts
 ]
 
 
@@ -71,7 +85,10 @@ def test_ring_tiles(M, N, K, dtype, epi, tile):
 
 FOLDED = [(1127, 4160, 64, wl.BF16, True, (128, 128, 1)), (2289, 1024, 128, wl.F16, False, (64, 96, 1)),
           (323, 5504, 192, wl.BF16, False, (96, 96, 1)), (1751, 5248, 64, wl.F16, False, (160, 256, 1)),
-          (834, 3520, 448, wl.BF16, True, (96, 128, 1)), (2225, 2240, 1024, wl.F16, False, (128, 192, 1))]
+          (834, 3520, 448, wl.BF16, True, (96, 128, 1)), (2225, 2240, 1024, wl.F16, False, (128, 192, 1)),
+          (102, 480, 704, wl.F16, False, (64, 64, 1)), (67, 8336, 576, wl.BF16, False, (64, 96, 1)),
+          (1558, 2440, 2112, wl.BF16, False, (96, 192, 1)), (769, 9504, 448, wl.F16, False, (160, 192, 1)),
+          (329, 12432, 320, wl.BF16, False, (128, 128, 1)), (769, 11056, 448, wl.F16, False, (160, 256, 1))]
 
 
 @pytest.mark.parametrize("M,N,K,dtype,gelu,tile", FOLDED)
