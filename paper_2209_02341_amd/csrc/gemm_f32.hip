@@ -25,6 +25,7 @@
 // 2^-110; all nine, with those operands found and a second pass for them, take 411 us.
 #include "common.h"
 #include <cmath>
+#include <type_traits>
 
 namespace energon {
 
@@ -41,55 +42,94 @@ struct LnRows {
 };
 constexpr int kLnMaxK = 512;   // of a row: a wavefront holds it in registers, gain and offset lie in LDS
 
-// Rows m0 .. m0 + 15 of x normalised as layernorm_kernel does it (two passes over a row in registers): a row per wavefront at a
-// time.  Mean and 1 / deviation to st, gain and offset to gb; with `write` the normalised rows to ln.u.
+// wave_sum without LDS: halves and rows of 16 lanes are swapped (both operands the same: one result holds the one half, the other the
+// other), and in a row a rotation by 8, 4, 2, 1 meets the same lane as the exclusive or, the values having that period by then:
+// the same bits.
+__device__ __forceinline__ float wave_sum_dpp(float v) {
+  const auto both = [](auto p) { return __uint_as_float(p[0]) + __uint_as_float(p[1]); };
+  v = both(__builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false));
+  v = both(__builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false));
+  v += __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x128, 0xf, 0xf, true));   // row_ror:8
+  v += __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x124, 0xf, 0xf, true));
+  v += __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x122, 0xf, 0xf, true));
+  v += __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x121, 0xf, 0xf, true));
+  return v;
+}
+
+// Rows m0 .. m0 + 15 of x normalised as layernorm_kernel does it (two passes over a row in registers), R of them per wavefront.
+// What it reads is requested first, ahead of the slabs, without a branch, and the reductions of the R rows run side by side: one row
+// after the other with its stores behind it, and that behind the loads of gain and offset, the linears of 77 x 768 x 256 and 77 x 1024 x
+// 256 took 6.8 and 7.4 us, which is what a LayerNorm launch and the plain linear take; now 5.2 and 6.1.
 template <int WK>
-__device__ __forceinline__ void ln_rows(const float* __restrict__ x, const LnRows& ln, int64_t m0, int64_t M, int32_t K, bool write,
-                                        int wave, int lane, float2* st, f32x4* gb) {
-  constexpr int V = kLnMaxK / 256;
-  const int32_t vecs = K / 4;   // K % 4 == 0
-  for (int32_t c = wave * 64 + lane; c < vecs; c += WK * 64) {
-    gb[c] = reinterpret_cast<const f32x4*>(ln.gamma)[c];
-    gb[kLnMaxK / 4 + c] = reinterpret_cast<const f32x4*>(ln.beta)[c];
+struct LnTile {
+  static constexpr int V = kLnMaxK / 256, R = 16 / WK;
+  static_assert(kLnMaxK / 4 <= WK * 64, "gain and offset: a vector per lane");
+  f32x4 v[R][V], g, b;
+  __device__ __forceinline__ void request(const float* __restrict__ x, const LnRows& ln, int64_t m0, int64_t M, int32_t K, int wave, int lane) {
+    const int32_t vecs = K / 4, c = wave * 64 + lane;   // K % 4 == 0
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      const int64_t m = m0 + wave * R + r;
+      const f32x4* row = reinterpret_cast<const f32x4*>(x + (size_t)(m < M ? m : M - 1) * K);
+#pragma unroll
+      for (int i = 0; i < V; ++i) v[r][i] = row[min(lane + 64 * i, vecs - 1)];   // past the end: left out of the sums
+    }
+    g = reinterpret_cast<const f32x4*>(ln.gamma)[min(c, vecs - 1)];
+    b = reinterpret_cast<const f32x4*>(ln.beta)[min(c, vecs - 1)];
   }
-  constexpr int R = 16 / WK;
-  f32x4 v[R][V];
+  // mean and 1 / deviation to st, gain and offset to gb; with `write` the normalised rows to ln.u
+  __device__ __forceinline__ void finish(const LnRows& ln, int64_t m0, int64_t M, int32_t K, bool write, int wave, int lane, float2* st, f32x4* gb) {
+    const int32_t vecs = K / 4, cw = wave * 64 + lane;
+    const float inv = 1.0f / (float)K;
+    float mean[R], rstd[R];
 #pragma unroll
-  for (int r = 0; r < R; ++r) {   // all rows requested before the first is summed
-    const int64_t m = m0 + wave * R + r;
-    const f32x4* row = reinterpret_cast<const f32x4*>(x + (size_t)(m < M ? m : M - 1) * K);
+    for (int r = 0; r < R; ++r) {
+      mean[r] = 0.f;
 #pragma unroll
-    for (int i = 0; i < V; ++i) v[r][i] = lane + 64 * i < vecs ? row[lane + 64 * i] : f32x4{0.f, 0.f, 0.f, 0.f};
-  }
-  const float inv = 1.0f / (float)K;
+      for (int i = 0; i < V; ++i) mean[r] += lane + 64 * i < vecs ? (v[r][i][0] + v[r][i][1]) + (v[r][i][2] + v[r][i][3]) : 0.f;
+    }
 #pragma unroll
-  for (int r = 0; r < R; ++r) {
-    float sum = 0.f, sq = 0.f;
+    for (int r = 0; r < R; ++r) mean[r] = wave_sum_dpp(mean[r]);
 #pragma unroll
-    for (int i = 0; i < V; ++i) sum += (v[r][i][0] + v[r][i][1]) + (v[r][i][2] + v[r][i][3]);
-    const float mean = wave_sum(sum) * inv;
+    for (int r = 0; r < R; ++r) {
+      mean[r] *= inv;
+      rstd[r] = 0.f;
 #pragma unroll
-    for (int i = 0; i < V; ++i)
-      if (lane + 64 * i < vecs) {
+      for (int i = 0; i < V; ++i)
 #pragma unroll
-        for (int e = 0; e < 4; ++e) sq += (v[r][i][e] - mean) * (v[r][i][e] - mean);
-      }
-    const float rstd = rsqrtf(wave_sum(sq) * inv + ln.eps);
-    if (lane == 0) st[wave * R + r] = make_float2(mean, rstd);
-    const int64_t m = m0 + wave * R + r;
-    if (write && m < M) {
-      f32x4* out = reinterpret_cast<f32x4*>(ln.u + (size_t)m * K);
+        for (int e = 0; e < 4; ++e) {
+          const float d = lane + 64 * i < vecs ? v[r][i][e] - mean[r] : 0.f;
+          rstd[r] += d * d;
+        }
+    }
+#pragma unroll
+    for (int r = 0; r < R; ++r) rstd[r] = wave_sum_dpp(rstd[r]);
+#pragma unroll
+    for (int r = 0; r < R; ++r) rstd[r] = rsqrtf(rstd[r] * inv + ln.eps);
+    if (cw < vecs) {
+      gb[cw] = g;
+      gb[kLnMaxK / 4 + cw] = b;
+    }
+    if (lane == 0) {
+#pragma unroll
+      for (int r = 0; r < R; ++r) st[wave * R + r] = make_float2(mean[r], rstd[r]);
+    }
+    __syncthreads();
+    if (write) {
 #pragma unroll
       for (int i = 0; i < V; ++i) {
         const int32_t c = lane + 64 * i;
-        if (c < vecs) {
-          const f32x4 g = reinterpret_cast<const f32x4*>(ln.gamma)[c], b = reinterpret_cast<const f32x4*>(ln.beta)[c];
-          out[c] = (v[r][i] - mean) * rstd * g + b;
+        if (c >= vecs) continue;
+        const f32x4 gc = gb[c], bc = gb[kLnMaxK / 4 + c];
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+          const int64_t m = m0 + wave * R + r;
+          if (m < M) reinterpret_cast<f32x4*>(ln.u + (size_t)m * K)[c] = (v[r][i] - mean[r]) * rstd[r] * gc + bc;
         }
       }
     }
   }
-}
+};
 
 // TN x TM tiles of 16 x 16 (columns x rows of y) per workgroup, WK wavefronts along K, kDepth slabs in flight each.
 // LN: the x rows are normalised on the way (a launch of its own costs 3 to 4 us, of which the work is a fraction): every
@@ -156,13 +196,14 @@ __global__ __launch_bounds__(WK * 64) void gemm_f32_kernel(const float* __restri
 #pragma unroll
   for (int h = 0; h < 2; ++h) foff[h] = (uint32_t)(lrow * 8 + ((4 * h + lq) ^ swz16(lrow)));
 
-  for (int32_t u = 0; u < kDepth && u < ns; ++u) issue(u, u);
   __shared__ float2 ln_st[LN ? 16 : 1];
   __shared__ f32x4 ln_gb[LN ? kLnMaxK / 2 : 1];
+  std::conditional_t<LN, LnTile<LN ? WK : 4>, char> ln_tile;
+  if constexpr (LN) ln_tile.request(x, ln, m0, M, K, wave, lane);
+  for (int32_t u = 0; u < kDepth && u < ns; ++u) issue(u, u);
   float mean = 0.f, rstd = 0.f;
   if constexpr (LN) {
-    ln_rows<WK>(x, ln, m0, M, K, n0 == 0, wave, lane, ln_st, ln_gb);
-    __syncthreads();
+    ln_tile.finish(ln, m0, M, K, n0 == 0, wave, lane, ln_st, ln_gb);
     mean = ln_st[lrow].x;
     rstd = ln_st[lrow].y;
   }
@@ -262,7 +303,8 @@ hipError_t launch_cfg(const float* x, const float* w, const float* bias, const f
 
 // Where the linear runs on 16 x 16 tiles and four wavefronts, at most two of them per CU, and rows are short: every workgroup reads
 // its 16 rows once more and normalises them for itself.  77 rows, 256 / 768 / 1024 wide: the step 41 -> 33.5 us; but 40 rows,
-// 1024 / 3072 / 4096 wide, with 576 and 768 workgroups: 40 -> 48.5.
+// 1024 / 3072 / 4096 wide, with 576 and 768 workgroups: 40 -> 48.5.  Replayed from a graph, where a launch costs less, 3400 such layers
+// take 0.955 of the time in the mean (0.86 to 1.04; the longest rows gain nothing).
 bool gemm_f32_takes_ln(int64_t M, int32_t N, int32_t K) {
   return M > 0 && N > 16 && K > 64 && K <= kLnMaxK && ((M + 15) / 16) * ((N + 15) / 16) <= 512 &&
          (M <= 16 || ((M + 31) / 32) * ((N + 31) / 32) < 168);

@@ -65,3 +65,51 @@ def test_the_timed_layer_is_the_one_that_runs(lens, H, nh, F):
     assert list(ms) == list(E.STAGE_NAMES) and all(v >= 0.0 for v in ms.values())
     for a, b in zip(*left):
         assert torch.equal(a.view(torch.uint8), b.view(torch.uint8))
+
+
+def _replayed_us(body):
+    """us per call of `body`, twenty of them captured into a graph: what the device takes, without the host's time between launches."""
+    body()
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        for _ in range(20):
+            body()
+    a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+    times = []
+    for _ in range(15):
+        a.record()
+        graph.replay()
+        b.record()
+        b.synchronize()
+        times.append(a.elapsed_time(b) * 50.0)
+    return sorted(times)[7]
+
+
+@pytest.mark.parametrize("lens,H,nh,F", [([12, 12, 12, 12], 512, 2, 512), ([30, 25, 22], 256, 4, 1024)])
+def test_a_replayed_layer_takes_no_longer_than_its_stages_apart(lens, H, nh, F):
+    """Normalising in the linear saves launches, also where they cost little.  A tenth is left for the clocks."""
+    lens = np.asarray(lens, np.int32)
+    T, A = int(lens.sum()), nh * 64
+    rng = np.random.default_rng(H)
+    layer = hz.DeviceLayer(wl.random_small_layer(rng, H, nh, 64, F), wl.F32)
+    p = layer.tensors
+    cfg = hz.layer_config(H, nh, 64, F, wl.F32, 1e-5)
+    x = hz.to_device(rng.normal(1.0, 2.0, (T, H)).astype(np.float32), wl.F32)
+    cu = torch.from_numpy(np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)).cuda()
+    ws = torch.empty(E.energon_workspace_bytes(cfg, T), dtype=torch.uint8, device="cuda")
+    new = lambda n: torch.empty((T, n), device="cuda")
+    u, qkv, att, y1, wn, m, y, whole = new(H), new(3 * A), new(A), new(H), new(H), new(F), new(H), new(H)
+
+    def apart():
+        E.energon_layernorm(x, p["ln1_g"], p["ln1_b"], u, 1e-5)
+        E.energon_linear(u, p["w_qkv"], p["b_qkv"], None, qkv, E.EPI_BIAS)
+        E.energon_attention(qkv, att, cu, len(lens), int(lens.max()), nh, 64)
+        E.energon_linear(att, p["w_o"], p["b_o"], x, y1, E.EPI_BIAS_RESIDUAL)
+        E.energon_layernorm(y1, p["ln2_g"], p["ln2_b"], wn, 1e-5)
+        E.energon_linear(wn, p["w_fc1"], p["b_fc1"], None, m, E.EPI_BIAS_GELU)
+        E.energon_linear(m, p["w_fc2"], p["b_fc2"], y1, y, E.EPI_BIAS_RESIDUAL)
+
+    together = lambda: E.energon_layer_forward(cfg, layer.struct, x, whole, T, cu, lens, int(lens.max()), ws)
+    assert _replayed_us(together) <= 1.1 * _replayed_us(apart)
+    assert (whole - y).abs().max() <= 1e-5 * y.abs().max()
