@@ -104,6 +104,13 @@ def test_ragged_widths_and_long_k_run_on_the_tiles_that_every_shape_has(M, N, K,
     assert E.energon_linear_plan(M, N, K, epi, scratch_bytes=E.energon_linear_scratch_bytes(M, N, K, E.BF16)) == plan
 
 
+@pytest.mark.parametrize("M,N,K,epi", [(1350, 768, 256, E.EPI_BIAS), (147, 7168, 64, E.EPI_BIAS_GELU), (353, 2816, 256, E.EPI_BIAS),
+                                       (2571, 440, 64, E.EPI_BIAS_GELU), (159, 6560, 192, E.EPI_BIAS)])
+def test_short_k_stays_off_the_smallest_tiles_where_they_make_many_rounds(M, N, K, epi):
+    """Replayed from a graph 5.3 to 5.8 us with 64x64 tiles before the ring kernel, 6.4 to 6.9 with 32x32."""
+    assert E.energon_linear_plan(M, N, K, epi)[0] == 2
+
+
 @pytest.mark.parametrize("M", [2 ** 31 - 1, 2 ** 31, 2 ** 32 - 100, 2 ** 32, 2 ** 32 + 5, 2 ** 40])
 def test_sizes_may_be_asked_for_any_number_of_rows(M):
     """No such call could run, but the sizes are host arithmetic: no plan cuts K for so many rows, so no room for sums."""

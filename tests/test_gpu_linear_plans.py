@@ -17,7 +17,7 @@ SHAPES = [
     # M, N, K, dtype, scratch that the plan takes
     (65, 40, 64, wl.BF16, False),          # 32x32, one slab
     (130, 264, 192, wl.BF16, False),       # 32x32, fewer slabs than wavefronts
-    (515, 1032, 1024, wl.F16, False),      # 64x64, with GeLU 32x32
+    (515, 1032, 1024, wl.F16, False),      # 64x64
     (131, 2056, 4096, wl.BF16, False),     # 64x32
     (513, 1032, 2048, wl.BF16, False),     # 64x64
     (1025, 2056, 1024, wl.F16, False),     # 96x96
@@ -83,8 +83,8 @@ TILES = [
     (515, 12296, 2560, wl.F16, (WIDE, SQUARE, WIDE)),
     (1463, 4920, 1600, wl.BF16, (WIDE, WIDE, WIDE)),
     (650, 1032, 1600, wl.BF16, (SHARED, SHARED, SHARED)),
-    (123, 7544, 5696, wl.F16, (CUT, CUT, CUT)),
-    (900, 264, 1600, wl.F16, ((1, 64, 32, 1), (1, 32, 32, 1), (1, 64, 32, 1))),
+    (123, 7544, 5696, wl.F16, (CUT, CUT, SHARED)),
+    (900, 264, 1600, wl.F16, ((1, 64, 32, 1),) * 3),
 ]
 
 
