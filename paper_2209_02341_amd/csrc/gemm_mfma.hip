@@ -767,9 +767,11 @@ static_assert((int)KsplitTile::k32x32 == 0 && (int)KsplitTile::k64x32 == 1 && (i
 
 // Tiles of gemm_ring.hip: launch, then rounds of workgroups; a round is its epilogue and its slabs, a slab as long as the
 // workgroups that share a CU make it, and shorter where not every CU has one more (power, memory).  `weights`: us per 100 MB of W;
-// `cold`: what a slab takes longer where W comes from HBM (W of 85 MB and more: with its neighbours in a stack or in a loop over
-// several it does not stay in the last cache's 256 MB); sums, sums_part, sums_res: the second kernel of a cut K, us and us per
-// million outputs, for each part and for the residual.
+// `cold`: what a slab takes longer where operands come from HBM: x and W of 85 MB and more together, which is where the sweep's three sets
+// in turn outgrow the last cache's 256 MB (in a stack whose layers add up to more smaller ones do too, alone in a loop larger ones do
+// not).  With W alone counted, a tall x took tiles that wait for it: 5462 x 512 x 22272 + GeLU 179 us on 96x128, 133 in pieces of
+// 256x256; 2857 x 1024 x 16896 + residual 138 on 96x128, 105 on 160x256 in parts.  1500 shapes that this changed: 0.92 of the time in the mean.
+// sums, sums_part, sums_res: the second kernel of a cut K, us and us per million outputs, for each part and for the residual.
 struct RingTime {
   double base, round, drop, gelu, residual, weights, cold, sums, sums_part, sums_res, slab[2];
   double us(int per_cu, int32_t n, int32_t cus, double slabs, int epi) const {   // n workgroups on an XCD of so many CUs
@@ -812,7 +814,7 @@ static TilePlan tile_plan(int64_t M, int32_t N, int32_t K, bool overlap_safe, in
   };
   const auto fits = [](int64_t tiles, int64_t threads) { return tiles * threads <= kMaxGridThreads; };
   const double w_bytes = 2.0 * N * K;
-  const bool from_hbm = w_bytes > 85.0e6;   // see RingTime
+  const bool from_hbm = 2.0 * K * ((double)M + N) > 85.0e6;   // see RingTime
   const double far = from_hbm ? 1.45 : 1.0;   // the same for the small tiles that cut K
   if (plain) {
     // a last step that not all four wavefronts take costs about half the difference to one that they do

@@ -104,6 +104,23 @@ def test_ragged_widths_and_long_k_run_on_the_tiles_that_every_shape_has(M, N, K,
     assert E.energon_linear_plan(M, N, K, epi, scratch_bytes=E.energon_linear_scratch_bytes(M, N, K, E.BF16)) == plan
 
 
+@pytest.mark.parametrize("M,N,K,epi,rows", [
+    # us on the tiles that W alone chose, in pieces or parts of tall ones before the ring kernel, and on these now
+    (3250, 1344, 24832, E.EPI_BIAS_RESIDUAL, 160),   # 257 / 213
+    (3054, 1216, 24448, E.EPI_BIAS_RESIDUAL, 256),   # 217 / 174 / 175
+    (1659, 2304, 16128, E.EPI_BIAS_GELU, 256),       # 146 / 125 / 128
+    (4071, 1216, 16128, E.EPI_BIAS, 256),            # 180 / 156 / 158
+    (2857, 1024, 16896, E.EPI_BIAS_RESIDUAL, 160),   # 138 / 108 / 105
+    (3736, 768, 24832, E.EPI_BIAS, 160),             # 194 / 142 / 131
+    (5536, 512, 18048, E.EPI_BIAS_RESIDUAL, 160),    # 153 / 118 / 111
+    (6567, 1792, 19584, E.EPI_BIAS, 256),            # 557 / 450 / 453
+    (5462, 512, 22272, E.EPI_BIAS_GELU, 160),        # 179 / 133
+    (918, 4864, 8448, E.EPI_BIAS, 160),              # 109 / 95
+])
+def test_a_tall_x_from_memory_counts_as_a_wide_w_does(M, N, K, epi, rows):
+    assert E.energon_linear_plan(M, N, K, epi, scratch_bytes=E.energon_linear_scratch_bytes(M, N, K, E.BF16))[1] == rows
+
+
 @pytest.mark.parametrize("M,N,K,epi", [(1350, 768, 256, E.EPI_BIAS), (147, 7168, 64, E.EPI_BIAS_GELU), (353, 2816, 256, E.EPI_BIAS),
                                        (2571, 440, 64, E.EPI_BIAS_GELU), (159, 6560, 192, E.EPI_BIAS)])
 def test_short_k_stays_off_the_smallest_tiles_where_they_make_many_rounds(M, N, K, epi):
