@@ -774,13 +774,14 @@ static_assert((int)KsplitTile::k32x32 == 0 && (int)KsplitTile::k64x32 == 1 && (i
 // sums, sums_part, sums_res: the second kernel of a cut K, us and us per million outputs, for each part and for the residual.
 struct RingTime {
   double base, round, drop, gelu, residual, weights, cold, sums, sums_part, sums_res, slab[2];
-  double us(int per_cu, int32_t n, int32_t cus, double slabs, int epi) const {   // n workgroups on an XCD of so many CUs
+  // n workgroups on an XCD of so many CUs
+  double us(int per_cu, int32_t n, int32_t cus, double slabs, int epi, bool streams) const {
     const double epilogue = round + (epi == EPI_BIAS_GELU || epi == EPI_LNFOLD_GELU ? gelu : 0.0) + (epi == EPI_BIAS_RESIDUAL ? residual : 0.0) +
                             (epi == EPI_LNFOLD || epi == EPI_LNFOLD_GELU ? 0.5 * round : 0.0);
     const int32_t whole = (n - 1) / (cus * per_cu), rest = n - whole * cus * per_cu;   // rounds before the last; the last one's workgroups
     const int level = rest <= cus ? 1 : 2;   // per_cu is 1 or 2
     return base + whole * (epilogue + slabs * slab[per_cu - 1]) + epilogue * (level + 1) / (per_cu + 1) +
-           slabs * slab[level - 1] * (1.0 - drop * (level - rest / (double)cus));
+           slabs * slab[level - 1] * (1.0 - (streams ? 0.0 : drop) * (level - rest / (double)cus));
   }
 };
 constexpr RingTime kRingTime[] = {   // the order of kRingShapes
@@ -815,6 +816,10 @@ static TilePlan tile_plan(int64_t M, int32_t N, int32_t K, bool overlap_safe, in
   const auto fits = [](int64_t tiles, int64_t threads) { return tiles * threads <= kMaxGridThreads; };
   const double w_bytes = 2.0 * N * K;
   const bool from_hbm = 2.0 * K * ((double)M + N) > 85.0e6;   // see RingTime
+  // Few rows and a W of 100 MB and more: hardly a line of W is in an L2 when a workgroup asks for it, so a slab does not get shorter where CUs
+  // are idle, and 64 rows ask for each line more than once.  On all plans of 1190 shapes (65 to 400 rows, W of 85 to 260 MB) the choice then
+  // costs 1.0 % over the best in the mean, 1.6 % without; 123 x 17216 x 3456 + residual 45.9 us on 64x96, 37.3 on 128x192 in parts.
+  const bool streams = w_bytes > 100.0e6 && M <= 256;
   const double far = from_hbm ? 1.45 : 1.0;   // the same for the small tiles that cut K
   if (plain) {
     // a last step that not all four wavefronts take costs about half the difference to one that they do
@@ -839,8 +844,10 @@ static TilePlan tile_plan(int64_t M, int32_t N, int32_t K, bool overlap_safe, in
       for (const int32_t parts : {1, fill, fill - 1, (fill + 1) / 2}) {
         if (parts < 1) continue;
         const int32_t units = (int32_t)n * parts;   // fits() above
-        double us = kRingTime[i].us(shape.per_cu, (units + kXcds - 1) / kXcds, wgs, (parts > 1 ? (KT + parts - 1) / parts : KT) * (from_hbm ? 1.0 + kRingTime[i].cold : 1.0),
-                                    parts > 1 ? EPI_BIAS : epi) + kRingTime[i].weights * 1.0e-8 * w_bytes;
+        const double cold = from_hbm ? kRingTime[i].cold + (streams && shape.rows == 64 && M > 64 ? 0.2 : 0.0) : 0.0;
+        double us = kRingTime[i].us(shape.per_cu, (units + kXcds - 1) / kXcds, wgs, (parts > 1 ? (KT + parts - 1) / parts : KT) * (1.0 + cold),
+                                    parts > 1 ? EPI_BIAS : epi, streams) + kRingTime[i].weights * 1.0e-8 * w_bytes;
+        if (streams) us *= 0.92;
         if (spills && units > 8 * wgs * shape.per_cu) us *= 1.2;
         if (parts > 1) us = 1.05 * (us + kRingTime[i].sums + elems * 1.0e-6 * (kRingTime[i].sums_part * parts + kRingTime[i].sums_res * res));
         consider({kRing, KsplitTile::k64x64, i, parts, parts > 1 ? (size_t)parts * (size_t)M * N * sizeof(float) : 0}, us);

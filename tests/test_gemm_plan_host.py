@@ -121,6 +121,19 @@ def test_a_tall_x_from_memory_counts_as_a_wide_w_does(M, N, K, epi, rows):
     assert E.energon_linear_plan(M, N, K, epi, scratch_bytes=E.energon_linear_scratch_bytes(M, N, K, E.BF16))[1] == rows
 
 
+@pytest.mark.parametrize("M,N,K,epi", [
+    # us in parts of 128x256 before the ring kernel, on 64x96 tiles, on these now
+    (123, 17216, 3456, E.EPI_BIAS_RESIDUAL),   # 35.7 / 45.9 / 37.3
+    (119, 17920, 4032, E.EPI_BIAS),            # 38.4 / 51.8 / 40.5
+    (124, 18560, 4416, E.EPI_BIAS_RESIDUAL),   # 43.3 / 58.0 / 45.4
+    (125, 17088, 3264, E.EPI_BIAS_GELU),       # 33.1 / 43.6 / 35.4
+    (107, 16704, 3264, E.EPI_BIAS_GELU),       # 31.7 / 40.9 / 33.3
+])
+def test_a_wide_w_from_memory_is_read_once_for_few_rows(M, N, K, epi):
+    _, rows, _, parts = E.energon_linear_plan(M, N, K, epi, scratch_bytes=E.energon_linear_scratch_bytes(M, N, K, E.BF16))
+    assert rows >= M and parts > 1
+
+
 @pytest.mark.parametrize("M,N,K,epi", [(1350, 768, 256, E.EPI_BIAS), (147, 7168, 64, E.EPI_BIAS_GELU), (353, 2816, 256, E.EPI_BIAS),
                                        (2571, 440, 64, E.EPI_BIAS_GELU), (159, 6560, 192, E.EPI_BIAS)])
 def test_short_k_stays_off_the_smallest_tiles_where_they_make_many_rounds(M, N, K, epi):
