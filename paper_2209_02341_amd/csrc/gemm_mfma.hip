@@ -724,18 +724,19 @@ size_t gemm_sched_scratch_bytes(int64_t M, int32_t N, int32_t K) {
 //            (sums in the scratch);
 //   kPieces  the 256x256 kernel with every tile cut into pieces (needs M, N >= 256 and K % 128 == 0).
 // The one with the least expected time, by a model that is fitted per tile to a sweep of 7300 shapes on all of them (65 to
-// 5000 rows of every layer width and others, K of 64 to 32768, the three epilogues, three sets of operands in turn).  On 11200
-// others of up to 9000 rows, a fifth of them of ragged widths and a sixth with K of eight N and more (up to 65536), it costs 1.3 %
-// over the best of them in the mean.  What the choice turns on is whole rounds: so many sizes, because each alone is the best
-// by 10 to 45 % wherever its tiles just fill the CUs.  Measured (us; in brackets the same shape on the tiles of the kernel before
-// this one, and the next best of these):
-//   387 x 4096 x 1024 + GeLU 9.8 64x64 [10.9; 10.5]   928 x 5120 x 5120 + residual 54 160x192 [72; 58]   200 x 20480 x 5120 73 160x192 [103; 77]
-//   600 x 4096 x 16384 86 160x256 in parts [102; 90]  2280 x 4096 x 4096 75 160x256 [109; 91]             333 x 5120 x 20480 87 128x256 in parts [99; 90]
-//   692 x 30536 x 192 21.3 128x128 [29.9]             5239 x 2840 x 192 + GeLU 20.2 128x128 [26.4]        369 x 1096 x 11456 + GeLU 19.2 96x128 in parts [25.2]
-// Against the choice before (64x64, 128x128 and 128x256 tiles of a compiler-scheduled kernel), over shapes that take 8 us and more:
-// widths that are multiples of 64 0.77 times the time in the mean, others 0.71, K of eight N and more 0.69.  What stayed on 64x64 tiles
-// at K of 320 and less and some 500 to 800 tiles loses up to 1.1 (8881 x 320 x 320 7.6 -> 8.4): three workgroups of that kernel
-// shared a CU, two of this one do.
+// 5000 rows of every layer width and others, K of 64 to 32768, the three epilogues, three sets of operands in turn).  What the choice
+// turns on is whole rounds: so many sizes, because each alone is the best by 10 to 45 % wherever its tiles just fill the CUs.  Measured
+// (us; in brackets the same shape on the tiles of the kernel before this one):
+//   387 x 4096 x 1024 + GeLU 10.1 64x64 [11.2]         928 x 5120 x 5120 + residual 54.9 128x192 [69.5]   200 x 20480 x 5120 70.4 128x192 [99]
+//   600 x 4096 x 16384 84.7 160x256 in parts [102]     2280 x 4096 x 4096 68.0 160x256 [109]              333 x 5120 x 20480 87.7 128x256 in parts [105]
+//   692 x 30536 x 192 21.9 128x128 [31.6]              5239 x 2840 x 192 + GeLU 20.7 128x128 [27.5]       369 x 1096 x 11456 + GeLU 21.4 96x128 in parts [26.2]
+// Against the choice before (64x64, 128x128 and 128x256 tiles of a compiler-scheduled kernel), 9000 random shapes of some 8 us and more (66 to 8192
+// rows), the time in the mean and how many take more than 3 % longer: widths that are multiples of 64 0.73, 15 of 5000; others 0.74, 9 of
+// 2500; K of eight N and more 0.65, 3 of 1500; at most 1.14 times (65 to 128 rows and a W of 100 MB and more, which 128x256 in parts
+// reads a little faster), but for a tall x over 256 columns in eight parts (3567 x 256 x 16384 52 -> 68, 4087 x 256 x 22016 72 -> 81: counting
+// x in `weights` as well mends those and takes 1.05 times as long in the mean of what it changes).  What stayed on 64x64 tiles at K of 320
+// and less and some 500 to 800 tiles loses up to 1.1 (8881 x 320 x 320 8.0 -> 8.8): three workgroups of that kernel shared a CU, two of
+// this one do.
 enum TileKind { kSplit, kRing, kPieces };
 struct TilePlan { TileKind kind; KsplitTile split; int32_t ring, ks; size_t scratch; double us; };   // ks: parts of K (kPieces: pieces per tile)
 
@@ -872,9 +873,10 @@ static TilePlan tile_plan(int64_t M, int32_t N, int32_t K, bool overlap_safe, in
 
 // The persistent kernel takes what gives it 192 tiles, but up to some 400 of them are one or two rounds with much of the last one
 // empty, and a ring tile can fill its own better: expected times of both, the persistent kernel's fitted to 1100 shapes of 192
-// to 420 tiles.  Taken where the ring kernel is expected to need under 0.87 of the time: a quarter of the shapes, 0.97 of the time in
-// the mean of all, 0.91 for 257 to 330 tiles (3074 x 5120 x 1280 + residual 75 -> 53 us, 306 x 24576 x 8192 195 -> 134); between that
-// and 1 the two come out as they may (0.97: a sixth of all shapes more than 3 % slower).
+// to 420 tiles (its slab time is the mean over W from HBM and from the last cache, which RingTime tells apart).  Taken where the ring kernel is
+// expected to need under 0.87 of the time: 1000 such shapes 0.71 of the time in the mean, four more than 3 % slower, at most 1.15 (3074 x 5120 x
+// 1280 + residual 75 -> 53 us, 306 x 24576 x 8192 204 -> 133; 997 x 22272 x 896 + residual 61 -> 70); between that and 1 the two come out as
+// they may (0.97: a sixth of all shapes more than 3 % slower).
 static double sched_us(const SchedPlan& p, int64_t M, int32_t N, int epi) {
   const double slab = 1.47, epilogue = 9.26 + (epi == EPI_BIAS_GELU ? 6.1 : 0.0) + (epi == EPI_BIAS_RESIDUAL ? 4.43 : 0.0);
   double worst = 0;
