@@ -52,6 +52,8 @@ SHAPES = [
     (1458, 5048, 576, wl.F16, RESIDUAL, (128, 256, 1)),
     (516, 13208, 448, wl.BF16, BIAS, (160, 256, 1)),
     (129, 7016, 6080, wl.F16, BIAS, (160, 192, 6)),        # 95 slabs in six parts
+    (1601, 760, 18496, wl.BF16, RESIDUAL, (160, 256, 7)),  # a tall x from memory, 289 slabs in seven parts
+    (3001, 248, 14400, wl.F16, GELU, (128, 256, 8)),       # 225 slabs in eight parts
 ]
 
 
